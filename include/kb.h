@@ -149,8 +149,7 @@ enum {
      * batch of searches of at most 64 candidates and 16 clusters runs one wave per
      * search with exact fp32 / fp64 distances instead, and a search stops at its
      * first step without a move, after which nothing could change: same results.)  Rows
-     * are fetched in 16-byte pieces when D is a multiple of 4 and feature by
-     * feature otherwise (about a third slower). */
+     * are fetched in 16-byte pieces for any D of 4 or more. */
     KB_SCORER_DEFAULT = 0,
     /* fp32 fused multiply-adds on the vector ALU, every candidate scored in every
      * step: the reference the matrix-core scorers are measured against. */

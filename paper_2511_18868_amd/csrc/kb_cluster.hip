@@ -573,7 +573,7 @@ __device__ __forceinline__ void tile_scores(const bf16x8 (&Bh)[DS], const bf16x8
 // per half-wave), reads their candidates' limits, and appends those the drift has
 // reached to a small queue in LDS; whenever 32 are waiting they are scored as one
 // tile of the matrix instruction, each lane fetching its own candidate's fp32 row
-// (in 16-byte pieces when D is a multiple of 4) and splitting it into the bf16
+// in 16-byte pieces and splitting it into the bf16
 // operands in registers.  A tile in which a third of the candidates are at risk
 // thus costs a third of a scoring instead of a whole one.
 template <int DS, int MT, int NT, bool VEC>
@@ -646,15 +646,12 @@ __device__ __forceinline__ int score_packed(const ClusterArgs& a, const float* _
                 if constexpr (VEC) {
                     if (d0 < D) r0[s] = *reinterpret_cast<const float4*>(xr + d0);
                     if (d0 + 4 < D) r1[s] = *reinterpret_cast<const float4*>(xr + d0 + 4);
+                } else if (s + 1 < DS) {
+                    r0[s] = load4(xr + d0);                 // (D > 16 (DS - 1): inside the row)
+                    r1[s] = load4(xr + d0 + 4);
                 } else {
-                    if (d0 + 0 < D) r0[s].x = xr[d0 + 0];
-                    if (d0 + 1 < D) r0[s].y = xr[d0 + 1];
-                    if (d0 + 2 < D) r0[s].z = xr[d0 + 2];
-                    if (d0 + 3 < D) r0[s].w = xr[d0 + 3];
-                    if (d0 + 4 < D) r1[s].x = xr[d0 + 4];
-                    if (d0 + 5 < D) r1[s].y = xr[d0 + 5];
-                    if (d0 + 6 < D) r1[s].z = xr[d0 + 6];
-                    if (d0 + 7 < D) r1[s].w = xr[d0 + 7];
+                    r0[s] = row_piece(xr, d0, D);
+                    r1[s] = row_piece(xr, d0 + 4, D);
                 }
             }
 #pragma unroll
@@ -833,14 +830,13 @@ __device__ __forceinline__ int score_first(const ClusterArgs& a, const float* __
                 if (valid && d0 < D) r[s][0] = *reinterpret_cast<const float4*>(xr + d0);
                 if (valid && d0 + 4 < D) r[s][1] = *reinterpret_cast<const float4*>(xr + d0 + 4);
             } else if (valid) {
-                if (d0 + 0 < D) r[s][0].x = xr[d0 + 0];
-                if (d0 + 1 < D) r[s][0].y = xr[d0 + 1];
-                if (d0 + 2 < D) r[s][0].z = xr[d0 + 2];
-                if (d0 + 3 < D) r[s][0].w = xr[d0 + 3];
-                if (d0 + 4 < D) r[s][1].x = xr[d0 + 4];
-                if (d0 + 5 < D) r[s][1].y = xr[d0 + 5];
-                if (d0 + 6 < D) r[s][1].z = xr[d0 + 6];
-                if (d0 + 7 < D) r[s][1].w = xr[d0 + 7];
+                if (s + 1 < DS) {
+                    r[s][0] = load4(xr + d0);               // (D > 16 (DS - 1): inside the row)
+                    r[s][1] = load4(xr + d0 + 4);
+                } else {
+                    r[s][0] = row_piece(xr, d0, D);
+                    r[s][1] = row_piece(xr, d0 + 4, D);
+                }
             }
         }
     };
@@ -1217,8 +1213,9 @@ __host__ __device__ inline Lds lds_layout(int Kmax, int D, int DP, int Nmax, int
 
 // DS = feature K-steps of 16 (D <= 16*DS); MT = centroid tiles of 32 held in
 // registers by the matrix-core scorer, MT = 0 selects the vector-ALU scorer.
-// VEC: D is a multiple of 4, so the matrix-core scorers fetch rows in 16-byte pieces;
-// otherwise (a compile-time choice, so the loops hold one form only) feature by feature.
+// VEC: D is a multiple of 4, so every row is a whole number of 16-byte pieces; otherwise
+// (a compile-time choice, so the loops hold one form only) the last piece of a row is
+// put together by row_piece.
 // Workgroups per compute unit in the 256-thread shape: three, and four (128 registers,
 // a few of them spilled) where at most 32 clusters and 48 features leave room for it -
 // batches of many short searches gain 10-17 % from the fourth resident search
@@ -1926,21 +1923,22 @@ hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t s
     const int ds = (b.D + 15) / 16;   // 1..4 K-steps of 16 features
     int mt = a.Kmax <= 32 ? 1 : (a.Kmax <= 64 ? 2 : 0);
     if (c.scorer == 1) mt = 0;
-    // the matrix-core kernels fetch rows in 16-byte pieces when D is a multiple of 4 and
-    // feature by feature otherwise (own instantiations, in the 256-thread shape only)
+    // (rows whose length is no multiple of 4 features have instantiations of their own,
+    // whose last 16-byte piece of a row is shifted into place)
     const bool vec = (b.D & 3) == 0;
     // few searches: every workgroup has a compute unit to itself and takes the wide shape
     const size_t lds_wide = lds_layout(a.Kmax, b.D, 16 * ds + 4, a.Nmax, kThreadsWide / kWave).total;
     // ... and so does a batch of long searches only (2048 candidates or more on average):
     // measured 13-20 % faster than three of them sharing a compute unit
-    const bool wide = (vec || mt == 0) && (b.G <= kWideMaxG || b.N >= (int64_t)2048 * b.G) && lds_wide <= kMaxLds;
+    const bool wide = (b.G <= kWideMaxG || b.N >= (int64_t)2048 * b.G) && lds_wide <= kMaxLds;
     const size_t lds = wide ? lds_wide
                             : lds_layout(a.Kmax, b.D, 16 * ds + 4, a.Nmax, kThreadsNarrow / kWave).total;
     if (lds > kMaxLds) return hipErrorInvalidValue;
     // a batch of very short searches, in the library's default mode: one wave per search
     if (wave_per_search(b, c)) return launch_wave(b, a, nullptr, st);
     const dim3 grid((unsigned)b.G), block(wide ? kThreadsWide : kThreadsNarrow);
-#define KB_NARROW_SCALAR kThreadsNarrow, false
+#define KB_NARROW_ANY kThreadsNarrow, false
+#define KB_WIDE_ANY kThreadsWide, false
 #define KB_LAUNCH_NT(DS_, MT_, NT_)                                                             \
     do {                                                                                        \
         hipError_t e = hipFuncSetAttribute(                                                     \
@@ -1951,9 +1949,10 @@ hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t s
     } while (0)
 #define KB_LAUNCH_MATRIX(DS_, MT_)                                                              \
     do {                                                                                        \
-        if (wide) KB_LAUNCH_NT(DS_, MT_, kThreadsWide);                                         \
+        if (wide && vec) KB_LAUNCH_NT(DS_, MT_, kThreadsWide);                                  \
+        else if (wide) KB_LAUNCH_NT(DS_, MT_, KB_WIDE_ANY);                                     \
         else if (vec) KB_LAUNCH_NT(DS_, MT_, kThreadsNarrow);                                   \
-        else KB_LAUNCH_NT(DS_, MT_, KB_NARROW_SCALAR);                                          \
+        else KB_LAUNCH_NT(DS_, MT_, KB_NARROW_ANY);                                             \
     } while (0)
 #define KB_LAUNCH_VECTOR_ALU(DS_)                                                               \
     do {                                                                                        \
@@ -1976,7 +1975,8 @@ hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t s
 #undef KB_LAUNCH_VECTOR_ALU
 #undef KB_LAUNCH_MATRIX
 #undef KB_LAUNCH_NT
-#undef KB_NARROW_SCALAR
+#undef KB_NARROW_ANY
+#undef KB_WIDE_ANY
     return hipGetLastError();
 }
 

@@ -222,6 +222,38 @@ __device__ __forceinline__ unsigned long long reward_fixed(float r) {
     return ((unsigned long long)(unsigned)hi << 30) + (unsigned)lo;
 }
 
+// Four consecutive floats from an address that is a multiple of 4 bytes only: one
+// 16-byte load all the same (global memory takes such loads at dword alignment).
+typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4(const float* p) {
+    const f32x4_dword v = *reinterpret_cast<const f32x4_dword*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+// Features d0 .. d0 + 3 of a row of D features, zeros beyond D, for any D: one 16-byte
+// load that stays inside the row (the last piece is loaded so that it ends with the row
+// and shifted down), so a row whose length is no multiple of 4 costs the load
+// instructions of one that is.  (Feature by feature, every lane of a wave in a row of
+// its own, the same bytes take four times the load instructions, each of which the
+// address unit splits into 64 lines: a round of 300 searches of 70-1900 rows of 50
+// features 688 us that way and 584 us with these loads, one search of 5128 rows of
+// 59 features 807 and 417 us, the latter with the 768-thread shape that only rows of whole
+// pieces had before.)
+__device__ __forceinline__ float4 row_piece(const float* row, int d0, int D) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (D >= 4) {                                        // (uniform)
+        const int o = d0 < D - 4 ? d0 : D - 4, r = d0 - o;
+        v = load4(row + o);
+        if (r & 1) v = make_float4(v.y, v.z, v.w, 0.f);
+        if (r & 2) v = make_float4(v.z, v.w, 0.f, 0.f);
+        if (r >= 4) v = make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
+        if (d0 + 0 < D) v.x = row[d0];
+        if (d0 + 1 < D) v.y = row[d0 + 1];
+        if (d0 + 2 < D) v.z = row[d0 + 2];
+    }
+    return v;
+}
+
 __device__ __forceinline__ int clampi(int v, int lo, int hi) {
     return v < lo ? lo : (v > hi ? hi : v);
 }
