@@ -70,10 +70,13 @@ struct ClusterArgs {
 
 // Threads per workgroup (a template parameter NT of the kernel and of the device
 // functions that stride by it): 256, three workgroups per compute unit, is the
-// shape of large batches; a batch with fewer searches than compute units runs 768,
-// so that a lone search still fills the unit it is on.
+// shape of large batches; a batch that is done when its longest search is runs 768, so
+// that a search fills the unit it is on (wide_shape).
 constexpr int kThreadsNarrow = 256, kThreadsWide = 768;
 constexpr int kWideMaxG = 256;     // most searches of a batch that takes the wide shape
+// Rows of features: whole 16-byte pieces (D a multiple of 4); 4 features or more with a
+// last piece that is shifted into place; 1 to 3 features, value by value.
+constexpr int kRowsWhole = 0, kRowsRagged = 1, kRowsTiny = 2;
 constexpr int kFlagCap = 256;      // LDS list of candidates waiting for the exact pass
 constexpr int kMoverBatch = 8;     // movers whose rows are requested together
 constexpr int kQueue = 128;        // per wave: candidates waiting to be scored (at most 31 + 64 at a time)
@@ -576,7 +579,7 @@ __device__ __forceinline__ void tile_scores(const bf16x8 (&Bh)[DS], const bf16x8
 // in 16-byte pieces and splitting it into the bf16
 // operands in registers.  A tile in which a third of the candidates are at risk
 // thus costs a third of a scoring instead of a whole one.
-template <int DS, int MT, int NT, bool VEC>
+template <int DS, int MT, int NT, int ROWS>
 __device__ __forceinline__ int score_packed(const ClusterArgs& a, const float* __restrict__ Xg,
                                             int n0, int ng, int K, int D, int DP, int SP,
                                             const float* cent, const float* cn, float cnmax,
@@ -643,16 +646,27 @@ __device__ __forceinline__ int score_packed(const ClusterArgs& a, const float* _
                 const int d0 = 16 * s + 8 * h;
                 r0[s] = make_float4(0.f, 0.f, 0.f, 0.f);
                 r1[s] = r0[s];
-                if constexpr (VEC) {
+                if constexpr (ROWS == kRowsWhole) {
                     if (d0 < D) r0[s] = *reinterpret_cast<const float4*>(xr + d0);
                     if (d0 + 4 < D) r1[s] = *reinterpret_cast<const float4*>(xr + d0 + 4);
+                } else if constexpr (ROWS == kRowsTiny) {
+                    if (h == 0) {
+                        r0[s].x = xr[0];
+                        if (D > 1) r0[s].y = xr[1];
+                        if (D > 2) r0[s].z = xr[2];
+                    }
                 } else if (s + 1 < DS) {
                     r0[s] = load4(xr + d0);                 // (D > 16 (DS - 1): inside the row)
                     r1[s] = load4(xr + d0 + 4);
                 } else {
-                    r0[s] = row_piece(xr, d0, D);
-                    r1[s] = row_piece(xr, d0 + 4, D);
+                    r0[s] = row_piece_load(xr, d0, D);
+                    r1[s] = row_piece_load(xr, d0 + 4, D);
                 }
+            }
+            if constexpr (ROWS == kRowsRagged) {
+                const int d0 = 16 * (DS - 1) + 8 * h;
+                r0[DS - 1] = row_piece_shift(r0[DS - 1], d0, D);
+                r1[DS - 1] = row_piece_shift(r1[DS - 1], d0 + 4, D);
             }
 #pragma unroll
             for (int s = 0; s < DS; ++s) {
@@ -790,7 +804,7 @@ __device__ __forceinline__ int score_packed(const ClusterArgs& a, const float* _
 // the fixed-point sums from the same registers; |x|^2 and the drift limit of every
 // candidate go to the workspace for the steps that follow.  Returns max |x| over the rows this thread saw in
 // `am_out`, which the caller checks against the estimate the scale was taken from.
-template <int DS, int MT, int NT, bool VEC>
+template <int DS, int MT, int NT, int ROWS>
 __device__ __forceinline__ int score_first(const ClusterArgs& a, const float* __restrict__ Xg,
                                            int n0, int ng, int K, int D,
                                            int SP, const float* cn, float cnmax, int fsh,
@@ -812,7 +826,7 @@ __device__ __forceinline__ int score_first(const ClusterArgs& a, const float* __
         const int p = tile * 32 + m;
         const bool valid = p < ng;
         const float* xr = Xg + (size_t)(valid ? p : 0) * D;
-        if (VEC && D == 16 * DS && tile * 32 + 32 <= ng) {
+        if (ROWS == kRowsWhole && D == 16 * DS && tile * 32 + 32 <= ng) {
             // (uniform) a whole tile of rows without padding: nothing to guard
 #pragma unroll
             for (int s = 0; s < DS; ++s) {
@@ -826,18 +840,29 @@ __device__ __forceinline__ int score_first(const ClusterArgs& a, const float* __
             const int d0 = 16 * s + 8 * h;
             r[s][0] = make_float4(0.f, 0.f, 0.f, 0.f);
             r[s][1] = r[s][0];
-            if constexpr (VEC) {
+            if constexpr (ROWS == kRowsWhole) {
                 if (valid && d0 < D) r[s][0] = *reinterpret_cast<const float4*>(xr + d0);
                 if (valid && d0 + 4 < D) r[s][1] = *reinterpret_cast<const float4*>(xr + d0 + 4);
+            } else if constexpr (ROWS == kRowsTiny) {
+                if (valid && h == 0) {
+                    r[s][0].x = xr[0];
+                    if (D > 1) r[s][0].y = xr[1];
+                    if (D > 2) r[s][0].z = xr[2];
+                }
             } else if (valid) {
                 if (s + 1 < DS) {
                     r[s][0] = load4(xr + d0);               // (D > 16 (DS - 1): inside the row)
                     r[s][1] = load4(xr + d0 + 4);
                 } else {
-                    r[s][0] = row_piece(xr, d0, D);
-                    r[s][1] = row_piece(xr, d0 + 4, D);
+                    r[s][0] = row_piece_load(xr, d0, D);
+                    r[s][1] = row_piece_load(xr, d0 + 4, D);
                 }
             }
+        }
+        if constexpr (ROWS == kRowsRagged) {
+            const int d0 = 16 * (DS - 1) + 8 * h;
+            r[DS - 1][0] = row_piece_shift(r[DS - 1][0], d0, D);
+            r[DS - 1][1] = row_piece_shift(r[DS - 1][1], d0 + 4, D);
         }
     };
 
@@ -1213,9 +1238,8 @@ __host__ __device__ inline Lds lds_layout(int Kmax, int D, int DP, int Nmax, int
 
 // DS = feature K-steps of 16 (D <= 16*DS); MT = centroid tiles of 32 held in
 // registers by the matrix-core scorer, MT = 0 selects the vector-ALU scorer.
-// VEC: D is a multiple of 4, so every row is a whole number of 16-byte pieces; otherwise
-// (a compile-time choice, so the loops hold one form only) the last piece of a row is
-// put together by row_piece.
+// ROWS: how the matrix-core scorers fetch rows (a compile-time choice, so the loops hold
+// one form only).
 // Workgroups per compute unit in the 256-thread shape: three, and four (128 registers,
 // a few of them spilled) where at most 32 clusters and 48 features leave room for it -
 // batches of many short searches gain 10-17 % from the fourth resident search
@@ -1223,7 +1247,7 @@ __host__ __device__ inline Lds lds_layout(int Kmax, int D, int DP, int Nmax, int
 // registers four were 4 % slower).
 constexpr int narrow_workgroups_per_cu(int DS, int MT) { return (MT == 1 && DS <= 3) ? 4 : 3; }
 
-template <int DS, int MT, int NT, bool VEC = true>
+template <int DS, int MT, int NT, int ROWS = kRowsWhole>
 __global__ void __launch_bounds__(NT, NT == kThreadsNarrow ? narrow_workgroups_per_cu(DS, MT) : 1)
 cluster_fused_kernel(ClusterArgs a) {
     constexpr int kThreads = NT, kWaves = NT / kWave;
@@ -1270,7 +1294,7 @@ cluster_fused_kernel(ClusterArgs a) {
     float am = 0.f;
     if constexpr (MT > 0) {
         const int srows = ng < 64 ? ng : 64;
-        if constexpr (VEC) {
+        if constexpr (ROWS == kRowsWhole) {
             const int quads = srows * (D >> 2);
             for (int i = tid; i < quads; i += kThreads) {
                 const float4 v = reinterpret_cast<const float4*>(Xg)[i];
@@ -1361,7 +1385,7 @@ cluster_fused_kernel(ClusterArgs a) {
         if constexpr (MT > 0) {
             if (first) {
                 float am_seen;
-                st = score_first<DS, MT, NT, VEC>(a, Xg, n0, ng, K, D, SP, cn, cm, fsh, sums, cnt, nflag,
+                st = score_first<DS, MT, NT, ROWS>(a, Xg, n0, ng, K, D, SP, cn, cm, fsh, sums, cnt, nflag,
                                          flist, aop, dw, thr, lim, am_seen, tsq);
                 am_seen = block_max_f<kWaves>(am_seen, red, phase);
                 tsq = block_sum_d<kWaves>(tsq, red, phase);
@@ -1387,7 +1411,7 @@ cluster_fused_kernel(ClusterArgs a) {
                     __syncthreads();
                 }
             } else
-            st = score_packed<DS, MT, NT, VEC>(a, Xg, n0, ng, K, D, DP, SP, cent, cn, cm, fsh, sums, cnt,
+            st = score_packed<DS, MT, NT, ROWS>(a, Xg, n0, ng, K, D, DP, SP, cent, cn, cm, fsh, sums, cnt,
                                       nflag, flist, aop, dw, thr, lim, queue, drift, Tc);
         } else {
             score_valu<4 * DS, NT>(a, Xg, n0, ng, K, D, DP, cent, cn, cm);
@@ -1923,13 +1947,8 @@ hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t s
     const int ds = (b.D + 15) / 16;   // 1..4 K-steps of 16 features
     int mt = a.Kmax <= 32 ? 1 : (a.Kmax <= 64 ? 2 : 0);
     if (c.scorer == 1) mt = 0;
-    // (rows whose length is no multiple of 4 features have instantiations of their own,
-    // whose last 16-byte piece of a row is shifted into place)
-    const bool vec = (b.D & 3) == 0;
-    // few searches: every workgroup has a compute unit to itself and takes the wide shape
+    const int rows = (b.D & 3) == 0 ? kRowsWhole : b.D >= 4 ? kRowsRagged : kRowsTiny;
     const size_t lds_wide = lds_layout(a.Kmax, b.D, 16 * ds + 4, a.Nmax, kThreadsWide / kWave).total;
-    // ... and so does a batch of long searches only (2048 candidates or more on average):
-    // measured 13-20 % faster than three of them sharing a compute unit
     const bool wide = (b.G <= kWideMaxG || b.N >= (int64_t)2048 * b.G) && lds_wide <= kMaxLds;
     const size_t lds = wide ? lds_wide
                             : lds_layout(a.Kmax, b.D, 16 * ds + 4, a.Nmax, kThreadsNarrow / kWave).total;
@@ -1937,27 +1956,29 @@ hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t s
     // a batch of very short searches, in the library's default mode: one wave per search
     if (wave_per_search(b, c)) return launch_wave(b, a, nullptr, st);
     const dim3 grid((unsigned)b.G), block(wide ? kThreadsWide : kThreadsNarrow);
-#define KB_NARROW_ANY kThreadsNarrow, false
-#define KB_WIDE_ANY kThreadsWide, false
-#define KB_LAUNCH_NT(DS_, MT_, NT_)                                                             \
+#define KB_LAUNCH_NT(DS_, MT_, NT_, ROWS_)                                                      \
     do {                                                                                        \
-        hipError_t e = hipFuncSetAttribute(                                                     \
-            reinterpret_cast<const void*>(cluster_fused_kernel<DS_, MT_, NT_>),                 \
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                              \
+        auto kern = cluster_fused_kernel<DS_, MT_, NT_, ROWS_>;                                 \
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                 \
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
         if (e != hipSuccess) return e;                                                          \
-        hipLaunchKernelGGL((cluster_fused_kernel<DS_, MT_, NT_>), grid, block, lds, st, a);     \
+        hipLaunchKernelGGL(kern, grid, block, lds, st, a);                                      \
+    } while (0)
+#define KB_LAUNCH_ROWS(DS_, MT_, NT_)                                                           \
+    do {                                                                                        \
+        if (rows == kRowsWhole) KB_LAUNCH_NT(DS_, MT_, NT_, kRowsWhole);                        \
+        else if (rows == kRowsRagged) KB_LAUNCH_NT(DS_, MT_, NT_, kRowsRagged);                 \
+        else KB_LAUNCH_NT(1, MT_, NT_, kRowsTiny);                                              \
     } while (0)
 #define KB_LAUNCH_MATRIX(DS_, MT_)                                                              \
     do {                                                                                        \
-        if (wide && vec) KB_LAUNCH_NT(DS_, MT_, kThreadsWide);                                  \
-        else if (wide) KB_LAUNCH_NT(DS_, MT_, KB_WIDE_ANY);                                     \
-        else if (vec) KB_LAUNCH_NT(DS_, MT_, kThreadsNarrow);                                   \
-        else KB_LAUNCH_NT(DS_, MT_, KB_NARROW_ANY);                                             \
+        if (wide) KB_LAUNCH_ROWS(DS_, MT_, kThreadsWide);                                       \
+        else KB_LAUNCH_ROWS(DS_, MT_, kThreadsNarrow);                                          \
     } while (0)
 #define KB_LAUNCH_VECTOR_ALU(DS_)                                                               \
     do {                                                                                        \
-        if (wide) KB_LAUNCH_NT(DS_, 0, kThreadsWide);                                           \
-        else KB_LAUNCH_NT(DS_, 0, kThreadsNarrow);                                              \
+        if (wide) KB_LAUNCH_NT(DS_, 0, kThreadsWide, kRowsWhole);                               \
+        else KB_LAUNCH_NT(DS_, 0, kThreadsNarrow, kRowsWhole);                                  \
     } while (0)
 #define KB_LAUNCH_DS(DS_)                                                                       \
     do {                                                                                        \
@@ -1974,9 +1995,8 @@ hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t s
 #undef KB_LAUNCH_DS
 #undef KB_LAUNCH_VECTOR_ALU
 #undef KB_LAUNCH_MATRIX
+#undef KB_LAUNCH_ROWS
 #undef KB_LAUNCH_NT
-#undef KB_NARROW_ANY
-#undef KB_WIDE_ANY
     return hipGetLastError();
 }
 

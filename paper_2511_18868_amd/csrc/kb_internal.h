@@ -229,28 +229,24 @@ __device__ __forceinline__ float4 load4(const float* p) {
     const f32x4_dword v = *reinterpret_cast<const f32x4_dword*>(p);
     return make_float4(v.x, v.y, v.z, v.w);
 }
-// Features d0 .. d0 + 3 of a row of D features, zeros beyond D, for any D: one 16-byte
-// load that stays inside the row (the last piece is loaded so that it ends with the row
-// and shifted down), so a row whose length is no multiple of 4 costs the load
+// Features d0 .. d0 + 3 of a row of D >= 4 features, zeros beyond D: one 16-byte load
+// that stays inside the row (the last piece is loaded so that it ends with the row and
+// shifted into place), so a row whose length is no multiple of 4 costs the load
 // instructions of one that is.  (Feature by feature, every lane of a wave in a row of
 // its own, the same bytes take four times the load instructions, each of which the
 // address unit splits into 64 lines: a round of 300 searches of 70-1900 rows of 50
 // features 688 us that way and 584 us with these loads, one search of 5128 rows of
 // 59 features 807 and 417 us, the latter with the 768-thread shape that only rows of whole
-// pieces had before.)
-__device__ __forceinline__ float4 row_piece(const float* row, int d0, int D) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (D >= 4) {                                        // (uniform)
-        const int o = d0 < D - 4 ? d0 : D - 4, r = d0 - o;
-        v = load4(row + o);
-        if (r & 1) v = make_float4(v.y, v.z, v.w, 0.f);
-        if (r & 2) v = make_float4(v.z, v.w, 0.f, 0.f);
-        if (r >= 4) v = make_float4(0.f, 0.f, 0.f, 0.f);
-    } else {
-        if (d0 + 0 < D) v.x = row[d0];
-        if (d0 + 1 < D) v.y = row[d0 + 1];
-        if (d0 + 2 < D) v.z = row[d0 + 2];
-    }
+// pieces had before.)  Loading and shifting are apart so that a caller requests all its
+// pieces first.
+__device__ __forceinline__ float4 row_piece_load(const float* row, int d0, int D) {
+    return load4(row + (d0 < D - 4 ? d0 : D - 4));
+}
+__device__ __forceinline__ float4 row_piece_shift(float4 v, int d0, int D) {
+    const int r = d0 > D - 4 ? d0 - (D - 4) : 0;         // features of the piece beyond the row
+    if (r & 1) v = make_float4(v.y, v.z, v.w, 0.f);
+    if (r & 2) v = make_float4(v.z, v.w, 0.f, 0.f);
+    if (r >= 4) v = make_float4(0.f, 0.f, 0.f, 0.f);
     return v;
 }
 
