@@ -1942,6 +1942,26 @@ hipError_t launch_round_wave(const kb_batch& b, const ClusterCall& c, const UcbC
     return launch_wave(b, a, &rd, st);
 }
 
+// Which shape a batch takes.  A search runs 1.7 times as fast with 768 threads and a
+// compute unit to itself, but the chip then gets through 30-40 % fewer rows per second
+// than with three or four 256-thread searches per unit.  So the wide shape pays while
+// the launch lasts as long as its longest search, i.e. while all searches together hold
+// only so many times the rows of the longest one; N / Nmax counts that, whatever the
+// lengths are.  Both shapes measured, a round, narrow / wide (us):
+//   lengths 64-4096, D = 48, K <= 64:   N/Nmax  71: 903 / 504   240: 1046 / 652   350: 1225 / 970
+//                                       960: 1685 / 2470
+//   lengths 70-1900, D = 50, K <= 24:    87: 544 / 341   225: 576 / 419   300: 709 / 558
+//   lengths 1000-1500, D = 32, K <= 32: 246: 383 / 337   420: 403 / 414   630: 483 / 570
+//   lengths 100-500, D = 20, K <= 16:   149: 150 / 139   254: 179 / 197   380: 172 / 259
+// Short searches gain less from more threads (a step is barriers and reductions), hence
+// the lower line for them.  Batches of long searches only (2048 rows or more on average)
+// are 13-20 % faster in the wide shape however many they are.
+constexpr int kWideLoad = 400, kWideLoadShort = 200, kWideShortN = 1024;
+static bool wide_shape(const kb_batch& b) {
+    const int load = b.Nmax >= kWideShortN ? kWideLoad : kWideLoadShort;
+    return b.G <= kWideMaxG || b.N <= (int64_t)load * b.Nmax || b.N >= (int64_t)2048 * b.G;
+}
+
 hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t st) {
     const ClusterArgs a = cluster_args(b, c);
     const int ds = (b.D + 15) / 16;   // 1..4 K-steps of 16 features
@@ -1949,7 +1969,7 @@ hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t s
     if (c.scorer == 1) mt = 0;
     const int rows = (b.D & 3) == 0 ? kRowsWhole : b.D >= 4 ? kRowsRagged : kRowsTiny;
     const size_t lds_wide = lds_layout(a.Kmax, b.D, 16 * ds + 4, a.Nmax, kThreadsWide / kWave).total;
-    const bool wide = (b.G <= kWideMaxG || b.N >= (int64_t)2048 * b.G) && lds_wide <= kMaxLds;
+    const bool wide = wide_shape(b) && lds_wide <= kMaxLds;
     const size_t lds = wide ? lds_wide
                             : lds_layout(a.Kmax, b.D, 16 * ds + 4, a.Nmax, kThreadsNarrow / kWave).total;
     if (lds > kMaxLds) return hipErrorInvalidValue;
