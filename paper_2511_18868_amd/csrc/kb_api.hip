@@ -183,6 +183,9 @@ static kb_status check_ucb(const kb_batch* b, const kb_params* p, const int32_t*
     return KB_OK;
 }
 
+// iterations that one launch runs at most (a call may ask for any number)
+constexpr int32_t kMaxRoundsPerLaunch = 1024;
+
 // device scratch of the selection step
 struct UcbScratch {
     int32_t* order;                 // [G]
@@ -603,7 +606,7 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
     const UcbScratch us = ucb_scratch_in_ws(batch, ws);
     bool tables_valid = false;
     for (int32_t r = 0; r < ip->rounds; ++r) {
-        const bool now = recluster && ((ip->t0 + r) % ip->tau_recluster) == 0;
+        const bool now = recluster && (((int64_t)ip->t0 + r) % ip->tau_recluster) == 0;
         if (now) {
             // K-Means on the frontier wherever |P| >= 2K, then the cluster representatives
             // and the mask their hardware signatures give (Alg. 1; Eq. 5)
@@ -625,6 +628,36 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
         }
         int32_t* sel = io->sel_log + (size_t)r * G * 3;
         int32_t* ksel = io->ksel_log + (size_t)r * G;
+        SampleCall sc;
+        sc.assign = io->assign; sc.alive = io->alive; sc.bound = nullptr; sc.incumbent = nullptr;
+        sc.sel = sel; sc.h = io->h; sc.target = io->target; sc.R = ip->R; sc.theta_sat = ip->theta_sat;
+        sc.seed = ip->sample.seed; sc.draw = ip->sample.draw + (uint64_t)r; sc.tau = ip->sample.tau;
+        sc.ksel = ksel;
+        sc.slot_key = (double*)(base + w.samp_key); sc.slot_idx = (int32_t*)(base + w.samp_idx);
+        if (rounds_in_one_launch(*batch)) {
+            // everything up to the next re-clustering in one launch
+            int32_t n = ip->rounds - r;
+            if (recluster) {
+                const int32_t left = ip->tau_recluster - (int32_t)(((int64_t)ip->t0 + r) % ip->tau_recluster);
+                n = left < n ? left : n;
+            }
+            n = n < kMaxRoundsPerLaunch ? n : kMaxRoundsPerLaunch;
+            if (!have_order && rounds_need_order(*batch)) {
+                if (launch_order(*batch, us.order, us.tile_off, nullptr, st) != hipSuccess) return KB_EDEVICE;
+                have_order = true;
+            }
+            UcbCall uc{};
+            uc.assign = io->assign; uc.alive = io->alive; uc.M = io->M; uc.visits = io->visits;
+            uc.rsum = io->rsum; uc.t = io->t; uc.c = params->c; uc.prior_n = params->prior_n;
+            uc.prior_mu = params->prior_mu; uc.Ncs = io->Ncs; uc.mu = io->mu; uc.ucb = io->ucb;
+            uc.order = us.order;
+            RoundsCall rc;
+            rc.rounds = n; rc.reward = io->reward + (size_t)r * G; rc.ok = io->ok + (size_t)r * G;
+            rc.visits = io->visits; rc.rsum = io->rsum; rc.t = io->t; rc.sel_log = sel; rc.ksel_log = ksel;
+            if (launch_rounds(*batch, uc, sc, rc, st) != hipSuccess) return KB_EDEVICE;
+            r += n - 1;
+            continue;
+        }
         // the cluster-arm tables are rebuilt from the per-candidate history, so they
         // follow every re-clustering; masked UCB argmax (Eq. 6)
         s = do_ucb(batch, params, io->assign, io->alive, nullptr, io->visits, io->rsum, io->t,
@@ -634,12 +667,6 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
         have_order = true;
         tables_valid = true;
         // draw of k_t with the potential theta_sat - h (Sec. 3.4)
-        SampleCall sc;
-        sc.assign = io->assign; sc.alive = io->alive; sc.bound = nullptr; sc.incumbent = nullptr;
-        sc.sel = sel; sc.h = io->h; sc.target = io->target; sc.R = ip->R; sc.theta_sat = ip->theta_sat;
-        sc.seed = ip->sample.seed; sc.draw = ip->sample.draw + (uint64_t)r; sc.tau = ip->sample.tau;
-        sc.ksel = ksel;
-        sc.slot_key = (double*)(base + w.samp_key); sc.slot_idx = (int32_t*)(base + w.samp_idx);
         if (launch_sample(*batch, sc, st) != hipSuccess) return KB_EDEVICE;
         // reward of the generated kernel -> statistics (Alg. 1, last lines)
         if (launch_update_stats(*batch, params->prior_n, sel, ksel, io->reward + (size_t)r * G,

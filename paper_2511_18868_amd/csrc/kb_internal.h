@@ -169,6 +169,25 @@ struct SampleCall {
 };
 hipError_t launch_sample(const kb_batch& b, const SampleCall& c, hipStream_t st);
 
+// Several iterations of Alg. 1 between two re-clusterings - masked selection, draw, update -
+// in one launch: true if the batch allows it (no search of more than 16384 candidates).
+// `order` of the UcbCall is read when rounds_need_order says so; its sel, and sel / ksel of
+// the SampleCall, are not used.
+struct RoundsCall {
+    int rounds;
+    const float* reward;       // [rounds][G]
+    const uint8_t* ok;         // [rounds][G]
+    int32_t* visits;           // the arrays of the UcbCall, advanced by the updates
+    float* rsum;
+    int64_t* t;
+    int32_t* sel_log;          // [rounds][G][3]
+    int32_t* ksel_log;         // [rounds][G]
+};
+bool rounds_in_one_launch(const kb_batch& b);
+bool rounds_need_order(const kb_batch& b);
+hipError_t launch_rounds(const kb_batch& b, const UcbCall& c, const SampleCall& sc, const RoundsCall& rc,
+                         hipStream_t st);
+
 struct GeoCall {
     const float* X;
     const float* cent;

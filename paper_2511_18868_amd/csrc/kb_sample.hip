@@ -16,7 +16,7 @@
 // each such search in index order.  Keys are fp64 and compared exactly, lowest
 // index on ties, so the result does not depend on the cutting.
 #include "kb_internal.h"
-#include "kb_rng_dev.h"
+#include "kb_sample_dev.h"
 
 namespace kb {
 
@@ -24,7 +24,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kNone = 0x7fffffff;
 // Searches of at most short_n candidates are drawn by one wave each (sample_wave).  In a
 // batch of many searches (1024 candidates or fewer on average, so that a range of the
 // range kernels holds several) that is 4096: a lane then walks up to 64 candidates,
@@ -38,47 +37,6 @@ static int sample_short(const kb_batch& b) {
     return b.N <= (int64_t)1024 * b.G ? kSampleShortMany : kShortSearch;
 }
 
-struct SampleArgs {
-    int G, Ksum;
-    int64_t N;
-    const int32_t* seg_off;
-    const int32_t* koff;
-    const int32_t* assign;
-    const uint8_t* alive;      // may be NULL: every candidate alive
-    const float* bound;
-    const float* incumbent;
-    const int32_t* sel;        // [G,3]
-    // paper-form potential (mode 1): V = theta_sat - h[k, target[S*]]
-    const float* h;
-    const int32_t* target;
-    int R, S, mode;
-    float theta_sat;
-    unsigned seed_lo, seed_hi, draw_lo, draw_hi;
-    double tau;
-    int32_t* ksel;             // [G]
-    double* slot_key;          // [2 * ranges]  left slot of range r at 2r, right slot at 2r+1
-    int32_t* slot_idx;         // [2 * ranges]
-    int short_n;               // sample_short() of the batch
-    int mixed;                 // 1: searches of at most short_n candidates go to sample_wave, longer
-                               //    ones to the range kernels, in the same call
-};
-
-// (key, index) pairs ordered by larger key, then lower index; index kNone = empty
-__device__ __forceinline__ bool better(double ka, int ia, double kb_, int ib) {
-    return ia != kNone && (ib == kNone || ka > kb_ || (ka == kb_ && ia < ib));
-}
-
-__device__ __forceinline__ double sample_key(const SampleArgs& a, int k, double pot_scale,
-                                             int tcol) {
-    double V;
-    if (a.mode == 0) {
-        V = 1.0 - (double)a.bound[k] / pot_scale;
-    } else {
-        V = (double)a.theta_sat - (double)a.h[(size_t)k * a.R + tcol];
-    }
-    return V / a.tau + gumbel_variate(a.seed_lo, a.seed_hi, a.draw_lo, a.draw_hi, k);
-}
-
 __global__ void __launch_bounds__(kThreads) sample_range(SampleArgs a) {
     __shared__ double redk[kWaves];
     __shared__ int redi[kWaves];
@@ -87,8 +45,8 @@ __global__ void __launch_bounds__(kThreads) sample_range(SampleArgs a) {
     if (r0 >= a.N) return;
     const int64_t r1 = r0 + kSampleRange < a.N ? r0 + kSampleRange : a.N;
     if (tid == 0) {
-        a.slot_idx[2 * (size_t)blockIdx.x] = kNone;
-        a.slot_idx[2 * (size_t)blockIdx.x + 1] = kNone;
+        a.slot_idx[2 * (size_t)blockIdx.x] = kNoCandidate;
+        a.slot_idx[2 * (size_t)blockIdx.x + 1] = kNoCandidate;
     }
     // largest g with seg_off[g] <= r0
     int lo = 0, hi = a.G;
@@ -111,7 +69,7 @@ __global__ void __launch_bounds__(kThreads) sample_range(SampleArgs a) {
         if (q0 >= q1) continue;
         const int I = a.sel[(size_t)g * 3];
         double bk = 0.0;
-        int bi = kNone;
+        int bi = kNoCandidate;
         if (I >= 0) {
             double pot_scale = 1.0;
             int tcol = 0;
@@ -153,7 +111,7 @@ __global__ void __launch_bounds__(kThreads) sample_range(SampleArgs a) {
         }
         if (tid == 0) {
             if (n0 >= r0 && n1 <= r1) {
-                a.ksel[g] = bi == kNone ? -1 : bi;
+                a.ksel[g] = bi == kNoCandidate ? -1 : bi;
             } else {
                 const size_t slot = 2 * (size_t)blockIdx.x + (n0 < r0 ? 0 : 1);
                 a.slot_key[slot] = bk;
@@ -182,7 +140,7 @@ __global__ void __launch_bounds__(kThreads) sample_final(SampleArgs a) {
         const int oi = a.slot_idx[2 * (size_t)r];
         if (better(ok, oi, bk, bi)) { bk = ok; bi = oi; }
     }
-    a.ksel[g] = bi == kNone ? -1 : bi;
+    a.ksel[g] = bi == kNoCandidate ? -1 : bi;
 }
 
 // Batches of short searches: one wave per search, four searches per workgroup, one
@@ -202,7 +160,7 @@ __global__ void __launch_bounds__(kThreads) sample_wave(SampleArgs a) {
     if (a.mixed && ng > a.short_n) return;         // the range kernels take this search
     const int I = a.sel[(size_t)g * 3];
     double bk = 0.0;
-    int bi = kNone;
+    int bi = kNoCandidate;
     if (I >= 0) {
         double pot_scale = 1.0;
         int tcol = 0;
@@ -225,21 +183,13 @@ __global__ void __launch_bounds__(kThreads) sample_wave(SampleArgs a) {
             if (better(ok, oi, bk, bi)) { bk = ok; bi = oi; }
         }
     }
-    if (lane == 0) a.ksel[g] = bi == kNone ? -1 : bi;
+    if (lane == 0) a.ksel[g] = bi == kNoCandidate ? -1 : bi;
 }
 
 }  // namespace
 
 hipError_t launch_sample(const kb_batch& b, const SampleCall& c, hipStream_t st) {
-    SampleArgs a;
-    a.G = b.G; a.Ksum = b.Ksum; a.N = b.N; a.seg_off = b.seg_off; a.koff = b.koff;
-    a.assign = c.assign; a.alive = c.alive; a.bound = c.bound; a.incumbent = c.incumbent;
-    a.sel = c.sel; a.h = c.h; a.target = c.target; a.R = c.R; a.S = b.S; a.mode = c.h ? 1 : 0;
-    a.theta_sat = c.theta_sat;
-    a.seed_lo = (unsigned)c.seed; a.seed_hi = (unsigned)(c.seed >> 32);
-    a.draw_lo = (unsigned)c.draw; a.draw_hi = (unsigned)(c.draw >> 32);
-    a.tau = (double)c.tau;
-    a.ksel = c.ksel; a.slot_key = c.slot_key; a.slot_idx = c.slot_idx;
+    SampleArgs a = make_sample_args(b, c);
     // a batch of short searches only: a wave per search, one launch; a batch of several
     // searches with longer ones among them: both kernels, each skipping the other's searches
     // (an empty launch of the other kernel costs a few microseconds)

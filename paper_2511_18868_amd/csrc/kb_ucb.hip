@@ -11,6 +11,7 @@
 // rounded to fp32 on output.
 #include "kb_internal.h"
 #include "kb_ucb_dev.h"
+#include "kb_sample_dev.h"
 
 namespace kb {
 
@@ -33,7 +34,7 @@ constexpr int kUcbLong = 16384;     // searches longer than this are cut into ca
 // cluster first, then the rows of the alive ones, then the atomics.
 // EXACT: the pieces of a row are a power of two in number, one per thread of its group
 // (no idle threads and no loop over pieces).
-template <int E, bool EXACT>
+template <int E, bool EXACT, int NT>
 __device__ __forceinline__ void ucb_accumulate_pieces(const UcbArgs& a, int n0, int K, int q0, int q1,
                                                       unsigned* Ncnt, unsigned long long* R,
                                                       unsigned* nalive, unsigned long long* kmin) {
@@ -41,8 +42,8 @@ __device__ __forceinline__ void ucb_accumulate_pieces(const UcbArgs& a, int n0, 
     const int S = a.S;
     const int pieces = S / E;
     int T = 1;
-    while (T < pieces && T < kThreads) T <<= 1;
-    const int rpp = kThreads / T;             // candidates per pass of the workgroup
+    while (T < pieces && T < NT) T <<= 1;
+    const int rpp = NT / T;                   // candidates per pass of the workgroup
     const int sq = tid & (T - 1), row = tid / T;
     constexpr int U = 4;
     for (int pb = q0 + row; pb < q1; pb += rpp * U) {
@@ -105,7 +106,7 @@ __device__ __forceinline__ void ucb_accumulate_pieces(const UcbArgs& a, int n0, 
         if constexpr (EXACT) {
             piece(sq);
         } else {
-            for (int c = sq; c < pieces; c += T) piece(c);     // (one round unless a row has more than 256 pieces)
+            for (int c = sq; c < pieces; c += T) piece(c);     // (one round unless a row has more than NT pieces)
         }
     }
 }
@@ -143,7 +144,7 @@ __global__ void __launch_bounds__(kThreads) ucb_kernel(UcbArgs a) {
     for (int i = tid; i < K; i += kThreads) { kmin[i] = ~0ull; nalive[i] = 0u; }
     __syncthreads();
 
-    ucb_accumulate_pieces<E, EXACT>(a, n0, K, 0, ng, Ncnt, R, nalive, kmin);
+    ucb_accumulate_pieces<E, EXACT, kThreads>(a, n0, K, 0, ng, Ncnt, R, nalive, kmin);
     __syncthreads();
 
     if (a.keep) {
@@ -191,16 +192,261 @@ __global__ void __launch_bounds__(kThreads) ucb_wave(UcbArgs a, int per) {
         ucb_add_candidate(a, (size_t)n0 + p, p, j, a.bound ? a.bound[(size_t)n0 + p] : 0.f, Ncnt, R, nalive, kmin);
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    if (a.keep) {
-        for (int i = lane; i < KS; i += kWave) {
-            a.gN[(size_t)k0 * S + i] = Ncnt[i];
-            a.gR[(size_t)k0 * S + i] = R[i];
-        }
-        for (int i = lane; i < K; i += kWave) { a.gnalive[k0 + i] = nalive[i]; a.gkmin[k0 + i] = kmin[i]; }
-    }
     ucb_finish<kWave>(a, g, n0, k0, K, Ncnt, R, nalive, kmin, nullptr, nullptr, lane);
 }
 
+
+// ---- several iterations of a search in one launch ----------------------------------
+// Between two re-clusterings an iteration of Alg. 1 is selection, draw of k_t and
+// statistics update, each a few microseconds of launch and one search's worth of work;
+// an iteration touches nothing of another search.  So a search runs all of them on its
+// own: the cluster-arm tables are aggregated once into LDS (integer tables: advanced by
+// the update they equal a fresh aggregation bit for bit), the alive members of every
+// cluster are listed once, and an iteration is then a pass over the K S arms, a draw over
+// the members of the chosen cluster, and one cell of the tables - two barriers'
+// worth of latency, bound by the dependent chain (logarithms, square roots, the gathers of
+// h and of the updated cell) and no longer by launches.  Scores, means and counts of
+// all arms are written in the last iteration only; the ones before would be overwritten.
+//
+// Launch by launch an iteration of 183 paper-size searches took 13.5 us and one of 512
+// searches of 64-4096 candidates 34 us; twenty and ten such iterations with their two
+// re-clusterings went 331 -> 147 us and 1779 -> 1422 us.
+//
+// NT threads per search, a workgroup each; or, for short searches, one wave (NT = 64) per
+// search and four searches per workgroup, without any barrier.
+struct RoundsArgs {
+    UcbArgs u;
+    SampleArgs s;               // .sel / .ksel unused (the logs below); draw number of the first iteration
+    int rounds;
+    unsigned long long draw0;
+    const float* reward;        // [rounds][G]
+    const uint8_t* ok;          // [rounds][G]
+    int32_t* visits;            // the history (u.visits, u.rsum), advanced
+    float* rsum;
+    int64_t* t;
+    int32_t* sel_log;           // [rounds][G][3]
+    int32_t* ksel_log;          // [rounds][G]
+    int Nmax;
+};
+
+struct RoundsLds {
+    size_t R, kmin, N, nalive, first, cursor, target, valid, member, total;
+};
+__host__ __device__ inline RoundsLds rounds_lds_layout(int Kmax, int S, int Nmax) {
+    const size_t KS = (size_t)Kmax * S;
+    RoundsLds l;
+    size_t off = 0;
+    l.R = off;      off += KS * 8;
+    l.kmin = off;   off += (size_t)Kmax * 8;
+    l.N = off;      off += KS * 4;
+    l.nalive = off; off += (size_t)Kmax * 4;
+    l.first = off;  off += ((size_t)Kmax + 1) * 4;      // first member of every cluster in `member`
+    l.cursor = off; off += (size_t)Kmax * 4;
+    l.target = off; off += (size_t)S * 4;
+    l.valid = off;  off += (KS + 3) & ~(size_t)3;       // arm allowed by mask and members
+    l.member = off; off += (size_t)Nmax * 2;            // alive members grouped by cluster (N_g <= 16384)
+    l.total = (off + 15) & ~(size_t)15;
+    return l;
+}
+
+template <int NT>
+__device__ __forceinline__ void rounds_sync() {
+    if constexpr (NT > kWave) __syncthreads();
+    else __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+}
+
+// E = 0: a lane owns a whole candidate in the aggregation (the wave form)
+template <int E, bool EXACT, int NT>
+__device__ __forceinline__ void rounds_search(const RoundsArgs& r, int g, unsigned char* smem, double* redv,
+                                              int* redi, int tid) {
+    constexpr int NW = NT / kWave;
+    const UcbArgs& a = r.u;
+    const int S = a.S;
+    int n0, ng, k0, K;
+    search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
+    if (K > a.Kmax) K = a.Kmax;
+    if (ng > r.Nmax) ng = r.Nmax;       // (LDS is sized from the host copy)
+    if (ng <= 0 || K <= 0) {
+        for (int it = tid; it < r.rounds; it += NT) {
+            const size_t at = (size_t)it * a.G + g;
+            for (int q = 0; q < 3; ++q) r.sel_log[at * 3 + q] = -1;
+            r.ksel_log[at] = -1;
+        }
+        if (tid == 0) r.t[g] += r.rounds;
+        return;
+    }
+    const int KS = K * S;
+    const RoundsLds L = rounds_lds_layout(a.Kmax, S, r.Nmax);
+    unsigned long long* R = reinterpret_cast<unsigned long long*>(smem + L.R);
+    unsigned long long* kmin = reinterpret_cast<unsigned long long*>(smem + L.kmin);
+    unsigned* Ncnt = reinterpret_cast<unsigned*>(smem + L.N);
+    unsigned* nalive = reinterpret_cast<unsigned*>(smem + L.nalive);
+    int* first = reinterpret_cast<int*>(smem + L.first);
+    int* cursor = reinterpret_cast<int*>(smem + L.cursor);
+    int* target = reinterpret_cast<int*>(smem + L.target);
+    unsigned char* valid = smem + L.valid;
+    unsigned short* member = reinterpret_cast<unsigned short*>(smem + L.member);
+
+    for (int i = tid; i < KS; i += NT) { R[i] = 0ull; Ncnt[i] = 0u; }
+    for (int i = tid; i < K; i += NT) { kmin[i] = ~0ull; nalive[i] = 0u; cursor[i] = 0; }
+    for (int i = tid; i < S; i += NT) target[i] = clampi(r.s.target[i], 0, r.s.R - 1);
+    rounds_sync<NT>();
+    // tables of the history, and the sizes of the member lists
+    if constexpr (E == 0) {
+        for (int p = tid; p < ng; p += NT) {
+            if (a.alive && !a.alive[(size_t)n0 + p]) continue;
+            int j = a.assign[(size_t)n0 + p];
+            j = (j >= 0 && j < K) ? j : 0;
+            ucb_add_candidate(a, (size_t)n0 + p, p, j, 0.f, Ncnt, R, nalive, kmin);
+        }
+    } else {
+        ucb_accumulate_pieces<E, EXACT, NT>(a, n0, K, 0, ng, Ncnt, R, nalive, kmin);
+    }
+    for (int p = tid; p < ng; p += NT) {
+        const int j = a.assign[(size_t)n0 + p];
+        if (j >= 0 && j < K && (!a.alive || a.alive[(size_t)n0 + p])) atomicAdd(&cursor[j], 1);
+    }
+    long long t = a.t[g];
+    rounds_sync<NT>();
+    for (int i = tid; i < KS; i += NT)
+        valid[i] = nalive[i / S] > 0u && (!a.M || a.M[(size_t)k0 * S + i] != 0);
+    if (tid < kWave) {
+        // exclusive prefix sums of the sizes (K <= 256: four clusters per lane)
+        int c[4], sum = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { c[e] = 4 * tid + e < K ? cursor[4 * tid + e] : 0; sum += c[e]; }
+        int inc = sum;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int up = __shfl_up(inc, o);
+            if (tid >= o) inc += up;
+        }
+        int at = inc - sum;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int j = 4 * tid + e;
+            if (j < K) { first[j] = at; cursor[j] = at; at += c[e]; if (j == K - 1) first[K] = at; }
+        }
+    }
+    rounds_sync<NT>();
+    for (int p = tid; p < ng; p += NT) {
+        const int j = a.assign[(size_t)n0 + p];
+        if (j >= 0 && j < K && (!a.alive || a.alive[(size_t)n0 + p]))
+            member[atomicAdd(&cursor[j], 1)] = (unsigned short)p;    // (in any order: the draw compares indices)
+    }
+    rounds_sync<NT>();
+
+    for (int it = 0; it < r.rounds; ++it) {
+        const bool last = it == r.rounds - 1;
+        const size_t at = (size_t)it * a.G + g;
+        const float reward = r.reward[at];           // (requested before they are needed)
+        const bool ok = r.ok[at] != 0;
+        const long long tg = t + it < 1 ? 1 : t + it;
+        const double lnt = log((double)tg);
+        double bu = -INFINITY;
+        int bf = -1;
+        for (int i = tid; i < KS; i += NT) {
+            const unsigned n = Ncnt[i];
+            double m;
+            const double u = ucb_score(a, n, R[i], valid[i] != 0, lnt, m);
+            if (last) {
+                const size_t o = (size_t)k0 * S + i;
+                a.Ncs[o] = (int32_t)n;
+                a.mu[o] = (float)m;
+                a.ucb[o] = (float)u;
+            }
+            if (valid[i] && (bf < 0 || u > bu)) { bu = u; bf = i; }
+        }
+        // argmax, lowest flat index on ties; every thread gets it
+        auto merge_arm = [&](double ou, int of) {
+            if (of >= 0 && (bf < 0 || ou > bu || (ou == bu && of < bf))) { bu = ou; bf = of; }
+        };
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) merge_arm(__shfl_xor(bu, o), __shfl_xor(bf, o));
+        if constexpr (NT > kWave) {
+            if ((tid & 63) == 0) { redv[tid >> 6] = bu; redi[tid >> 6] = bf; }
+            __syncthreads();
+            bu = redv[0]; bf = redi[0];
+            for (int w = 1; w < NW; ++w) merge_arm(redv[w], redi[w]);
+        }
+        const int I = bf >= 0 ? bf / S : -1, s = bf >= 0 ? bf - I * S : -1;
+        if (tid == 0) {
+            r.sel_log[at * 3 + 0] = I;
+            r.sel_log[at * 3 + 1] = s;
+            r.sel_log[at * 3 + 2] = bf >= 0 ? n0 + (int)(unsigned)(kmin[I] & 0xffffffffull) : -1;
+        }
+        int k = kNoCandidate;
+        if (I >= 0) {                                // (uniform over the search's threads)
+            // A key that is not a number loses to every other, except that of the first
+            // member, which then stays chosen: the result of scanning the members in order.
+            const int lead = n0 + (int)(unsigned)(kmin[I] & 0xffffffffull);
+            SampleArgs sa = r.s;
+            const unsigned long long draw = r.draw0 + (unsigned long long)it;
+            sa.draw_lo = (unsigned)draw; sa.draw_hi = (unsigned)(draw >> 32);
+            const int tcol = target[s];
+            const int m1 = first[I + 1];
+            double bk = 0.0;
+            for (int q = first[I] + tid; q < m1; q += NT) {
+                const int p = n0 + member[q];
+                double key = sample_key(sa, p, 1.0, tcol);
+                if (!(key == key)) key = p == lead ? INFINITY : -INFINITY;
+                if (better(key, p, bk, k)) { bk = key; k = p; }
+            }
+            auto merge_key = [&](double ok2, int oi) {
+                if (better(ok2, oi, bk, k)) { bk = ok2; k = oi; }
+            };
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) merge_key(__shfl_xor(bk, o), __shfl_xor(k, o));
+            if constexpr (NT > kWave) {
+                // (slots of their own: the first reduction's may still be read)
+                if ((tid & 63) == 0) { redv[NW + (tid >> 6)] = bk; redi[NW + (tid >> 6)] = k; }
+                __syncthreads();
+                bk = redv[NW]; k = redi[NW];
+                for (int w = 1; w < NW; ++w) merge_key(redv[NW + w], redi[NW + w]);
+            }
+        }
+        if (tid == 0) r.ksel_log[at] = k == kNoCandidate ? -1 : k;
+        // statistics update (as in update_stats_kernel): by the thread that wrote the arm's
+        // score, so that its stores to an arm and to the arm's cells stay in order
+        if (ok && k != kNoCandidate && tid == bf % NT) {
+            const double rw = (double)reward;
+            if (last) {
+                const size_t arm = (size_t)k0 * S + bf;
+                const int nn = (int32_t)Ncnt[bf] + 1;
+                const double m = (double)a.mu[arm];
+                a.Ncs[arm] = nn;
+                a.mu[arm] = (float)(m + (rw - m) / ((double)nn + (double)a.prior_n));
+            }
+            const size_t cell = (size_t)k * S + s;
+            r.visits[cell] += 1;
+            const float r_old = r.rsum[cell];
+            const float r_new = (float)((double)r_old + rw);
+            r.rsum[cell] = r_new;
+            Ncnt[bf] += 1u;
+            R[bf] += reward_fixed(r_new) - reward_fixed(r_old);
+        }
+        rounds_sync<NT>();
+    }
+    if (tid == 0) r.t[g] = t + r.rounds;
+}
+
+template <int E, bool EXACT, int NT>
+__global__ void __launch_bounds__(NT) rounds_kernel(RoundsArgs r) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double redv[2 * NT / kWave];
+    __shared__ int redi[2 * NT / kWave];
+    int g = r.u.order ? r.u.order[blockIdx.x] : (int)blockIdx.x;
+    g = clampi(g, 0, r.u.G - 1);
+    rounds_search<E, EXACT, NT>(r, g, smem, redv, redi, (int)threadIdx.x);
+}
+
+__global__ void __launch_bounds__(kThreads) rounds_wave(RoundsArgs r, int per) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = (int)blockIdx.x * kWaves + wv;
+    if (g >= r.u.G) return;               // (a whole wave leaves: no wave waits for another in this kernel)
+    rounds_search<0, false, kWave>(r, g, smem + (size_t)wv * per, nullptr, nullptr, (int)(threadIdx.x & 63));
+}
 
 // ---- searches too long for one workgroup: partial tables per candidate range,
 // ---- merged in global memory with integer atomics (still order-independent)
@@ -248,7 +494,7 @@ __global__ void __launch_bounds__(kThreads) ucb_partial(UcbArgs a) {
         for (int i = tid; i < KS; i += kThreads) { R[i] = 0ull; Ncnt[i] = 0u; }
         for (int i = tid; i < K; i += kThreads) { kmin[i] = ~0ull; nalive[i] = 0u; }
         __syncthreads();
-        ucb_accumulate_pieces<E, EXACT>(a, n0, K, (int)(q0 - n0), (int)(q1 - n0), Ncnt, R, nalive, kmin);
+        ucb_accumulate_pieces<E, EXACT, kThreads>(a, n0, K, (int)(q0 - n0), (int)(q1 - n0), Ncnt, R, nalive, kmin);
         __syncthreads();
         for (int i = tid; i < KS; i += kThreads) {
             if (Ncnt[i]) atomicAdd(&a.gN[(size_t)k0 * S + i], Ncnt[i]);
@@ -380,6 +626,55 @@ hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
         return hipGetLastError();
     }
     return launch_search_kernel(a, lds, st);
+}
+
+static size_t rounds_lds(const kb_batch& b) {
+    return rounds_lds_layout(b.Kmax > 0 ? b.Kmax : 1, b.S, b.Nmax).total;
+}
+static bool rounds_wave_per_search(const kb_batch& b) {
+    return b.Nmax <= kShortSearch && rounds_lds(b) * kWaves <= 64 * 1024;
+}
+bool rounds_in_one_launch(const kb_batch& b) {
+    return b.G > 0 && b.Nmax <= kUcbLong && rounds_lds(b) + 1024 <= 160 * 1024;
+}
+bool rounds_need_order(const kb_batch& b) { return b.G > 1 && !rounds_wave_per_search(b); }
+
+// Batches of up to two searches per compute unit give every search 1024 threads, larger ones 256.
+constexpr int kRoundsWideMaxG = 512;
+
+template <int NT>
+static hipError_t launch_rounds_nt(const RoundsArgs& r, size_t lds, hipStream_t st) {
+    const auto go = [&](auto kern) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)r.u.G), dim3(NT), lds, st, r);
+        return hipGetLastError();
+    };
+    switch (row_form(r.u.S)) {
+        case 0: return go(rounds_kernel<4, true, NT>);
+        case 1: return go(rounds_kernel<4, false, NT>);
+        case 2: return go(rounds_kernel<2, false, NT>);
+        default: return go(rounds_kernel<1, false, NT>);
+    }
+}
+
+hipError_t launch_rounds(const kb_batch& b, const UcbCall& c, const SampleCall& sc, const RoundsCall& rc,
+                         hipStream_t st) {
+    if (!rounds_in_one_launch(b) || c.bound || !sc.h || rc.rounds < 1) return hipErrorInvalidValue;
+    RoundsArgs r;
+    r.u = make_ucb_args(b, c);
+    r.s = make_sample_args(b, sc);
+    r.rounds = rc.rounds; r.draw0 = sc.draw; r.reward = rc.reward; r.ok = rc.ok;
+    r.visits = rc.visits; r.rsum = rc.rsum; r.t = rc.t; r.sel_log = rc.sel_log; r.ksel_log = rc.ksel_log;
+    r.Nmax = b.Nmax;
+    const size_t lds = rounds_lds(b);
+    if (rounds_wave_per_search(b)) {
+        hipLaunchKernelGGL(rounds_wave, dim3((unsigned)((b.G + kWaves - 1) / kWaves)), dim3(kThreads),
+                           lds * kWaves, st, r, (int)lds);
+        return hipGetLastError();
+    }
+    return b.G <= kRoundsWideMaxG ? launch_rounds_nt<1024>(r, lds, st) : launch_rounds_nt<256>(r, lds, st);
 }
 
 }  // namespace kb

@@ -73,6 +73,18 @@ __device__ __forceinline__ void ucb_add_candidate(const UcbArgs& a, size_t row, 
     atomicMin(&kmin[j], ((unsigned long long)ordered_bits(bd) << 32) | (unsigned)p);
 }
 
+// Mean reward `m` and UCB index (returned) of an arm with n visits and the reward sum R,
+// lnt = ln t of its search.
+__device__ __forceinline__ double ucb_score(const UcbArgs& a, unsigned n, unsigned long long R, bool valid,
+                                            double lnt, double& m) {
+    const double pn = (double)a.prior_n, pm = (double)a.prior_mu, cc = (double)a.c;
+    const double nt = (double)n + pn;
+    const double rt = (double)(long long)R * kRewardInv + pn * pm;
+    m = nt > 0.0 ? rt / nt : NAN;
+    if (!valid) return -INFINITY;
+    return nt > 0.0 ? m + cc * sqrt(lnt / nt) : INFINITY;
+}
+
 // Scores, outputs and selection of one search from its accumulated tables
 // (which may live in LDS or in global memory).  Called by a whole workgroup of NT
 // threads, or, with NT = 64, by one wave on its own (tid = the lane; redv and redi
@@ -87,21 +99,15 @@ __device__ __forceinline__ void ucb_finish(const UcbArgs& a, int g, int n0, int 
     long long tg = a.t[g];
     if (tg < 1) tg = 1;
     const double lnt = log((double)tg);
-    const double pn = (double)a.prior_n, pm = (double)a.prior_mu, cc = (double)a.c;
 
     double bu = -INFINITY;
     int bf = -1;
     for (int i = tid; i < KS; i += NT) {
         const int cl = i / S;
         const unsigned n = Ncnt[i];
-        const double nt = (double)n + pn;
-        const double rt = (double)(long long)R[i] * kRewardInv + pn * pm;
-        const double m = nt > 0.0 ? rt / nt : NAN;
-        double u;
         const bool valid = nalive[cl] > 0u && (!a.M || a.M[(size_t)k0 * S + i] != 0);
-        if (!valid) u = -INFINITY;
-        else if (nt > 0.0) u = m + cc * sqrt(lnt / nt);
-        else u = INFINITY;
+        double m;
+        const double u = ucb_score(a, n, R[i], valid, lnt, m);
         const size_t o = (size_t)k0 * S + i;
         a.Ncs[o] = (int32_t)n;
         a.mu[o] = (float)m;

@@ -1,0 +1,75 @@
+"""The iterations between two re-clusterings, which kb_iterate runs in one launch, against
+the same stages called one by one (masked selection, draw, update): every output of
+every round byte for byte, over the strategy counts that select the forms of the
+aggregation and over the batch sizes that select wave, narrow and wide workgroups."""
+import numpy as np
+import pytest
+
+from paper_2511_18868_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def kb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2511_18868_amd import binding
+    binding.lib()
+    return binding
+
+
+def _batch(shape, S):
+    if shape == "wave":           # a wave per search; 183 searches fill no whole workgroup at the end
+        return synth.config5(G=183, nmin=2, nmax=70, D=8, S=S, kcap=6, kdiv=2, iters=3, seed=301)
+    if shape == "waveedge":       # the longest searches a wave takes, and searches of one candidate
+        return synth.config5(G=37, nmin=1, nmax=256, D=8, S=S, kcap=16, kdiv=1, iters=3, seed=302)
+    if shape == "wide":           # 257 candidates and more, few searches
+        return synth.config5(G=9, nmin=200, nmax=4100, D=8, S=S, kcap=64, kdiv=16, iters=3, seed=303)
+    if shape == "narrow":         # more searches than the wide form takes
+        return synth.config5(G=520, nmin=40, nmax=600, D=8, S=S, kcap=24, kdiv=16, iters=3, seed=304)
+    return synth.config2(seed=305, N=16384, D=8, K=2, S=S, iters=3)     # the longest search of one workgroup
+
+
+@pytest.mark.parametrize("S", [1, 6, 12, 32])
+@pytest.mark.parametrize("shape", ["wave", "waveedge", "wide", "narrow", "longest"])
+def test_rounds_in_one_launch_equal_the_stages_one_by_one(kb, shape, S):
+    import torch
+    b = _batch(shape, S)
+    T, R = 5, 3
+    h, target, _ = synth.signatures(b, R)
+    theta = 0.9                   # (few arms masked)
+    fb = [synth.feedback(b, seed=r) for r in range(T)]
+    rw, ok = np.stack([f[0] for f in fb]), np.stack([f[1] for f in fb])
+    alive = (np.arange(b.N) % 4 != 1).astype(np.uint8)
+
+    def start():
+        d = kb.DeviceBatch(b)
+        up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(d.device)  # noqa: E731
+        d.cluster()
+        d.cluster_geometry()
+        arr = dict(h=up(h), target=up(target), rw=up(rw), ok=up(ok), alive=up(alive))
+        kb.kb_strategy_mask(d.batch, R, arr["h"], arr["target"], d.rep, theta, d.M, d.nvalid)
+        return d, arr
+
+    d, x = start()
+    sel_log = torch.full((T, b.G, 3), -7, dtype=torch.int32, device=d.device)
+    ksel_log = torch.full((T, b.G), -7, dtype=torch.int32, device=d.device)
+    ip = kb.kb_iterate_params(T, 0, 0, 0, R, theta, kb.kb_sample_params(5, 40, 0.7))
+    d.iterate(ip, x["h"], x["target"], x["rw"], x["ok"], sel_log, ksel_log, alive=x["alive"])
+
+    e, y = start()
+    for r in range(T):
+        kb.kb_ucb_select_masked(e.batch, e.params, e.assign, y["alive"], None, e.M, e.visits, e.rsum, e.t,
+                                e.Ncs, e.mu, e.ucb, e.sel, e.ws, e.ws_bytes)
+        kb.kb_sample_signature(e.batch, kb.kb_sample_params(5, 40 + r, 0.7), e.assign, y["alive"], R,
+                               y["h"], y["target"], theta, e.sel, e.ksel, e.ws, e.ws_bytes)
+        torch.testing.assert_close(sel_log[r], e.sel, rtol=0, atol=0)
+        torch.testing.assert_close(ksel_log[r], e.ksel, rtol=0, atol=0)
+        kb.kb_update_stats(e.batch, e.params, e.sel, e.ksel, y["rw"][r], y["ok"][r], e.visits, e.rsum,
+                           e.Ncs, e.mu, e.t)
+    assert (ksel_log >= 0).any()
+    for name in ("visits", "rsum", "t", "Ncs", "mu", "ucb"):
+        a, c = d.host(name), e.host(name)
+        np.testing.assert_array_equal(a.view(np.uint8), c.view(np.uint8), err_msg=name)
