@@ -40,6 +40,7 @@
 // fp32; an empty cluster keeps its centroid.
 #include "kb_cluster_dev.h"
 #include "kb_ucb_dev.h"
+#include "kb_wave_dev.h"
 
 namespace kb {
 
@@ -80,66 +81,6 @@ constexpr int kRowsWhole = 0, kRowsRagged = 1, kRowsTiny = 2;
 constexpr int kFlagCap = 256;      // LDS list of candidates waiting for the exact pass
 constexpr int kMoverBatch = 8;     // movers whose rows are requested together
 constexpr int kQueue = 128;        // per wave: candidates waiting to be scored (at most 31 + 64 at a time)
-
-// Cross-lane steps inside rows of 16 lanes (data-parallel primitives: no LDS
-// traffic): lanes 1,0,3,2 and 2,3,0,1 of every four, then mirrors inside every
-// eight and every sixteen.  After the four steps every lane of a row holds the
-// row's result; rows are combined through scalar registers.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = (int)(unsigned)b, hi = (int)(b >> 32);
-    const unsigned lo2 = (unsigned)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
-    const unsigned hi2 = (unsigned)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
-    return __longlong_as_double((long long)(((unsigned long long)hi2 << 32) | lo2));
-}
-__device__ __forceinline__ float row_max_f(float v) {
-    v = fmaxf(v, dpp_f<0xB1>(v));
-    v = fmaxf(v, dpp_f<0x4E>(v));
-    v = fmaxf(v, dpp_f<0x141>(v));
-    v = fmaxf(v, dpp_f<0x140>(v));
-    return v;
-}
-__device__ __forceinline__ float row_min_f(float v) {
-    v = fminf(v, dpp_f<0xB1>(v));
-    v = fminf(v, dpp_f<0x4E>(v));
-    v = fminf(v, dpp_f<0x141>(v));
-    v = fminf(v, dpp_f<0x140>(v));
-    return v;
-}
-// sum over the 16 lanes of a row, in a fixed order, delivered to all 16
-__device__ __forceinline__ double row_sum_d(double v) {
-    v += dpp_d<0xB1>(v);
-    v += dpp_d<0x4E>(v);
-    v += dpp_d<0x141>(v);
-    v += dpp_d<0x140>(v);
-    return v;
-}
-__device__ __forceinline__ float lane_f(float v, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-__device__ __forceinline__ double lane_d(double v, int l) {
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ float wave_max_f(float v) {
-    v = row_max_f(v);
-    return fmaxf(fmaxf(lane_f(v, 0), lane_f(v, 16)), fmaxf(lane_f(v, 32), lane_f(v, 48)));
-}
-__device__ __forceinline__ float wave_min_f(float v) {
-    v = row_min_f(v);
-    return fminf(fminf(lane_f(v, 0), lane_f(v, 16)), fminf(lane_f(v, 32), lane_f(v, 48)));
-}
-__device__ __forceinline__ double wave_sum_d(double v) {
-    v = row_sum_d(v);
-    return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
-}
 
 // Block-wide reductions over the NW waves of a workgroup.  `red` is LDS scratch of
 // 2 * NW doubles used as two alternating slots (`phase` counts the calls,

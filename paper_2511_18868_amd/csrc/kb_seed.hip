@@ -6,15 +6,26 @@
 //
 // One workgroup per search, K_g passes over the search's rows.  A thread owns the
 // rows tid, tid + 512, ...  The first R of them are read once and stay in
-// registers for all passes, together with their running minima (R x 512 rows,
-// 2048 at 48 features: a whole search in most cases, and the workgroup then
-// touches memory only for the newest centroid); rows beyond that are streamed
-// again in every pass, four in flight per thread, with their minima in the
-// workspace.  Per pass a row's squared distance to the newest centroid is formed
-// exactly as the plain definition does (fp64, direct differences, summed over the
-// features in index order with separate multiply and add); the workgroup reduces
-// to the maximum with the lowest index on ties.  Distances are exact, so the
-// choice needs no tolerance.
+// registers for all passes (R x 512 rows, 1536 at 48 features), the next ones in LDS;
+// rows beyond that are streamed again in every pass.
+//
+// The definition is in fp64: squared distances from direct differences, summed over the
+// features in index order with separate multiply and add, the largest running minimum
+// (or, for the D^2-weighted draw, the largest ln(minimum) + Gumbel variate), lowest
+// index on ties.  A pass forms all of that in fp32 only - a sum of non-negative terms
+// is good to (D + 2) 2^-24 of itself, a key to 5e-5 - and keeps best and second best.
+// If no other row comes within a margin of several times those errors, the best is the
+// definition's choice.  Otherwise ("contested", about one pass in a thousand on data
+// without repeated rows) the rows within the margin get their fp64 values; a row's fp64
+// minimum is brought up to date only then, from the centroid it was left at, so a search
+// full of repeated rows costs no more fp64 work than forming it in every pass did.
+// In fp64 throughout a row and pass was 48 conversions, 144 fp64 operations and three
+// fp64 logarithms; in fp32 it is 96 operations, the counter-based generator (17 32-bit
+// multiplications, a quarter of the rate each) and two hardware logarithms.  1024 searches
+// of 64-4096 rows of 48 features, D^2-weighted: 1672 -> 665 us; what bounds it now is the
+// latency of a pass in short searches (2.6 us: two barriers, the reduction, the generator)
+// and the streamed rows in the longest.  The register share R is as large as fits without
+// spilling (one more row per thread: 256 searches of 2048 rows 320 -> 455 us).
 //
 // Searches longer than kBigRows rows would keep one compute unit busy for K_g
 // passes over memory; they take one launch per centroid instead.  The candidate
@@ -25,6 +36,7 @@
 // pairs alternate between launches.
 #include "kb_internal.h"
 #include "kb_rng_dev.h"
+#include "kb_wave_dev.h"
 
 namespace kb {
 
@@ -38,13 +50,22 @@ constexpr int kRange = 1024;       // its rows per workgroup (at most kBigRows, 
                                    // it, one that begins inside)
 constexpr int kBigThreads = 256;
 constexpr int kNone = 0x7fffffff;
+constexpr int kListed = 64;        // rows of a contest that are settled a wave at a time
 // rows a workgroup keeps in LDS after the registers are full: padded to 16 DS + 4
 // words (16-byte reads of consecutive rows fall into different banks), at most
-// two per thread, within 155 KB
+// two per thread, within 140 KB; the fp32 minima of the streamed rows lie behind them
 constexpr int lds_stride(int DS) { return 16 * DS + 4; }
 constexpr int lds_rows(int DS) {
-    return 158720 / (4 * lds_stride(DS)) < 2 * kThreads ? 158720 / (4 * lds_stride(DS)) : 2 * kThreads;
+    return 143360 / (4 * lds_stride(DS)) < 2 * kThreads ? 143360 / (4 * lds_stride(DS)) : 2 * kThreads;
 }
+constexpr int streamed_rows(int DS, int R) {
+    return kBigRows > R * kThreads + lds_rows(DS) ? kBigRows - R * kThreads - lds_rows(DS) : 0;
+}
+// Fast keys are log2(minimum) - log2(-log2 u).  Outside these bounds of the largest one
+// an fp32 minimum may have lost its relative accuracy to underflow or overflow (a variate
+// lies between -6 and 53): every row is then formed in fp64.
+constexpr float kKeyLow = -40.f, kKeyHigh = 100.f, kKeyMargin = 0x1p-11f;
+constexpr float kFarLow = 0x1p-100f, kFarHigh = 0x1p100f;
 
 struct SeedArgs {
     int G, D, Ksum;
@@ -55,6 +76,7 @@ struct SeedArgs {
     float* cent;
     int32_t* pick;       // may be NULL
     double* mind;        // [N] running minimum of every candidate
+    int32_t* upto;       // [N] one-workgroup path: centroids that minimum has seen
     const int32_t* order;
     // randomised (D^2-weighted) seeding instead of the farthest point
     int dsquared;
@@ -74,90 +96,240 @@ __device__ __forceinline__ double add_sq(double acc, float x, double c) {
     return __dadd_rn(acc, __dmul_rn(diff, diff));
 }
 
+// Features d .. d + 3 of a row, zeros beyond D: one 16-byte load whatever D is (rows
+// start at multiples of 4 bytes: load4).  `inside`: the piece ends inside the row.
+__device__ __forceinline__ float4 row_piece(const float* row, int d, int D, bool inside) {
+    if (inside) return load4(row + d);
+    if (D >= 4) return row_piece_shift(row_piece_load(row, d, D), d, D);
+    return d > 0 ? make_float4(0.f, 0.f, 0.f, 0.f)
+                 : make_float4(row[0], D > 1 ? row[1] : 0.f, D > 2 ? row[2] : 0.f, 0.f);
+}
+__device__ __forceinline__ float add_sq4(float acc, const float4& x, const float4& c) {
+    const float e0 = x.x - c.x, e1 = x.y - c.y, e2 = x.z - c.z, e3 = x.w - c.w;
+    return fmaf(e3, e3, fmaf(e2, e2, fmaf(e1, e1, fmaf(e0, e0, acc))));
+}
+
+// log2(E) of the exponential variate E = -ln u behind gumbel_variate, up to the constant
+// log2(ln 2), to 3e-5: u from its 32 leading bits, with a series where u is so close to 1
+// that its logarithm would cancel, and in fp64 for the one variate in 10^7 whose
+// leading bits do not determine it well enough.
+__device__ __forceinline__ float log2_exponential(unsigned seed_lo, unsigned seed_hi, unsigned draw_lo,
+                                                  unsigned draw_hi, int k) {
+    unsigned x0, x1;
+    philox4x32_10((unsigned)k, 0u, draw_lo, draw_hi, seed_lo, seed_hi, x0, x1);
+    const unsigned nx = ~x0;
+    const float u = fmaf((float)x0, 0x1p-32f, 0x1p-33f), v = fmaf((float)nx, 0x1p-32f, 0x1p-33f);
+    const float near1 = v * fmaf(v, fmaf(v, 0.333333343f, 0.5f), 1.f) * 1.44269502f;
+    const float E = nx < 0x04000000u ? near1 : -__builtin_amdgcn_logf(u);
+    float l = __builtin_amdgcn_logf(E);
+    if (x0 < 256u || nx < 256u)
+        l = (float)((-gumbel_variate(seed_lo, seed_hi, draw_lo, draw_hi, k) - log(M_LN2)) * M_LOG2E);
+    return l;
+}
+
 // DS: features padded to 16 DS (zeros add +0.0 to a sum); R: rows per thread kept in registers
 template <int DS, int R, bool DSQ>
 __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
     constexpr int Q = 4 * DS;
     constexpr int RS = lds_stride(DS), LROWS = lds_rows(DS), LV = (LROWS + kThreads - 1) / kThreads;
+    constexpr int FIRST = R * kThreads + LROWS;        // first streamed row
     extern __shared__ __align__(16) float lx[];        // [LROWS][RS]
+    float* ms = lx + (size_t)LROWS * RS;               // [streamed_rows] minima of the streamed rows
     __shared__ __align__(16) float c[16 * DS];
+    __shared__ unsigned short picks[kBigRows];         // rows chosen so far (K <= N_g)
+    __shared__ float redf[kWaves];
+    __shared__ int redk[kWaves];                       // the row, or -1 - row if contested inside the wave
     __shared__ double redv[kWaves];
     __shared__ int redi[kWaves];
+    __shared__ int nlist;
+    __shared__ unsigned short list[kListed];           // rows of a contest
     const int tid = threadIdx.x;
     const int D = a.D;
-    const bool vec = (D & 3) == 0;
     int g = a.order ? a.order[blockIdx.x] : (int)blockIdx.x;
     g = clampi(g, 0, a.G - 1);
     int n0, ng, k0, K;
     search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
     if (ng <= 0 || K <= 0 || ng > kBigRows) return;
+    if (K > kBigRows) K = kBigRows;      // (more clusters than candidates: not a consistent batch)
     const float* Xg = a.X + (size_t)n0 * D;
     double* mind = a.mind + n0;
+    int32_t* upto = a.upto + n0;
+    const float far_keep = 1.f - 4.f * (float)(D + 4) * 0x1p-24f;     // farthest point: margin of a contest
+
+    // what a row offers in draw `drawn`: its minimum (farthest point) or its fast key
+    auto offer = [&](float m, int k, unsigned long long drawn) {
+        if constexpr (!DSQ) return m;
+        // (opaque: the generator's first products, the same in every pass, would be kept
+        // in registers for every row)
+        asm volatile("" : "+v"(k));
+        return __builtin_amdgcn_logf(m) - log2_exponential(a.seed_lo, a.seed_hi, (unsigned)drawn,
+                                                           (unsigned)(drawn >> 32), n0 + k);
+    };
+    float best, second;         // this thread's best and second best offer
+    int arg;
+    auto take = [&](float v, int k) {
+        const bool gt = v > best;               // (false for a NaN, which is never chosen)
+        second = gt ? best : fmaxf(second, v);
+        arg = gt ? k : arg;
+        best = gt ? v : best;
+    };
+    // The row to choose: the one with the best offer, if nothing else comes close.  Every
+    // thread returns the row, or -1 for a contest over the rows that offer `thr` or more.
+    // (One barrier: every thread merges the waves' results itself.  The slots are written
+    // again only after the barrier that follows the staging of the next centroid.)
+    auto keep_from = [&](float m) { return DSQ ? m - kKeyMargin : m * far_keep; };
+    auto choose = [&](float& thr) {
+        const float m = wave_max_f(best);
+        const float t = keep_from(m);
+        const unsigned long long same = __ballot(best >= t);
+        const unsigned long long top = __ballot(best == m);
+        const bool alone = __popcll(same) == 1 && !__any(second >= t);
+        const int row = __builtin_amdgcn_readlane(arg, top ? __ffsll((long long)top) - 1 : 0);
+        if ((tid & 63) == 0) { redf[tid >> 6] = m; redk[tid >> 6] = alone ? row : -1 - row; }
+        __syncthreads();
+        float bm = redf[0];
+        int bk = redk[0];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) {
+            const float om = redf[w];
+            bk = om > bm ? redk[w] : bk;
+            bm = om > bm ? om : bm;
+        }
+        thr = keep_from(bm);
+        int close = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) close += redf[w] >= thr ? 1 : 0;
+        const bool sane = DSQ ? (bm > kKeyLow && bm < kKeyHigh) : (bm > kFarLow && bm < kFarHigh);
+        if (!sane) thr = -INFINITY;             // every row
+        return sane && close == 1 && bk >= 0 && bk < ng ? bk : -1;
+    };
+    // A contest: the definition's choice among the rows that offer thr or more.  A few of
+    // them (the usual case) take a wave each, lanes over the j + 1 centroids chosen so far
+    // (none for the first draw, whose keys are the variates alone).  When they are many,
+    // their owners bring their fp64 minima up to date, from the centroid each was left at.
+    double far;
+    int farg;
+    auto sq_dist = [&](const float* row, const float* cr) {
+        double acc = 0.0;
+        for (int d0 = 0; d0 < D; d0 += 16) {
+            float4 xv[4], cv[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int d = d0 + 4 * q;
+                xv[q] = row_piece(row, d, D, false);
+                cv[q] = row_piece(cr, d, D, false);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {                // (+0.0 beyond D)
+                acc = add_sq(acc, xv[q].x, (double)cv[q].x);
+                acc = add_sq(acc, xv[q].y, (double)cv[q].y);
+                acc = add_sq(acc, xv[q].z, (double)cv[q].z);
+                acc = add_sq(acc, xv[q].w, (double)cv[q].w);
+            }
+        }
+        return acc;
+    };
+    auto settle = [&](double mn, int k, int j, unsigned long long drawn) {
+        double key = mn;
+        if constexpr (DSQ)
+            key = (j >= 0 ? log(mn) : 0.0) + gumbel_variate(a.seed_lo, a.seed_hi, (unsigned)drawn,
+                                                             (unsigned)(drawn >> 32), n0 + k);
+        if (key > far || (key == far && k < farg)) { far = key; farg = k; }
+    };
+    // minima are formed as m = m < d ? m : d centroid by centroid, so a NaN is forgotten
+    // with the next centroid's distance
+    auto contest_wave = [&](int k, int j, unsigned long long drawn) {
+        const int lane = tid & 63;
+        double mn = INFINITY;
+        for (int i0 = 0; i0 <= j; i0 += 64) {
+            const bool in = i0 + lane <= j;
+            const double acc = sq_dist(Xg + (size_t)k * D, Xg + (size_t)picks[in ? i0 + lane : j] * D);
+            const unsigned long long nan = __ballot(in && acc != acc);
+            const int last = nan ? 63 - __clzll((long long)nan) : -1;
+            double m = in && lane > last ? acc : INFINITY;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                const double om = __shfl_xor(m, o);
+                m = om < m ? om : m;
+            }
+            if (nan) mn = NAN;
+            if (!nan || i0 + last < (j < i0 + 63 ? j : i0 + 63)) mn = mn < m ? mn : m;
+        }
+        settle(mn, k, j, drawn);
+    };
+    auto contest_owner = [&](int k, int j, unsigned long long drawn) {
+        double mn = INFINITY;
+        if (j >= 0) {
+            int i = upto[k];
+            if (i > 0) mn = mind[k];
+            for (; i <= j; ++i) {
+                const double acc = sq_dist(Xg + (size_t)k * D, Xg + (size_t)picks[i] * D);
+                mn = mn < acc ? mn : acc;
+            }
+            mind[k] = mn;
+            upto[k] = j + 1;
+        }
+        settle(mn, k, j, drawn);
+    };
     // largest (value, lowest index) of the workgroup; every thread returns the index.
-    // (One barrier: every thread merges the waves' results itself.  The slots are
-    // written again only after the barrier that follows the staging of the next
-    // centroid, which every thread passes after it has read them.)
-    auto block_argmax = [&](double far, int arg) {
+    // (The slots are read before the barrier that follows the next staging.)
+    auto block_argmax = [&]() {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             const double of = __shfl_xor(far, o);
-            const int oa = __shfl_xor(arg, o);
-            if (of > far || (of == far && oa < arg)) { far = of; arg = oa; }
+            const int oa = __shfl_xor(farg, o);
+            if (of > far || (of == far && oa < farg)) { far = of; farg = oa; }
         }
-        if ((tid & 63) == 0) { redv[tid >> 6] = far; redi[tid >> 6] = arg; }
+        if ((tid & 63) == 0) { redv[tid >> 6] = far; redi[tid >> 6] = farg; }
         __syncthreads();
-        far = redv[0]; arg = redi[0];
+        far = redv[0]; farg = redi[0];
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) {
             const double of = redv[w];
             const int oa = redi[w];
-            if (of > far || (of == far && oa < arg)) { far = of; arg = oa; }
+            if (of > far || (of == far && oa < farg)) { far = of; farg = oa; }
         }
-        return (arg >= 0 && arg < ng) ? arg : 0;
+        return (farg >= 0 && farg < ng) ? farg : 0;
     };
-    // what a row contributes to the choice of the next centroid: its running minimum
-    // (farthest point), or ln(minimum) plus the variate of this pass's draw (a draw
-    // with probability proportional to the minimum)
-    auto offer = [&](double mk, int k, bool need_key, unsigned long long drawn, double& far, int& arg) {
-        double v = mk;
-        if constexpr (DSQ)
-            v = need_key ? log(mk) + gumbel_variate(a.seed_lo, a.seed_hi, (unsigned)drawn,
-                                                    (unsigned)(drawn >> 32), n0 + k)
-                         : 0.0;
-        if (v > far || (v == far && k < arg)) { far = v; arg = k; }
+
+    // (`minimum(k)`: the fp32 minimum of a row of this thread)
+    auto resolve = [&](int j, unsigned long long drawn, float thr, auto minimum) {
+        far = -INFINITY; farg = kNone;
+#pragma unroll 1
+        for (int k = tid; k < ng; k += kThreads) {
+            if (offer(minimum(k), k, drawn) >= thr) {
+                const int at = atomicAdd(&nlist, 1);
+                if (at < kListed) list[at] = (unsigned short)k;
+            }
+        }
+        __syncthreads();
+        const int n = nlist;
+        if (n <= kListed) {
+            for (int i = __builtin_amdgcn_readfirstlane(tid >> 6); i < n; i += kWaves) contest_wave(list[i], j, drawn);
+        } else {
+#pragma unroll 1
+            for (int k = tid; k < ng; k += kThreads)
+                if (offer(minimum(k), k, drawn) >= thr) contest_owner(k, j, drawn);
+        }
+        return block_argmax();
     };
 
     // the rows that stay in registers; `ru`: how many of them any lane of this wave has
     float4 xr[R][Q];
-    double mk[R];
+    float mk[R];
     int ru = 0;
 #pragma unroll
     for (int u = 0; u < R; ++u) {
         if ((tid & ~63) + u * kThreads < ng) ru = u + 1;
         const int k = tid + u * kThreads;
         const bool ex = k < ng;
-        const float* row = Xg + (size_t)(ex ? k : 0) * D;
+        const float* row = Xg + (size_t)(ex ? k : 0) * D;      // (D > 16 (DS - 1))
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int d = 4 * q;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ex && d < D) {
-                if (vec) {
-                    v = *reinterpret_cast<const float4*>(row + d);
-                } else {
-                    v.x = row[d];
-                    if (d + 1 < D) v.y = row[d + 1];
-                    if (d + 2 < D) v.z = row[d + 2];
-                    if (d + 3 < D) v.w = row[d + 3];
-                }
-            }
-            xr[u][q] = v;
-        }
+        for (int q = 0; q < Q; ++q) xr[u][q] = row_piece(row, 4 * q, D, q < Q - 4);
         mk[u] = INFINITY;
     }
-
     // the next LROWS rows go to LDS, row R * 512 + tid + 512 v to thread tid
-    double ml[LV];
+    float ml[LV];
 #pragma unroll
     for (int v = 0; v < LV; ++v) {
         const int sl = tid + v * kThreads, k = R * kThreads + sl;
@@ -165,187 +337,174 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
         if (sl < LROWS && k < ng) {
             const float* row = Xg + (size_t)k * D;
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const int d = 4 * q;
-                float4 x4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (d < D) {
-                    if (vec) {
-                        x4 = *reinterpret_cast<const float4*>(row + d);
-                    } else {
-                        x4.x = row[d];
-                        if (d + 1 < D) x4.y = row[d + 1];
-                        if (d + 2 < D) x4.z = row[d + 2];
-                        if (d + 3 < D) x4.w = row[d + 3];
-                    }
-                }
-                *reinterpret_cast<float4*>(lx + (size_t)sl * RS + d) = x4;
-            }
+            for (int q = 0; q < Q; ++q)
+                *reinterpret_cast<float4*>(lx + (size_t)sl * RS + 4 * q) = row_piece(row, 4 * q, D, q < Q - 4);
         }
     }
+    for (int k = tid; k < ng; k += kThreads) upto[k] = 0;
+    for (int k = FIRST + tid; k < ng; k += kThreads) ms[k - FIRST] = INFINITY;
 
+    float thr;
     int chosen = 0;
+    if (tid == 0) nlist = 0;       // (before the barrier of the first choice)
     if constexpr (DSQ) {
         // first centroid: a uniform draw, i.e. the largest variate of draw number draw0
-        double far = -INFINITY;
-        int arg = 0x7fffffff;
-        for (int k = tid; k < ng; k += kThreads) {
-            const double key = gumbel_variate(a.seed_lo, a.seed_hi, (unsigned)a.draw0,
-                                              (unsigned)(a.draw0 >> 32), n0 + k);
-            if (key > far || (key == far && k < arg)) { far = key; arg = k; }
+        best = -INFINITY; second = -INFINITY; arg = kNone;
+        for (int k = tid; k < ng; k += kThreads) take(offer(1.f, k, a.draw0), k);
+        chosen = choose(thr);
+        if (chosen < 0) {                        // (uniform over the workgroup)
+            chosen = resolve(-1, a.draw0, thr, [](int) { return 1.f; });
         }
-        chosen = block_argmax(far, arg);
     }
     for (int j = 0; j < K; ++j) {
         const unsigned long long drawn = a.draw0 + (unsigned long long)j + 1ull;
-        const bool need_key = DSQ && j + 1 < K;
-        // the chosen row becomes centroid j: out of its owner's registers, or from
-        // memory if it is one of the streamed rows
+        // the chosen row becomes centroid j: out of its owner's registers, from LDS, or
+        // from memory if it is one of the streamed rows
         chosen = __builtin_amdgcn_readfirstlane(chosen);     // (the same in every thread)
+        if (tid == 0) { picks[j] = (unsigned short)chosen; nlist = 0; }
+        if (j + 1 == K) break;         // the last centroid is followed by no choice
         if (chosen < R * kThreads) {
 #pragma unroll
             for (int u = 0; u < R; ++u) {
                 if (u == chosen / kThreads && tid == (chosen & (kThreads - 1))) {
 #pragma unroll
                     for (int q = 0; q < Q; ++q) reinterpret_cast<float4*>(c)[q] = xr[u][q];
-                    if (a.pick) a.pick[k0 + j] = n0 + chosen;
                 }
             }
         } else if (tid < 16 * DS) {
-            c[tid] = chosen < R * kThreads + LROWS ? lx[(size_t)(chosen - R * kThreads) * RS + tid]
-                     : tid < D                     ? Xg[(size_t)chosen * D + tid]
-                                                   : 0.f;
-            if (tid == 0 && a.pick) a.pick[k0 + j] = n0 + chosen;
+            c[tid] = chosen < FIRST ? lx[(size_t)(chosen - R * kThreads) * RS + tid]
+                     : tid < D      ? Xg[(size_t)chosen * D + tid]
+                                    : 0.f;
         }
         __syncthreads();
-        if (tid < D) a.cent[((size_t)k0 + j) * D + tid] = c[tid];
-        if (j + 1 == K) break;         // the last centroid is followed by no choice
-        double far = -INFINITY;
-        int arg = 0x7fffffff;
-        // rows in registers
+        best = -INFINITY; second = -INFINITY; arg = kNone;
+        // rows in registers and in LDS, one walk over the centroid; its next two pieces are
+        // requested while two are worked on (all of them at once, as the compiler would
+        // have it, do not fit beside the rows)
         if (ru > 0) {
-            double acc[R];
+            const bool inlds = (tid & ~63) + R * kThreads < ng;       // (uniform over the wave)
+            float acc[R], accl[LV];
+            const float* lrow[LV];
 #pragma unroll
-            for (int u = 0; u < R; ++u) acc[u] = 0.0;
+            for (int u = 0; u < R; ++u) acc[u] = 0.f;
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                if (4 * q < D) {
-                    const float4 cv = *reinterpret_cast<const float4*>(c + 4 * q);
-                    const double cx = (double)cv.x, cy = (double)cv.y, cz = (double)cv.z, cw = (double)cv.w;
+            for (int v = 0; v < LV; ++v) {
+                accl[v] = 0.f;
+                // (a slot beyond the search's rows is read all the same: inside the array)
+                lrow[v] = lx + (size_t)(tid + v * kThreads < LROWS ? tid + v * kThreads : tid) * RS;
+            }
+            float4 cv[2];
+            cv[0] = *reinterpret_cast<const float4*>(c);
+            cv[1] = *reinterpret_cast<const float4*>(c + 4);
 #pragma unroll
-                    for (int u = 0; u < R; ++u) {
-                        if (u < ru) {
-                            // (opaque to the compiler, which would otherwise widen every
-                            // row to fp64 once, outside the passes, at twice the registers)
-                            asm volatile("" : "+v"(xr[u][q].x), "+v"(xr[u][q].y), "+v"(xr[u][q].z),
-                                              "+v"(xr[u][q].w));
-                            acc[u] = add_sq(acc[u], xr[u][q].x, cx);
-                            acc[u] = add_sq(acc[u], xr[u][q].y, cy);
-                            acc[u] = add_sq(acc[u], xr[u][q].z, cz);
-                            acc[u] = add_sq(acc[u], xr[u][q].w, cw);
+            for (int q = 0; q < Q; q += 2) {
+                if (q <= Q - 4 || 4 * q < D) {
+                    float4 cn[2];
+                    cn[0] = cv[0]; cn[1] = cv[1];
+                    if (q + 2 < Q) {
+                        cn[0] = *reinterpret_cast<const float4*>(c + 4 * q + 8);
+                        cn[1] = *reinterpret_cast<const float4*>(c + 4 * q + 12);
+                    }
+                    if (inlds) {
+#pragma unroll
+                        for (int v = 0; v < LV; ++v) {
+                            const float4 x0 = *reinterpret_cast<const float4*>(lrow[v] + 4 * q);
+                            const float4 x1 = *reinterpret_cast<const float4*>(lrow[v] + 4 * q + 4);
+                            accl[v] = add_sq4(add_sq4(accl[v], x0, cv[0]), x1, cv[1]);
                         }
                     }
+#pragma unroll
+                    for (int u = 0; u < R; ++u)
+                        if (u < ru) acc[u] = add_sq4(add_sq4(acc[u], xr[u][q], cv[0]), xr[u][q + 1], cv[1]);
+                    cv[0] = cn[0]; cv[1] = cn[1];
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
             for (int u = 0; u < R; ++u) {
                 const int k = tid + u * kThreads;
-                if (k < ng) {
+                if (u < ru) {
                     mk[u] = mk[u] < acc[u] ? mk[u] : acc[u];
-                    offer(mk[u], k, need_key, drawn, far, arg);
+                    const float v = offer(mk[u], k, drawn);
+                    take(k < ng ? v : -INFINITY, k);
+                }
+            }
+            if (inlds) {
+#pragma unroll
+                for (int v = 0; v < LV; ++v) {
+                    const int sl = tid + v * kThreads, k = R * kThreads + sl;
+                    if (sl < LROWS && k < ng) {
+                        ml[v] = ml[v] < accl[v] ? ml[v] : accl[v];
+                        take(offer(ml[v], k, drawn), k);
+                    }
                 }
             }
         }
-        // rows in LDS
-        if ((tid & ~63) + R * kThreads < ng) {
-            double acc[LV];
+        // Rows beyond the registers' and the LDS's share: four lanes per row, so that a
+        // load takes 64 consecutive bytes of each of 16 rows.  (A lane per row took 16
+        // bytes of each of 64 rows and the cache line had left the vector cache by the
+        // next piece: a pass over 4096 rows of 48 features was 12.1 us and is 9.2 us.)  Lane
+        // l then offers row 16 (l & 3) + l / 4 of the wave's 64.
+        if constexpr (FIRST < kBigRows) {
+            const int lane = tid & 63, quad = lane & 3;
+            for (int kb = FIRST + (tid & ~63); kb < ng; kb += kThreads) {     // (uniform over the wave)
+                float mine = 0.f;
 #pragma unroll
-            for (int v = 0; v < LV; ++v) acc[v] = 0.0;
+                for (int half = 0; half < 2; ++half) {
+                    float4 xs[2][DS];
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                if (4 * q < D) {
-                    const float4 cv = *reinterpret_cast<const float4*>(c + 4 * q);
-                    const double cx = (double)cv.x, cy = (double)cv.y, cz = (double)cv.z, cw = (double)cv.w;
+                    for (int u = 0; u < 2; ++u) {
+                        const int k = kb + 16 * (2 * half + u) + (lane >> 2);
+                        const float* row = Xg + (size_t)(k < ng ? k : kb) * D;
 #pragma unroll
-                    for (int v = 0; v < LV; ++v) {
-                        // (a slot beyond the search's rows is read all the same: inside the array)
-                        const int sl = tid + v * kThreads < LROWS ? tid + v * kThreads : tid;
-                        const float4 x4 = *reinterpret_cast<const float4*>(lx + (size_t)sl * RS + 4 * q);
-                        acc[v] = add_sq(acc[v], x4.x, cx);
-                        acc[v] = add_sq(acc[v], x4.y, cy);
-                        acc[v] = add_sq(acc[v], x4.z, cz);
-                        acc[v] = add_sq(acc[v], x4.w, cw);
+                        for (int i = 0; i < DS; ++i)
+                            xs[u][i] = row_piece(row, 16 * i + 4 * quad, D, i + 1 < DS);
                     }
-                }
-            }
+                    float acc[2] = {0.f, 0.f};
 #pragma unroll
-            for (int v = 0; v < LV; ++v) {
-                const int sl = tid + v * kThreads, k = R * kThreads + sl;
-                if (sl < LROWS && k < ng) {
-                    ml[v] = ml[v] < acc[v] ? ml[v] : acc[v];
-                    offer(ml[v], k, need_key, drawn, far, arg);
-                }
-            }
-        }
-        // rows beyond the registers' and the LDS's share
-        constexpr int U = 2;      // rows in flight per thread
-        for (int kb = tid + R * kThreads + LROWS; kb < ng; kb += U * kThreads) {
-            double acc[U];
+                    for (int i = 0; i < DS; ++i) {
+                        const float4 cv = *reinterpret_cast<const float4*>(c + 16 * i + 4 * quad);
 #pragma unroll
-            for (int u = 0; u < U; ++u) acc[u] = 0.0;
-            if (vec) {
-                // 8 features of each of the U rows are requested together; the sum of a
-                // row still runs over its features in index order
-                for (int d0 = 0; d0 < D; d0 += 8) {
-                    float4 xv[U][2];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int k = kb + u * kThreads;
-                        const float* row = Xg + (size_t)(k < ng ? k : kb) * D + d0;
-#pragma unroll
-                        for (int q = 0; q < 2; ++q)
-                            xv[u][q] = d0 + 4 * q < D ? *reinterpret_cast<const float4*>(row + 4 * q)
-                                                      : make_float4(0.f, 0.f, 0.f, 0.f);
+                        for (int u = 0; u < 2; ++u) acc[u] = add_sq4(acc[u], xs[u][i], cv);
                     }
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        if (d0 + 4 * q < D) {
-                            const float4 cv = *reinterpret_cast<const float4*>(c + d0 + 4 * q);
-                            const double cx = (double)cv.x, cy = (double)cv.y, cz = (double)cv.z,
-                                         cw = (double)cv.w;
-#pragma unroll
-                            for (int u = 0; u < U; ++u) {
-                                acc[u] = add_sq(acc[u], xv[u][q].x, cx);
-                                acc[u] = add_sq(acc[u], xv[u][q].y, cy);
-                                acc[u] = add_sq(acc[u], xv[u][q].z, cz);
-                                acc[u] = add_sq(acc[u], xv[u][q].w, cw);
-                            }
-                        }
+                    for (int u = 0; u < 2; ++u) {
+                        acc[u] += dpp_f<0xB1>(acc[u]);
+                        acc[u] += dpp_f<0x4E>(acc[u]);
+                        mine = quad == 2 * half + u ? acc[u] : mine;
                     }
                 }
-            } else {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int k = kb + u * kThreads;
-                    const float* row = Xg + (size_t)(k < ng ? k : kb) * D;
-                    for (int d = 0; d < D; ++d) acc[u] = add_sq(acc[u], row[d], (double)c[d]);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int k = kb + u * kThreads;
+                const int k = kb + 16 * quad + (lane >> 2);
                 if (k < ng) {
-                    double m = acc[u];
-                    if (j > 0) {
-                        const double old = mind[k];
-                        m = old < acc[u] ? old : acc[u];
-                    }
-                    mind[k] = m;
-                    offer(m, k, need_key, drawn, far, arg);
+                    const float old = ms[k - FIRST];
+                    const float m = old < mine ? old : mine;
+                    ms[k - FIRST] = m;
+                    take(offer(m, k, drawn), k);
                 }
             }
         }
-        chosen = block_argmax(far, arg);
+        chosen = choose(thr);
+        if (chosen < 0) {                        // (uniform over the workgroup)
+            chosen = resolve(j, drawn, thr, [&](int k) {
+                float m = 0.f;
+                const int u0 = k / kThreads;     // (a register array is not indexed by a variable)
+#pragma unroll
+                for (int u = 0; u < R; ++u) m = u == u0 ? mk[u] : m;
+#pragma unroll
+                for (int v = 0; v < LV; ++v) m = u0 == R + v ? ml[v] : m;
+                return k >= FIRST ? ms[k - FIRST] : m;
+            });
+        }
     }
+    // the chosen rows (written at the end: a store on the way would be waited for at the
+    // next barrier)
+    __syncthreads();
+    for (int idx = tid; idx < K * D; idx += kThreads) {
+        const int j = idx / D, d = idx - j * D;
+        a.cent[(size_t)k0 * D + idx] = Xg[(size_t)picks[j] * D + d];
+    }
+    if (a.pick)
+        for (int j = tid; j < K; j += kThreads) a.pick[k0 + j] = n0 + (int)picks[j];
 }
 
 // One launch per centroid for the searches of more than kBigRows rows.  `j`: the
@@ -512,27 +671,27 @@ __global__ void __launch_bounds__(kBigThreads) seed_big_pass(SeedArgs a, int j, 
 size_t seed_ranges(const kb_batch& b) { return (size_t)((b.N + kRange - 1) / kRange) + 1; }
 
 hipError_t launch_seed(const kb_batch& b, const float* X, float* cent, int32_t* pick, double* mind,
-                       double* skey, int32_t* sidx, const int32_t* order, int dsquared,
+                       int32_t* upto, double* skey, int32_t* sidx, const int32_t* order, int dsquared,
                        uint64_t seed, uint64_t draw0, hipStream_t st) {
     SeedArgs a;
     a.dsquared = dsquared; a.seed_lo = (unsigned)seed; a.seed_hi = (unsigned)(seed >> 32);
     a.draw0 = draw0;
     a.G = b.G; a.D = b.D; a.Ksum = b.Ksum; a.N = b.N; a.seg_off = b.seg_off; a.koff = b.koff;
-    a.X = X; a.cent = cent; a.pick = pick; a.mind = mind; a.order = order;
+    a.X = X; a.cent = cent; a.pick = pick; a.mind = mind; a.upto = upto; a.order = order;
     a.skey = skey; a.sidx = sidx; a.nranges = (int)seed_ranges(b);
     const dim3 grid((unsigned)b.G), block(kThreads);
     hipError_t err = hipSuccess;
-    auto go = [&](auto far, auto dsq, int DS) {
-        const size_t lds = (size_t)4 * lds_stride(DS) * lds_rows(DS);
+    auto go = [&](auto far, auto dsq, int DS, int R) {
+        const size_t lds = (size_t)4 * (lds_stride(DS) * lds_rows(DS) + streamed_rows(DS, R));
         auto kern = dsquared ? dsq : far;
         err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (err == hipSuccess) hipLaunchKernelGGL(kern, grid, block, lds, st, a);
     };
-    if (b.D <= 16) go(seed_farthest_kernel<1, 8, false>, seed_farthest_kernel<1, 8, true>, 1);
-    else if (b.D <= 32) go(seed_farthest_kernel<2, 6, false>, seed_farthest_kernel<2, 6, true>, 2);
-    else if (b.D <= 48) go(seed_farthest_kernel<3, 4, false>, seed_farthest_kernel<3, 4, true>, 3);
-    else go(seed_farthest_kernel<4, 3, false>, seed_farthest_kernel<4, 3, true>, 4);
+    if (b.D <= 16) go(seed_farthest_kernel<1, 8, false>, seed_farthest_kernel<1, 8, true>, 1, 8);
+    else if (b.D <= 32) go(seed_farthest_kernel<2, 4, false>, seed_farthest_kernel<2, 4, true>, 2, 4);
+    else if (b.D <= 48) go(seed_farthest_kernel<3, 3, false>, seed_farthest_kernel<3, 3, true>, 3, 3);
+    else go(seed_farthest_kernel<4, 2, false>, seed_farthest_kernel<4, 2, true>, 4, 2);
     if (err != hipSuccess) return err;
     if (b.Nmax > kBigRows) {
         const dim3 bgrid((unsigned)a.nranges), bblock(kBigThreads);
