@@ -9,33 +9,65 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// M[i,s] = [ h(rep_i)[target(s)] < theta_sat ], one wave per search; nvalid[g] =
-// number of valid cluster arms of the search.
+// M[i,s] = [ h(rep_i)[target(s)] < theta_sat ]; nvalid[g] = number of valid cluster arms of
+// the search.  NT threads per search: a wave, or a workgroup where a search may have more
+// than kMaskWave arms.  Bound by the dependent loads rep -> h: a thread has kMaskU of its
+// arms in flight, so a search is one or two such chains (a wave per search went through its
+// 2048 arms in 32 chains: 512 searches of up to 64 clusters and 32 strategies 37.5 us, now 6 us).
+constexpr int kMaskWave = 256;
+constexpr int kMaskU = 8;
+
+template <int NT>
 __global__ void __launch_bounds__(kThreads)
 strategy_mask_kernel(int G, int S, int R, int Ksum, int64_t N, const int32_t* __restrict__ koff,
                      const float* __restrict__ h, const int32_t* __restrict__ target,
                      const int32_t* __restrict__ rep, float theta_sat, uint8_t* __restrict__ M,
                      int32_t* __restrict__ nvalid) {
-    const int lane = threadIdx.x & 63;
-    const int g = blockIdx.x * (kThreads / kWave) + (threadIdx.x >> 6);
-    if (g >= G) return;
+    __shared__ int part[kThreads / kWave];
+    const int lane = threadIdx.x & (NT - 1);
+    const int g = blockIdx.x * (kThreads / NT) + threadIdx.x / NT;
+    if (g >= G) return;                   // (whole waves; with NT = 256 never)
     const int k0 = clampi(koff[g], 0, Ksum);
     const int k1 = clampi(koff[g + 1], k0, Ksum);
     const int arms = (k1 - k0) * S;
     int n = 0;
-    for (int q = lane; q < arms; q += kWave) {
-        const int i = k0 + q / S, s = q - (q / S) * S;
-        const int r = rep[i];
-        int m = 0;
-        if (r >= 0 && (int64_t)r < N) {
-            const int col = clampi(target[s], 0, R - 1);
-            m = h[(size_t)r * R + col] < theta_sat ? 1 : 0;
+    for (int q0 = lane; q0 < arms; q0 += NT * kMaskU) {
+        int r[kMaskU], col[kMaskU];
+        float v[kMaskU];
+#pragma unroll
+        for (int u = 0; u < kMaskU; ++u) {
+            const int q = q0 + u * NT;
+            r[u] = -1;
+            if (q < arms) {
+                const int i = q / S;
+                r[u] = rep[k0 + i];
+                col[u] = clampi(target[q - i * S], 0, R - 1);
+            }
         }
-        M[(size_t)k0 * S + q] = (uint8_t)m;
-        n += m;
+#pragma unroll
+        for (int u = 0; u < kMaskU; ++u) {
+            if (r[u] >= 0 && (int64_t)r[u] < N) v[u] = h[(size_t)r[u] * R + col[u]];
+            else r[u] = -1;
+        }
+#pragma unroll
+        for (int u = 0; u < kMaskU; ++u) {
+            const int q = q0 + u * NT;
+            if (q < arms) {
+                const int m = r[u] >= 0 && v[u] < theta_sat ? 1 : 0;
+                M[(size_t)k0 * S + q] = (uint8_t)m;
+                n += m;
+            }
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+    if constexpr (NT > kWave) {
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = n;
+        __syncthreads();
+        n = 0;
+#pragma unroll
+        for (int w = 0; w < NT / kWave; ++w) n += part[w];
+    }
     if (lane == 0) nvalid[g] = n;
 }
 
@@ -84,9 +116,12 @@ update_stats_kernel(int G, int S, int Ksum, int64_t N, const int32_t* __restrict
 hipError_t launch_strategy_mask(const kb_batch& b, int R, const float* h, const int32_t* target,
                                 const int32_t* rep, float theta_sat, uint8_t* M, int32_t* nvalid,
                                 hipStream_t st) {
-    const int per = kThreads / kWave;
-    hipLaunchKernelGGL(strategy_mask_kernel, dim3((unsigned)((b.G + per - 1) / per)), dim3(kThreads),
-                       0, st, b.G, b.S, R, b.Ksum, b.N, b.koff, h, target, rep, theta_sat, M, nvalid);
+    const auto go = [&](auto kern, int per) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)((b.G + per - 1) / per)), dim3(kThreads), 0, st, b.G, b.S, R,
+                           b.Ksum, b.N, b.koff, h, target, rep, theta_sat, M, nvalid);
+    };
+    if ((int64_t)b.Kmax * b.S <= kMaskWave) go(strategy_mask_kernel<kWave>, kThreads / kWave);
+    else go(strategy_mask_kernel<kThreads>, 1);
     return hipGetLastError();
 }
 
