@@ -420,6 +420,7 @@ kb_status kb_cluster_diameter(const kb_batch* batch, const float* X, const int32
     c.off = (int32_t*)(base + w.dia_off);
     c.toff = (int32_t*)(base + w.dia_toff);
     c.bsum = (long long*)(base + w.dia_bsum);
+    c.slots = base + w.geo_d2;
     return dev(launch_diameter(*batch, c, (hipStream_t)stream));
 }
 

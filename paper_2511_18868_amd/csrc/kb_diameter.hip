@@ -3,24 +3,28 @@
 // Theorem 1.
 //
 //   dia_zero     per-cluster counters and maxima <- 0
-//   dia_hist     cluster sizes: flat candidate ranges walk the searches that
+//   dia_group    one workgroup per search: sizes, grouped indices, unit numbers; or, in batches
+//                with searches of more than kGroupMax candidates,
+//   dia_walk<false>
+//                cluster sizes: flat candidate ranges walk the searches that
 //                intersect them, LDS histogram per search piece, one global atomic
 //                per touched cluster and piece
 //   dia_bsum / dia_bscan / dia_apply
-//                exclusive prefix sums of the sizes and of the tile counts,
+//                exclusive prefix sums of the sizes and of the unit counts,
 //                counters reset
-//   dia_scatter  candidate indices grouped by cluster (same walk; a piece reserves
+//   dia_walk<true>
+//                candidate indices grouped by cluster (same walk; a piece reserves
 //                its slots per cluster with one global atomic, positions inside the
 //                piece come from LDS atomics).  The order inside a cluster varies
 //                from run to run; the maximum over its pairs does not.
-//   dia_pairs    the tiles of 64 x 64 member pairs of all clusters (32 x 32 for
-//                clusters of up to 32 members) are numbered in one sequence and
-//                every workgroup takes an equal share; a thread owns 4 x 4 (2 x 2)
-//                pairs of a tile, features pass through LDS 16 at a time; squared
-//                distances from direct differences in fp32 (relative error at most
+//   dia_pairs    the squares of 64 x 64 member pairs of all clusters are numbered and
+//                every wave takes an equal share; the matrix cores form the distances of
+//                32 x 32 pairs at a time in fp32, and the pairs that may be the farthest
+//                are evaluated from direct differences in fp32 (relative error at most
 //                (D + 2) 2^-24 each, being sums of non-negative terms)
 //   dia_final    square root
 #include "kb_internal.h"
+#include "kb_wave_dev.h"
 
 namespace kb {
 
@@ -33,6 +37,18 @@ constexpr int kDiaShort = 64;    // searches of at most this many candidates: al
                                  // beyond, a lane's loop over the later members gets long (a search of 256
                                  // candidates took 0.34 ms that way against 0.03 ms through the tiles)
 
+constexpr int kGroupMax = 16384; // batches without longer searches: members grouped by dia_group, a
+                                 // workgroup per search
+constexpr int kGroupThreads = 512;
+constexpr int kUnitBits = 40;    // units of a batch < 2^40 (fewer than 2^31 candidates in searches of at
+                                 // most 16384), searches <= 2^20
+
+// consecutive unit numbers: clusters c0 .. c1 - 1 from unit `first` on
+struct DiaSlot {
+    long long first;
+    int c0, c1;
+};
+
 struct DiaArgs {
     int G, D, Ksum, Kmax;
     int64_t N;
@@ -43,8 +59,10 @@ struct DiaArgs {
     float* diam;          // [Ksum] out
     int32_t* cnt;         // [Ksum] sizes, then cursors
     int32_t* off;         // [Ksum + 1] first slot of every cluster in perm
-    int32_t* toff;        // [Ksum + 1] first tile of every cluster in the global tile numbering
-    long long* bsum;      // [2 * blocks of the prefix sum] (members, tiles) per block
+    int32_t* toff;        // [Ksum + 1] first unit of every cluster in the numbering of its slot
+    long long* bsum;      // [2 * blocks of the prefix sum] (members, units) per block
+    DiaSlot* slots;       // [searches with units] one per search (dia_group); null: one slot, the whole batch
+    unsigned long long* reserved;   // slots (upper bits) and units (lower kUnitBits) handed out so far
     unsigned* dmax;       // [Ksum] bits of the largest squared distance (aliases diam)
     int32_t* perm;        // [N]
     int mixed;            // 1: searches of at most kDiaShort candidates go to dia_wave, longer ones
@@ -54,6 +72,7 @@ struct DiaArgs {
 __global__ void __launch_bounds__(kThreads) dia_zero(DiaArgs a) {
     const int i = blockIdx.x * kThreads + threadIdx.x;
     if (i < a.Ksum) { a.cnt[i] = 0; a.dmax[i] = 0u; }
+    if (i == 0 && a.slots) *a.reserved = 0ull;
 }
 
 // SCATTER = false: sizes; true: grouped indices
@@ -112,11 +131,10 @@ __global__ void __launch_bounds__(kThreads) dia_walk(DiaArgs a) {
     }
 }
 
-// Tiles of member pairs of a cluster of n members: none below two members, one tile
-// of 32 x 32 up to 32 members, otherwise the tiles of 64 x 64 on and above the diagonal.
-__device__ __forceinline__ long long tiles_of(int n) {
+// Units of member pairs of a cluster of n members: none below two members, otherwise the
+// squares of 64 x 64 pairs on and above the diagonal.
+__device__ __forceinline__ long long units_of(int n) {
     if (n < 2) return 0;
-    if (n <= 32) return 1;
     const long long T = (n + 63) >> 6;
     return T * (T + 1) / 2;
 }
@@ -148,7 +166,7 @@ __global__ void __launch_bounds__(kThreads) dia_bsum(DiaArgs a) {
         const int i = i0 + u * kThreads;
         const int v = i < a.Ksum ? a.cnt[i] : 0;
         m += v;
-        t += tiles_of(v);
+        t += units_of(v);
     }
     block_sum2(m, t, red);
     if (threadIdx.x == 0) { a.bsum[2 * blockIdx.x] = m; a.bsum[2 * blockIdx.x + 1] = t; }
@@ -198,7 +216,7 @@ __global__ void __launch_bounds__(kThreads) dia_apply(DiaArgs a) {
 #pragma unroll
     for (int u = 0; u < kScanU; ++u) {
         const int i = i0 + u * kThreads;
-        const long long m = v[u], t = tiles_of(v[u]);
+        const long long m = v[u], t = units_of(v[u]);
         long long im = m, it = t;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -228,146 +246,430 @@ __global__ void __launch_bounds__(kThreads) dia_apply(DiaArgs a) {
     }
 }
 
-// Squared distances of a tile of T x T member pairs, T = 16 * R: the 256 threads
-// form a 16 x 16 grid and each owns R x R pairs.  Features pass through LDS 16 at
-// a time, feature-major, so that a thread reads its R rows' and R columns' values
-// of one feature with one LDS read each and spends R * R subtract / multiply-add
-// pairs on them.  Rows beyond the cluster are replaced by its last member, whose
-// distances are genuine ones, so nothing needs masking.
-template <int R>
-__device__ __forceinline__ float tile_pairs_max(const DiaArgs& a, int base, int n, int ta, int tb,
-                                                float* As, float* Bs) {
-    constexpr int T = 16 * R;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int D = a.D;
-    float acc[R][R];
+// Batches whose searches all have at most kGroupMax candidates: one workgroup per search
+// does in one launch what the walks and the prefix sums do in five.  The members of a
+// search are grouped inside its own part of `perm`, so no prefix sum over the batch is
+// needed; a search reserves its unit numbers and a slot of the slot list together with one
+// 64-bit atomic, so the slots are in the order of their first units whatever the order of
+// the workgroups.  (1024 searches of 64-4096 candidates: 19 us, the five launches 71 us.)
+__global__ void __launch_bounds__(kGroupThreads) dia_group(DiaArgs a) {
+    __shared__ int lcnt[KB_MAX_K];
+    const int tid = threadIdx.x, g = blockIdx.x;
+    int n0, ng, k0, K;
+    search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
+    if (K > KB_MAX_K) K = KB_MAX_K;
+    if (ng <= 0 || K <= 0) return;
+    for (int j = tid; j < K; j += kGroupThreads) lcnt[j] = 0;
+    __syncthreads();
+    constexpr int U = 4;
+    const int32_t* as = a.assign + n0;
+    for (int p0 = tid; p0 < ng; p0 += U * kGroupThreads) {
+        int j[U];
 #pragma unroll
-    for (int i = 0; i < R; ++i)
+        for (int u = 0; u < U; ++u) j[u] = p0 + u * kGroupThreads < ng ? as[p0 + u * kGroupThreads] : 0;
 #pragma unroll
-        for (int j = 0; j < R; ++j) acc[i][j] = 0.f;
-    // loader: thread -> (row of the tile, group of features); T rows x 16 features per
-    // side and step = T * 16 values, 256 threads -> T / 16 = R values each
-    const int lrow = tid % T, lf0 = (tid / T) * R;        // R consecutive features of one row
-    int ia = ta * T + lrow, ib = tb * T + lrow;
-    ia = ia < n ? ia : n - 1;
-    ib = ib < n ? ib : n - 1;
-    int ra = a.perm[base + ia], rb = a.perm[base + ib];
-    ra = (ra >= 0 && ra < a.N) ? ra : 0;
-    rb = (rb >= 0 && rb < a.N) ? rb : 0;
-    const float* xa = a.X + (size_t)ra * D;
-    const float* xb = a.X + (size_t)rb * D;
-    const bool vec = (D & 3) == 0 && R == 4;     // the R = 4 features of a thread are one 16-byte piece
-    float va[R], vb[R];
-    auto fetch = [&](int d0) {
-        if (vec) {
-            const int d = d0 + lf0;
-            const float4 pa = d < D ? *reinterpret_cast<const float4*>(xa + d) : make_float4(0.f, 0.f, 0.f, 0.f);
-            const float4 pb = d < D ? *reinterpret_cast<const float4*>(xb + d) : make_float4(0.f, 0.f, 0.f, 0.f);
-            va[0] = pa.x; va[1 % R] = pa.y; va[2 % R] = pa.z; va[3 % R] = pa.w;
-            vb[0] = pb.x; vb[1 % R] = pb.y; vb[2 % R] = pb.z; vb[3 % R] = pb.w;
-        } else {
+        for (int u = 0; u < U; ++u)
+            if (p0 + u * kGroupThreads < ng) atomicAdd(&lcnt[(j[u] >= 0 && j[u] < K) ? j[u] : 0], 1);
+    }
+    __syncthreads();
+    if (tid < kWave) {
+        // exclusive prefix sums of members and units, four clusters per lane (K <= 256)
+        int n[4], m = 0, t = 0;
 #pragma unroll
-            for (int e = 0; e < R; ++e) {
-                const int d = d0 + lf0 + e;
-                va[e] = d < D ? xa[d] : 0.f;
-                vb[e] = d < D ? xb[d] : 0.f;
+        for (int e = 0; e < 4; ++e) {
+            const int j = 4 * tid + e;
+            n[e] = j < K ? lcnt[j] : 0;
+            m += n[e];
+            t += (int)units_of(n[e]);
+        }
+        int im = m, it = t;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int um = __shfl_up(im, o), ut = __shfl_up(it, o);
+            if (tid >= o) { im += um; it += ut; }
+        }
+        const int total = __shfl(it, kWave - 1);
+        int om = n0 + im - m, ot = it - t;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int j = 4 * tid + e;
+            if (j < K) {
+                a.cnt[k0 + j] = n[e]; a.off[k0 + j] = om; a.toff[k0 + j] = ot;
+                lcnt[j] = om - n0;
             }
+            om += n[e];
+            ot += (int)units_of(n[e]);
         }
-    };
-    fetch(0);
-    for (int d0 = 0; d0 < D; d0 += 16) {
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < R; ++e) {
-            As[(lf0 + e) * T + lrow] = va[e];
-            Bs[(lf0 + e) * T + lrow] = vb[e];
-        }
-        __syncthreads();
-        if (d0 + 16 < D) fetch(d0 + 16);      // the next step's values travel while this one is worked on
-#pragma unroll
-        for (int f = 0; f < 16; ++f) {
-            float av[R], bv[R];
-#pragma unroll
-            for (int i = 0; i < R; ++i) av[i] = As[f * T + ty * R + i];
-#pragma unroll
-            for (int j = 0; j < R; ++j) bv[j] = Bs[f * T + tx * R + j];
-#pragma unroll
-            for (int i = 0; i < R; ++i)
-#pragma unroll
-                for (int j = 0; j < R; ++j) {
-                    const float e = av[i] - bv[j];
-                    acc[i][j] = fmaf(e, e, acc[i][j]);
-                }
+        if (tid == 0 && total > 0) {
+            const unsigned long long old = atomicAdd(a.reserved, (1ull << kUnitBits) | (unsigned long long)total);
+            DiaSlot s;
+            s.first = (long long)(old & ((1ull << kUnitBits) - 1));
+            s.c0 = k0; s.c1 = k0 + K;
+            a.slots[old >> kUnitBits] = s;
         }
     }
-    float far = 0.f;
+    __syncthreads();
+    for (int p0 = tid; p0 < ng; p0 += U * kGroupThreads) {
+        int j[U];
 #pragma unroll
-    for (int i = 0; i < R; ++i)
+        for (int u = 0; u < U; ++u) j[u] = p0 + u * kGroupThreads < ng ? as[p0 + u * kGroupThreads] : 0;
 #pragma unroll
-        for (int j = 0; j < R; ++j) far = fmaxf(far, acc[i][j]);
-    return far;
+        for (int u = 0; u < U; ++u) {
+            if (p0 + u * kGroupThreads < ng) {
+                const int pos = atomicAdd(&lcnt[(j[u] >= 0 && j[u] < K) ? j[u] : 0], 1);
+                if (pos < ng) a.perm[(size_t)n0 + pos] = n0 + p0 + u * kGroupThreads;
+            }
+        }
+    }
 }
 
-// All tiles of all clusters are numbered in one sequence (toff); every workgroup
-// takes an equal, contiguous share of the numbers, so the work is balanced
-// whatever the cluster sizes are.  The maximum of a run of tiles of one cluster
-// goes to the cluster's maximum with an integer atomic max on the float's bits
-// (non-negative floats order like their bit patterns).
-__global__ void __launch_bounds__(kThreads) dia_pairs(DiaArgs a) {
-    __shared__ __align__(16) float As[16 * 64];
-    __shared__ __align__(16) float Bs[16 * 64];
-    __shared__ float redm[kWaves];
-    const int tid = threadIdx.x;
-    const long long total = a.toff[a.Ksum];
-    const long long per = (total + gridDim.x - 1) / gridDim.x;
-    long long t = per * blockIdx.x;
-    const long long t1 = t + per < total ? t + per : total;
-    if (t >= t1) return;
-    // cluster of the first tile: the last c with toff[c] <= t
-    int c = 0;
-    {
-        int lo = 0, hi = a.Ksum;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if ((long long)a.toff[mid] <= t) lo = mid; else hi = mid;
-        }
-        c = lo;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// 32 members of a cluster in the operand layout of v_mfma_f32_32x32x2_f32: lanes l and
+// l + 32 share member l, the first holds features 8c .. 8c + 3, the second 8c + 4 .. 8c + 7
+// of every chunk c (the order of the features inside a product is free as long as both
+// operands have the same); zeros beyond D.
+template <int CH>
+struct DiaBlock {
+    float v[4 * CH];
+    float norm;          // |x|^2
+    int row;
+};
+// Piece of chunk c of CH = ceil(D / 8): only the last chunk can reach beyond the row.
+__device__ __forceinline__ float4 dia_piece(const float* x, int c, int CH, int half, int D) {
+    const int d0 = 8 * c + 4 * half;
+    if (c < CH - 1) return load4(x + d0);
+    if (D >= 4) return row_piece_shift(row_piece_load(x, d0, D), d0, D);
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (half == 0) {
+        v.x = x[0];
+        if (D > 1) v.y = x[1];
+        if (D > 2) v.z = x[2];
     }
-    auto flush = [&](int cid, float far) {
+    return v;
+}
+// (all loads before the first use: the norms are formed by dia_finish)
+template <int CH>
+__device__ __forceinline__ void dia_load(const DiaArgs& a, DiaBlock<CH>& b, int base, int n, int m0, int lane) {
+    int m = m0 + (lane & 31);
+    m = m < n ? m : n - 1;           // rows beyond the cluster: its last member, whose distances are genuine ones
+    int row = a.perm[base + m];
+    row = (row >= 0 && row < a.N) ? row : 0;
+    b.row = row;
+    const float* x = a.X + (size_t)row * a.D;
+    __builtin_assume(CH == 1 || a.D >= 4);
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) far = fmaxf(far, __shfl_xor(far, o));
-        __syncthreads();
-        if ((tid & 63) == 0) redm[tid >> 6] = far;
-        __syncthreads();
-        if (tid == 0) {
-            for (int w = 1; w < kWaves; ++w) far = fmaxf(far, redm[w]);
-            if (far > 0.f) atomicMax(&a.dmax[cid], __float_as_uint(far));
-        }
-    };
-    while (t < t1) {
-        while (c + 1 < a.Ksum && (long long)a.toff[c + 1] <= t) ++c;      // skips clusters without tiles
-        const int base = a.off[c];
-        const int n = a.off[c + 1] - base;
-        const long long tend = (long long)a.toff[c + 1] < t1 ? (long long)a.toff[c + 1] : t1;
-        if (base < 0 || n < 2 || (long long)base + n > a.N || tend <= t) { t = tend > t ? tend : t + 1; continue; }
-        float far = 0.f;
-        if (n <= 32) {
-            far = tile_pairs_max<2>(a, base, n, 0, 0, As, Bs);
-            ++t;
-        } else {
-            // tiles of the cluster are numbered row by row over the upper triangle
-            const int T = (n + 63) >> 6;
-            int ta = 0;
-            long long rem = t - a.toff[c];
-            while (ta < T && rem >= T - ta) { rem -= T - ta; ++ta; }
-            for (; t < tend && ta < T; ++t) {
-                far = fmaxf(far, tile_pairs_max<4>(a, base, n, ta, ta + (int)rem, As, Bs));
-                if (++rem >= T - ta) { rem = 0; ++ta; }
-            }
-            if (ta >= T) t = tend;
-        }
-        flush(c, far);
+    for (int c = 0; c < CH; ++c) {
+        const float4 p = dia_piece(x, c, CH, lane >> 5, a.D);
+        b.v[4 * c + 0] = p.x; b.v[4 * c + 1] = p.y; b.v[4 * c + 2] = p.z; b.v[4 * c + 3] = p.w;
     }
+}
+// the norms; before that, if `centred`, the rows relative to the row `ctr`
+template <int CH>
+__device__ __forceinline__ void dia_finish(DiaBlock<CH>& b, const float* ctr, bool centred, int D, int lane) {
+    if (centred) {
+        __builtin_assume(CH == 1 || D >= 4);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const float4 o = dia_piece(ctr, c, CH, lane >> 5, D);
+            b.v[4 * c + 0] -= o.x; b.v[4 * c + 1] -= o.y; b.v[4 * c + 2] -= o.z; b.v[4 * c + 3] -= o.w;
+            if (c & 1) asm volatile("" ::: "memory");    // (two pieces of the centre at a time: registers)
+        }
+    }
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4 * CH; ++i) s = fmaf(b.v[i], b.v[i], s);
+    b.norm = s + __shfl_xor(s, 32);
+}
+
+// The squared distance of two rows, direct differences in fp32: fused multiply-adds over
+// the features in index order.
+__device__ __forceinline__ float dia_exact(const float* x, const float* y, int D) {
+    float acc = 0.f;
+    int d = 0;
+#pragma unroll 4
+    for (; d + 4 <= D; d += 4) {
+        const float4 u = load4(x + d), v = load4(y + d);
+        float e = u.x - v.x; acc = fmaf(e, e, acc);
+        e = u.y - v.y; acc = fmaf(e, e, acc);
+        e = u.z - v.z; acc = fmaf(e, e, acc);
+        e = u.w - v.w; acc = fmaf(e, e, acc);
+    }
+    for (; d < D; ++d) {
+        const float e = x[d] - y[d];
+        acc = fmaf(e, e, acc);
+    }
+    return acc;
+}
+
+// The farthest of 32 x 32 pairs.  The matrix cores give -d^2 / 2 = x.y - |x|^2 / 2 - |y|^2 / 2 in
+// fp32; with M the largest |x|^2 in the tile, that and the value of dia_exact differ by at most
+// err = M (10 D + 40) 2^-23 on d^2:
+//   - the accumulation, at most 2 D + 8 roundings (taken as 2^-23 each, truncation included) of
+//     partial sums of at most 2 M, and the norms' own inside that count:  2 (2 D + 8) 2 M 2^-23
+//   - where the rows are centred, 2^-24 of every component of both:        8 M 2^-24
+//   - the chain of dia_exact, (D + 2) 2^-24 of at most 4 M:                (D + 2) 4 M 2^-24
+// So the pair with the largest dia_exact lies within 2 err of the largest matrix value and, where
+// the cluster's maximum is known to be `least` or more, above least - err.  Those pairs, nearly
+// always one or none per tile, wait in the wave's queue until 64 can be evaluated side by side
+// (or the wave ends), so the result is the maximum of dia_exact over all pairs, bit for bit.
+struct DiaQueue {
+    int row[kWave], col[kWave], cluster[kWave];
+};
+
+// evaluates the waiting pairs, one per lane
+__device__ __noinline__ void dia_drain(const float* X, int D, unsigned* dmax, const DiaQueue* q, int count) {
+    const int lane = threadIdx.x & 63;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    if (lane < count) {
+        const float d2 = dia_exact(X + (size_t)q->row[lane] * D, X + (size_t)q->col[lane] * D, D);
+        if (d2 > 0.f) atomicMax(&dmax[q->cluster[lane]], __float_as_uint(d2));
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+}
+
+// Pair of C/D element r: column lane & 31, row dia_row(r, lane / 32) of the tile.
+__device__ __forceinline__ int dia_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
+
+// Appends the pairs of the lanes' mask bits; `same`: both operands are the same rows, only
+// the pairs above the diagonal count.  Returns the new number of waiting pairs.
+__device__ __forceinline__ int dia_push(const float* X, int D, unsigned* dmax, DiaQueue* q, int count, unsigned mask,
+                                        int ra, int rb, int cid, bool same, int lane) {
+    while (__ballot(mask != 0u) != 0ull) {
+        const int r = mask ? __builtin_ctz(mask) : 0;
+        const int i = dia_row(r, lane >> 5), row = __shfl(ra, i);
+        const bool take = mask != 0u && !(same && i >= (lane & 31));
+        mask &= mask - 1u;
+        const unsigned long long takers = __ballot(take);
+        const int n = __popcll(takers);
+        if (count + n > kWave) { dia_drain(X, D, dmax, q, count); count = 0; }
+        if (take) {
+            const int at = count + __popcll(takers & ((1ull << lane) - 1ull));
+            q->row[at] = row; q->col[at] = rb; q->cluster[at] = cid;
+        }
+        count += n;
+    }
+    return count;
+}
+
+__device__ __forceinline__ f32x16 dia_norms(float na, float nb, f32x16 acc, int half) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(half ? 1.f : -0.5f * na, half ? -0.5f * nb : 1.f, acc, 0, 0, 0);
+}
+__device__ __forceinline__ float dia_min(const f32x16& acc) {
+    float v = acc[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) v = fminf(v, acc[r]);
+    return wave_min_f(v);
+}
+__device__ __forceinline__ float dia_err(float M, int D) { return M * ((float)(10 * D + 40) * 0x1p-23f); }
+// bits of the elements at or below -lim / 2
+__device__ __forceinline__ unsigned dia_contenders(const f32x16& acc, float lim) {
+    const float at = -0.5f * lim;
+    unsigned mask = 0u;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mask |= acc[r] <= at ? 1u << r : 0u;
+    return mask;
+}
+
+// What the fast form leaves: err not small against the largest value (a tight cluster far from
+// the origin) - the tile is formed again relative to the cluster's first member `ctr`; rows that
+// are not finite, or whose norms could overflow or vanish - every pair is evaluated.  Not
+// inlined: its registers would cost dia_pairs a resident wave.
+__device__ __noinline__ float2 dia_tile_slow(const float* X, int D, unsigned* dmax, DiaQueue* q, int count,
+                                             const float* ctr, int ra, int rb, int cid, bool same, float least) {
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    const float* x = X + (size_t)ra * D;
+    const float* y = X + (size_t)rb * D;
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    float na = 0.f, nb = 0.f;
+    bool differ = false;
+    const int chunks = (D + 7) >> 3;
+    for (int c = 0; c < chunks; ++c) {
+        const float4 o = dia_piece(ctr, c, chunks, half, D), u = dia_piece(x, c, chunks, half, D),
+                     v = dia_piece(y, c, chunks, half, D);
+        const float ov[4] = {o.x, o.y, o.z, o.w}, uv[4] = {u.x, u.y, u.z, u.w}, vv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float xa = uv[e] - ov[e], xb = vv[e] - ov[e];
+            differ = differ || !(uv[e] == ov[e] && vv[e] == ov[e]);
+            na = fmaf(xa, xa, na);
+            nb = fmaf(xb, xb, nb);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa, xb, acc, 0, 0, 0);
+        }
+    }
+    if (__ballot(differ) != 0ull) {                      // (all rows equal: no distance to add)
+        na += __shfl_xor(na, 32);
+        nb += __shfl_xor(nb, 32);
+        acc = dia_norms(na, nb, acc, half);
+        unsigned mask = 0xffffu;
+        const float M = wave_max_f(fmaxf(na, nb));
+        if (__ballot(!(na < 1e37f && nb < 1e37f)) == 0ull && M >= 1e-30f) {
+            const float err = dia_err(M, D), far = -2.f * dia_min(acc);
+            mask = dia_contenders(acc, fmaxf(far - 2.f * err, least - err));
+            least = fmaxf(least, far - err);
+        }
+        count = dia_push(X, D, dmax, q, count, mask, ra, rb, cid, same, lane);
+    }
+    return make_float2(least, __int_as_float(count));
+}
+
+// One tile: pairs that may be the farthest go to the queue; returns the cluster's new `least`.
+template <int CH>
+__device__ __forceinline__ float dia_tile(const DiaArgs& a, DiaQueue* q, int& count, bool& tight,
+                                          const DiaBlock<CH>& A, const DiaBlock<CH>& B, bool same, const float* ctr,
+                                          int cid, float least, int lane) {
+    const int half = lane >> 5;
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    acc = dia_norms(A.norm, B.norm, acc, half);
+#pragma unroll
+    for (int i = 0; i < 4 * CH; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A.v[i], B.v[i], acc, 0, 0, 0);
+    const bool odd = __ballot(!(A.norm < 1e37f && B.norm < 1e37f)) != 0ull;
+    const float M = wave_max_f(fmaxf(A.norm, B.norm)), far = -2.f * dia_min(acc), err = dia_err(M, a.D);
+    if (odd || M < 1e-30f || err > 0.03f * fmaxf(far, least)) {
+        const float2 r = dia_tile_slow(a.X, a.D, a.dmax, q, count, ctr, A.row, B.row, cid, same, least);
+        count = __builtin_amdgcn_readfirstlane(__float_as_int(r.y));
+        tight = true;
+        return lane_f(r.x, 0);
+    }
+    if (far < least - err) return least;
+    const unsigned mask = dia_contenders(acc, fmaxf(far - 2.f * err, least - err));
+    count = dia_push(a.X, a.D, a.dmax, q, count, mask, A.row, B.row, cid, same, lane);
+    return fmaxf(least, far - err);
+}
+
+// Units t .. t1 - 1.  Rows as they are need no centre to be read; CENTRED: rows relative to the
+// first member of their cluster.  Returns where it stopped: at t1 or, without CENTRED,
+// after a unit too tight for rows as they are.
+template <int CH, bool CENTRED>
+__device__ __forceinline__ long long dia_share(const DiaArgs& a, DiaQueue* q, int& waiting, long long t, long long t1,
+                                               long long total, int nslots, int lane) {
+    bool tight = false;
+    int s = 0;                            // slot of the first unit: the last with first <= t
+    for (int hi = nslots; hi - s > 1;) {
+        const int mid = (s + hi) >> 1;
+        if (a.slots[mid].first <= t) s = mid; else hi = mid;
+    }
+    for (; s < nslots && t < t1; ++s) {
+        long long first = 0, next = total;
+        int c0 = 0, c1 = a.Ksum;
+        if (a.slots) {
+            first = a.slots[s].first; c0 = a.slots[s].c0; c1 = a.slots[s].c1;
+            if (s + 1 < nslots) next = a.slots[s + 1].first;
+        }
+        long long u = t - first;
+        const long long uend = (t1 < next ? t1 : next) - first;
+        if (c1 - c0 > kWave) {            // a cluster at or before that of unit u
+            for (int hi = c1; hi - c0 > 1;) {
+                const int mid = (c0 + hi) >> 1;
+                if ((long long)a.toff[mid] <= u) c0 = mid; else hi = mid;
+            }
+        }
+        for (; c0 < c1 && u < uend; c0 += kWave) {
+            // 64 clusters at a time, one per lane
+            const int cl = c0 + lane;
+            const int wn = cl < c1 ? a.cnt[cl] : 0;
+            const int wbase = cl < c1 ? a.off[cl] : 0;
+            const int wfirst = cl < c1 ? a.toff[cl] : 0;
+            const long long wend = wfirst + units_of(wn);
+            while (u < uend) {
+                const unsigned long long at = __ballot(wfirst <= u && u < wend);
+                if (at == 0ull) break;
+                const int l = (int)__builtin_ctzll(at);
+                const int n = __builtin_amdgcn_readlane(wn, l);
+                const int base = __builtin_amdgcn_readlane(wbase, l);
+                const long long cf = __builtin_amdgcn_readlane(wfirst, l);
+                long long ce = cf + units_of(n);
+                ce = ce < uend ? ce : uend;
+                if (base < 0 || (long long)base + n > a.N) { u = ce; continue; }
+                const int cid = c0 + l;
+                int r0 = __builtin_amdgcn_readfirstlane(a.perm[base]);
+                r0 = (r0 >= 0 && r0 < a.N) ? r0 : 0;
+                const float* ctr = a.X + (size_t)r0 * a.D;
+                float least = lane_f(__uint_as_float(__hip_atomic_load(&a.dmax[cid], __ATOMIC_RELAXED,
+                                                                       __HIP_MEMORY_SCOPE_AGENT)), 0);
+                // units are numbered row by row over the upper triangle
+                const int T = (n + 63) >> 6;
+                int ta = 0;
+                long long rem = u - cf;
+                if (rem >= T) {
+                    // rows before unit rem: ta T - ta (ta - 1) / 2 <= rem
+                    const double h = (double)T + 0.5;
+                    ta = (int)(h - sqrt(h * h - 2.0 * (double)rem));
+                    ta = ta < 0 ? 0 : (ta > T - 1 ? T - 1 : ta);
+                    const auto before = [T](long long r) { return r * T - r * (r - 1) / 2; };
+                    while (ta > 0 && before(ta) > rem) --ta;
+                    while (ta < T - 1 && before(ta + 1) <= rem) ++ta;
+                    rem -= before(ta);
+                }
+                DiaBlock<CH> A0, A1, B;
+                int held = -1;
+                for (; u < ce && ta < T; ++u) {
+                    const int ma = 64 * ta, mb = 64 * (ta + (int)rem);
+                    const bool two = ma + 32 < n;
+                    if (held != ta) {
+                        dia_load<CH>(a, A0, base, n, ma, lane);
+                        dia_load<CH>(a, A1, base, n, ma + 32, lane);
+                        dia_finish<CH>(A0, ctr, CENTRED, a.D, lane);
+                        dia_finish<CH>(A1, ctr, CENTRED, a.D, lane);
+                        held = ta;
+                    }
+                    for (int h = 0; h < 2 && mb + 32 * h < n; ++h) {
+                        if (rem > 0) {
+                            dia_load<CH>(a, B, base, n, mb + 32 * h, lane);
+                            dia_finish<CH>(B, ctr, CENTRED, a.D, lane);
+                        } else {
+                            B = h ? A1 : A0;
+                        }
+                        least = dia_tile<CH>(a, q, waiting, tight, A0, B, rem == 0 && h == 0, ctr, cid, least, lane);
+                        // (on the diagonal the tile of A1 and the first half mirrors that of A0 and the second)
+                        if (two && rem + h > 0)
+                            least = dia_tile<CH>(a, q, waiting, tight, A1, B, rem == 0, ctr, cid, least, lane);
+                    }
+                    if (!CENTRED && tight) return first + u + 1;
+                    if (++rem >= T - ta) { rem = 0; ++ta; }
+                }
+                u = ce;
+            }
+        }
+        t = first + uend;
+    }
+    return t1;
+}
+
+// The units of member pairs (units_of) of all clusters are numbered in one sequence and every wave
+// takes an equal, contiguous share, so the work is balanced whatever the cluster sizes are.
+// A wave keeps the 64 rows of a unit in the operand registers (no LDS, no barrier) and the
+// 64 columns beside them; the row side stays for the next unit of the same rows.  The
+// maximum of a run of units of one cluster goes to the cluster's maximum with an integer
+// atomic max on the float's bits (non-negative floats order like their bit patterns).
+//
+// 43000 units of 36000 clusters of 48 features, mostly below 64 members (1024 searches of 64-4096
+// candidates): 144 us, of which the matrix instructions are 50 us and the vector ones about as
+// much; 16 x 16 threads with 4 x 4 pairs each of direct differences through LDS, two barriers
+// per 16 features, took 247 us.  Representatives and diameters of that batch
+// 390 -> 269 us; clusters of 100-1000 members twice as fast.
+template <int CH>
+__global__ void __launch_bounds__(kThreads, CH <= 6 ? 3 : 2) dia_pairs(DiaArgs a) {
+    __shared__ DiaQueue queue[kWaves];
+    const int lane = threadIdx.x & 63;
+    DiaQueue* q = &queue[threadIdx.x >> 6];
+    int waiting = 0;
+    const long long wave = (long long)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long waves = (long long)gridDim.x * kWaves;
+    const unsigned long long res = a.slots ? *a.reserved : 0ull;
+    const long long total = a.slots ? (long long)(res & ((1ull << kUnitBits) - 1)) : (long long)a.toff[a.Ksum];
+    const int nslots = a.slots ? (int)(res >> kUnitBits) : 1;
+    const long long per = (total + waves - 1) / waves;
+    const long long t0 = per * wave;
+    const long long t1 = t0 + per < total ? t0 + per : total;
+    if (t0 >= t1) return;
+    const long long t = dia_share<CH, false>(a, q, waiting, t0, t1, total, nslots, lane);
+    if (t < t1) dia_share<CH, true>(a, q, waiting, t, t1, total, nslots, lane);
+    dia_drain(a.X, a.D, a.dmax, q, waiting);
 }
 
 // Short searches: one wave per search, four searches per workgroup.  (The walks above
@@ -437,12 +739,30 @@ __global__ void __launch_bounds__(kThreads) dia_final(DiaArgs a) {
 
 }  // namespace
 
+// As many workgroups as the chip holds at once (three or two per compute unit); each wave takes an
+// equal share of the units, whose number is only known on the device.  (1024 searches of
+// 64-4096 candidates: 144 us; twice as many workgroups 150 us, 2048 156 us, 4096 161 us.)
+static void launch_pairs(const DiaArgs& a, hipStream_t st) {
+    const dim3 grid(a.D <= 48 ? 768 : 512), block(kThreads);
+    switch ((a.D + 7) / 8) {
+        case 1: hipLaunchKernelGGL(dia_pairs<1>, grid, block, 0, st, a); break;
+        case 2: hipLaunchKernelGGL(dia_pairs<2>, grid, block, 0, st, a); break;
+        case 3: hipLaunchKernelGGL(dia_pairs<3>, grid, block, 0, st, a); break;
+        case 4: hipLaunchKernelGGL(dia_pairs<4>, grid, block, 0, st, a); break;
+        case 5: hipLaunchKernelGGL(dia_pairs<5>, grid, block, 0, st, a); break;
+        case 6: hipLaunchKernelGGL(dia_pairs<6>, grid, block, 0, st, a); break;
+        case 7: hipLaunchKernelGGL(dia_pairs<7>, grid, block, 0, st, a); break;
+        default: hipLaunchKernelGGL(dia_pairs<8>, grid, block, 0, st, a); break;      // (KB_MAX_D = 64)
+    }
+}
+
 hipError_t launch_diameter(const kb_batch& b, const DiameterCall& c, hipStream_t st) {
     if (b.Ksum <= 0) return hipSuccess;
     DiaArgs a;
     a.G = b.G; a.D = b.D; a.Ksum = b.Ksum; a.Kmax = b.Kmax > 0 ? b.Kmax : 1; a.N = b.N;
     a.seg_off = b.seg_off; a.koff = b.koff; a.X = c.X; a.assign = c.assign; a.diam = c.diam;
     a.cnt = c.cnt; a.off = c.off; a.toff = c.toff; a.bsum = c.bsum; a.dmax = reinterpret_cast<unsigned*>(c.diam); a.perm = c.perm;
+    a.slots = nullptr; a.reserved = nullptr;
     const unsigned kblocks = (unsigned)((b.Ksum + kThreads - 1) / kThreads);
     const unsigned ranges = (unsigned)((b.N + kRange - 1) / kRange);
     // a batch of short searches only: a wave per search, one launch; a batch of mostly
@@ -456,6 +776,15 @@ hipError_t launch_diameter(const kb_batch& b, const DiameterCall& c, hipStream_t
         hipLaunchKernelGGL(dia_wave, wgrid, dim3(kThreads), wlds, st, a);
         return hipGetLastError();
     }
+    if (b.Nmax <= kGroupMax) {
+        a.slots = reinterpret_cast<DiaSlot*>(c.slots);
+        a.reserved = reinterpret_cast<unsigned long long*>(c.bsum);
+        hipLaunchKernelGGL(dia_zero, dim3(kblocks), dim3(kThreads), 0, st, a);
+        hipLaunchKernelGGL(dia_group, dim3((unsigned)b.G), dim3(kGroupThreads), 0, st, a);
+        launch_pairs(a, st);
+        hipLaunchKernelGGL(dia_final, dim3(kblocks), dim3(kThreads), 0, st, a);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(dia_zero, dim3(kblocks), dim3(kThreads), 0, st, a);
     if (a.mixed) hipLaunchKernelGGL(dia_wave, wgrid, dim3(kThreads), wlds, st, a);
     if (ranges) hipLaunchKernelGGL(dia_walk<false>, dim3(ranges), dim3(kThreads), 0, st, a);
@@ -464,9 +793,7 @@ hipError_t launch_diameter(const kb_batch& b, const DiameterCall& c, hipStream_t
     hipLaunchKernelGGL(dia_bscan, dim3(1), dim3(kThreads), 0, st, a, nscan);
     hipLaunchKernelGGL(dia_apply, dim3((unsigned)nscan), dim3(kThreads), 0, st, a);
     if (ranges) hipLaunchKernelGGL(dia_walk<true>, dim3(ranges), dim3(kThreads), 0, st, a);
-    // enough workgroups to fill the chip several times over; each takes an equal share of
-    // the tiles, whose number is only known on the device
-    hipLaunchKernelGGL(dia_pairs, dim3(8192), dim3(kThreads), 0, st, a);
+    launch_pairs(a, st);
     hipLaunchKernelGGL(dia_final, dim3(kblocks), dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }

@@ -67,7 +67,7 @@ struct WsLayout {
     size_t geo_min;    // uint64 [Ksum]  bit pattern of the smallest such distance per cluster
     size_t geo_max;    // uint64 [Ksum]  and of the largest
     size_t dia_off;    // int32 [Ksum + 1] first slot of every cluster in the grouped index list
-    size_t dia_toff;   // int32 [Ksum + 1] first tile of every cluster in the global tile numbering
+    size_t dia_toff;   // int32 [Ksum + 1] first unit of member pairs of every cluster
     size_t dia_bsum;   // int64 [2 * (Ksum / 4096 + 1)] block sums of the two prefix sums
     size_t samp_key;   // double [2*ranges]  partial best keys of searches that cross range borders
     size_t samp_idx;   // int32  [2*ranges]  their candidates
@@ -210,6 +210,7 @@ struct DiameterCall {
     int32_t* toff;    // [Ksum + 1]
     long long* bsum;  // [2 * (Ksum / 4096 + 1)]
     int32_t* perm;    // [N]
+    void* slots;      // 8 N bytes, 16-byte aligned
 };
 hipError_t launch_diameter(const kb_batch& b, const DiameterCall& c, hipStream_t st);
 
