@@ -397,6 +397,7 @@ kb_status kb_cluster_geometry(const kb_batch* batch, const float* X, const float
     c.d2 = (double*)(base + w.geo_d2);
     c.gmin = (unsigned long long*)(base + w.geo_min);
     c.gmax = (unsigned long long*)(base + w.geo_max);
+    c.spare = (int32_t*)(base + w.a_new);
     return dev(launch_geometry(*batch, c, (hipStream_t)stream));
 }
 
@@ -622,6 +623,7 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
             gc.radius = io->radius; gc.d2 = (double*)(base + w.geo_d2);
             gc.gmin = (unsigned long long*)(base + w.geo_min);
             gc.gmax = (unsigned long long*)(base + w.geo_max);
+            gc.spare = (int32_t*)(base + w.a_new);
             if (launch_geometry(*batch, gc, st) != hipSuccess) return KB_EDEVICE;
             if (launch_strategy_mask(*batch, ip->R, io->h, io->target, io->rep, ip->theta_sat, io->M,
                                      io->nvalid, st) != hipSuccess)

@@ -7,6 +7,8 @@
 // minimum (the representative, lowest index on ties) and maximum (the radius)
 // are exact and need no tolerance.
 //
+//   geo_dist and geo_merge, or in batches with searches of more than kGeoMergeMax candidates and
+//   in mixed ones geo_init, geo_dist, geo_rep, geo_final:
 //   geo_init   per-cluster tables: min = all ones, max = 0, rep = none
 //   geo_dist   one workgroup per flat range of candidates walks the searches that
 //              intersect it.  Per search piece the centroids are staged in LDS;
@@ -17,6 +19,11 @@
 //              per cluster with 64-bit integer LDS atomics on their bit patterns
 //              (non-negative doubles order like unsigned integers), then merged
 //              into the global tables.  The distance of every candidate is kept.
+//              With geo_merge to follow, the workgroup itself finds the representatives
+//              of its pieces: a search that lies inside the range is finished, of the at
+//              most two others (one that began before it, one that goes on after it) the
+//              results per cluster wait in a slot of the range.
+//   geo_merge  a wave per search merges the slots of a search that crosses a border.
 //   geo_rep    second, light pass (12 bytes per candidate): the candidates whose
 //              distance equals their cluster's minimum compete for the lowest
 //              index with an integer atomic min.
@@ -29,6 +36,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kNone = 0x7fffffff;
+constexpr int kGeoMergeMax = 16384;    // longer searches: a wave of geo_merge would walk many slots
 
 struct GeoArgs {
     int G, D, Ksum, Kmax;
@@ -43,9 +51,31 @@ struct GeoArgs {
     double* d2;                    // [N]
     unsigned long long* gmin;      // [Ksum]
     unsigned long long* gmax;      // [Ksum]
+    unsigned char* spare;          // [4 N] bytes: slots of searches that began before a range
+    int merged;                    // 1: geo_merge follows, gmin / gmax are not used
     int mixed;                     // 1: searches of at most kShortSearch candidates go to geo_wave, longer
                                    //    ones to the range kernels, in the same call
 };
+
+// Slot of a range: what one piece of a search gives, per cluster.  A piece that began before
+// range r: slot in the 4 bytes per candidate of range r - 1 in `spare` (r >= 1, so that range
+// is whole); a piece that goes on after range r: in the 8 bytes per candidate of range r in
+// d2, whose distances only this workgroup reads, and it has.
+struct GeoSlot {
+    unsigned long long* least;     // [Kmax] bits of the smallest squared distance
+    unsigned long long* most;      // [Kmax] and of the largest
+    int32_t* rep;                  // [Kmax] lowest candidate at the smallest, kNone
+};
+static_assert(20 * KB_MAX_K <= 4 * kGeoRange, "a slot fits the bytes of a range");
+__device__ __forceinline__ GeoSlot geo_slot(const GeoArgs& a, int64_t range, bool began_before) {
+    unsigned char* base = began_before ? a.spare + (range - 1) * (4 * kGeoRange)
+                                       : reinterpret_cast<unsigned char*>(a.d2) + range * (8 * kGeoRange);
+    GeoSlot s;
+    s.least = reinterpret_cast<unsigned long long*>(base);
+    s.most = s.least + a.Kmax;
+    s.rep = reinterpret_cast<int32_t*>(s.most + a.Kmax);
+    return s;
+}
 
 __global__ void __launch_bounds__(kThreads) geo_init(GeoArgs a) {
     const int i = blockIdx.x * kThreads + threadIdx.x;
@@ -227,6 +257,32 @@ __global__ void __launch_bounds__(kThreads) geo_dist(GeoArgs a) {
             }
             __syncthreads();
         }
+        if (a.merged) {
+            int* lrep = reinterpret_cast<int*>(lx);       // (the tile is done with)
+            for (int j = tid; j < K; j += kThreads) lrep[j] = kNone;
+            __syncthreads();
+            // (a thread reads back the distances it wrote itself)
+            for (int p = q0 + tid; p < q1; p += kThreads) {
+                int j = a.assign[p];
+                j = (j >= 0 && j < K) ? j : 0;
+                if ((unsigned long long)__double_as_longlong(a.d2[p]) == lmin[j]) atomicMin(&lrep[j], p);
+            }
+            __syncthreads();
+            const bool before = n0 < r0, after = (int64_t)n0 + ng > r1;
+            if (before || after) {
+                const GeoSlot o = geo_slot(a, blockIdx.x, before);
+                for (int j = tid; j < K; j += kThreads) {
+                    o.least[j] = lmin[j]; o.most[j] = lmax[j]; o.rep[j] = lrep[j];
+                }
+            } else {
+                for (int j = tid; j < K; j += kThreads) {
+                    a.rep[k0 + j] = lrep[j] == kNone ? -1 : lrep[j];
+                    a.radius[k0 + j] = (float)sqrt(__longlong_as_double((long long)lmax[j]));
+                }
+            }
+            __syncthreads();
+            continue;
+        }
         for (int j = tid; j < K; j += kThreads) {
             if (lmin[j] != ~0ull) {
                 atomicMin(&a.gmin[k0 + j], lmin[j]);
@@ -273,6 +329,36 @@ __global__ void __launch_bounds__(kThreads) geo_final(GeoArgs a) {
     if (i >= a.Ksum) return;
     if (a.rep[i] == kNone) a.rep[i] = -1;
     a.radius[i] = (float)sqrt(__longlong_as_double((long long)a.gmax[i]));
+}
+
+// Searches that cross a border of ranges, and the clusters of searches without candidates.
+// (With it one light launch follows geo_dist in place of two, one of them over all candidates,
+// and one before it: representatives and diameters of 1024 searches of 64-4096 candidates 269 -> 255 us,
+// ten iterations of 512 such searches with two re-clusterings 1359 -> 1337 us.)
+__global__ void __launch_bounds__(kThreads) geo_merge(GeoArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int g = (int)blockIdx.x * (kThreads / kWave) + (int)(threadIdx.x >> 6);
+    if (g >= a.G) return;
+    int n0, ng, k0, K;
+    search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
+    const int Kc = ng <= 0 ? 0 : (K > a.Kmax ? a.Kmax : K);
+    for (int j = Kc + lane; j < K; j += kWave) { a.rep[k0 + j] = -1; a.radius[k0 + j] = 0.f; }
+    if (Kc <= 0) return;
+    const int64_t ra = n0 / kGeoRange, rb = ((int64_t)n0 + ng - 1) / kGeoRange;
+    if (ra == rb) return;                                // finished by its range
+    for (int j = lane; j < Kc; j += kWave) {
+        unsigned long long least = ~0ull, most = 0ull;
+        int rep = kNone;
+        for (int64_t r = ra; r <= rb; ++r) {             // (ascending: the lowest candidate on ties)
+            const GeoSlot o = geo_slot(a, r, r != ra);
+            const unsigned long long m = o.least[j], x = o.most[j];
+            const int p = o.rep[j];
+            if (m < least) { least = m; rep = p; }
+            most = x > most ? x : most;
+        }
+        a.rep[k0 + j] = rep == kNone ? -1 : rep;
+        a.radius[k0 + j] = (float)sqrt(__longlong_as_double((long long)most));
+    }
 }
 
 // Batches of short searches: one wave per search, four searches per workgroup, the
@@ -362,6 +448,7 @@ hipError_t launch_geometry(const kb_batch& b, const GeoCall& c, hipStream_t st) 
     a.G = b.G; a.D = b.D; a.Ksum = b.Ksum; a.Kmax = b.Kmax > 0 ? b.Kmax : 1; a.N = b.N;
     a.seg_off = b.seg_off; a.koff = b.koff; a.X = c.X; a.cent = c.cent; a.assign = c.assign;
     a.rep = c.rep; a.radius = c.radius; a.d2 = c.d2; a.gmin = c.gmin; a.gmax = c.gmax;
+    a.spare = reinterpret_cast<unsigned char*>(c.spare); a.merged = 0;
     if (b.Ksum <= 0) return hipSuccess;
     // a batch of short searches only: a wave per search, one launch; a batch of mostly
     // short searches (256 candidates or fewer on average) with longer ones among them: the
@@ -378,7 +465,8 @@ hipError_t launch_geometry(const kb_batch& b, const GeoCall& c, hipStream_t st) 
         return hipGetLastError();
     }
     const unsigned kblocks = (unsigned)((b.Ksum + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(geo_init, dim3(kblocks), dim3(kThreads), 0, st, a);
+    a.merged = !a.mixed && b.Nmax <= kGeoMergeMax;
+    if (!a.merged) hipLaunchKernelGGL(geo_init, dim3(kblocks), dim3(kThreads), 0, st, a);
     if (a.mixed) {
         if ((b.D & 3) == 0) hipLaunchKernelGGL(geo_wave<4>, wgrid, dim3(kThreads), wlds, st, a);
         else hipLaunchKernelGGL(geo_wave<1>, wgrid, dim3(kThreads), wlds, st, a);
@@ -398,9 +486,10 @@ hipError_t launch_geometry(const kb_batch& b, const GeoCall& c, hipStream_t st) 
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL(geo_dist<1>, dim3(ranges), dim3(kThreads), lds, st, a);
         }
-        hipLaunchKernelGGL(geo_rep, dim3(ranges), dim3(kThreads), 0, st, a);
+        if (!a.merged) hipLaunchKernelGGL(geo_rep, dim3(ranges), dim3(kThreads), 0, st, a);
     }
-    hipLaunchKernelGGL(geo_final, dim3(kblocks), dim3(kThreads), 0, st, a);
+    if (a.merged) hipLaunchKernelGGL(geo_merge, wgrid, dim3(kThreads), 0, st, a);
+    else hipLaunchKernelGGL(geo_final, dim3(kblocks), dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }
 

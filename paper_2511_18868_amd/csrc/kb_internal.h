@@ -197,6 +197,7 @@ struct GeoCall {
     double* d2;
     unsigned long long* gmin;
     unsigned long long* gmax;
+    int32_t* spare;                // [N]
 };
 hipError_t launch_geometry(const kb_batch& b, const GeoCall& c, hipStream_t st);
 size_t geometry_lds_bytes(int Kmax, int D);
