@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(kThreads) dia_walk(DiaArgs a) {
         if (n0 >= r1) break;
         if (ng <= 0 || K <= 0) continue;
         if (a.mixed && ng <= kDiaShort) continue;         // (uniform) a wave of dia_wave takes this search:
-                                                          // its clusters keep size 0 here and get no tiles
+                                                          // its clusters keep size 0 here and get no units
         const int q0 = r0 > n0 ? (int)r0 : n0;
         const int q1 = r1 < (int64_t)n0 + ng ? (int)r1 : n0 + ng;
         if (q0 >= q1) continue;
@@ -139,13 +139,13 @@ __device__ __forceinline__ long long units_of(int n) {
     return T * (T + 1) / 2;
 }
 
-// off = exclusive prefix sum of cnt, toff = that of the tile counts, cnt <- 0, in
+// off = exclusive prefix sum of cnt, toff = that of the unit counts, cnt <- 0, in
 // three launches with coalesced accesses: sums of blocks of kScanBlock entries,
 // their prefix sums (one workgroup), then the entries of every block.
 constexpr int kScanBlock = 4096;
 constexpr int kScanU = kScanBlock / kThreads;
 
-// (members, tiles) summed over the workgroup; every thread gets the result
+// (members, units) summed over the workgroup; every thread gets the result
 __device__ __forceinline__ void block_sum2(long long& m, long long& t, long long* red) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { m += __shfl_xor(m, o); t += __shfl_xor(t, o); }
