@@ -776,6 +776,8 @@ hipError_t launch_diameter(const kb_batch& b, const DiameterCall& c, hipStream_t
         hipLaunchKernelGGL(dia_wave, wgrid, dim3(kThreads), wlds, st, a);
         return hipGetLastError();
     }
+    // (dia_group takes the short searches in passing: 3000 searches of 20-90 candidates 139 us with
+    // the wave kernel, the walks and the prefix sums, 73 us here)
     if (b.Nmax <= kGroupMax) {
         a.slots = reinterpret_cast<DiaSlot*>(c.slots);
         a.reserved = reinterpret_cast<unsigned long long*>(c.bsum);
