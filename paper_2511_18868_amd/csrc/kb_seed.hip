@@ -63,7 +63,9 @@ constexpr int streamed_rows(int DS, int R) {
 }
 // Fast keys are log2(minimum) - log2(-log2 u).  Outside these bounds of the largest one
 // an fp32 minimum may have lost its relative accuracy to underflow or overflow (a variate
-// lies between -6 and 53): every row is then formed in fp64.
+// lies between -6 and 53): every row is then formed in fp64.  The margin is ten times the
+// 5e-5 of a key (log2_exponential 3e-5; the minimum's (D + 2) 2^-24, its logarithm and the
+// difference 1.7e-5), of which two compare.
 constexpr float kKeyLow = -40.f, kKeyHigh = 100.f, kKeyMargin = 0x1p-11f;
 constexpr float kFarLow = 0x1p-100f, kFarHigh = 0x1p100f;
 
@@ -111,8 +113,12 @@ __device__ __forceinline__ float add_sq4(float acc, const float4& x, const float
 
 // log2(E) of the exponential variate E = -ln u behind gumbel_variate, up to the constant
 // log2(ln 2), to 3e-5: u from its 32 leading bits, with a series where u is so close to 1
-// that its logarithm would cancel, and in fp64 for the one variate in 10^7 whose
-// leading bits do not determine it well enough.
+// that its logarithm would cancel, and in fp64 for the 9 variates in 10^6 whose leading
+// bits do not determine it well enough.  The bits left out are worth up to 2^-33 of u: beside
+// 1 - u >= kNearOne 2^-32 that is 2^-16 of E, 2.2e-5 on log2(E); beside u >= kNearZero 2^-32 it is
+// 2^-13 of u, that much of an E of 13.8 nats, 1.3e-5.  (Series, logarithms and fp32 roundings
+// add 4e-6.)  These are the variates that win draws, so the lines are generous.
+constexpr unsigned kNearZero = 1u << 12, kNearOne = 1u << 15;
 __device__ __forceinline__ float log2_exponential(unsigned seed_lo, unsigned seed_hi, unsigned draw_lo,
                                                   unsigned draw_hi, int k) {
     unsigned x0, x1;
@@ -122,7 +128,7 @@ __device__ __forceinline__ float log2_exponential(unsigned seed_lo, unsigned see
     const float near1 = v * fmaf(v, fmaf(v, 0.333333343f, 0.5f), 1.f) * 1.44269502f;
     const float E = nx < 0x04000000u ? near1 : -__builtin_amdgcn_logf(u);
     float l = __builtin_amdgcn_logf(E);
-    if (x0 < 256u || nx < 256u)
+    if (x0 < kNearZero || nx < kNearOne)
         l = (float)((-gumbel_variate(seed_lo, seed_hi, draw_lo, draw_hi, k) - log(M_LN2)) * M_LOG2E);
     return l;
 }
