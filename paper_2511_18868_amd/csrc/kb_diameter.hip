@@ -61,7 +61,8 @@ struct DiaArgs {
     int32_t* off;         // [Ksum + 1] first slot of every cluster in perm
     int32_t* toff;        // [Ksum + 1] first unit of every cluster in the numbering of its slot
     long long* bsum;      // [2 * blocks of the prefix sum] (members, units) per block
-    DiaSlot* slots;       // [searches with units] one per search (dia_group); null: one slot, the whole batch
+    DiaSlot* slots;       // [max_slots] one per search with units (dia_group); null: one slot, the whole batch
+    long long max_slots;  // N / 2: such a search has two candidates or more of its own
     unsigned long long* reserved;   // slots (upper bits) and units (lower kUnitBits) handed out so far
     unsigned* dmax;       // [Ksum] bits of the largest squared distance (aliases diam)
     int32_t* perm;        // [N]
@@ -252,12 +253,15 @@ __global__ void __launch_bounds__(kThreads) dia_apply(DiaArgs a) {
 // needed; a search reserves its unit numbers and a slot of the slot list together with one
 // 64-bit atomic, so the slots are in the order of their first units whatever the order of
 // the workgroups.  (1024 searches of 64-4096 candidates: 19 us, the five launches 71 us.)
+// Malformed offsets (overlapping searches) can ask for more slots or units than there can
+// be: lengths are cut to what the host announced, slots beyond the list are dropped.
 __global__ void __launch_bounds__(kGroupThreads) dia_group(DiaArgs a) {
     __shared__ int lcnt[KB_MAX_K];
     const int tid = threadIdx.x, g = blockIdx.x;
     int n0, ng, k0, K;
     search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
     if (K > KB_MAX_K) K = KB_MAX_K;
+    if (ng > kGroupMax) ng = kGroupMax;
     if (ng <= 0 || K <= 0) return;
     for (int j = tid; j < K; j += kGroupThreads) lcnt[j] = 0;
     __syncthreads();
@@ -305,7 +309,7 @@ __global__ void __launch_bounds__(kGroupThreads) dia_group(DiaArgs a) {
             DiaSlot s;
             s.first = (long long)(old & ((1ull << kUnitBits) - 1));
             s.c0 = k0; s.c1 = k0 + K;
-            a.slots[old >> kUnitBits] = s;
+            if ((long long)(old >> kUnitBits) < a.max_slots) a.slots[old >> kUnitBits] = s;
         }
     }
     __syncthreads();
@@ -662,7 +666,8 @@ __global__ void __launch_bounds__(kThreads, CH <= 6 ? 3 : 2) dia_pairs(DiaArgs a
     const long long waves = (long long)gridDim.x * kWaves;
     const unsigned long long res = a.slots ? *a.reserved : 0ull;
     const long long total = a.slots ? (long long)(res & ((1ull << kUnitBits) - 1)) : (long long)a.toff[a.Ksum];
-    const int nslots = a.slots ? (int)(res >> kUnitBits) : 1;
+    const long long taken = (long long)(res >> kUnitBits);
+    const int nslots = a.slots ? (int)(taken < a.max_slots ? taken : a.max_slots) : 1;
     const long long per = (total + waves - 1) / waves;
     const long long t0 = per * wave;
     const long long t1 = t0 + per < total ? t0 + per : total;
@@ -762,7 +767,7 @@ hipError_t launch_diameter(const kb_batch& b, const DiameterCall& c, hipStream_t
     a.G = b.G; a.D = b.D; a.Ksum = b.Ksum; a.Kmax = b.Kmax > 0 ? b.Kmax : 1; a.N = b.N;
     a.seg_off = b.seg_off; a.koff = b.koff; a.X = c.X; a.assign = c.assign; a.diam = c.diam;
     a.cnt = c.cnt; a.off = c.off; a.toff = c.toff; a.bsum = c.bsum; a.dmax = reinterpret_cast<unsigned*>(c.diam); a.perm = c.perm;
-    a.slots = nullptr; a.reserved = nullptr;
+    a.slots = nullptr; a.reserved = nullptr; a.max_slots = b.N / 2;
     const unsigned kblocks = (unsigned)((b.Ksum + kThreads - 1) / kThreads);
     const unsigned ranges = (unsigned)((b.N + kRange - 1) / kRange);
     // a batch of short searches only: a wave per search, one launch; a batch of mostly

@@ -108,3 +108,26 @@ def test_diameters_beside_a_search_too_long_for_one_workgroup(kb, D):
     assert (np.abs(got - want) <= (D + 4) * 2.0 ** -24 * want).all()
     parts, _, _, _ = _diameters(kb, sizes[:len(LONG)], X[:sum(LONG)])
     np.testing.assert_array_equal(got[:len(LONG)].view(np.uint32), parts.view(np.uint32))
+
+
+def test_overlapping_searches_stay_inside_the_workspace(kb):
+    """Offsets that go up and down (a violated precondition) make every second search the whole
+    batch: far more searches with pairs than the workspace has slots for.  The numbers are then
+    meaningless, but nothing beside the workspace and the output is written."""
+    dev = torch.device("cuda:0")
+    N, G = 200, 200_000
+    off = torch.zeros(G + 1, dtype=torch.int32, device=dev)
+    off[1::2] = N
+    koff = torch.zeros(G + 1, dtype=torch.int32, device=dev)
+    koff[1::2] = 1
+    X = torch.randn(N, 8, device=dev)
+    assign = torch.zeros(N, dtype=torch.int32, device=dev)
+    b = kb.make_batch(G, 8, 4, N, 1, 1, N, off, koff)
+    wb = kb.kb_workspace_bytes(b, kb.make_params(1e15, 1e12, 1.0, 0.0, 0.5, 1))
+    wb = (wb + 255) // 256 * 256
+    ws = torch.full((wb + 32 * G,), 0xA5, dtype=torch.uint8, device=dev)
+    diam = torch.full((256,), -1.0, device=dev)
+    kb.kb_cluster_diameter(b, X, assign, diam, ws, wb)
+    torch.cuda.synchronize()
+    assert (ws[wb:] == 0xA5).all()
+    assert (diam[1:] == -1.0).all()
