@@ -368,6 +368,10 @@ __device__ __forceinline__ void rounds_search(const RoundsArgs& r, int g, unsign
             __syncthreads();
             bu = redv[0]; bf = redi[0];
             for (int w = 1; w < NW; ++w) merge_arm(redv[w], redi[w]);
+        } else {
+            // scores that are not numbers (c = +inf at t = 1) leave the lanes with different
+            // arms: lane 0 decides, as in a selection call of its own
+            bf = __builtin_amdgcn_readfirstlane(bf);
         }
         const int I = bf >= 0 ? bf / S : -1, s = bf >= 0 ? bf - I * S : -1;
         if (tid == 0) {

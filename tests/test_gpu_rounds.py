@@ -32,12 +32,10 @@ def _batch(shape, S):
     return synth.config2(seed=305, N=16384, D=8, K=2, S=S, iters=3)     # the longest search of one workgroup
 
 
-@pytest.mark.parametrize("S", [1, 6, 12, 32])
-@pytest.mark.parametrize("shape", ["wave", "waveedge", "wide", "narrow", "longest"])
-def test_rounds_in_one_launch_equal_the_stages_one_by_one(kb, shape, S):
+def _compare_with_the_stages(kb, b, T, **params):
+    """T iterations of one kb_iterate call against the stages called one by one."""
     import torch
-    b = _batch(shape, S)
-    T, R = 5, 3
+    R = 3
     h, target, _ = synth.signatures(b, R)
     theta = 0.9                   # (few arms masked)
     fb = [synth.feedback(b, seed=r) for r in range(T)]
@@ -46,6 +44,8 @@ def test_rounds_in_one_launch_equal_the_stages_one_by_one(kb, shape, S):
 
     def start():
         d = kb.DeviceBatch(b)
+        for name, value in params.items():
+            setattr(d.params, name, value)
         up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(d.device)  # noqa: E731
         d.cluster()
         d.cluster_geometry()
@@ -73,3 +73,21 @@ def test_rounds_in_one_launch_equal_the_stages_one_by_one(kb, shape, S):
     for name in ("visits", "rsum", "t", "Ncs", "mu", "ucb"):
         a, c = d.host(name), e.host(name)
         np.testing.assert_array_equal(a.view(np.uint8), c.view(np.uint8), err_msg=name)
+
+
+@pytest.mark.parametrize("S", [1, 6, 12, 32])
+@pytest.mark.parametrize("shape", ["wave", "waveedge", "wide", "narrow", "longest"])
+def test_rounds_in_one_launch_equal_the_stages_one_by_one(kb, shape, S):
+    _compare_with_the_stages(kb, _batch(shape, S), 5)
+
+
+@pytest.mark.parametrize("prior_n", [0.0, 1.0])
+@pytest.mark.parametrize("shape", ["wave", "narrow"])
+def test_scores_that_are_not_numbers_choose_one_arm(kb, shape, prior_n):
+    """c = +inf passes the checks and gives inf * sqrt(ln 1 / n) = NaN in a search's first
+    iteration (beside +inf for untried arms when there are no pseudo-visits), +inf later."""
+    b = _batch(shape, 6)
+    b.t[:] = 1
+    b.visits[:, ::2] = 0
+    b.rsum[:, ::2] = 0.0
+    _compare_with_the_stages(kb, b, 3, c=float("inf"), prior_n=prior_n)
