@@ -418,8 +418,8 @@ kb_status kb_update_stats(const kb_batch *batch, const kb_params *params,
  *       (the cluster-arm statistics are those an aggregation of visits / rsum over the
  *       alive members of every cluster gives, so they follow a re-clustering: they
  *       are aggregated in the first round and after every re-clustering, kept as
- *       integer tables in the workspace and advanced by the update step in between,
- *       which gives the same bits as aggregating again)
+ *       integer tables on chip or in the workspace and advanced by the updates in
+ *       between, which gives the same bits as aggregating again)
  *   kb_sample_signature, draw number sample.draw + r       -> ksel_log[r]
  *   kb_update_stats with reward[r], ok[r]                  -> visits, rsum, Ncs, mu, t
  * The frontier is fixed during the call (new kernels are appended by the caller

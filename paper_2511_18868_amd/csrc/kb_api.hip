@@ -601,10 +601,11 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
     bool ordered = false;
     // The cluster-arm tables (visit counts and fixed-point reward sums of the alive
     // members of every cluster) are aggregated from the per-candidate history in the
-    // first round and after every re-clustering, kept in the workspace, and advanced by
-    // the update step in between: integer tables, so the carried ones equal a fresh
-    // aggregation bit for bit and a round without re-clustering reads K_g*S entries per
-    // search instead of N_g*S.
+    // first round and after every re-clustering and advanced by the updates in between:
+    // integer tables, so the carried ones equal a fresh aggregation bit for bit and a
+    // round without re-clustering reads K_g*S entries per search instead of N_g*S.  They
+    // live in LDS where the rounds between two re-clusterings are one launch
+    // (rounds_in_one_launch), in the workspace where every round is launches of its own.
     const UcbScratch us = ucb_scratch_in_ws(batch, ws);
     bool tables_valid = false;
     for (int32_t r = 0; r < ip->rounds; ++r) {

@@ -140,7 +140,7 @@ struct UcbCall {
     int chunked, keep_tables, from_tables;
 };
 hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st);
-bool ucb_wave_per_search(const kb_batch& b);   // a plain or table-keeping selection call runs one wave per search (no scheduling order needed)
+bool ucb_wave_per_search(const kb_batch& b);   // a plain selection call runs one wave per search (no scheduling order needed)
 
 // The whole round of a batch of very short searches in one launch (one wave per
 // search): true if batch and mode allow it; the launch itself takes the three

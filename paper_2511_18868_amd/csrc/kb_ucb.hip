@@ -624,6 +624,8 @@ hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
     // a batch of short searches only: a wave per search (if four searches' tables fit the
     // 64 KB of LDS a kernel gets without asking); needs no scheduling order
     if (ucb_wave_per_search(b)) {
+        if (a.keep) return hipErrorInvalidValue;      // ucb_wave leaves no tables (rounds_in_one_launch holds for
+                                                      // every such batch, so kb_iterate does not ask for them)
         const int per = wave_table_bytes(b);
         hipLaunchKernelGGL(ucb_wave, dim3((unsigned)((b.G + kWaves - 1) / kWaves)), dim3(kThreads),
                            (size_t)per * kWaves, st, a, per);
