@@ -91,3 +91,11 @@ def test_scores_that_are_not_numbers_choose_one_arm(kb, shape, prior_n):
     b.visits[:, ::2] = 0
     b.rsum[:, ::2] = 0.0
     _compare_with_the_stages(kb, b, 3, c=float("inf"), prior_n=prior_n)
+
+
+@pytest.mark.parametrize("nmax", [40, 600], ids=["wave", "workgroup"])
+def test_more_rounds_than_one_launch_runs(kb, nmax):
+    """A launch runs 1024 iterations at most: the next one rebuilds its tables from the
+    advanced history and goes on with the logs, rewards, draws and t where the first ended."""
+    b = synth.config5(G=3, nmin=nmax // 2, nmax=nmax, D=8, S=6, kcap=4, kdiv=4, iters=3, seed=306)
+    _compare_with_the_stages(kb, b, 1030)
