@@ -421,24 +421,139 @@ struct DiaQueue {
     int row[kWave], col[kWave], cluster[kWave];
 };
 
-// evaluates the waiting pairs, one per lane
+// evaluates the waiting pairs, one per lane.  Pairs of a cluster wait side by side, so each run of
+// them sends its largest alone to the cluster's maximum, and only if it is larger than what is there:
+// a line of 16 maxima takes atomics one after the other.  (40000 candidates in 16 clusters of 16
+// features, the pair kernel: 137 us with an atomic per pair, 69 us.)
 __device__ __noinline__ void dia_drain(const float* X, int D, unsigned* dmax, const DiaQueue* q, int count) {
     const int lane = threadIdx.x & 63;
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    float d2 = 0.f;
+    int cid = -1;
     if (lane < count) {
-        const float d2 = dia_exact(X + (size_t)q->row[lane] * D, X + (size_t)q->col[lane] * D, D);
-        if (d2 > 0.f) atomicMax(&dmax[q->cluster[lane]], __float_as_uint(d2));
+        cid = q->cluster[lane];
+        const unsigned have = __hip_atomic_load(&dmax[cid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        d2 = dia_exact(X + (size_t)q->row[lane] * D, X + (size_t)q->col[lane] * D, D);
+        if (!(d2 > __uint_as_float(have))) d2 = 0.f;     // (a NaN does not count)
+    }
+    if (__ballot(d2 > 0.f) != 0ull) {
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {            // the largest from this lane to the end of its run
+            const float od = __shfl_down(d2, o);
+            const int oc = __shfl_down(cid, o);
+            if (lane + o < kWave && oc == cid) d2 = fmaxf(d2, od);
+        }
+        const int before = __shfl_up(cid, 1);
+        if (d2 > 0.f && (lane == 0 || before != cid)) atomicMax(&dmax[cid], __float_as_uint(d2));
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+}
+
+// All pairs of a unit from direct differences, for units with many contenders (equal distances:
+// rows of few distinct values, rows that occur many times).  Rows and columns stay in registers, one
+// of each per lane.  Every group of 16 lanes takes the pairs of 16 columns and 16 rows; the rows are
+// turned through the group (a modifier of the subtraction, no instruction of its own), so a pair and
+// feature is two vector instructions, as in a kernel that forms every pair this way.  Four group
+// squares at a time: four passes, three on the diagonal, one for 32 members or fewer.
+template <int S>
+__device__ __forceinline__ float dia_turned(float v) {
+    if constexpr (S == 0) return v;
+    else return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + S, 0xf, 0xf, true));
+}
+template <int S = 0>
+__device__ __forceinline__ void dia_turn(float (&acc)[16], float x, float y) {
+    const float e = dia_turned<S>(x) - y;
+    acc[S] = fmaf(e, e, acc[S]);
+    if constexpr (S < 15) dia_turn<S + 1>(acc, x, y);
+}
+// Members m0 .. m0 + 63, one per lane (beyond the cluster: its last member), features in order.
+// Lanes l and l + 32 load halves of the rows l and 32 + l, so a load takes 32 consecutive bytes of
+// a row, and trade them.
+template <int CH>
+__device__ __forceinline__ void dia_load_rows(float (&v)[8 * CH], const float* X, const int32_t* perm, int N, int D,
+                                              int base, int n, int m0, int lane) {
+    const auto row_of = [&](int m) {
+        const int row = perm[(size_t)base + (m < n ? m : n - 1)];
+        return X + (size_t)((row >= 0 && row < N) ? row : 0) * D;
+    };
+    const float* lo = row_of(m0 + (lane & 31));
+    const float* hi = row_of(m0 + 32 + (lane & 31));
+    __builtin_assume(CH == 1 || D >= 4);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const float4 p = dia_piece(lo, c, CH, lane >> 5, D), q = dia_piece(hi, c, CH, lane >> 5, D);
+        v[8 * c + 0] = p.x; v[8 * c + 1] = p.y; v[8 * c + 2] = p.z; v[8 * c + 3] = p.w;
+        v[8 * c + 4] = q.x; v[8 * c + 5] = q.y; v[8 * c + 6] = q.z; v[8 * c + 7] = q.w;
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[8 * c + e]),
+                                                            __float_as_uint(v[8 * c + 4 + e]), false, false);
+            v[8 * c + e] = __uint_as_float(w[0]);
+            v[8 * c + 4 + e] = __uint_as_float(w[1]);
+        }
+    }
+}
+// Returns the largest squared distance of the unit.
+template <int CH>
+__device__ __noinline__ float dia_unit_direct(const float* X, const int32_t* perm, int N, int D, int base, int n,
+                                              int ma, int mb) {
+    const int lane = threadIdx.x & 63, group = lane >> 4;
+    D = __builtin_amdgcn_readfirstlane(D);
+    const bool one = ma == mb && n - ma <= 32;
+    const int passes = __builtin_amdgcn_readfirstlane(one ? 1 : (ma == mb ? 3 : 4));
+    float x[8 * CH], y[8 * CH];
+    dia_load_rows<CH>(y, X, perm, N, D, base, n, mb, lane);
+    dia_load_rows<CH>(x, X, perm, N, D, base, n, ma, lane);
+    if (one) {
+        // group squares (columns, rows) of the one pass: (0,0) (1,1) (1,0) and (0,0) once more
+        const int from = group == 1 || group == 2 ? 16 + (lane & 15) : lane & 15;
+#pragma unroll
+        for (int i = 0; i < 8 * CH; ++i) {
+            y[i] = __shfl(y[i], from);
+            x[i] = __shfl(x[i], group == 1 ? lane : lane & 15);
+        }
+    }
+    float far = 0.f;
+    for (int p = 0;; ++p) {
+        float acc[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        // (a branch for every four features: in one block the compiler turns the values of all of
+        // them ahead of their use, into registers that there are not)
+#pragma unroll
+        for (int q = 0; q < 2 * CH; ++q) {
+            if (4 * q < D) {
+#pragma unroll
+                for (int i = 4 * q; i < 4 * q + 4; ++i) dia_turn(acc, x[i], y[i]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) far = fmaxf(far, acc[r]);
+        if (p + 1 >= passes) break;
+#pragma unroll
+        for (int i = 0; i < 8 * CH; ++i) x[i] = __shfl(x[i], (lane + 16) & 63);
+    }
+    return wave_max_f(far);
 }
 
 // Pair of C/D element r: column lane & 31, row dia_row(r, lane / 32) of the tile.
 __device__ __forceinline__ int dia_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
 
 // Appends the pairs of the lanes' mask bits; `same`: both operands are the same rows, only
-// the pairs above the diagonal count.  Returns the new number of waiting pairs.
+// the pairs above the diagonal count.  Returns the new number of waiting pairs.  If a tile has
+// more than kFlood, none of them stay and the unit and what is left of the cluster's share are
+// evaluated whole (dia_unit_direct).  64: fewer, and continuous rows come near it (16: clusters of 350
+// members of 32 features 93 -> 147 us).  One-hot rows, every distance the same, without / with
+// the line: 1024 searches of 64-4096 rows of 48 features 3.5 / 0.40 ms, one of 40000 rows of 16
+// features in 16 clusters 537 / 0.11 ms (every pair directly, as the kernel before the matrix
+// cores did: 0.28 and 0.12 ms).
+constexpr int kFlood = 64, kFloodBit = 1 << 16;
 __device__ __forceinline__ int dia_push(const float* X, int D, unsigned* dmax, DiaQueue* q, int count, unsigned mask,
                                         int ra, int rb, int cid, bool same, int lane) {
+    int pushed = 0, others = count;          // (waiting pairs of other tiles)
     while (__ballot(mask != 0u) != 0ull) {
         const int r = mask ? __builtin_ctz(mask) : 0;
         const int i = dia_row(r, lane >> 5), row = __shfl(ra, i);
@@ -446,7 +561,9 @@ __device__ __forceinline__ int dia_push(const float* X, int D, unsigned* dmax, D
         mask &= mask - 1u;
         const unsigned long long takers = __ballot(take);
         const int n = __popcll(takers);
-        if (count + n > kWave) { dia_drain(X, D, dmax, q, count); count = 0; }
+        pushed += n;
+        if (pushed > kFlood) return others | kFloodBit;
+        if (count + n > kWave) { dia_drain(X, D, dmax, q, count); count = 0; others = 0; }
         if (take) {
             const int at = count + __popcll(takers & ((1ull << lane) - 1ull));
             q->row[at] = row; q->col[at] = rb; q->cluster[at] = cid;
@@ -478,7 +595,8 @@ __device__ __forceinline__ unsigned dia_contenders(const f32x16& acc, float lim)
 // What the fast form leaves: err not small against the largest value (a tight cluster far from
 // the origin) - the tile is formed again relative to the cluster's first member `ctr`; rows that
 // are not finite, or whose norms could overflow or vanish - every pair is evaluated.  Not
-// inlined: its registers would cost dia_pairs a resident wave.
+// inlined: its registers would cost dia_pairs a resident wave.  Returns `least` and the
+// number of waiting pairs, kFloodBit beside it as in dia_push.
 __device__ __noinline__ float2 dia_tile_slow(const float* X, int D, unsigned* dmax, DiaQueue* q, int count,
                                              const float* ctr, int ra, int rb, int cid, bool same, float least) {
     const int lane = threadIdx.x & 63, half = lane >> 5;
@@ -521,9 +639,10 @@ __device__ __noinline__ float2 dia_tile_slow(const float* X, int D, unsigned* dm
 
 // One tile: pairs that may be the farthest go to the queue; returns the cluster's new `least`.
 template <int CH>
-__device__ __forceinline__ float dia_tile(const DiaArgs& a, DiaQueue* q, int& count, bool& tight,
+__device__ __forceinline__ float dia_tile(const DiaArgs& a, DiaQueue* q, int& count, bool& tight, bool& flood,
                                           const DiaBlock<CH>& A, const DiaBlock<CH>& B, bool same, const float* ctr,
                                           int cid, float least, int lane) {
+    if (flood) return least;
     const int half = lane >> 5;
     f32x16 acc;
 #pragma unroll
@@ -536,12 +655,16 @@ __device__ __forceinline__ float dia_tile(const DiaArgs& a, DiaQueue* q, int& co
     if (odd || M < 1e-30f || err > 0.03f * fmaxf(far, least)) {
         const float2 r = dia_tile_slow(a.X, a.D, a.dmax, q, count, ctr, A.row, B.row, cid, same, least);
         count = __builtin_amdgcn_readfirstlane(__float_as_int(r.y));
+        flood = flood || (count & kFloodBit) != 0;
+        count &= kFloodBit - 1;
         tight = true;
         return lane_f(r.x, 0);
     }
     if (far < least - err) return least;
     const unsigned mask = dia_contenders(acc, fmaxf(far - 2.f * err, least - err));
     count = dia_push(a.X, a.D, a.dmax, q, count, mask, A.row, B.row, cid, same, lane);
+    flood = flood || (count & kFloodBit) != 0;
+    count &= kFloodBit - 1;
     return fmaxf(least, far - err);
 }
 
@@ -611,6 +734,7 @@ __device__ __forceinline__ long long dia_share(const DiaArgs& a, DiaQueue* q, in
                 }
                 DiaBlock<CH> A0, A1, B;
                 int held = -1;
+                bool flood = false;
                 for (; u < ce && ta < T; ++u) {
                     const int ma = 64 * ta, mb = 64 * (ta + (int)rem);
                     const bool two = ma + 32 < n;
@@ -628,14 +752,28 @@ __device__ __forceinline__ long long dia_share(const DiaArgs& a, DiaQueue* q, in
                         } else {
                             B = h ? A1 : A0;
                         }
-                        least = dia_tile<CH>(a, q, waiting, tight, A0, B, rem == 0 && h == 0, ctr, cid, least, lane);
+                        least = dia_tile<CH>(a, q, waiting, tight, flood, A0, B, rem == 0 && h == 0, ctr, cid, least, lane);
                         // (on the diagonal the tile of A1 and the first half mirrors that of A0 and the second)
                         if (two && rem + h > 0)
-                            least = dia_tile<CH>(a, q, waiting, tight, A1, B, rem == 0, ctr, cid, least, lane);
+                            least = dia_tile<CH>(a, q, waiting, tight, flood, A1, B, rem == 0, ctr, cid, least, lane);
                     }
-                    if (!CENTRED && tight) return first + u + 1;
+                    if (flood) break;
+                    if (!CENTRED && tight) { ce = u + 1; break; }
                     if (++rem >= T - ta) { rem = 0; ++ta; }
                 }
+                if (flood) {
+                    // many contenders: this unit and the rest of the cluster's share whole
+                    float whole = 0.f;
+                    for (; u < ce && ta < T; ++u) {
+                        whole = fmaxf(whole, dia_unit_direct<CH>(a.X, a.perm, (int)a.N, a.D, base, n, 64 * ta,
+                                                                 64 * (ta + (int)rem)));
+                        if (++rem >= T - ta) { rem = 0; ++ta; }
+                    }
+                    if (lane == 0 && __float_as_uint(whole) >
+                                         __hip_atomic_load(&a.dmax[cid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                        atomicMax(&a.dmax[cid], __float_as_uint(whole));
+                }
+                if (!CENTRED && tight) return first + ce;
                 u = ce;
             }
         }

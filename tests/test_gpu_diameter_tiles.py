@@ -29,6 +29,10 @@ def _rows(kind, N, D, rng):
         return np.rint(x)
     if kind == "repeated":
         return x[rng.integers(0, max(1, N // 40), N)].copy()
+    if kind == "few":                     # eight distinct rows
+        return x[rng.integers(0, min(8, N), N)].copy()
+    if kind == "onehot":                  # all distances 0 or sqrt(2)
+        return np.eye(D, dtype=np.float32)[rng.integers(0, D, N)]
     if kind == "equal":
         return np.ones((N, D), np.float32)
     if kind == "far":
@@ -81,8 +85,9 @@ def _want(X, assign, off, koff):
     return out
 
 
-@pytest.mark.parametrize("kind", ["plain", "grid", "repeated", "equal", "far", "tiny", "huge", "infinite"])
-@pytest.mark.parametrize("D", [1, 3, 4, 7, 8, 9, 21, 48, 50, 64])
+@pytest.mark.parametrize("kind", ["plain", "grid", "repeated", "few", "onehot", "equal", "far", "tiny", "huge",
+                                  "infinite"])
+@pytest.mark.parametrize("D", [1, 3, 4, 7, 8, 9, 21, 40, 48, 50, 64])
 def test_diameters_at_the_edges_of_the_tiles(kb, D, kind):
     rng = np.random.default_rng([D, len(kind)])
     short, long_ = [[n] for n in SHORT] + [[5, 30, 1, 20]], [[n] for n in LONG] + [[40, 70, 1, 33, 2] * 3]
@@ -108,6 +113,26 @@ def test_diameters_beside_a_search_too_long_for_one_workgroup(kb, D):
     assert (np.abs(got - want) <= (D + 4) * 2.0 ** -24 * want).all()
     parts, _, _, _ = _diameters(kb, sizes[:len(LONG)], X[:sum(LONG)])
     np.testing.assert_array_equal(got[:len(LONG)].view(np.uint32), parts.view(np.uint32))
+
+
+@pytest.mark.parametrize("D", [3, 8, 30, 50])
+@pytest.mark.parametrize("sizes", [[[16384]], [[5000, 70, 40], [9000, 31], [12000]], [[20000, 64]]],
+                         ids=["one", "several", "long"])
+def test_equal_distances_in_clusters_of_many_units(kb, sizes, D):
+    """Distances of 0 and sqrt(2) everywhere, so that every unit is evaluated whole, several in a
+    row by one wave - and one pair farther apart in each search's first cluster."""
+    rng = np.random.default_rng(D)
+    X = _rows("onehot", sum(map(sum, sizes)), D, rng)
+    _, assign, off, _ = _diameters(kb, sizes, X)
+    want = []
+    for g, c in enumerate(sizes):
+        first = off[g] + np.flatnonzero(assign[off[g]:off[g + 1]] == 0)
+        i, j = rng.choice(first, 2, replace=False)
+        X[i], X[j] = 0.0, 0.0
+        X[i, D - 1], X[j, D - 1] = 3.0, -2.5
+        want += [5.5] + [np.sqrt(np.float32(2.0))] * (len(c) - 1)
+    got, _, _, _ = _diameters(kb, sizes, X)
+    np.testing.assert_array_equal(got, np.array(want, np.float32))
 
 
 def test_overlapping_searches_stay_inside_the_workspace(kb):
