@@ -40,6 +40,7 @@ constexpr int kDiaShort = 64;    // searches of at most this many candidates: al
 constexpr int kGroupMax = 16384; // batches without longer searches: members grouped by dia_group, a
                                  // workgroup per search
 constexpr int kGroupThreads = 512;
+constexpr int kGroupMany = 4096, kGroupSearches = 8;     // batches of so many searches: 8 per workgroup
 constexpr int kUnitBits = 40;    // units of a batch < 2^40 (fewer than 2^31 candidates in searches of at
                                  // most 16384), searches <= 2^20
 
@@ -250,78 +251,112 @@ __global__ void __launch_bounds__(kThreads) dia_apply(DiaArgs a) {
 // Batches whose searches all have at most kGroupMax candidates: one workgroup per search
 // does in one launch what the walks and the prefix sums do in five.  The members of a
 // search are grouped inside its own part of `perm`, so no prefix sum over the batch is
-// needed; a search reserves its unit numbers and a slot of the slot list together with one
+// needed; a workgroup reserves its unit numbers and slots of the slot list together with one
 // 64-bit atomic, so the slots are in the order of their first units whatever the order of
 // the workgroups.  (1024 searches of 64-4096 candidates: 19 us, the five launches 71 us.)
+// The atomics of all workgroups queue up, 12 ns each, so in a batch of many searches a
+// workgroup takes B = 8 of them with one reservation (20000 searches of 100 candidates
+// 244 -> 47 us).
 // Malformed offsets (overlapping searches) can ask for more slots or units than there can
 // be: lengths are cut to what the host announced, slots beyond the list are dropped.
+template <int B>
 __global__ void __launch_bounds__(kGroupThreads) dia_group(DiaArgs a) {
-    __shared__ int lcnt[KB_MAX_K];
-    const int tid = threadIdx.x, g = blockIdx.x;
-    int n0, ng, k0, K;
-    search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
-    if (K > KB_MAX_K) K = KB_MAX_K;
-    if (ng > kGroupMax) ng = kGroupMax;
-    if (ng <= 0 || K <= 0) return;
-    for (int j = tid; j < K; j += kGroupThreads) lcnt[j] = 0;
+    __shared__ int lcnt[B][KB_MAX_K];
+    __shared__ int units[B];
+    const int tid = threadIdx.x, g0 = blockIdx.x * B;
+    int n0[B], ng[B], k0[B], K[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        n0[b] = ng[b] = k0[b] = K[b] = 0;
+        if (g0 + b < a.G) search_bounds(a.seg_off, a.koff, g0 + b, a.N, a.Ksum, n0[b], ng[b], k0[b], K[b]);
+        if (K[b] > KB_MAX_K) K[b] = KB_MAX_K;
+        if (ng[b] > kGroupMax) ng[b] = kGroupMax;
+        for (int j = tid; j < K[b]; j += kGroupThreads) lcnt[b][j] = 0;
+    }
     __syncthreads();
     constexpr int U = 4;
-    const int32_t* as = a.assign + n0;
-    for (int p0 = tid; p0 < ng; p0 += U * kGroupThreads) {
-        int j[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) j[u] = p0 + u * kGroupThreads < ng ? as[p0 + u * kGroupThreads] : 0;
+    for (int b = 0; b < B; ++b) {
+        if (K[b] <= 0) continue;
+        const int32_t* as = a.assign + n0[b];
+        for (int p0 = tid; p0 < ng[b]; p0 += U * kGroupThreads) {
+            int j[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (p0 + u * kGroupThreads < ng) atomicAdd(&lcnt[(j[u] >= 0 && j[u] < K) ? j[u] : 0], 1);
+            for (int u = 0; u < U; ++u) j[u] = p0 + u * kGroupThreads < ng[b] ? as[p0 + u * kGroupThreads] : 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (p0 + u * kGroupThreads < ng[b]) atomicAdd(&lcnt[b][(j[u] >= 0 && j[u] < K[b]) ? j[u] : 0], 1);
+        }
     }
     __syncthreads();
-    if (tid < kWave) {
-        // exclusive prefix sums of members and units, four clusters per lane (K <= 256)
-        int n[4], m = 0, t = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int j = 4 * tid + e;
-            n[e] = j < K ? lcnt[j] : 0;
-            m += n[e];
-            t += (int)units_of(n[e]);
-        }
-        int im = m, it = t;
+    for (int b = 0; b < B; ++b) {
+        if ((tid >> 6) == b) {                           // (B <= 8 waves: one search each)
+            // exclusive prefix sums of members and units, four clusters per lane (K <= 256)
+            const int lane = tid & 63;
+            int n[4], m = 0, t = 0;
 #pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int um = __shfl_up(im, o), ut = __shfl_up(it, o);
-            if (tid >= o) { im += um; it += ut; }
-        }
-        const int total = __shfl(it, kWave - 1);
-        int om = n0 + im - m, ot = it - t;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int j = 4 * tid + e;
-            if (j < K) {
-                a.cnt[k0 + j] = n[e]; a.off[k0 + j] = om; a.toff[k0 + j] = ot;
-                lcnt[j] = om - n0;
+            for (int e = 0; e < 4; ++e) {
+                const int j = 4 * lane + e;
+                n[e] = j < K[b] && ng[b] > 0 ? lcnt[b][j] : 0;
+                m += n[e];
+                t += (int)units_of(n[e]);
             }
-            om += n[e];
-            ot += (int)units_of(n[e]);
+            int im = m, it = t;
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const int um = __shfl_up(im, o), ut = __shfl_up(it, o);
+                if (lane >= o) { im += um; it += ut; }
+            }
+            if (lane == kWave - 1) units[b] = it;
+            int om = n0[b] + im - m, ot = it - t;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int j = 4 * lane + e;
+                if (j < K[b] && ng[b] > 0) {
+                    a.cnt[k0[b] + j] = n[e]; a.off[k0[b] + j] = om; a.toff[k0[b] + j] = ot;
+                    lcnt[b][j] = om - n0[b];
+                }
+                om += n[e];
+                ot += (int)units_of(n[e]);
+            }
         }
-        if (tid == 0 && total > 0) {
-            const unsigned long long old = atomicAdd(a.reserved, (1ull << kUnitBits) | (unsigned long long)total);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        unsigned long long want = 0;
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            if (units[b] > 0) want += (1ull << kUnitBits) | (unsigned long long)units[b];
+        if (want) {
+            const unsigned long long old = atomicAdd(a.reserved, want);
+            long long at = (long long)(old >> kUnitBits);
             DiaSlot s;
             s.first = (long long)(old & ((1ull << kUnitBits) - 1));
-            s.c0 = k0; s.c1 = k0 + K;
-            if ((long long)(old >> kUnitBits) < a.max_slots) a.slots[old >> kUnitBits] = s;
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                if (units[b] <= 0) continue;
+                s.c0 = k0[b]; s.c1 = k0[b] + K[b];
+                if (at < a.max_slots) a.slots[at] = s;
+                ++at;
+                s.first += units[b];
+            }
         }
     }
-    __syncthreads();
-    for (int p0 = tid; p0 < ng; p0 += U * kGroupThreads) {
-        int j[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) j[u] = p0 + u * kGroupThreads < ng ? as[p0 + u * kGroupThreads] : 0;
+    for (int b = 0; b < B; ++b) {
+        if (K[b] <= 0) continue;
+        const int32_t* as = a.assign + n0[b];
+        for (int p0 = tid; p0 < ng[b]; p0 += U * kGroupThreads) {
+            int j[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (p0 + u * kGroupThreads < ng) {
-                const int pos = atomicAdd(&lcnt[(j[u] >= 0 && j[u] < K) ? j[u] : 0], 1);
-                if (pos < ng) a.perm[(size_t)n0 + pos] = n0 + p0 + u * kGroupThreads;
+            for (int u = 0; u < U; ++u) j[u] = p0 + u * kGroupThreads < ng[b] ? as[p0 + u * kGroupThreads] : 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (p0 + u * kGroupThreads < ng[b]) {
+                    const int pos = atomicAdd(&lcnt[b][(j[u] >= 0 && j[u] < K[b]) ? j[u] : 0], 1);
+                    if (pos < ng[b]) a.perm[(size_t)n0[b] + pos] = n0[b] + p0 + u * kGroupThreads;
+                }
             }
         }
     }
@@ -925,7 +960,11 @@ hipError_t launch_diameter(const kb_batch& b, const DiameterCall& c, hipStream_t
         a.slots = reinterpret_cast<DiaSlot*>(c.slots);
         a.reserved = reinterpret_cast<unsigned long long*>(c.bsum);
         hipLaunchKernelGGL(dia_zero, dim3(kblocks), dim3(kThreads), 0, st, a);
-        hipLaunchKernelGGL(dia_group, dim3((unsigned)b.G), dim3(kGroupThreads), 0, st, a);
+        if (b.G >= kGroupMany)
+            hipLaunchKernelGGL(dia_group<kGroupSearches>, dim3((unsigned)((b.G + kGroupSearches - 1) / kGroupSearches)),
+                               dim3(kGroupThreads), 0, st, a);
+        else
+            hipLaunchKernelGGL(dia_group<1>, dim3((unsigned)b.G), dim3(kGroupThreads), 0, st, a);
         launch_pairs(a, st);
         hipLaunchKernelGGL(dia_final, dim3(kblocks), dim3(kThreads), 0, st, a);
         return hipGetLastError();

@@ -135,6 +135,19 @@ def test_equal_distances_in_clusters_of_many_units(kb, sizes, D):
     np.testing.assert_array_equal(got, np.array(want, np.float32))
 
 
+@pytest.mark.parametrize("G", [4095, 4096, 4101])
+def test_diameters_of_many_searches(kb, G):
+    """From 4096 searches on a workgroup groups eight of them; the last one has fewer.  Empty
+    searches, searches without a pair and one long search among them."""
+    rng = np.random.default_rng(G)
+    D, sizes = 6, [[int(v)] if v < 12 else [int(v) // 2, 1, int(v) - int(v) // 2] for v in rng.integers(0, 90, G)]
+    sizes[G // 2] = [3000, 40, 2]
+    X = _rows("plain", sum(map(sum, sizes)), D, rng)
+    got, assign, off, koff = _diameters(kb, sizes, X)
+    want = _want(X, assign, off, koff)
+    assert (np.abs(got - want) <= (D + 4) * 2.0 ** -24 * want).all()
+
+
 def test_overlapping_searches_stay_inside_the_workspace(kb):
     """Offsets that go up and down (a violated precondition) make every second search the whole
     batch: far more searches with pairs than the workspace has slots for.  The numbers are then
