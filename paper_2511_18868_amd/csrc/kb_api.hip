@@ -441,9 +441,8 @@ static kb_status do_seed(const kb_batch* batch, const float* X, float* cent, int
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = launch_order(*batch, order, (int32_t*)(base + w.tile_off), nullptr, st);
     if (e != hipSuccess) return KB_EDEVICE;
-    return dev(launch_seed(*batch, X, cent, pick, (double*)(base + w.geo_d2), (int32_t*)(base + w.a_new),
-                           (double*)(base + w.seed_key), (int32_t*)(base + w.seed_idx), order,
-                           dsquared, seed, draw0, st));
+    return dev(launch_seed(*batch, X, cent, pick, (double*)(base + w.geo_d2), (double*)(base + w.seed_key),
+                           (int32_t*)(base + w.seed_idx), order, dsquared, seed, draw0, st));
 }
 
 kb_status kb_seed_farthest(const kb_batch* batch, const float* X, float* cent, int32_t* pick,

@@ -218,8 +218,8 @@ hipError_t launch_diameter(const kb_batch& b, const DiameterCall& c, hipStream_t
 // number of candidate ranges of the launch-per-centroid seeding (sizes skey / sidx: 4 per range)
 size_t seed_ranges(const kb_batch& b);
 hipError_t launch_seed(const kb_batch& b, const float* X, float* cent, int32_t* pick, double* mind,
-                       int32_t* upto, double* skey, int32_t* sidx, const int32_t* order, int dsquared,
-                       uint64_t seed, uint64_t draw0, hipStream_t st);
+                       double* skey, int32_t* sidx, const int32_t* order, int dsquared, uint64_t seed,
+                       uint64_t draw0, hipStream_t st);
 
 hipError_t launch_strategy_mask(const kb_batch& b, int R, const float* h, const int32_t* target,
                                 const int32_t* rep, float theta_sat, uint8_t* M, int32_t* nvalid,

@@ -16,13 +16,17 @@
 // is good to (D + 2) 2^-24 of itself, a key to 5e-5 - and keeps best and second best.
 // If no other row comes within a margin of several times those errors, the best is the
 // definition's choice.  Otherwise ("contested", about one pass in a thousand on data
-// without repeated rows) the rows within the margin get their fp64 values; a row's fp64
-// minimum is brought up to date only then, from the centroid it was left at, so a search
-// full of repeated rows costs no more fp64 work than forming it in every pass did.
+// without repeated rows) the rows within the margin get their fp64 values, unless they are
+// all the same row.  A contest of many rows, or contests in most passes, are the mark of
+// coarsely quantised or often repeated rows, where a pass in fp64 throughout costs less: the
+// search then goes through the centroids chosen so far once more, and on, in such passes.
+// (One-hot rows, farthest point, 1024 searches of 64-4096 rows of 48 features: 3500 us with
+// a contest in every pass, 1070 us now, 980 us in fp64 from the start; each row five times:
+// 1220, 760 and 1040 us.)
 // In fp64 throughout a row and pass was 48 conversions, 144 fp64 operations and three
 // fp64 logarithms; in fp32 it is 96 operations, the counter-based generator (17 32-bit
 // multiplications, a quarter of the rate each) and two hardware logarithms.  1024 searches
-// of 64-4096 rows of 48 features, D^2-weighted: 1672 -> 665 us; what bounds it now is the
+// of 64-4096 rows of 48 features, D^2-weighted: 1850 -> 705 us; what bounds it now is the
 // latency of a pass in short searches (2.6 us: two barriers, the reduction, the generator)
 // and the streamed rows in the longest.  The register share R is as large as fits without
 // spilling (one more row per thread: 256 searches of 2048 rows 320 -> 455 us).
@@ -50,7 +54,9 @@ constexpr int kRange = 1024;       // its rows per workgroup (at most kBigRows, 
                                    // it, one that begins inside)
 constexpr int kBigThreads = 256;
 constexpr int kNone = 0x7fffffff;
-constexpr int kListed = 64;        // rows of a contest that are settled a wave at a time
+constexpr int kListed = 64;        // rows of a contest that are listed
+constexpr int kSettled = 16;       // more of them, unless all are the same row: the search goes on in fp64
+constexpr int kContests = 4;       // or after so many contests, in most passes
 // rows a workgroup keeps in LDS after the registers are full: padded to 16 DS + 4
 // words (16-byte reads of consecutive rows fall into different banks), at most
 // two per thread, within 140 KB; the fp32 minima of the streamed rows lie behind them
@@ -78,7 +84,6 @@ struct SeedArgs {
     float* cent;
     int32_t* pick;       // may be NULL
     double* mind;        // [N] running minimum of every candidate
-    int32_t* upto;       // [N] one-workgroup path: centroids that minimum has seen
     const int32_t* order;
     // randomised (D^2-weighted) seeding instead of the farthest point
     int dsquared;
@@ -147,8 +152,8 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
     __shared__ int redk[kWaves];                       // the row, or -1 - row if contested inside the wave
     __shared__ double redv[kWaves];
     __shared__ int redi[kWaves];
-    __shared__ int nlist;
-    __shared__ unsigned short list[kListed];           // rows of a contest
+    __shared__ int nlist, differ;                      // rows of a contest; not all of them the same row
+    __shared__ unsigned short list[kListed];
     const int tid = threadIdx.x;
     const int D = a.D;
     int g = a.order ? a.order[blockIdx.x] : (int)blockIdx.x;
@@ -159,7 +164,6 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
     if (K > kBigRows) K = kBigRows;      // (more clusters than candidates: not a consistent batch)
     const float* Xg = a.X + (size_t)n0 * D;
     double* mind = a.mind + n0;
-    int32_t* upto = a.upto + n0;
     const float far_keep = 1.f - 4.f * (float)(D + 4) * 0x1p-24f;     // farthest point: margin of a contest
 
     // what a row offers in draw `drawn`: its minimum (farthest point) or its fast key
@@ -188,9 +192,9 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
         const float m = wave_max_f(best);
         const float t = keep_from(m);
         const unsigned long long same = __ballot(best >= t);
-        const unsigned long long top = __ballot(best == m);
+        const unsigned long long most = __ballot(best == m);
         const bool alone = __popcll(same) == 1 && !__any(second >= t);
-        const int row = __builtin_amdgcn_readlane(arg, top ? __ffsll((long long)top) - 1 : 0);
+        const int row = __builtin_amdgcn_readlane(arg, most ? __ffsll((long long)most) - 1 : 0);
         if ((tid & 63) == 0) { redf[tid >> 6] = m; redk[tid >> 6] = alone ? row : -1 - row; }
         __syncthreads();
         float bm = redf[0];
@@ -209,10 +213,9 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
         if (!sane) thr = -INFINITY;             // every row
         return sane && close == 1 && bk >= 0 && bk < ng ? bk : -1;
     };
-    // A contest: the definition's choice among the rows that offer thr or more.  A few of
-    // them (the usual case) take a wave each, lanes over the j + 1 centroids chosen so far
-    // (none for the first draw, whose keys are the variates alone).  When they are many,
-    // their owners bring their fp64 minima up to date, from the centroid each was left at.
+    // A contest: the definition's choice among the rows that offer thr or more, listed by
+    // the threads that own them.  They take a wave each, lanes over the j + 1 centroids
+    // chosen so far (none for the first draw, whose keys are the variates alone).
     double far;
     int farg;
     auto sq_dist = [&](const float* row, const float* cr) {
@@ -237,9 +240,11 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
     };
     auto settle = [&](double mn, int k, int j, unsigned long long drawn) {
         double key = mn;
-        if constexpr (DSQ)
+        if constexpr (DSQ) {
+            asm volatile("" : "+v"(k));          // (as in `offer`)
             key = (j >= 0 ? log(mn) : 0.0) + gumbel_variate(a.seed_lo, a.seed_hi, (unsigned)drawn,
                                                              (unsigned)(drawn >> 32), n0 + k);
+        }
         if (key > far || (key == far && k < farg)) { far = key; farg = k; }
     };
     // minima are formed as m = m < d ? m : d centroid by centroid, so a NaN is forgotten
@@ -260,20 +265,6 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
             }
             if (nan) mn = NAN;
             if (!nan || i0 + last < (j < i0 + 63 ? j : i0 + 63)) mn = mn < m ? mn : m;
-        }
-        settle(mn, k, j, drawn);
-    };
-    auto contest_owner = [&](int k, int j, unsigned long long drawn) {
-        double mn = INFINITY;
-        if (j >= 0) {
-            int i = upto[k];
-            if (i > 0) mn = mind[k];
-            for (; i <= j; ++i) {
-                const double acc = sq_dist(Xg + (size_t)k * D, Xg + (size_t)picks[i] * D);
-                mn = mn < acc ? mn : acc;
-            }
-            mind[k] = mn;
-            upto[k] = j + 1;
         }
         settle(mn, k, j, drawn);
     };
@@ -298,7 +289,8 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
         return (farg >= 0 && farg < ng) ? farg : 0;
     };
 
-    // (`minimum(k)`: the fp32 minimum of a row of this thread)
+    // (`minimum(k)`: the fp32 minimum of a row of this thread; -1: to be decided in fp64 passes)
+    int contests = 0;
     auto resolve = [&](int j, unsigned long long drawn, float thr, auto minimum) {
         far = -INFINITY; farg = kNone;
 #pragma unroll 1
@@ -309,14 +301,33 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
             }
         }
         __syncthreads();
-        const int n = nlist;
-        if (n <= kListed) {
-            for (int i = __builtin_amdgcn_readfirstlane(tid >> 6); i < n; i += kWaves) contest_wave(list[i], j, drawn);
-        } else {
-#pragma unroll 1
-            for (int k = tid; k < ng; k += kThreads)
-                if (offer(minimum(k), k, drawn) >= thr) contest_owner(k, j, drawn);
+        const int n = nlist, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+        if (n > kListed) {                       // (uniform over the workgroup)
+            if (j >= 0) return -1;
+            for (int k = tid; k < ng; k += kThreads) settle(0.0, k, -1, drawn);
+            return block_argmax();
         }
+        if constexpr (!DSQ) {
+            // rows that are copies of one: the lowest, whatever their distance is
+            const float* first = Xg + (size_t)list[0] * D;
+            bool other = false;
+            for (int i = w; i < n; i += kWaves)
+                if (lane < D) other |= __float_as_uint(first[lane]) != __float_as_uint(Xg[(size_t)list[i] * D + lane]);
+            if (__any(other) && lane == 0) differ = 1;
+            __syncthreads();
+            if (!differ) {
+                int k = lane < n ? (int)list[lane] : kNone;
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) {
+                    const int ok = __shfl_xor(k, o);
+                    k = ok < k ? ok : k;
+                }
+                return k < ng ? k : 0;
+            }
+        }
+        if (j >= 0 && n > kSettled) return -1;
+        ++contests;
+        for (int i = w; i < n; i += kWaves) contest_wave(list[i], j, drawn);
         return block_argmax();
     };
 
@@ -347,12 +358,11 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
                 *reinterpret_cast<float4*>(lx + (size_t)sl * RS + 4 * q) = row_piece(row, 4 * q, D, q < Q - 4);
         }
     }
-    for (int k = tid; k < ng; k += kThreads) upto[k] = 0;
     for (int k = FIRST + tid; k < ng; k += kThreads) ms[k - FIRST] = INFINITY;
 
     float thr;
     int chosen = 0;
-    if (tid == 0) nlist = 0;       // (before the barrier of the first choice)
+    if (tid == 0) { nlist = 0; differ = 0; }     // (before the barrier of the first choice)
     if constexpr (DSQ) {
         // first centroid: a uniform draw, i.e. the largest variate of draw number draw0
         best = -INFINITY; second = -INFINITY; arg = kNone;
@@ -362,26 +372,30 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
             chosen = resolve(-1, a.draw0, thr, [](int) { return 1.f; });
         }
     }
-    for (int j = 0; j < K; ++j) {
-        const unsigned long long drawn = a.draw0 + (unsigned long long)j + 1ull;
-        // the chosen row becomes centroid j: out of its owner's registers, from LDS, or
-        // from memory if it is one of the streamed rows
-        chosen = __builtin_amdgcn_readfirstlane(chosen);     // (the same in every thread)
-        if (tid == 0) { picks[j] = (unsigned short)chosen; nlist = 0; }
-        if (j + 1 == K) break;         // the last centroid is followed by no choice
-        if (chosen < R * kThreads) {
+    // The chosen row becomes the centroid: out of its owner's registers, from LDS, or from
+    // memory if it is one of the streamed rows.
+    auto stage = [&](int row) {
+        if (row < R * kThreads) {
 #pragma unroll
             for (int u = 0; u < R; ++u) {
-                if (u == chosen / kThreads && tid == (chosen & (kThreads - 1))) {
+                if (u == row / kThreads && tid == (row & (kThreads - 1))) {
 #pragma unroll
                     for (int q = 0; q < Q; ++q) reinterpret_cast<float4*>(c)[q] = xr[u][q];
                 }
             }
         } else if (tid < 16 * DS) {
-            c[tid] = chosen < FIRST ? lx[(size_t)(chosen - R * kThreads) * RS + tid]
-                     : tid < D      ? Xg[(size_t)chosen * D + tid]
-                                    : 0.f;
+            c[tid] = row < FIRST ? lx[(size_t)(row - R * kThreads) * RS + tid]
+                     : tid < D   ? Xg[(size_t)row * D + tid]
+                                 : 0.f;
         }
+    };
+    int known = K;                     // (known < K: so many centroids are chosen, the rest in fp64 passes)
+    for (int j = 0; j < K; ++j) {
+        const unsigned long long drawn = a.draw0 + (unsigned long long)j + 1ull;
+        chosen = __builtin_amdgcn_readfirstlane(chosen);     // (the same in every thread)
+        if (tid == 0) { picks[j] = (unsigned short)chosen; nlist = 0; differ = 0; }
+        if (j + 1 == K) break;         // the last centroid is followed by no choice
+        stage(chosen);
         __syncthreads();
         best = -INFINITY; second = -INFINITY; arg = kNone;
         // rows in registers and in LDS, one walk over the centroid; its next two pieces are
@@ -490,7 +504,7 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
             }
         }
         chosen = choose(thr);
-        if (chosen < 0) {                        // (uniform over the workgroup)
+        if (__builtin_expect(chosen < 0, 0)) {   // (uniform over the workgroup)
             chosen = resolve(j, drawn, thr, [&](int k) {
                 float m = 0.f;
                 const int u0 = k / kThreads;     // (a register array is not indexed by a variable)
@@ -500,6 +514,155 @@ __global__ void __launch_bounds__(kThreads) seed_farthest_kernel(SeedArgs a) {
                 for (int v = 0; v < LV; ++v) m = u0 == R + v ? ml[v] : m;
                 return k >= FIRST ? ms[k - FIRST] : m;
             });
+            if (chosen < 0 || (contests >= kContests && 2 * contests > j + 1)) {
+                known = j + 1;
+                if (chosen >= 0) {
+                    if (tid == 0) picks[known] = (unsigned short)chosen;
+                    ++known;
+                }
+                break;
+            }
+        }
+    }
+    if (known < K) {
+        // fp64 passes over the centroids chosen so far and on from there
+        // Minima of the rows on chip stay in registers where they are the offers themselves.  For
+        // the draw they go to memory like those of the streamed rows, and the variates, eight
+        // sets of fp64 logarithms in one pass, come one at a time from there.
+        double m64[DSQ ? 1 : R], l64[DSQ ? 1 : LV];
+        const auto keep = [&](double d, int k, int j) {
+            if (j > 0) {
+                const double old = mind[k];
+                d = old < d ? old : d;
+            }
+            mind[k] = d;
+            return d;
+        };
+        __syncthreads();
+        for (int j = 0; j < K; ++j) {
+            const unsigned long long drawn = a.draw0 + (unsigned long long)j + 1ull;
+            chosen = __builtin_amdgcn_readfirstlane(j < known ? (int)picks[j] : chosen);
+            if (tid == 0 && j >= known) picks[j] = (unsigned short)chosen;
+            if (j + 1 == K) break;
+            stage(chosen);
+            __syncthreads();
+            const bool choosing = j + 1 >= known;
+            far = -INFINITY; farg = kNone;
+            if (ru > 0) {
+                const bool inlds = (tid & ~63) + R * kThreads < ng;       // (uniform over the wave)
+                double acc[R], accl[LV];
+                const float* lrow[LV];
+#pragma unroll
+                for (int u = 0; u < R; ++u) acc[u] = 0.0;
+#pragma unroll
+                for (int v = 0; v < LV; ++v) {
+                    accl[v] = 0.0;
+                    lrow[v] = lx + (size_t)(tid + v * kThreads < LROWS ? tid + v * kThreads : tid) * RS;
+                }
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    if (4 * q < D) {
+                        const float4 cv = *reinterpret_cast<const float4*>(c + 4 * q);
+                        const double cx = (double)cv.x, cy = (double)cv.y, cz = (double)cv.z, cw = (double)cv.w;
+#pragma unroll
+                        for (int u = 0; u < R; ++u) {
+                            if (u < ru) {
+                                // (opaque to the compiler, which would otherwise widen every
+                                // row to fp64 once, outside the passes, at twice the registers)
+                                asm volatile("" : "+v"(xr[u][q].x), "+v"(xr[u][q].y), "+v"(xr[u][q].z),
+                                                  "+v"(xr[u][q].w));
+                                acc[u] = add_sq(acc[u], xr[u][q].x, cx);
+                                acc[u] = add_sq(acc[u], xr[u][q].y, cy);
+                                acc[u] = add_sq(acc[u], xr[u][q].z, cz);
+                                acc[u] = add_sq(acc[u], xr[u][q].w, cw);
+                            }
+                        }
+                        if (inlds) {
+#pragma unroll
+                            for (int v = 0; v < LV; ++v) {
+                                const float4 x4 = *reinterpret_cast<const float4*>(lrow[v] + 4 * q);
+                                accl[v] = add_sq(accl[v], x4.x, cx);
+                                accl[v] = add_sq(accl[v], x4.y, cy);
+                                accl[v] = add_sq(accl[v], x4.z, cz);
+                                accl[v] = add_sq(accl[v], x4.w, cw);
+                            }
+                        }
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < R; ++u) {
+                    const int k = tid + u * kThreads;
+                    if constexpr (DSQ) {
+                        if (k < ng) keep(acc[u], k, j);
+                    } else {
+                        m64[u] = j > 0 && m64[u] < acc[u] ? m64[u] : acc[u];
+                        if (k < ng) settle(m64[u], k, j, drawn);
+                    }
+                }
+                if (inlds) {
+#pragma unroll
+                    for (int v = 0; v < LV; ++v) {
+                        const int sl = tid + v * kThreads, k = R * kThreads + sl;
+                        if constexpr (DSQ) {
+                            if (sl < LROWS && k < ng) keep(accl[v], k, j);
+                        } else {
+                            l64[v] = j > 0 && l64[v] < accl[v] ? l64[v] : accl[v];
+                            if (sl < LROWS && k < ng) settle(l64[v], k, j, drawn);
+                        }
+                    }
+                }
+            }
+            if constexpr (FIRST < kBigRows) {
+                constexpr int U = 2;      // rows in flight per thread
+                // (row k to thread k mod 512, as all others)
+                const int k0s = FIRST + ((tid + kThreads - FIRST % kThreads) & (kThreads - 1));
+                for (int kb = k0s; kb < ng; kb += U * kThreads) {
+                    double acc[U];
+                    const float* row[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        acc[u] = 0.0;
+                        row[u] = Xg + (size_t)(kb + u * kThreads < ng ? kb + u * kThreads : kb) * D;
+                    }
+                    for (int d0 = 0; d0 < D; d0 += 8) {
+                        float4 xv[U][2];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            xv[u][0] = row_piece(row[u], d0, D, false);
+                            xv[u][1] = row_piece(row[u], d0 + 4, D, false);
+                        }
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {                // (zeros beyond D, also in c)
+                            const float4 cv = *reinterpret_cast<const float4*>(c + d0 + 4 * q);
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                acc[u] = add_sq(acc[u], xv[u][q].x, (double)cv.x);
+                                acc[u] = add_sq(acc[u], xv[u][q].y, (double)cv.y);
+                                acc[u] = add_sq(acc[u], xv[u][q].z, (double)cv.z);
+                                acc[u] = add_sq(acc[u], xv[u][q].w, (double)cv.w);
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int k = kb + u * kThreads;
+                        if (k < ng) {
+                            const double m = keep(acc[u], k, j);
+                            if constexpr (!DSQ) settle(m, k, j, drawn);
+                        }
+                    }
+                }
+            }
+            if (choosing) {
+                if constexpr (DSQ) {
+                    // (a thread reads back what it wrote)
+#pragma unroll 1
+                    for (int k = tid; k < ng; k += kThreads) settle(mind[k], k, j, drawn);
+                }
+                chosen = block_argmax();
+            } else {
+                __syncthreads();                 // (every thread has read the centroid)
+            }
         }
     }
     // the chosen rows (written at the end: a store on the way would be waited for at the
@@ -677,13 +840,13 @@ __global__ void __launch_bounds__(kBigThreads) seed_big_pass(SeedArgs a, int j, 
 size_t seed_ranges(const kb_batch& b) { return (size_t)((b.N + kRange - 1) / kRange) + 1; }
 
 hipError_t launch_seed(const kb_batch& b, const float* X, float* cent, int32_t* pick, double* mind,
-                       int32_t* upto, double* skey, int32_t* sidx, const int32_t* order, int dsquared,
-                       uint64_t seed, uint64_t draw0, hipStream_t st) {
+                       double* skey, int32_t* sidx, const int32_t* order, int dsquared, uint64_t seed,
+                       uint64_t draw0, hipStream_t st) {
     SeedArgs a;
     a.dsquared = dsquared; a.seed_lo = (unsigned)seed; a.seed_hi = (unsigned)(seed >> 32);
     a.draw0 = draw0;
     a.G = b.G; a.D = b.D; a.Ksum = b.Ksum; a.N = b.N; a.seg_off = b.seg_off; a.koff = b.koff;
-    a.X = X; a.cent = cent; a.pick = pick; a.mind = mind; a.upto = upto; a.order = order;
+    a.X = X; a.cent = cent; a.pick = pick; a.mind = mind; a.order = order;
     a.skey = skey; a.sidx = sidx; a.nranges = (int)seed_ranges(b);
     const dim3 grid((unsigned)b.G), block(kThreads);
     hipError_t err = hipSuccess;

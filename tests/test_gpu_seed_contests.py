@@ -27,6 +27,14 @@ def _features(kind, N, D, rng):
         return np.rint(x).astype(np.float32)
     if kind == "repeated":
         return x[rng.integers(0, max(1, N // 40), N)].copy()
+    if kind == "binary":
+        return (x > 0).astype(np.float32)
+    if kind == "onehot":
+        return np.eye(D, dtype=np.float32)[rng.integers(0, D, N)]
+    if kind == "few":
+        return x[rng.integers(0, min(8, N), N)].copy()
+    if kind == "late":                   # a few rows far apart, chosen first, then ties everywhere
+        return np.where(rng.random((N, 1)) < 0.004, 100 * x, np.float32(0.1) * (x > 0)).astype(np.float32)
     if kind == "equal":
         return np.ones((N, D), np.float32)
     if kind == "tiny":
@@ -38,11 +46,12 @@ def _features(kind, N, D, rng):
     return x
 
 
-@pytest.mark.parametrize("D", [2, 13, 32, 47, 64])
-@pytest.mark.parametrize("kind", ["plain", "grid", "repeated", "equal", "tiny", "huge", "mixed_scale"])
+@pytest.mark.parametrize("D", [2, 13, 32, 47, 48, 64])
+@pytest.mark.parametrize("kind", ["plain", "grid", "repeated", "binary", "onehot", "few", "late", "equal", "tiny", "huge",
+                                  "mixed_scale"])
 def test_seeds_where_fp32_cannot_decide(kb, kind, D):
     rng = np.random.default_rng(1000 * D + len(kind))
-    n = np.array([1, 63, 64, 65, 511, 513, 1537, 2120, 2771, 3100, 4095, 4096])
+    n = np.array([1, 63, 64, 65, 511, 513, 1537, 2120, 2225, 2226, 2771, 3100, 4095, 4096])
     k = np.minimum(np.maximum(1, n // 40), 24)
     seg_off = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
     koff = np.concatenate([[0], np.cumsum(k)]).astype(np.int32)
