@@ -1885,22 +1885,44 @@ hipError_t launch_round_wave(const kb_batch& b, const ClusterCall& c, const UcbC
 
 // Which shape a batch takes.  A search runs 1.7 times as fast with 768 threads and a
 // compute unit to itself, but the chip then gets through 30-40 % fewer rows per second
-// than with three or four 256-thread searches per unit.  So the wide shape pays while
+// than with three or four 256-thread searches per unit, and through fewer searches: each
+// costs a unit its steps' barriers whatever its length.  So the wide shape pays while
 // the launch lasts as long as its longest search, i.e. while all searches together hold
-// only so many times the rows of the longest one; N / Nmax counts that, whatever the
-// lengths are.  Both shapes measured, a round, narrow / wide (us):
-//   lengths 64-4096, D = 48, K <= 64:   N/Nmax  71: 903 / 504   240: 1046 / 652   350: 1225 / 970
-//                                       960: 1685 / 2470
-//   lengths 70-1900, D = 50, K <= 24:    87: 544 / 341   225: 576 / 419   300: 709 / 558
-//   lengths 1000-1500, D = 32, K <= 32: 246: 383 / 337   420: 403 / 414   630: 483 / 570
-//   lengths 100-500, D = 20, K <= 16:   149: 150 / 139   254: 179 / 197   380: 172 / 259
+// only so many times the rows of the longest one (N / Nmax), and are not many beside it
+// (G / Nmax).  Both shapes measured, 20 steps, narrow / wide (us); rows around centres of
+// different width and weight, in brackets around well-separated ones:
+//   lengths 64-4096, D = 48, K <= 64:   N/Nmax  67: 757 / 421   232: 1001 / 611   346: 1065 / 907
+//                                       592: 1244 / 1512
+//   lengths 70-1900, D = 50, K <= 24:   141: 504 / 305   240: 712 / 440 (290 / 306)   278: 545 / 483
+//                                       (296 / 355)   357: 555 / 588
+//   lengths 70-1900, D = 48, K <= 64:   239: 439 / 378 (291 / 296)   294: 396 / 435 (245 / 336)
+//   lengths 100-500, D = 48, K <= 64:   154: 139 / 136   291: 174 / 226
+//   one of 4096 and G of 70, D = 48:    1200: 661 / 362 (483 / 298)  1638: 613 / 401 (420 / 350)
+//                                       2048: 945 / 528 (391 / 434)  8000: (573 / 1515)
+//   one of 4096 and G of 300:           1200: 829 / 486 (377 / 360)  2048: 649 / 680 (416 / 573)
+//   one of 2000 and G of 100, D = 32:   800: 279 / 229 (183 / 183)   1000: 235 / 244 (168 / 215)
+//   one of 600 and G of 100, D = 48:    300: 133 / 135   600: 113 / 190   1000: 143 / 262
 // Short searches gain less from more threads (a step is barriers and reductions), hence
-// the lower line for them.  Batches of long searches only (2048 rows or more on average)
-// are 13-20 % faster in the wide shape however many they are.
-constexpr int kWideLoad = 400, kWideLoadShort = 200, kWideShortN = 1024;
-static bool wide_shape(const kb_batch& b) {
-    const int load = b.Nmax >= kWideShortN ? kWideLoad : kWideLoadShort;
-    return b.G <= kWideMaxG || b.N <= (int64_t)load * b.Nmax || b.N >= (int64_t)2048 * b.G;
+// the lower line for them, and so does a single step (64-4096, N/Nmax 242: 123 / 119, 358:
+// 154 / 179).  Rows of no whole 16-byte pieces cost the narrow shape more, hence their
+// higher line in G.  Batches of long searches only (2048 rows or more on average) are 13-20 %
+// faster in the wide shape however many they are.
+// In a batch that holds searches of the multi-workgroup path as well, the longest is one of
+// those and the others' longest is not known: four times their average is taken, the ratio
+// of lengths that are spread evenly over their logarithm (4000 searches of 64-4096 rows
+// beside one of 100000, by the longest of all: 3666 / 3776).
+constexpr int kWideLoad = 400, kWideLoadStep = 250, kWideLoadShort = 200, kWideShortN = 1024;
+static bool wide_shape(const kb_batch& b, int iters, bool mixed) {
+    if (b.G <= kWideMaxG) return true;
+    int64_t N = b.N, longest = b.Nmax;
+    if (mixed) {
+        N -= b.Nmax;
+        longest = 4 * N / b.G;
+        if (longest > one_wg_limit_n(b)) longest = one_wg_limit_n(b);
+    }
+    const int load = longest < kWideShortN ? kWideLoadShort : (iters == 1 ? kWideLoadStep : kWideLoad);
+    const int many = (b.D & 3) == 0 ? 9 : 11;
+    return (N <= load * longest && 20 * (int64_t)b.G <= many * longest) || N >= (int64_t)2048 * b.G;
 }
 
 hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t st) {
@@ -1910,7 +1932,7 @@ hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t s
     if (c.scorer == 1) mt = 0;
     const int rows = (b.D & 3) == 0 ? kRowsWhole : b.D >= 4 ? kRowsRagged : kRowsTiny;
     const size_t lds_wide = lds_layout(a.Kmax, b.D, 16 * ds + 4, a.Nmax, kThreadsWide / kWave).total;
-    const bool wide = wide_shape(b) && lds_wide <= kMaxLds;
+    const bool wide = wide_shape(b, c.iters, c.mixed != 0) && lds_wide <= kMaxLds;
     const size_t lds = wide ? lds_wide
                             : lds_layout(a.Kmax, b.D, 16 * ds + 4, a.Nmax, kThreadsNarrow / kWave).total;
     if (lds > kMaxLds) return hipErrorInvalidValue;
