@@ -31,6 +31,14 @@ def assert_rel_close(got, want, rel=REL, what="values"):
                           f"{(err / np.maximum(np.abs(want[fin]), 1e-300)).max():.3e}"
 
 
+def takes_256_threads(b):
+    """A batch that the one-workgroup Lloyd kernel runs with 256 threads per search whatever its
+    row length: more searches than compute units, too many of them beside the longest one for the
+    768-thread shape (9 or 11 for every 20 of its candidates), and not all of them long."""
+    n = np.diff(b.seg_off)
+    return b.G > 256 and 20 * b.G > 11 * n.max() and b.N < 2048 * b.G
+
+
 def search_of(seg_off):
     """Search index of every candidate."""
     seg_off = np.asarray(seg_off)

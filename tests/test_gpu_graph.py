@@ -25,7 +25,7 @@ def kb():
 CASES = {
     # one-workgroup kernels, 768-thread shape (a single launch sequence without the ordering kernel)
     "cfg2": lambda: synth.config2(iters=6),
-    # one-workgroup kernels, 256-thread shape
+    # one-workgroup kernels, 256-thread shape (many searches beside the longest)
     "manysmall": lambda: synth.config5(G=300, nmin=64, nmax=260, D=16, S=4, iters=6, seed=123),
     # the multi-workgroup launch sequence (four launches per Lloyd step)
     "cfg4s": lambda: synth.config4(N=8192, K=256, ncentres=256, iters=4),

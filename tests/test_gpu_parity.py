@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_2511_18868_amd import synth
-from kbcheck import (assert_cent_close, assert_rel_close, compare_step, search_of)
+from kbcheck import (assert_cent_close, assert_rel_close, compare_step, search_of, takes_256_threads)
 
 pytestmark = pytest.mark.gpu
 
@@ -39,9 +39,9 @@ def _late_outliers():
 
 def _mixed_k():
     """Searches of both clustering paths in one batch: five with up to 128 clusters in the
-    middle of 300 ordinary ones."""
+    middle of 540 ordinary ones (256 threads each: most are short)."""
     kw = dict(D=40, S=4, iters=8)
-    a = synth.config5(G=180, nmin=64, nmax=900, seed=78, **kw)
+    a = synth.config5(G=420, nmin=64, nmax=200, seed=78, **kw)
     big = synth.config5(G=5, nmin=1500, nmax=5000, kcap=128, seed=77, **kw)
     c = synth.config5(G=120, nmin=64, nmax=2000, seed=79, **kw)
     return synth.concat(synth.concat(a, big), c, "mixedK")
@@ -63,8 +63,8 @@ SMALL = {
     # 183 searches of 12 to 41 candidates, 5 features, 3 clusters, 6 strategies
     "paperscale": lambda: synth.paper_scale(),
     "ragged": lambda: synth.config5(G=17, nmin=64, nmax=700, D=20, S=6, seed=99),
-    # more searches than compute units: the one-workgroup kernel takes its 256-thread
-    # shape (batches of up to 256 searches run 768 threads per search)
+    # more searches than compute units, many beside the longest: the one-workgroup kernel
+    # takes its 256-thread shape (batches of up to 256 searches run 768 threads per search)
     "manysmall": lambda: synth.config5(G=300, nmin=64, nmax=260, D=16, S=4, iters=8, seed=123),
     # more searches than compute units, all of them long: the 768-thread shape again
     "manylong": lambda: synth.config5(G=258, nmin=2048, nmax=2100, D=8, S=4, iters=3, seed=321),
@@ -356,14 +356,14 @@ def test_mixed_batch_equals_the_two_paths_run_apart(kb):
 
 def test_workgroup_shapes_agree(kb, scorer):
     """The one-workgroup Lloyd kernel runs 768 threads per search in a batch of up to
-    256 searches and 256 threads in a larger one: the same searches give the same
-    bytes either way (the fixed-point sums do not depend on how the rows are spread
-    over the waves)."""
+    256 searches and 256 threads in a larger one with many searches beside its longest:
+    the same searches give the same bytes either way (the fixed-point sums do not depend
+    on how the rows are spread over the waves)."""
     kw = dict(D=32, S=4, iters=7)
     few = synth.config5(G=60, nmin=64, nmax=2000, seed=83, **kw)
-    filler = synth.config5(G=240, nmin=64, nmax=120, seed=84, **kw)
+    filler = synth.config5(G=1100, nmin=64, nmax=120, seed=84, **kw)
     many = synth.concat(few, filler)
-    assert few.G <= 256 < many.G
+    assert few.G <= 256 and takes_256_threads(many)
     out = []
     for b in (few, many):
         d = kb.DeviceBatch(b, scorer=scorer)
@@ -428,9 +428,10 @@ def test_stopping_at_the_fixed_point_changes_nothing(kb, scorer):
     60 steps) and on searches that do not, in every scorer mode and in both workgroup
     shapes; the multi-workgroup path runs all steps either way."""
     cases = [synth.config5(G=40, nmin=64, nmax=400, D=16, S=4, iters=60, seed=31),            # 768 threads
-             synth.config5(G=300, nmin=64, nmax=1500, D=32, S=4, iters=25, seed=32),          # 256 threads
+             synth.config5(G=840, nmin=64, nmax=1500, D=32, S=4, iters=25, seed=32),          # 256 threads
              synth.config1(),
              synth.config5(G=3, nmin=1500, nmax=3000, kcap=128, D=40, S=4, iters=4, seed=33)]  # multi-workgroup
+    assert [takes_256_threads(b) for b in cases] == [False, True, False, False]
     for b in cases:
         out = []
         for stop in (0, 1):

@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 from paper_2511_18868_amd import synth
-from kbcheck import assert_cent_close, assert_rel_close, search_of
+from kbcheck import assert_cent_close, assert_rel_close, search_of, takes_256_threads
 
 pytestmark = pytest.mark.gpu
 
@@ -29,22 +29,23 @@ def kb():
 
 def _batch(D, S, seed, many=False):
     """One search per cluster count, lengths with ragged tails (not multiples of 32).
-    many: followed by 250 short searches, so that the batch holds more searches than
-    the chip has compute units and the one-workgroup kernel runs its 256-thread shape."""
+    many: shorter ones, followed by 450 short searches, so that the one-workgroup kernel
+    runs its 256-thread shape."""
     rng = np.random.default_rng(seed)
     b = None
     for i, K in enumerate(KS):
-        n = int(rng.integers(3 * K + 1, 40 * K + 40))
+        n = int(rng.integers(3 * K + 1, (12 if many else 40) * K + 40))
         one = synth.config2(seed=seed * 100 + i, N=n, D=D, K=K, S=S, iters=6)
         b = one if b is None else synth.concat(b, one, f"sweepD{D}")
     if many:
-        b = synth.concat(b, synth.config5(G=250, nmin=17, nmax=90, D=D, S=S, iters=6, seed=seed + 7),
+        b = synth.concat(b, synth.config5(G=450, nmin=17, nmax=90, D=D, S=S, iters=6, seed=seed + 7),
                          f"sweepD{D}many")
+    assert takes_256_threads(b) == many
     return b
 
 
 # feature counts: one to four 16-feature steps, with and without padding; 6 and 17
-# are not multiples of 4: rows are then fetched feature by feature
+# are not multiples of 4: the last piece of a row is then shifted into place
 @pytest.mark.parametrize("D", [4, 6, 8, 12, 16, 17, 20, 28, 32, 36, 44, 48, 52, 60, 64])
 @pytest.mark.parametrize("scorer", [0, 2], ids=["bounds", "matrixcore"])
 @pytest.mark.parametrize("many", [False, True], ids=["few", "many"])
