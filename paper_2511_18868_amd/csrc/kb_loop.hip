@@ -11,13 +11,17 @@ constexpr int kThreads = 256;
 
 // M[i,s] = [ h(rep_i)[target(s)] < theta_sat ]; nvalid[g] = number of valid cluster arms of
 // the search.  NT threads per search: a wave, or a workgroup where a search may have more
-// than kMaskWave arms.  Bound by the dependent loads rep -> h: a thread has kMaskU of its
-// arms in flight, so a search is one or two such chains (a wave per search went through its
+// than kMaskWave arms.  Bound by the dependent loads rep -> h: a thread of a workgroup has U of
+// its arms in flight, so a search is a few such chains (a wave per search went through its
 // 2048 arms in 32 chains: 512 searches of up to 64 clusters and 32 strategies 37.5 us, now 6 us).
+// Where many searches share the chip they hide each other's loads, and a wave each, one arm
+// per lane, gets through more of them (whole calls, wave / workgroup: 4000 searches of 1024 arms
+// 13.1 / 12.4 us, 20000 of 272 14.8 / 25.6, of 1024 34.7 / 38.2, of 8192 235 / 212).
 constexpr int kMaskWave = 256;
-constexpr int kMaskU = 8;
+constexpr int kMaskFewG = 4096;           // more searches: a workgroup each only for kMaskMany arms on average
+constexpr int kMaskMany = 4096;
 
-template <int NT>
+template <int NT, int U>
 __global__ void __launch_bounds__(kThreads)
 strategy_mask_kernel(int G, int S, int R, int Ksum, int64_t N, const int32_t* __restrict__ koff,
                      const float* __restrict__ h, const int32_t* __restrict__ target,
@@ -31,11 +35,11 @@ strategy_mask_kernel(int G, int S, int R, int Ksum, int64_t N, const int32_t* __
     const int k1 = clampi(koff[g + 1], k0, Ksum);
     const int arms = (k1 - k0) * S;
     int n = 0;
-    for (int q0 = lane; q0 < arms; q0 += NT * kMaskU) {
-        int r[kMaskU], col[kMaskU];
-        float v[kMaskU];
+    for (int q0 = lane; q0 < arms; q0 += NT * U) {
+        int r[U], col[U];
+        float v[U];
 #pragma unroll
-        for (int u = 0; u < kMaskU; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int q = q0 + u * NT;
             r[u] = -1;
             if (q < arms) {
@@ -45,12 +49,12 @@ strategy_mask_kernel(int G, int S, int R, int Ksum, int64_t N, const int32_t* __
             }
         }
 #pragma unroll
-        for (int u = 0; u < kMaskU; ++u) {
+        for (int u = 0; u < U; ++u) {
             if (r[u] >= 0 && (int64_t)r[u] < N) v[u] = h[(size_t)r[u] * R + col[u]];
             else r[u] = -1;
         }
 #pragma unroll
-        for (int u = 0; u < kMaskU; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int q = q0 + u * NT;
             if (q < arms) {
                 const int m = r[u] >= 0 && v[u] < theta_sat ? 1 : 0;
@@ -120,8 +124,10 @@ hipError_t launch_strategy_mask(const kb_batch& b, int R, const float* h, const 
         hipLaunchKernelGGL(kern, dim3((unsigned)((b.G + per - 1) / per)), dim3(kThreads), 0, st, b.G, b.S, R,
                            b.Ksum, b.N, b.koff, h, target, rep, theta_sat, M, nvalid);
     };
-    if ((int64_t)b.Kmax * b.S <= kMaskWave) go(strategy_mask_kernel<kWave>, kThreads / kWave);
-    else go(strategy_mask_kernel<kThreads>, 1);
+    const bool groups = b.G <= kMaskFewG ? (int64_t)b.Kmax * b.S > kMaskWave
+                                         : (int64_t)b.Ksum * b.S >= (int64_t)kMaskMany * b.G;
+    if (groups) go(strategy_mask_kernel<kThreads, 4>, 1);
+    else go(strategy_mask_kernel<kWave, 1>, kThreads / kWave);
     return hipGetLastError();
 }
 

@@ -357,3 +357,32 @@ def test_seeds_of_mixed_search_lengths(kb, D):
     assert ok.mean() > 0.9
     np.testing.assert_array_equal(d.host("rep")[ok], want.pick[ok])
     np.testing.assert_array_equal(d.host("cent2")[ok].view(np.uint32), want.cent[ok].view(np.uint32))
+
+
+@pytest.mark.parametrize("G,K,S", [(4096, 33, 8), (4097, 33, 8), (4097, 128, 32), (5, 32, 8), (5, 33, 8), (1, 256, 32)])
+def test_strategy_mask_over_batch_sizes(kb, G, K, S):
+    """A wave or a workgroup per search, on both sides of the lines between them (256 arms in
+    batches of up to 4096 searches, 4096 arms on average in larger ones); searches of fewer
+    clusters and of none among them, representatives that are missing."""
+    import torch
+    rng = np.random.default_rng(G + K)
+    k = np.full(G, K)
+    k[G // 2:G // 2 + 1] = K if G == 1 else 0
+    k[:G // 3:7] = 1
+    koff = np.concatenate([[0], np.cumsum(k)]).astype(np.int32)
+    n, R, ksum = max(K, 4), 3, int(koff[-1])
+    N = n * G
+    h = rng.random((N, R)).astype(np.float32)
+    target = rng.integers(0, R, S).astype(np.int32)
+    rep = rng.integers(-1, N, ksum).astype(np.int32)
+    dev = torch.device("cuda:0")
+    up = lambda v: torch.from_numpy(v).to(dev)  # noqa: E731
+    seg, ko, dh, dt, dr = (up(v) for v in ((n * np.arange(G + 1)).astype(np.int32), koff, h, target, rep))
+    batch = kb.make_batch(G, 4, S, N, K, ksum, n, seg, ko)
+    M = torch.full((ksum, S), 7, dtype=torch.uint8, device=dev)
+    nvalid = torch.full((G,), -1, dtype=torch.int32, device=dev)
+    kb.kb_strategy_mask(batch, R, dh, dt, dr, 0.6, M, nvalid)
+    torch.cuda.synchronize()
+    want = oracle.strategy_mask(koff, S, h, target, rep, 0.6)
+    np.testing.assert_array_equal(M.cpu().numpy(), want.M)
+    np.testing.assert_array_equal(nvalid.cpu().numpy(), want.nvalid)
