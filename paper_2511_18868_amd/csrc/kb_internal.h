@@ -170,7 +170,8 @@ struct SampleCall {
 hipError_t launch_sample(const kb_batch& b, const SampleCall& c, hipStream_t st);
 
 // Several iterations of Alg. 1 between two re-clusterings - masked selection, draw, update -
-// in one launch: true if the batch allows it (no search of more than 16384 candidates).
+// in one launch: true if the batch allows it (no search of more than 16384 candidates, nor a long
+// one in a single cluster).
 // `order` of the UcbCall is read when rounds_need_order says so; its sel, and sel / ksel of
 // the SampleCall, are not used.
 struct RoundsCall {

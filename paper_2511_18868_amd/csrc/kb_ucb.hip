@@ -640,8 +640,16 @@ static size_t rounds_lds(const kb_batch& b) {
 static bool rounds_wave_per_search(const kb_batch& b) {
     return b.Nmax <= kShortSearch && rounds_lds(b) * kWaves <= 64 * 1024;
 }
+// One workgroup draws over all members of the chosen cluster.  Where that is most of a long
+// search (a single cluster), launches that spread the draw over the chip are faster, the sooner the
+// fewer searches there are: ten iterations, launches / one launch, one search of 8192 rows 291 / 264 us,
+// of 12000 310 / 361, of 16384 329 / 476; 100 searches of 12000 482 / 386, of 16384 499 / 511; 300 of
+// 12000 780 / 783, of 16384 903 / 1022.  (Two clusters: one search of 16384 318 / 281.)
+constexpr int kRoundsFew = 8, kRoundsMembersFew = 9000, kRoundsMembers = 14000;
 bool rounds_in_one_launch(const kb_batch& b) {
-    return b.G > 0 && b.Nmax <= kUcbLong && rounds_lds(b) + 1024 <= 160 * 1024;
+    const int64_t members = b.G <= kRoundsFew ? kRoundsMembersFew : kRoundsMembers;
+    return b.G > 0 && b.Nmax <= kUcbLong && b.Nmax <= members * (b.Kmax > 0 ? b.Kmax : 1) &&
+           rounds_lds(b) + 1024 <= 160 * 1024;
 }
 bool rounds_need_order(const kb_batch& b) { return b.G > 1 && !rounds_wave_per_search(b); }
 

@@ -29,6 +29,8 @@ def _batch(shape, S):
         return synth.config5(G=9, nmin=200, nmax=4100, D=8, S=S, kcap=64, kdiv=16, iters=3, seed=303)
     if shape == "narrow":         # more searches than the wide form takes
         return synth.config5(G=520, nmin=40, nmax=600, D=8, S=S, kcap=24, kdiv=16, iters=3, seed=304)
+    if shape == "onecluster":     # too many members for the draw of one workgroup: launches of their own
+        return synth.config2(seed=307, N=12000, D=8, K=1, S=S, iters=3)
     return synth.config2(seed=305, N=16384, D=8, K=2, S=S, iters=3)     # the longest search of one workgroup
 
 
@@ -76,7 +78,7 @@ def _compare_with_the_stages(kb, b, T, **params):
 
 
 @pytest.mark.parametrize("S", [1, 6, 12, 32])
-@pytest.mark.parametrize("shape", ["wave", "waveedge", "wide", "narrow", "longest"])
+@pytest.mark.parametrize("shape", ["wave", "waveedge", "wide", "narrow", "longest", "onecluster"])
 def test_rounds_in_one_launch_equal_the_stages_one_by_one(kb, shape, S):
     _compare_with_the_stages(kb, _batch(shape, S), 5)
 
