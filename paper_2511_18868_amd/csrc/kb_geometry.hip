@@ -331,34 +331,39 @@ __global__ void __launch_bounds__(kThreads) geo_final(GeoArgs a) {
     a.radius[i] = (float)sqrt(__longlong_as_double((long long)a.gmax[i]));
 }
 
-// Searches that cross a border of ranges, and the clusters of searches without candidates.
+// Searches that cross a border of ranges, and the clusters of searches without candidates: a
+// wave for every 64 clusters of a search, four slots' values in flight.
 // (With it one light launch follows geo_dist in place of two, one of them over all candidates,
 // and one before it: representatives and diameters of 1024 searches of 64-4096 candidates 269 -> 255 us,
-// ten iterations of 512 such searches with two re-clusterings 1359 -> 1337 us.)
-__global__ void __launch_bounds__(kThreads) geo_merge(GeoArgs a) {
+// ten iterations of 512 such searches with two re-clusterings 1359 -> 1337 us.  With a wave for all
+// clusters of a search, slot by slot, one search of 16384 candidates and 256 clusters took 50 us in
+// place of the 43 us before; now 37.)
+__global__ void __launch_bounds__(kThreads) geo_merge(GeoArgs a, int parts) {
     const int lane = threadIdx.x & 63;
-    const int g = (int)blockIdx.x * (kThreads / kWave) + (int)(threadIdx.x >> 6);
+    const int64_t w = (int64_t)blockIdx.x * (kThreads / kWave) + (int64_t)(threadIdx.x >> 6);
+    const int g = (int)(w / parts), part = (int)(w - (int64_t)g * parts);
     if (g >= a.G) return;
     int n0, ng, k0, K;
     search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
     const int Kc = ng <= 0 ? 0 : (K > a.Kmax ? a.Kmax : K);
-    for (int j = Kc + lane; j < K; j += kWave) { a.rep[k0 + j] = -1; a.radius[k0 + j] = 0.f; }
-    if (Kc <= 0) return;
+    for (int j = Kc + kWave * part + lane; j < K; j += kWave * parts) { a.rep[k0 + j] = -1; a.radius[k0 + j] = 0.f; }
+    const int j = kWave * part + lane;
+    if (j >= Kc) return;
     const int64_t ra = n0 / kGeoRange, rb = ((int64_t)n0 + ng - 1) / kGeoRange;
     if (ra == rb) return;                                // finished by its range
-    for (int j = lane; j < Kc; j += kWave) {
-        unsigned long long least = ~0ull, most = 0ull;
-        int rep = kNone;
-        for (int64_t r = ra; r <= rb; ++r) {             // (ascending: the lowest candidate on ties)
-            const GeoSlot o = geo_slot(a, r, r != ra);
-            const unsigned long long m = o.least[j], x = o.most[j];
-            const int p = o.rep[j];
-            if (m < least) { least = m; rep = p; }
-            most = x > most ? x : most;
-        }
-        a.rep[k0 + j] = rep == kNone ? -1 : rep;
-        a.radius[k0 + j] = (float)sqrt(__longlong_as_double((long long)most));
+    unsigned long long least = ~0ull, most = 0ull;
+    int rep = kNone;
+#pragma unroll 4
+    for (int64_t r = ra; r <= rb; ++r) {                 // (ascending: the lowest candidate on ties)
+        const GeoSlot o = geo_slot(a, r, r != ra);
+        const unsigned long long m = o.least[j], x = o.most[j];
+        const int p = o.rep[j];
+        rep = m < least ? p : rep;
+        least = m < least ? m : least;
+        most = x > most ? x : most;
     }
+    a.rep[k0 + j] = rep == kNone ? -1 : rep;
+    a.radius[k0 + j] = (float)sqrt(__longlong_as_double((long long)most));
 }
 
 // Batches of short searches: one wave per search, four searches per workgroup, the
@@ -488,8 +493,13 @@ hipError_t launch_geometry(const kb_batch& b, const GeoCall& c, hipStream_t st) 
         }
         if (!a.merged) hipLaunchKernelGGL(geo_rep, dim3(ranges), dim3(kThreads), 0, st, a);
     }
-    if (a.merged) hipLaunchKernelGGL(geo_merge, wgrid, dim3(kThreads), 0, st, a);
-    else hipLaunchKernelGGL(geo_final, dim3(kblocks), dim3(kThreads), 0, st, a);
+    if (a.merged) {
+        const int parts = (a.Kmax + kWave - 1) / kWave;
+        const unsigned waves = (unsigned)((int64_t)b.G * parts);      // (G <= 2^20, parts <= 4)
+        hipLaunchKernelGGL(geo_merge, dim3((waves + kThreads / kWave - 1) / (kThreads / kWave)), dim3(kThreads), 0, st,
+                           a, parts);
+    }
+    if (!a.merged) hipLaunchKernelGGL(geo_final, dim3(kblocks), dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }
 
