@@ -188,10 +188,10 @@ def main():
         del drw10, dok10, sl, kl
         loop = {k: round(v, 4) for k, v in loop.items()}
         nk_rows = float(np.sum(np.diff(b.seg_off).astype(np.float64) * np.diff(b.koff)))
-        # four fp64-rate vector instructions (widen, subtract, multiply, add) per feature,
-        # row and pass against 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
-        loop["seed_farthest_fp64_frac"] = round(
-            nk_rows * 4 * b.D / (loop["seed_farthest"] * 1e-3) / (256 * 4 * 16 * 2.4e9), 3)
+        # two fp32 vector instructions (subtract, multiply-add) per feature, row and pass
+        # against 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
+        loop["seed_farthest_fp32_frac"] = round(
+            nk_rows * 2 * b.D / (loop["seed_farthest"] * 1e-3) / (256 * 4 * 16 * 2.4e9), 3)
         loop["cluster_geometry_GBs"] = round(
             b.N * (4 * b.D + 4) / (loop["cluster_geometry"] * 1e-3) / 1e9, 1)
         loop["sample_GBs"] = round(b.N * 4 / (loop["sample"] * 1e-3) / 1e9, 1)
