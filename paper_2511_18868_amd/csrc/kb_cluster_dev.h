@@ -43,6 +43,21 @@ __device__ __forceinline__ int fixed_shift(float amax, int ng) {
     return 62 - e - (32 - __clz(ng));
 }
 
+// fp32 rounding of the correctly rounded fp64 quotient t / c, from one reciprocal
+// rc = 1 / c shared by a row's features.  t * rc lies within 2^-52 (relative) of
+// t / c, and so does the rounded quotient; the two round to the same fp32 unless
+// an fp32 rounding boundary - a 1 followed by 28 zeros in the low 29 mantissa
+// bits - lies within 2^-51 (at most 4 units of the last place) of t * rc.  Then,
+// and for results near the subnormal fp32 range where the boundaries sit
+// elsewhere, the quotient itself is formed.
+__device__ __forceinline__ float mean_f32(double t, double c, double rc) {
+    const double q = t * rc;
+    const unsigned low = (unsigned)__double_as_longlong(q) & 0x1fffffffu;
+    const unsigned off = low - 0x10000000u + 8u;
+    if (off <= 16u || (fabs(q) < 0x1p-100 && t != 0.0)) return (float)(t / c);
+    return (float)q;
+}
+
 // the value lane l holds, l the same in every lane (a scalar-register read, no
 // cross-lane traffic through LDS)
 __device__ __forceinline__ float lane_value(float v, int l) {

@@ -110,6 +110,7 @@ struct ClusterCall {
 hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t st);
 hipError_t launch_cluster_big(const kb_batch& b, const ClusterCall& c, const BigWs& w, char* ws,
                               hipStream_t st);
+hipError_t launch_cluster_wave(const kb_batch& b, const ClusterCall& c, hipStream_t st);   // one wave per search
 bool cluster_supported(const kb_batch& b);   // shape fits the compiled clustering kernels
 bool cluster_wave_per_search(const kb_batch& b, int scorer);   // the batch runs one wave per search (no scheduling order needed)
 

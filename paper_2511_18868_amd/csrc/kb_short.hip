@@ -1,0 +1,525 @@
+// Very short searches: batches in which every search has at most 64 candidates and 16
+// clusters - the size of a search in the paper's own runs (Sec. 3.6: a frontier of a few
+// dozen kernels, K = 3).  Such a search is one wave's work: lane l keeps candidate l's row in
+// registers, centroids and fixed-point sums sit in the wave's own piece of LDS, and since
+// nothing is shared with another wave no step needs a workgroup barrier or a block-wide
+// reduction (what a step of a short search mostly consists of in the kernels that give a
+// search a workgroup).
+//
+// What bounds it is one wave's chain of dependent instructions, so a Lloyd step is kept to the
+// pieces that it cannot do without:
+//   score    every lane forms the fp32 direct-difference distances of its candidate to all
+//            centroids, four centroids at a time (independent chains); no distance bounds, since
+//            a step without a move ends the search anyway (below) and in every other step some
+//            lane has to score, which costs the wave the same as all lanes.
+//   decide   relative error <= (D + 2) 2^-24, sums of non-negative terms: if the two smallest are
+//            further apart than twice that bound allows, the smallest is the unique nearest
+//            centroid; otherwise fp64, summed over the features in index order with separate
+//            multiply and add (the plain definition), lowest index on ties.
+//   move     a lane whose cluster changed moves its row between the fixed-point sums (integer
+//            LDS atomics: any order gives the same sums).
+//   renew    one lane per centroid coordinate: the mean, in fp64, rounded once to fp32.
+// Same fixed-point grid and same rounding as in the workgroup kernels, so the same centroid bytes.
+// A search stops at its first step without a move: such a step leaves sums, sizes and centroids
+// as they were, so every later step would repeat it and all outputs are the same bytes as
+// after the full count of steps.
+//
+// Measured against the form with distance bounds, four lanes per centroid and a centroid at a time
+// in the score: ten steps of 183 searches of 12-41 candidates (D = 5, K = 3) 22.4 -> 12.0 us, the
+// whole round 27.2 -> 15.5 us; rounds of 20000 searches of 1-40 111 -> 58 us, of 4000 searches of 64
+// candidates, K = 16, D = 64 (20 steps) 362 -> 242 us, of 20000 with D = 32 526 -> 353 us.  What a lane
+// could keep over the steps beside its row - its fixed-point image, its fp64 form - is formed
+// again in each: kept, the registers leave one wave per SIMD (D = 32: 1022 us).
+#include "kb_cluster_dev.h"
+#include "kb_ucb_dev.h"
+#include "kb_wave_dev.h"
+
+namespace kb {
+
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / kWave;     // searches per workgroup
+constexpr int kShortMaxN = 64, kShortMaxK = 16;
+
+struct ShortArgs {
+    int G, D, Ksum, Kmax;
+    int64_t N;
+    const int32_t* seg_off;
+    const int32_t* koff;
+    const float* X;
+    const float* cent_init;     // NULL: the first K_g rows
+    int iters;
+    int guard;                  // leave searches with N_g < 2 K_g as they are (re-clustering rule of Alg. 1)
+    int32_t* assign;
+    float* cent_out;
+    int32_t* counts;
+    float* objective;
+};
+
+__device__ __forceinline__ void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
+
+// A wave's piece of LDS.  NC: 16-byte pieces of a row.
+struct ShortLds {
+    size_t sums, cent, cnt, touched, total;
+};
+__host__ __device__ inline ShortLds short_lds_layout(int Kmax, int D, int NC) {
+    ShortLds l;
+    size_t off = 0;
+    l.sums = off; off += (size_t)Kmax * (D | 1) * 8;      // odd row stride: clusters spread over the LDS banks
+    off = (off + 15) & ~(size_t)15;
+    l.cent = off; off += (size_t)((Kmax + 3) & ~3) * (4 * NC + 4) * 4;      // (rows are read four at a time)
+    l.cnt = off;  off += (size_t)Kmax * 4;
+    l.touched = off; off += (size_t)Kmax;                 // a byte per cluster: moves in this step
+    l.total = (off + 15) & ~(size_t)15;
+    return l;
+}
+
+// This lane's row, zero-padded to 4 NC features (a lane without a candidate holds zeros).
+template <int NC>
+__device__ __forceinline__ void short_row(const float* __restrict__ xr, int D, bool valid, float (&x)[4 * NC]) {
+#pragma unroll
+    for (int d = 0; d < 4 * NC; ++d) x[d] = 0.f;
+    if (!valid) return;
+    if (D >= 4) {
+        float4 v[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c] = row_piece_load(xr, 4 * c, D);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const float4 w = row_piece_shift(v[c], 4 * c, D);
+            x[4 * c] = w.x; x[4 * c + 1] = w.y; x[4 * c + 2] = w.z; x[4 * c + 3] = w.w;
+        }
+    } else {
+        x[0] = xr[0];
+        if (D > 1) x[1] = xr[1];
+        if (D > 2) x[2] = xr[2];
+    }
+}
+
+// The initial centroids, from memory or (init == NULL) the rows of the first K lanes; sums and sizes 0.
+template <int NC>
+__device__ __forceinline__ void short_begin(const float* __restrict__ init, int D, int ng, int K,
+                                            const float (&x)[4 * NC], int lane, long long* sums, float* cent,
+                                            int* cnt, unsigned char* touched) {
+    constexpr int DP = 4 * NC + 4;
+    if (init) {
+        for (int i = lane; i < K * DP; i += kWave) {
+            const int j = i / DP, d = i - j * DP;
+            cent[i] = d < D ? init[(size_t)j * D + d] : 0.f;
+        }
+    } else {
+        // (a malformed search of fewer candidates than clusters repeats its last row)
+        for (int j = lane; j < K && (j == lane || lane == ng - 1); ++j) {
+            if (j != lane && j < ng) continue;
+            if (lane < ng) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+                    *reinterpret_cast<float4*>(cent + (size_t)j * DP + 4 * c) =
+                        make_float4(x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]);
+            }
+        }
+    }
+    for (int i = lane; i < K * (D | 1); i += kWave) sums[i] = 0;
+    if (lane < K) { cnt[lane] = 0; touched[lane] = 0; }
+    wave_sync();
+}
+
+// `iters` >= 1 Lloyd steps of one search by one wave, from the centroids in `cent`; returns the
+// objective (in every lane) and leaves new centroids, sizes and this lane's cluster.
+template <int NC>
+__device__ __forceinline__ float short_cluster(int iters, int D, int ng, int K, const float (&x)[4 * NC],
+                                               bool valid, int lane, long long* sums, float* cent, int* cnt,
+                                               unsigned char* touched, int& mine) {
+    constexpr int DP = 4 * NC + 4;
+    const int SP = D | 1;
+    float am = 0.f;
+    double tsq = 0.0;
+#pragma unroll
+    for (int d = 0; d < 4 * NC; ++d) {
+        am = fmaxf(am, fabsf(x[d]));
+        tsq = fma((double)x[d], (double)x[d], tsq);
+    }
+    am = wave_max_f(am);
+    tsq = wave_sum_d(tsq);
+    const int sh = fixed_shift(am, ng);
+    const int fsh = sh - 32;
+    const double inv = ldexp(1.0, -sh);
+    const float eps = 2.f * (float)(D + 2) * 5.9604644775390625e-08f;
+    // coordinate e of the centroids: feature e mod 2^lg of cluster e / 2^lg (2^lg >= D)
+    const int lg = D > 1 ? 32 - __clz(D - 1) : 0;
+    const int E = K << lg, dmask = (1 << lg) - 1;
+
+    mine = -1;
+    double J = 0.0;
+    for (int it = 0;; ++it) {
+        float b32 = INFINITY, s32 = INFINITY;
+        int bj = 0;
+        for (int j0 = 0; j0 < K; j0 += 4) {
+            float acc[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                // (one address for all lanes; rows and centroids are zero-padded: the extra terms are +0.0)
+                const float4* cr = reinterpret_cast<const float4*>(cent + (size_t)(j0 + u) * DP);
+                float a0 = 0.f, a1 = 0.f;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const float4 cv = cr[c];
+                    const float e0 = x[4 * c] - cv.x, e1 = x[4 * c + 1] - cv.y;
+                    const float e2 = x[4 * c + 2] - cv.z, e3 = x[4 * c + 3] - cv.w;
+                    a0 = fmaf(e0, e0, a0);
+                    a1 = fmaf(e1, e1, a1);
+                    a0 = fmaf(e2, e2, a0);
+                    a1 = fmaf(e3, e3, a1);
+                }
+                acc[u] = a0 + a1;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float v = j0 + u < K ? acc[u] : INFINITY;
+                const bool lt = v < b32;
+                s32 = lt ? b32 : (v < s32 ? v : s32);
+                bj = lt ? j0 + u : bj;
+                b32 = lt ? v : b32;
+            }
+        }
+        if (valid && !(s32 * (1.f - eps) > b32 * (1.f + eps) + 1.0e-35f)) {
+            double bd = INFINITY;
+            bj = 0;
+            for (int j = 0; j < K; ++j) {
+                const float* cr = cent + (size_t)j * DP;
+                double acc = 0.0;
+#pragma unroll
+                for (int d = 0; d < 4 * NC; ++d) {
+                    float xv = x[d];
+                    asm volatile("" : "+v"(xv));          // (likewise)
+                    const double diff = __dsub_rn((double)xv, (double)cr[d]);
+                    acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+                }
+                if (acc < bd) { bd = acc; bj = j; }
+            }
+        }
+        const bool move = valid && bj != mine;
+        const bool moved = __ballot(move) != 0;
+        if (move) {
+            // (formed again in every step: kept over the loop, the images take twice a row's registers)
+            int f = fsh;
+            asm volatile("" : "+v"(f));
+            auto shift = [&](int d) __attribute__((always_inline)) {
+                const long long q = to_fixed(x[d], f);
+                atomicAdd(reinterpret_cast<unsigned long long*>(sums + bj * SP + d), (unsigned long long)q);
+                if (it > 0)
+                    atomicAdd(reinterpret_cast<unsigned long long*>(sums + mine * SP + d), (unsigned long long)-q);
+            };
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                if (4 * c + 4 <= D) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) shift(4 * c + e);
+                } else if (4 * c < D) {
+                    shift(4 * c);
+                    if (4 * c + 1 < D) shift(4 * c + 1);
+                    if (4 * c + 2 < D) shift(4 * c + 2);
+                }
+            }
+            atomicAdd(&cnt[bj], 1);
+            if (it > 0) atomicSub(&cnt[mine], 1);
+            touched[bj] = 1;
+            if (it > 0) touched[mine] = 1;
+            mine = bj;
+        }
+        wave_sync();
+        const bool last = it == iters - 1 || !moved;
+        if (last) {
+            // Objective relative to the centroids c_j that entered this step: with S_j the exact sum
+            // and n_j the size of cluster j, sum |x|^2 - sum_j c_j . (2 S_j - n_j c_j) in fp64;
+            // member by member when the subtraction leaves less than 1e-7 of the first term.
+            double part = 0.0;
+            for (int e = lane; e < E; e += kWave) {
+                const int j = e >> lg, d = e & dmask;
+                if (d < D) {
+                    const double cj = (double)cent[(size_t)j * DP + d];
+                    const double Sj = (double)sums[j * SP + d] * inv;
+                    part += cj * (2.0 * Sj - (double)cnt[j] * cj);
+                }
+            }
+            J = tsq - wave_sum_d(part);
+            if (!(J >= 1.0e-7 * tsq)) {
+                double acc = 0.0;
+                if (valid) {
+                    const float4* cr = reinterpret_cast<const float4*>(cent + (size_t)mine * DP);
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        const float4 cv = cr[c];
+                        const float e0 = x[4 * c] - cv.x, e1 = x[4 * c + 1] - cv.y;
+                        const float e2 = x[4 * c + 2] - cv.z, e3 = x[4 * c + 3] - cv.w;
+                        acc += (double)fmaf(e0, e0, fmaf(e1, e1, fmaf(e2, e2, e3 * e3)));
+                    }
+                }
+                J = wave_sum_d(acc);
+            }
+            wave_sync();
+        }
+        if (moved) {
+            // (an empty cluster keeps its centroid)
+            if (E <= kWave) {
+                // a lane per coordinate, reciprocals and all
+                const int j = lane >> lg, d = lane & dmask;
+                if (lane < E && d < D) {
+                    const int c = cnt[j];
+                    const double t = (double)sums[j * SP + d] * inv;
+                    const double cd = (double)(c > 0 ? c : 1);
+                    const float v = mean_f32(t, cd, 1.0 / cd);
+                    if (c > 0) cent[(size_t)j * DP + d] = v;
+                }
+            } else {
+                // several passes: a cluster's reciprocal is formed once, clusters without a move
+                // are left out (a pass covers whole clusters)
+                const int cl = lane < K ? cnt[lane] : 0;
+                const double rl = 1.0 / (double)(cl > 0 ? cl : 1);
+                const unsigned dirty = (unsigned)__ballot(lane < K && touched[lane] != 0);
+                const int per = kWave >> lg;                 // clusters per pass (lg <= 6)
+                for (int j0 = 0; j0 < K; j0 += per) {
+                    if (!((dirty >> j0) & ((1u << per) - 1u))) continue;      // (uniform)
+                    const int j = j0 + (lane >> lg), d = lane & dmask;
+                    const double rc = __shfl(rl, j);
+                    const int c = __shfl(cl, j);
+                    if (j < K && d < D && c > 0) {
+                        const double t = (double)sums[j * SP + d] * inv;
+                        cent[(size_t)j * DP + d] = mean_f32(t, (double)c, rc);
+                    }
+                }
+                if (lane < K) touched[lane] = 0;
+            }
+            wave_sync();
+        }
+        if (last) break;
+    }
+    return (float)J;
+}
+
+// What the whole-round kernel needs beyond the clustering arguments: the pruning
+// step's inputs and outputs (Eq. 2 and the mask of Eq. 5) and the selection call.
+struct ShortRound {
+    const float* flops;
+    const float* bytes;
+    const float* incumbent;
+    float peak_flops, peak_bw;
+    float* bound;
+    uint8_t* alive;
+    UcbArgs u;
+};
+
+// bytes of the selection tables of a wave
+__host__ __device__ inline size_t arm_lds_bytes(int Kmax, int S) {
+    return ((size_t)Kmax * S * 12 + (size_t)Kmax * 12 + 15) & ~(size_t)15;
+}
+
+constexpr int kHeldS = 8;      // strategies whose visits and rewards a lane holds from the start of the call
+
+// ROUND: the whole round of the search in this one wave - the roofline bound and the
+// mask of every candidate first (the same correctly rounded divisions and strict
+// compare as the pruning kernel), the clustering, then the cluster-arm statistics
+// from the lanes' own clusters (integer LDS atomics, as in the selection kernel, so
+// the same tables), scores and selection.  (The host takes this path with a.iters >= 1
+// and a.guard = 0.)  Everything that comes from memory is requested before the clustering: on
+// fresh inputs a trip to memory costs as much as two steps.
+template <int NC, bool ROUND>
+__device__ __forceinline__ void short_search(const ShortArgs& a, const ShortRound* rd, unsigned char* smem) {
+    constexpr int DP = 4 * NC + 4;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = (int)blockIdx.x * kWaves + wv;
+    if (g >= a.G) return;                 // (a whole wave leaves: nothing in this kernel waits for another wave)
+    const int D = a.D;
+    int n0, ng, k0, K;
+    search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
+    if (K > a.Kmax) K = a.Kmax;
+    if (ng > kShortMaxN) ng = kShortMaxN;   // (the host launches this kernel only for such batches)
+    const bool valid = lane < ng;
+    const size_t row = (size_t)n0 + (valid ? lane : 0);
+    float x[4 * NC];
+    short_row<NC>(a.X + row * D, D, valid && K > 0, x);
+    bool live = true;                     // this lane's candidate passed the pruning step
+    float rbound = 0.f;
+    int hv[kHeldS];
+    float hr[kHeldS];
+    long long tg = 1;
+    bool held = false;
+    if constexpr (ROUND) {
+        const UcbArgs& u = rd->u;
+        float fl = 0.f, by = 0.f;
+        if (valid) { fl = rd->flops[row]; by = rd->bytes[row]; }
+        const float inc = rd->incumbent[g];
+        tg = u.t[g];
+        held = u.S <= kHeldS;             // (uniform)
+        if (held && valid) {
+#pragma unroll
+            for (int s = 0; s < kHeldS; ++s) {
+                if (s < u.S) { hv[s] = u.visits[row * u.S + s]; hr[s] = u.rsum[row * u.S + s]; }
+            }
+        }
+        if (valid) {
+            const float t_compute = fl / rd->peak_flops;
+            const float t_memory = by / rd->peak_bw;
+            rbound = t_compute > t_memory ? t_compute : t_memory;
+            live = rbound < inc;
+            rd->bound[row] = rbound;
+            rd->alive[row] = live ? 1 : 0;
+        }
+    }
+    if (ng <= 0 || K <= 0) {
+        if (lane == 0 && a.iters > 0 && a.objective) a.objective[g] = 0.f;
+        if constexpr (ROUND) {
+            if (lane < 3) rd->u.sel[(size_t)g * 3 + lane] = -1;
+        }
+        return;
+    }
+    if (a.guard && ng < 2 * K) return;
+
+    const ShortLds L = short_lds_layout(a.Kmax, D, NC);
+    const size_t arm = ROUND ? arm_lds_bytes(a.Kmax, rd->u.S) : 0;
+    unsigned char* base = smem + (size_t)wv * (L.total + arm);
+    long long* sums = reinterpret_cast<long long*>(base + L.sums);      // [Kmax][D | 1]
+    float* cent = reinterpret_cast<float*>(base + L.cent);              // [Kmax][DP]
+    int* cnt = reinterpret_cast<int*>(base + L.cnt);                    // [Kmax]
+    unsigned char* touched = base + L.touched;                          // [Kmax]
+
+    short_begin<NC>(a.cent_init ? a.cent_init + (size_t)k0 * D : nullptr, D, ng, K, x, lane, sums, cent, cnt, touched);
+    int mine = 0;
+    if (a.iters > 0) {
+        const float J = short_cluster<NC>(a.iters, D, ng, K, x, valid, lane, sums, cent, cnt, touched, mine);
+        if (lane == 0) a.objective[g] = J;
+        if (valid) a.assign[row] = mine;
+        if (lane < K) a.counts[k0 + lane] = cnt[lane];
+    }
+    for (int i = lane; i < K * D; i += kWave) {
+        const int j = i / D, d = i - j * D;
+        a.cent_out[(size_t)(k0 + j) * D + d] = cent[(size_t)j * DP + d];
+    }
+
+    if constexpr (ROUND) {
+        const UcbArgs& u = rd->u;
+        const int S = u.S, KS = K * S;
+        unsigned long long* R = reinterpret_cast<unsigned long long*>(base + L.total);       // [Kmax*S]
+        unsigned long long* kmin = R + (size_t)a.Kmax * S;                                   // [Kmax]
+        unsigned* Ncnt = reinterpret_cast<unsigned*>(kmin + a.Kmax);                         // [Kmax*S]
+        unsigned* nalive = Ncnt + (size_t)a.Kmax * S;                                        // [Kmax]
+        for (int i = lane; i < KS; i += kWave) { R[i] = 0ull; Ncnt[i] = 0u; }
+        if (lane < K) { kmin[lane] = ~0ull; nalive[lane] = 0u; }
+        wave_sync();
+        if (valid && live) {      // (iters >= 1: every candidate has a cluster)
+            if (held) {
+#pragma unroll
+                for (int s = 0; s < kHeldS; ++s) {
+                    if (s < S) {
+                        atomicAdd(&Ncnt[mine * S + s], (unsigned)hv[s]);
+                        atomicAdd(&R[mine * S + s], reward_fixed(hr[s]));
+                    }
+                }
+                ucb_count_candidate(lane, mine, rbound, nalive, kmin);
+            } else {
+                ucb_add_candidate(u, row, lane, mine, rbound, Ncnt, R, nalive, kmin);
+            }
+        }
+        wave_sync();
+        ucb_finish<kWave>(u, g, n0, k0, K, Ncnt, R, nalive, kmin, nullptr, nullptr, lane, tg);
+    }
+}
+
+template <int NC>
+__global__ void __launch_bounds__(kThreads) cluster_wave_kernel(ShortArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    short_search<NC, false>(a, nullptr, smem);
+}
+
+template <int NC>
+__global__ void __launch_bounds__(kThreads) round_wave_kernel(ShortArgs a, ShortRound rd) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    short_search<NC, true>(a, &rd, smem);
+}
+
+// 16-byte pieces of a row that a kernel is compiled for, from the feature count
+int row_pieces(int D) {
+    const int n = (D + 3) / 4;
+    return n <= 4 ? (n < 2 ? 2 : n) : n <= 8 ? 8 : n <= 12 ? 12 : 16;
+}
+
+// go(std::integral_constant<int, NC>) for the batch's NC
+template <class F>
+hipError_t with_pieces(int D, F go) {
+    switch (row_pieces(D)) {
+        case 2: return go(std::integral_constant<int, 2>{});
+        case 3: return go(std::integral_constant<int, 3>{});
+        case 4: return go(std::integral_constant<int, 4>{});
+        case 8: return go(std::integral_constant<int, 8>{});
+        case 12: return go(std::integral_constant<int, 12>{});
+        default: return go(std::integral_constant<int, 16>{});
+    }
+}
+
+template <class K, class... A>
+hipError_t launch(K kern, unsigned grid, size_t lds, hipStream_t st, const A&... args) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, args...);
+    return hipGetLastError();
+}
+
+int kmax_of(const kb_batch& b) { return b.Kmax > 0 ? b.Kmax : 1; }
+unsigned wave_grid(const kb_batch& b) { return (unsigned)((b.G + kWaves - 1) / kWaves); }
+
+ShortArgs short_args(const kb_batch& b, const ClusterCall& c) {
+    ShortArgs a;
+    a.G = b.G; a.D = b.D; a.Ksum = b.Ksum; a.Kmax = kmax_of(b); a.N = b.N;
+    a.seg_off = b.seg_off; a.koff = b.koff; a.X = c.X; a.cent_init = c.cent_init;
+    a.iters = c.iters; a.guard = c.guard; a.assign = c.assign; a.cent_out = c.cent_out;
+    a.counts = c.counts; a.objective = c.objective;
+    return a;
+}
+
+}  // namespace
+
+bool cluster_wave_per_search(const kb_batch& b, int scorer) {
+    return scorer == KB_SCORER_DEFAULT && b.Nmax <= kShortMaxN && b.Kmax <= kShortMaxK;
+}
+
+hipError_t launch_cluster_wave(const kb_batch& b, const ClusterCall& c, hipStream_t st) {
+    if (!cluster_wave_per_search(b, c.scorer) || c.mixed) return hipErrorInvalidValue;
+    const ShortArgs a = short_args(b, c);
+    return with_pieces(b.D, [&](auto nc) {
+        constexpr int NC = decltype(nc)::value;
+        return launch(cluster_wave_kernel<NC>, wave_grid(b), kWaves * short_lds_layout(a.Kmax, a.D, NC).total, st, a);
+    });
+}
+
+// A batch of searches of at most 64 candidates and 16 clusters each, in the default
+// mode: the whole round (Sec. 3.5: prune, cluster, select) is one launch, a wave per
+// search.  (The selection tables share the wave's piece of LDS; strategy counts that
+// would leave fewer than two workgroups per compute unit take the three-stage path.)
+bool round_in_one_launch(const kb_batch& b, int scorer) {
+    if (!cluster_wave_per_search(b, scorer)) return false;
+    return kWaves * (short_lds_layout(kmax_of(b), b.D, row_pieces(b.D)).total + arm_lds_bytes(kmax_of(b), b.S)) <=
+           64 * 1024;
+}
+
+hipError_t launch_round_wave(const kb_batch& b, const ClusterCall& c, const UcbCall& uc,
+                             const float* flops, const float* bytes, const float* incumbent,
+                             float peak_flops, float peak_bw, float* bound, uint8_t* alive,
+                             hipStream_t st) {
+    if (!round_in_one_launch(b, c.scorer) || c.mixed || c.guard || c.iters < 1 || c.cent_init)
+        return hipErrorInvalidValue;
+    const ShortArgs a = short_args(b, c);
+    ShortRound rd;
+    rd.flops = flops; rd.bytes = bytes; rd.incumbent = incumbent;
+    rd.peak_flops = peak_flops; rd.peak_bw = peak_bw; rd.bound = bound; rd.alive = alive;
+    rd.u = make_ucb_args(b, uc);
+    return with_pieces(b.D, [&](auto nc) {
+        constexpr int NC = decltype(nc)::value;
+        const size_t lds = kWaves * (short_lds_layout(a.Kmax, a.D, NC).total + arm_lds_bytes(a.Kmax, b.S));
+        return launch(round_wave_kernel<NC>, wave_grid(b), lds, st, a, rd);
+    });
+}
+
+}  // namespace kb

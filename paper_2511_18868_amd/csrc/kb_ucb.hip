@@ -155,7 +155,7 @@ __global__ void __launch_bounds__(kThreads) ucb_kernel(UcbArgs a) {
         }
         for (int i = tid; i < K; i += kThreads) { a.gnalive[k0 + i] = nalive[i]; a.gkmin[k0 + i] = kmin[i]; }
     }
-    ucb_finish<kThreads>(a, g, n0, k0, K, Ncnt, R, nalive, kmin, redv, redi, tid);
+    ucb_finish<kThreads>(a, g, n0, k0, K, Ncnt, R, nalive, kmin, redv, redi, tid, a.t[g]);
 }
 
 
@@ -192,7 +192,7 @@ __global__ void __launch_bounds__(kThreads) ucb_wave(UcbArgs a, int per) {
         ucb_add_candidate(a, (size_t)n0 + p, p, j, a.bound ? a.bound[(size_t)n0 + p] : 0.f, Ncnt, R, nalive, kmin);
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    ucb_finish<kWave>(a, g, n0, k0, K, Ncnt, R, nalive, kmin, nullptr, nullptr, lane);
+    ucb_finish<kWave>(a, g, n0, k0, K, Ncnt, R, nalive, kmin, nullptr, nullptr, lane, a.t[g]);
 }
 
 
@@ -527,7 +527,7 @@ __global__ void __launch_bounds__(kThreads) ucb_final(UcbArgs a) {
         return;
     }
     ucb_finish<kThreads>(a, g, n0, k0, K, a.gN + (size_t)k0 * a.S, a.gR + (size_t)k0 * a.S,
-                         a.gnalive + k0, a.gkmin + k0, redv, redi, (int)threadIdx.x);
+                         a.gnalive + k0, a.gkmin + k0, redv, redi, (int)threadIdx.x, a.t[g]);
 }
 
 }  // namespace

@@ -2,6 +2,7 @@
 // kernels and the one-launch round of very short searches.
 #pragma once
 #include "kb_internal.h"
+#include "kb_wave_dev.h"
 
 namespace kb {
 
@@ -42,6 +43,12 @@ __device__ __forceinline__ unsigned ordered_bits(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+__device__ __forceinline__ void ucb_count_candidate(int p, int j, float bd, unsigned* nalive,
+                                                    unsigned long long* kmin) {
+    atomicAdd(&nalive[j], 1u);
+    atomicMin(&kmin[j], ((unsigned long long)ordered_bits(bd) << 32) | (unsigned)p);
+}
+
 // One alive candidate's visits and reward sums (row `row` of the two arrays) into the
 // tables of its cluster j; p is its index inside the search and bd its roofline bound
 // (the member with the smallest bound, lowest index on ties, is the cluster's k*).
@@ -69,8 +76,7 @@ __device__ __forceinline__ void ucb_add_candidate(const UcbArgs& a, size_t row, 
             atomicAdd(rr + s, reward_fixed(rs[s]));
         }
     }
-    atomicAdd(&nalive[j], 1u);
-    atomicMin(&kmin[j], ((unsigned long long)ordered_bits(bd) << 32) | (unsigned)p);
+    ucb_count_candidate(p, j, bd, nalive, kmin);
 }
 
 // Mean reward `m` and UCB index (returned) of an arm with n visits and the reward sum R,
@@ -85,6 +91,26 @@ __device__ __forceinline__ double ucb_score(const UcbArgs& a, unsigned n, unsign
     return nt > 0.0 ? m + cc * sqrt(lnt / nt) : INFINITY;
 }
 
+// The best arm of a wave: the largest score, lowest flat index on ties; arm < 0: none in this
+// lane.  Cross-lane moves inside the vector registers (a chain of shuffles through LDS takes
+// four times as long).  Scores that are not numbers (c = +inf at t = 1) have no order: with one
+// of them in the wave the result is that of the pairwise exchange, in lane 0.
+__device__ __forceinline__ void wave_best_arm(double& u, int& arm) {
+    if (__any(arm >= 0 && !(u == u))) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const double ou = __shfl_xor(u, o);
+            const int of = __shfl_xor(arm, o);
+            if (of >= 0 && (arm < 0 || ou > u || (ou == u && of < arm))) { u = ou; arm = of; }
+        }
+        return;
+    }
+    const double best = wave_max_d(arm >= 0 ? u : -INFINITY);
+    const int low = wave_min_i(arm >= 0 && u == best ? arm : 0x7fffffff);
+    u = best;
+    arm = low == 0x7fffffff ? -1 : low;
+}
+
 // Scores, outputs and selection of one search from its accumulated tables
 // (which may live in LDS or in global memory).  Called by a whole workgroup of NT
 // threads, or, with NT = 64, by one wave on its own (tid = the lane; redv and redi
@@ -93,10 +119,9 @@ template <int NT>
 __device__ __forceinline__ void ucb_finish(const UcbArgs& a, int g, int n0, int k0, int K,
                                            const unsigned* Ncnt, const unsigned long long* R,
                                            const unsigned* nalive, const unsigned long long* kmin,
-                                           double* redv, int* redi, int tid) {
+                                           double* redv, int* redi, int tid, long long tg) {
     const int S = a.S;
     const int KS = K * S;
-    long long tg = a.t[g];
     if (tg < 1) tg = 1;
     const double lnt = log((double)tg);
 
@@ -115,12 +140,7 @@ __device__ __forceinline__ void ucb_finish(const UcbArgs& a, int g, int n0, int 
         if (valid && (bf < 0 || u > bu)) { bu = u; bf = i; }
     }
     // argmax with the lowest flat index on ties: waves, then the block
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const double ou = __shfl_xor(bu, o);
-        const int of = __shfl_xor(bf, o);
-        if (of >= 0 && (bf < 0 || ou > bu || (ou == bu && of < bf))) { bu = ou; bf = of; }
-    }
+    wave_best_arm(bu, bf);
     if constexpr (NT > 64) {
         if ((tid & 63) == 0) { redv[tid >> 6] = bu; redi[tid >> 6] = bf; }
         __syncthreads();
