@@ -607,8 +607,9 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
     // (rounds_in_one_launch), in the workspace where every round is launches of its own.
     const UcbScratch us = ucb_scratch_in_ws(batch, ws);
     bool tables_valid = false;
+    const bool one_launch = iterate_in_one_launch(*batch, params->scorer, ip->R);
     for (int32_t r = 0; r < ip->rounds; ++r) {
-        const bool now = recluster && (((int64_t)ip->t0 + r) % ip->tau_recluster) == 0;
+        const bool now = !one_launch && recluster && (((int64_t)ip->t0 + r) % ip->tau_recluster) == 0;
         if (now) {
             // K-Means on the frontier wherever |P| >= 2K, then the cluster representatives
             // and the mask their hardware signatures give (Alg. 1; Eq. 5)
@@ -637,15 +638,16 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
         sc.seed = ip->sample.seed; sc.draw = ip->sample.draw + (uint64_t)r; sc.tau = ip->sample.tau;
         sc.ksel = ksel;
         sc.slot_key = (double*)(base + w.samp_key); sc.slot_idx = (int32_t*)(base + w.samp_idx);
-        if (rounds_in_one_launch(*batch)) {
-            // everything up to the next re-clustering in one launch
+        if (one_launch || rounds_in_one_launch(*batch)) {
+            // very short searches: everything, re-clusterings included, in one launch;
+            // otherwise everything up to the next re-clustering
             int32_t n = ip->rounds - r;
-            if (recluster) {
-                const int32_t left = ip->tau_recluster - (int32_t)(((int64_t)ip->t0 + r) % ip->tau_recluster);
-                n = left < n ? left : n;
-            }
+            // iterations up to the next one that re-clusters, this one not counted
+            const int32_t left = !recluster ? 0
+                : ip->tau_recluster - (int32_t)(((int64_t)ip->t0 + r) % ip->tau_recluster);
+            if (recluster && !one_launch) n = left < n ? left : n;
             n = n < kMaxRoundsPerLaunch ? n : kMaxRoundsPerLaunch;
-            if (!have_order && rounds_need_order(*batch)) {
+            if (!one_launch && !have_order && rounds_need_order(*batch)) {
                 if (launch_order(*batch, us.order, us.tile_off, nullptr, st) != hipSuccess) return KB_EDEVICE;
                 have_order = true;
             }
@@ -657,6 +659,19 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
             RoundsCall rc;
             rc.rounds = n; rc.reward = io->reward + (size_t)r * G; rc.ok = io->ok + (size_t)r * G;
             rc.visits = io->visits; rc.rsum = io->rsum; rc.t = io->t; rc.sel_log = sel; rc.ksel_log = ksel;
+            if (one_launch) {
+                ClusterCall cc{};
+                cc.X = io->X; cc.iters = params->iters; cc.assign = io->assign; cc.cent_out = io->cent;
+                cc.counts = io->counts; cc.objective = io->objective; cc.scorer = params->scorer; cc.guard = 1;
+                IterateCall ic;
+                ic.tau = recluster ? ip->tau_recluster : 0;
+                ic.first_due = recluster ? left % ip->tau_recluster : 0;
+                ic.warm = ip->warm_start ? 1 : 0;
+                ic.M = io->M; ic.nvalid = io->nvalid; ic.rep = io->rep; ic.radius = io->radius;
+                if (launch_iterate(*batch, cc, uc, sc, rc, ic, st) != hipSuccess) return KB_EDEVICE;
+                r += n - 1;
+                continue;
+            }
             if (launch_rounds(*batch, uc, sc, rc, st) != hipSuccess) return KB_EDEVICE;
             r += n - 1;
             continue;

@@ -190,6 +190,21 @@ bool rounds_need_order(const kb_batch& b);
 hipError_t launch_rounds(const kb_batch& b, const UcbCall& c, const SampleCall& sc, const RoundsCall& rc,
                          hipStream_t st);
 
+// Whole iterations - re-clusterings, representatives and masks included - of a batch of very short
+// searches in one launch: `first_due` is the first iteration of the launch that re-clusters (every
+// tau-th one then does; tau <= 0: none).  The ClusterCall carries the clustering's arrays and steps
+// (cent_init unused: `warm` says where its centroids start from).
+struct IterateCall {
+    int tau, first_due, warm;
+    uint8_t* M;
+    int32_t* nvalid;
+    int32_t* rep;
+    float* radius;
+};
+bool iterate_in_one_launch(const kb_batch& b, int scorer, int R);
+hipError_t launch_iterate(const kb_batch& b, const ClusterCall& c, const UcbCall& uc, const SampleCall& sc,
+                          const RoundsCall& rc, const IterateCall& ic, hipStream_t st);
+
 struct GeoCall {
     const float* X;
     const float* cent;

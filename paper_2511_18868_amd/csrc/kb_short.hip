@@ -33,6 +33,8 @@
 #include "kb_cluster_dev.h"
 #include "kb_ucb_dev.h"
 #include "kb_wave_dev.h"
+#include "kb_sample_dev.h"
+#include <type_traits>
 
 namespace kb {
 
@@ -97,13 +99,15 @@ __device__ __forceinline__ void short_row(const float* __restrict__ xr, int D, b
     }
 }
 
-// The initial centroids, from memory or (init == NULL) the rows of the first K lanes; sums and sizes 0.
+// The initial centroids - from memory, (init == NULL) the rows of the first K lanes, or (keep) the
+// present ones -; sums and sizes 0.
 template <int NC>
-__device__ __forceinline__ void short_begin(const float* __restrict__ init, int D, int ng, int K,
+__device__ __forceinline__ void short_begin(const float* __restrict__ init, bool keep, int D, int ng, int K,
                                             const float (&x)[4 * NC], int lane, long long* sums, float* cent,
                                             int* cnt, unsigned char* touched) {
     constexpr int DP = 4 * NC + 4;
-    if (init) {
+    if (keep) {
+    } else if (init) {
         for (int i = lane; i < K * DP; i += kWave) {
             const int j = i / DP, d = i - j * DP;
             cent[i] = d < D ? init[(size_t)j * D + d] : 0.f;
@@ -385,7 +389,7 @@ __device__ __forceinline__ void short_search(const ShortArgs& a, const ShortRoun
     int* cnt = reinterpret_cast<int*>(base + L.cnt);                    // [Kmax]
     unsigned char* touched = base + L.touched;                          // [Kmax]
 
-    short_begin<NC>(a.cent_init ? a.cent_init + (size_t)k0 * D : nullptr, D, ng, K, x, lane, sums, cent, cnt, touched);
+    short_begin<NC>(a.cent_init ? a.cent_init + (size_t)k0 * D : nullptr, false, D, ng, K, x, lane, sums, cent, cnt, touched);
     int mine = 0;
     if (a.iters > 0) {
         const float J = short_cluster<NC>(a.iters, D, ng, K, x, valid, lane, sums, cent, cnt, touched, mine);
@@ -439,6 +443,389 @@ __global__ void __launch_bounds__(kThreads) round_wave_kernel(ShortArgs a, Short
     short_search<NC, true>(a, &rd, smem);
 }
 
+// ---- whole iterations of Alg. 1 in one launch ------------------------------------------
+// Nothing of an iteration - re-clustering, representatives and mask every tau-th time, masked
+// selection, draw of k_t, statistics update - touches another search, so a search runs all of
+// them on its own, in a workgroup of four waves.  The first wave carries the search: its rows,
+// centroids, clusters and cluster arms (A arms per lane) stay in registers and LDS from the first
+// iteration to the last, the history (visits and reward sums) in LDS, written back at the end.  The other three form the Gumbel variates of the draws, which depend on
+// nothing but the draw's number and the candidate, kAhead iterations ahead in one of two buffers;
+// one barrier per kAhead iterations hands them over.  What is left of an iteration for the first
+// wave is the dependent chain score - argmax - key - argmax - one cell of the history: no
+// logarithm, no trip to memory, no shuffle through LDS.
+//
+// What bounds it is one wave's chain of fp64 instructions, 1.1 us an iteration.  With eight launches and
+// a wave per search twenty iterations of 183 searches of 12-41 candidates (D = 5, K = 3, S = 6) with two
+// re-clusterings took 122 us, now 48 us.
+//
+// NW = 1: one wave does both, the variates of the next kAhead iterations after every kAhead.  A search
+// takes a fifth longer, but no wave waits for another: beyond the searches that fit the chip with
+// four waves each (three workgroups per compute unit with rows of at most 16 features and an arm per
+// lane, one otherwise) the batch is done sooner.  The searches above, launches / four waves / one
+// (us): 768 139 / 56 / 68, 4000 303 / 400 / 222 (D = 12, K = 6, S = 10), 20000 752 / 1178 / 372; 768 of
+// 40-64 candidates, D = 40, K = S = 16 342 / 560 / 366 (300: 327 / 373 / 304).
+constexpr int kAhead = 8;
+constexpr int kIterateMaxR = 8, kIterateMaxArms = 256;
+
+struct IterateArgs {
+    ShortArgs c;
+    UcbArgs u;                  // sel unused
+    SampleArgs s;               // sel, ksel unused
+    int rounds, tau, first_due, warm;     // the first re-clustering comes before iteration first_due (tau <= 0: never)
+    unsigned long long draw0;
+    const float* reward;        // [rounds][G]
+    const uint8_t* ok;          // [rounds][G]
+    int32_t* visits;
+    float* rsum;
+    int64_t* t;
+    int32_t* sel_log;           // [rounds][G][3]
+    int32_t* ksel_log;          // [rounds][G]
+    uint8_t* M;
+    int32_t* nvalid;
+    int32_t* rep;
+    float* radius;
+    int Nmax;
+};
+
+struct IterateLds {
+    ShortLds c;
+    size_t gum, pot, R, gmin, gmax, N, grep, vis, rs, total;
+};
+__host__ __device__ inline IterateLds iterate_lds_layout(int Kmax, int D, int NC, int S, int R, int Nmax) {
+    IterateLds l;
+    l.c = short_lds_layout(Kmax, D, NC);
+    size_t off = l.c.total;
+    l.gum = off;  off += (size_t)2 * kAhead * Nmax * 8;
+    l.pot = off;  off += (size_t)R * Nmax * 8;           // (theta_sat - h) / tau, [resource][candidate]
+    l.R = off;    off += (size_t)Kmax * S * 8;
+    l.gmin = off; off += (size_t)Kmax * 8;
+    l.gmax = off; off += (size_t)Kmax * 8;
+    l.N = off;    off += (size_t)Kmax * S * 4;
+    l.grep = off; off += (size_t)Kmax * 4;
+    l.vis = off;  off += (size_t)Nmax * S * 4;
+    l.rs = off;   off += (size_t)Nmax * S * 4;
+    l.total = (off + 15) & ~(size_t)15;
+    return l;
+}
+
+constexpr int kNoMember = 0x7fffffff;
+
+template <int NC, int A, int NW>
+__global__ void __launch_bounds__(NW * kWave, NW == 1 ? (NC <= 4 ? 4 : 2) : 1) iterate_kernel(IterateArgs r) {
+    constexpr int kThreads = NW * kWave;
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int DP = 4 * NC + 4;
+    const ShortArgs& a = r.c;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = NW > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
+    const int g = (int)blockIdx.x;
+    const int D = a.D, S = r.u.S, T = r.rounds, NM = r.Nmax;
+    int n0, ng, k0, K;
+    search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
+    const bool due = r.tau > 0 && r.first_due < T;         // some iteration of this launch re-clusters
+    if (K > a.Kmax) K = a.Kmax;
+    if (ng > NM) ng = NM;                 // (LDS is sized from the host copies)
+    if (ng <= 0 || K <= 0) {
+        // nothing to choose from (the workgroup leaves as a whole)
+        for (int it = tid; it < T; it += kThreads) {
+            const size_t at = (size_t)it * a.G + g;
+            for (int q = 0; q < 3; ++q) r.sel_log[at * 3 + q] = -1;
+            r.ksel_log[at] = -1;
+        }
+        if (due) {
+            for (int i = tid; i < K; i += kThreads) { r.rep[k0 + i] = -1; r.radius[k0 + i] = 0.f; }
+            for (int i = tid; i < K * S; i += kThreads) r.M[(size_t)k0 * S + i] = 0;
+            if (tid == 0) { a.objective[g] = 0.f; r.nvalid[g] = 0; }
+        }
+        if (tid == 0) r.t[g] += T;
+        return;
+    }
+    const int KS = K * S;
+    const IterateLds L = iterate_lds_layout(a.Kmax, D, NC, S, r.s.R, NM);
+    long long* sums = reinterpret_cast<long long*>(smem + L.c.sums);
+    float* cent = reinterpret_cast<float*>(smem + L.c.cent);
+    int* cnt = reinterpret_cast<int*>(smem + L.c.cnt);
+    unsigned char* touched = smem + L.c.touched;
+    double* gum = reinterpret_cast<double*>(smem + L.gum);              // [2][kAhead][NM]
+    double* pot = reinterpret_cast<double*>(smem + L.pot);              // [R][NM]
+    unsigned long long* tR = reinterpret_cast<unsigned long long*>(smem + L.R);          // [KS]
+    unsigned long long* gmin = reinterpret_cast<unsigned long long*>(smem + L.gmin);     // [K]
+    unsigned long long* gmax = reinterpret_cast<unsigned long long*>(smem + L.gmax);     // [K]
+    unsigned* tN = reinterpret_cast<unsigned*>(smem + L.N);             // [KS]
+    int* grep = reinterpret_cast<int*>(smem + L.grep);                  // [K]
+    int* vis = reinterpret_cast<int*>(smem + L.vis);                    // [ng][S]
+    float* rs = reinterpret_cast<float*>(smem + L.rs);                  // [ng][S]
+
+    // the first wave's candidate and arms
+    const bool valid = wv == 0 && lane < ng;
+    const size_t row = (size_t)n0 + (valid ? lane : 0);
+    float x[4 * NC];
+    bool live = false;
+    int raw = 0;                          // this lane's cluster as the arrays have it
+    long long t = 0;
+    int cl[A], st[A], col[A];             // cluster, strategy and resource of this lane's arms
+    bool allowed[A];                      // by the mask
+    if (wv == 0) {
+        short_row<NC>(a.X + row * D, D, valid && due, x);
+        live = valid && (!r.u.alive || r.u.alive[row] != 0);
+        if (valid) raw = r.u.assign[row];
+        t = r.t[g];
+#pragma unroll
+        for (int q = 0; q < A; ++q) {
+            const int i = lane + q * kWave;
+            cl[q] = i / S;
+            st[q] = i - cl[q] * S;
+            col[q] = clampi(r.s.target[st[q]], 0, r.s.R - 1);
+            allowed[q] = i < KS && r.M[(size_t)k0 * S + i] != 0;
+        }
+    }
+    {
+        const int R = r.s.R;
+        for (int i = tid; i < ng * S; i += kThreads) {
+            vis[i] = r.visits[(size_t)n0 * S + i];
+            rs[i] = r.rsum[(size_t)n0 * S + i];
+        }
+        for (int i = tid; i < ng * R; i += kThreads) {
+            const int k = i / R;
+            pot[(i - k * R) * NM + k] = ((double)r.s.theta_sat - (double)r.s.h[(size_t)n0 * R + i]) / r.s.tau;
+        }
+    }
+    if (NW > 1) __syncthreads();
+    else wave_sync();
+
+    unsigned n[A];
+    unsigned long long Rw[A];
+    double mean[A];
+    bool arm[A];
+    int mine = 0;                         // this lane's cluster, 0 where the array names none of the search
+    double lnl = 0.0;                     // lane l: ln t, reward and verification of iteration 64 i + l
+    float rwl = 0.f;
+    int okl = 0;
+    int rd = 0;
+    int64_t next = r.tau > 0 ? r.first_due : (int64_t)T;
+    bool fresh = true, have = false;      // tables to be built; centroids in LDS
+    // the last iteration, for the arms' outputs
+    double u[A];
+    int bf = -1;
+    bool updated = false;
+    double rw = 0.0;
+    int log_I = -1, log_s = -1, log_lead = -1, log_k = -1;     // lane l: the log of iteration 64 i + l
+    const int chunks = (T + kAhead - 1) / kAhead;
+    auto variates = [&](int c, int first, int stride) __attribute__((always_inline)) {
+        double* out = gum + (c & 1) * kAhead * NM;
+        const int left = T - c * kAhead, m = (left < kAhead ? left : kAhead) * ng;
+        for (int i = first; i < m; i += stride) {
+            const int it = i / ng, k = i - it * ng;
+            const unsigned long long draw = r.draw0 + (unsigned long long)(c * kAhead + it);
+            out[it * NM + k] = gumbel_variate(r.s.seed_lo, r.s.seed_hi, (unsigned)draw, (unsigned)(draw >> 32),
+                                              n0 + k);
+        }
+    };
+    for (int c = 0; c <= chunks; ++c) {
+        if (NW > 1 && wv > 0) {
+            if (c < chunks) variates(c, tid - kWave, kThreads - kWave);
+        } else {
+            const int stop = c * kAhead < T ? c * kAhead : T;
+            const double* gb = gum + ((c - 1) & 1) * kAhead * NM;
+            while (true) {
+                if (fresh) {
+                    fresh = false;
+                    if (rd == next) {
+                        next += r.tau;
+                        if (ng >= 2 * K) {
+                            short_begin<NC>(r.warm ? a.cent_out + (size_t)k0 * D : nullptr, r.warm && have, D, ng, K,
+                                            x, lane, sums, cent, cnt, touched);
+                            const float J = short_cluster<NC>(a.iters, D, ng, K, x, valid, lane, sums, cent, cnt,
+                                                              touched, raw);
+                            if (lane == 0) a.objective[g] = J;
+                            if (valid) a.assign[row] = raw;
+                            if (lane < K) a.counts[k0 + lane] = cnt[lane];
+                            for (int i = lane; i < K * D; i += kWave) {
+                                const int j = i / D;
+                                a.cent_out[(size_t)k0 * D + i] = cent[(size_t)j * DP + i - j * D];
+                            }
+                        } else if (!have) {
+                            short_begin<NC>(a.cent_out + (size_t)k0 * D, false, D, ng, K, x, lane, sums, cent, cnt,
+                                            touched);
+                        }
+                        have = true;
+                        // representatives and radii: fp64 distances as the definition forms them
+                        const int j = raw >= 0 && raw < K ? raw : 0;
+                        if (lane < K) { gmin[lane] = ~0ull; gmax[lane] = 0ull; grep[lane] = kNoMember; }
+                        wave_sync();
+                        double acc = 0.0;
+                        const float* cr = cent + (size_t)j * DP;
+#pragma unroll
+                        for (int d = 0; d < 4 * NC; ++d) {
+                            float xv = x[d];
+                            asm volatile("" : "+v"(xv));          // (its fp64 form is not kept over the loop)
+                            const double diff = __dsub_rn((double)xv, (double)cr[d]);
+                            acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+                        }
+                        const unsigned long long bits = (unsigned long long)__double_as_longlong(acc);
+                        if (valid) { atomicMin(&gmin[j], bits); atomicMax(&gmax[j], bits); }
+                        wave_sync();
+                        if (valid && bits == gmin[j]) atomicMin(&grep[j], lane);
+                        wave_sync();
+                        if (lane < K) {
+                            r.rep[k0 + lane] = grep[lane] == kNoMember ? -1 : n0 + grep[lane];
+                            r.radius[k0 + lane] = (float)sqrt(__longlong_as_double((long long)gmax[lane]));
+                        }
+                        // Eq. 5: h < theta_sat exactly where theta_sat - h is above 0
+                        int nv = 0;
+#pragma unroll
+                        for (int q = 0; q < A; ++q) {
+                            const int i = lane + q * kWave;
+                            allowed[q] = false;
+                            if (i < KS) {
+                                const int rp = grep[cl[q]];
+                                allowed[q] = rp != kNoMember && pot[col[q] * NM + rp] > 0.0;
+                                r.M[(size_t)k0 * S + i] = allowed[q] ? 1 : 0;
+                            }
+                            nv += __popcll(__ballot(allowed[q]));
+                        }
+                        if (lane == 0) r.nvalid[g] = nv;
+                    }
+                    // tables of the history under the present clusters
+                    mine = raw >= 0 && raw < K ? raw : 0;
+                    for (int i = lane; i < KS; i += kWave) { tR[i] = 0ull; tN[i] = 0u; }
+                    wave_sync();
+                    if (live) {
+                        for (int s = 0; s < S; ++s) {
+                            atomicAdd(&tN[mine * S + s], (unsigned)vis[lane * S + s]);
+                            atomicAdd(&tR[mine * S + s], reward_fixed(rs[lane * S + s]));
+                        }
+                    }
+                    wave_sync();
+#pragma unroll
+                    for (int q = 0; q < A; ++q) arm[q] = false;
+                    for (int j = 0; j < K; ++j) {
+                        const bool any = __ballot(live && mine == j) != 0;
+#pragma unroll
+                        for (int q = 0; q < A; ++q) arm[q] = cl[q] == j ? any : arm[q];
+                    }
+#pragma unroll
+                    for (int q = 0; q < A; ++q) {
+                        const int i = lane + q * kWave;
+                        n[q] = i < KS ? tN[i] : 0u;
+                        Rw[q] = i < KS ? tR[i] : 0ull;
+                        mean[q] = ucb_mean(r.u, n[q], Rw[q]);
+                        arm[q] = i < KS && arm[q] && allowed[q];
+                    }
+                }
+                if (rd >= stop) break;
+
+                const bool last = rd == T - 1;
+                const int l64 = rd & 63;
+                if (l64 == 0) {
+                    const long long tt = t + rd + lane;
+                    lnl = log((double)(tt < 1 ? 1 : tt));
+                    if (rd + lane < T) {
+                        const size_t al = (size_t)(rd + lane) * a.G + g;
+                        rwl = r.reward[al];
+                        okl = r.ok[al];
+                    }
+                }
+                const double lnt = lane_d(lnl, l64);
+                double bu = -INFINITY;
+                bf = -1;
+#pragma unroll
+                for (int q = 0; q < A; ++q) {
+                    u[q] = ucb_index(r.u, n[q], arm[q], lnt, mean[q]);
+                    if (arm[q] && (bf < 0 || u[q] > bu)) { bu = u[q]; bf = lane + q * kWave; }
+                }
+                wave_best_arm<(A > 1)>(bu, bf);
+                bf = __builtin_amdgcn_readfirstlane(bf);
+                int I = -1, s = -1, lead = -1, k = -1;
+                if (bf >= 0) {
+                    const int ow = bf & 63;
+                    int tc = 0;
+#pragma unroll
+                    for (int q = 0; q < A; ++q) {
+                        if (bf >> 6 == q) {
+                            I = __builtin_amdgcn_readlane(cl[q], ow);
+                            s = __builtin_amdgcn_readlane(st[q], ow);
+                            tc = __builtin_amdgcn_readlane(col[q], ow);
+                        }
+                    }
+                    lead = __ffsll((long long)__ballot(live && mine == I)) - 1;
+                    const bool member = live && raw == I;
+                    double key = -INFINITY;
+                    if (member) {
+                        key = pot[tc * NM + lane] + gb[(rd & (kAhead - 1)) * NM + lane];
+                        // A key that is not a number loses to every other, except that of the first
+                        // member, which then stays chosen: the result of scanning the members in order.
+                        if (!(key == key)) key = lane == lead ? INFINITY : -INFINITY;
+                    }
+                    k = wave_top_lane(key, member);           // (lowest candidate on ties)
+                }
+                const bool log_here = lane == l64;
+                log_I = log_here ? I : log_I;
+                log_s = log_here ? s : log_s;
+                log_lead = log_here ? lead : log_lead;
+                log_k = log_here ? k : log_k;
+                updated = k >= 0 && __builtin_amdgcn_readlane(okl, l64) != 0;
+                if (updated) {
+                    rw = (double)lane_f(rwl, l64);
+                    const int cell = k * S + s;
+                    const float r_old = rs[cell];
+                    const float r_new = (float)((double)r_old + rw);
+                    if (lane == 0) { vis[cell] += 1; rs[cell] = r_new; }
+                    wave_sync();
+                    if (!last) {
+                        const unsigned long long step = reward_fixed(r_new) - reward_fixed(r_old);
+#pragma unroll
+                        for (int q = 0; q < A; ++q) {
+                            if (lane + q * kWave == bf) {
+                                n[q] += 1u;
+                                Rw[q] += step;
+                                mean[q] = ucb_mean(r.u, n[q], Rw[q]);
+                            }
+                        }
+                    }
+                }
+                if (l64 == 63 || last) {
+                    // 64 iterations' logs, one per lane
+                    const int it = rd - l64 + lane;
+                    if (it <= rd) {
+                        const size_t at = (size_t)it * a.G + g;
+                        r.sel_log[at * 3 + 0] = log_I;
+                        r.sel_log[at * 3 + 1] = log_s;
+                        r.sel_log[at * 3 + 2] = log_lead >= 0 ? n0 + log_lead : -1;
+                        r.ksel_log[at] = log_k >= 0 ? n0 + log_k : -1;
+                    }
+                }
+                ++rd;
+                fresh = rd < T && rd == next;
+            }
+            if (NW == 1 && c < chunks) variates(c, lane, kWave);
+        }
+        if (NW > 1) __syncthreads();
+        else wave_sync();
+    }
+    if (wv == 0) {
+        // counts, means and scores as the last iteration saw them, with its update of one arm
+#pragma unroll
+        for (int q = 0; q < A; ++q) {
+            const int i = lane + q * kWave;
+            if (i < KS) {
+                const size_t o = (size_t)k0 * S + i;
+                const bool up = updated && i == bf;
+                const int nn = (int32_t)n[q] + (up ? 1 : 0);
+                const double mo = (double)(float)mean[q];
+                r.u.Ncs[o] = nn;
+                r.u.mu[o] = up ? (float)(mo + (rw - mo) / ((double)nn + (double)r.u.prior_n)) : (float)mean[q];
+                r.u.ucb[o] = (float)u[q];
+            }
+        }
+    }
+    for (int i = tid; i < ng * S; i += kThreads) {
+        r.visits[(size_t)n0 * S + i] = vis[i];
+        r.rsum[(size_t)n0 * S + i] = rs[i];
+    }
+    if (tid == 0) r.t[g] = t + T;
+}
+
 // 16-byte pieces of a row that a kernel is compiled for, from the feature count
 int row_pieces(int D) {
     const int n = (D + 3) / 4;
@@ -459,11 +846,11 @@ hipError_t with_pieces(int D, F go) {
 }
 
 template <class K, class... A>
-hipError_t launch(K kern, unsigned grid, size_t lds, hipStream_t st, const A&... args) {
+hipError_t launch(K kern, unsigned grid, unsigned threads, size_t lds, hipStream_t st, const A&... args) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, args...);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, st, args...);
     return hipGetLastError();
 }
 
@@ -490,7 +877,7 @@ hipError_t launch_cluster_wave(const kb_batch& b, const ClusterCall& c, hipStrea
     const ShortArgs a = short_args(b, c);
     return with_pieces(b.D, [&](auto nc) {
         constexpr int NC = decltype(nc)::value;
-        return launch(cluster_wave_kernel<NC>, wave_grid(b), kWaves * short_lds_layout(a.Kmax, a.D, NC).total, st, a);
+        return launch(cluster_wave_kernel<NC>, wave_grid(b), kThreads, kWaves * short_lds_layout(a.Kmax, a.D, NC).total, st, a);
     });
 }
 
@@ -518,7 +905,40 @@ hipError_t launch_round_wave(const kb_batch& b, const ClusterCall& c, const UcbC
     return with_pieces(b.D, [&](auto nc) {
         constexpr int NC = decltype(nc)::value;
         const size_t lds = kWaves * (short_lds_layout(a.Kmax, a.D, NC).total + arm_lds_bytes(a.Kmax, b.S));
-        return launch(round_wave_kernel<NC>, wave_grid(b), lds, st, a, rd);
+        return launch(round_wave_kernel<NC>, wave_grid(b), kThreads, lds, st, a, rd);
+    });
+}
+
+// `kb_iterate` on a batch of such searches is one launch per 1024 iterations, provided that the
+// resources and strategies are few enough for the tables of a search (a lane holds one or four
+// cluster arms; at least four workgroups' tables fit a compute unit).
+bool iterate_in_one_launch(const kb_batch& b, int scorer, int R) {
+    return cluster_wave_per_search(b, scorer) && b.G > 0 && R <= kIterateMaxR &&
+           (int64_t)kmax_of(b) * b.S <= kIterateMaxArms && b.Nmax > 0 &&
+           iterate_lds_layout(kmax_of(b), b.D, row_pieces(b.D), b.S, R, b.Nmax).total <= 40 * 1024;
+}
+
+hipError_t launch_iterate(const kb_batch& b, const ClusterCall& c, const UcbCall& uc, const SampleCall& sc,
+                          const RoundsCall& rc, const IterateCall& ic, hipStream_t st) {
+    if (!iterate_in_one_launch(b, c.scorer, sc.R) || c.mixed || uc.bound || !sc.h || rc.rounds < 1)
+        return hipErrorInvalidValue;
+    IterateArgs r;
+    r.c = short_args(b, c);
+    r.u = make_ucb_args(b, uc);
+    r.s = make_sample_args(b, sc);
+    r.rounds = rc.rounds; r.tau = ic.tau; r.first_due = ic.first_due; r.warm = ic.warm;
+    r.draw0 = sc.draw; r.reward = rc.reward; r.ok = rc.ok; r.visits = rc.visits; r.rsum = rc.rsum; r.t = rc.t;
+    r.sel_log = rc.sel_log; r.ksel_log = rc.ksel_log;
+    r.M = ic.M; r.nvalid = ic.nvalid; r.rep = ic.rep; r.radius = ic.radius;
+    r.Nmax = b.Nmax;
+    return with_pieces(b.D, [&](auto nc) {
+        constexpr int NC = decltype(nc)::value;
+        const size_t lds = iterate_lds_layout(r.c.Kmax, b.D, NC, b.S, sc.R, b.Nmax).total;
+        const auto go = [&](auto kern, int waves) { return launch(kern, (unsigned)b.G, waves * kWave, lds, st, r); };
+        const bool one = r.c.Kmax * b.S <= kWave;
+        const bool few = b.G <= (one && NC <= 4 ? 768 : 256);      // (the line: see above)
+        return few ? (one ? go(iterate_kernel<NC, 1, 4>, 4) : go(iterate_kernel<NC, 4, 4>, 4))
+                   : (one ? go(iterate_kernel<NC, 1, 1>, 1) : go(iterate_kernel<NC, 4, 1>, 1));
     });
 }
 

@@ -347,8 +347,8 @@ __device__ __forceinline__ void rounds_search(const RoundsArgs& r, int g, unsign
         int bf = -1;
         for (int i = tid; i < KS; i += NT) {
             const unsigned n = Ncnt[i];
-            double m;
-            const double u = ucb_score(a, n, R[i], valid[i] != 0, lnt, m);
+            const double m = ucb_mean(a, n, R[i]);
+            const double u = ucb_index(a, n, valid[i] != 0, lnt, m);
             if (last) {
                 const size_t o = (size_t)k0 * S + i;
                 a.Ncs[o] = (int32_t)n;

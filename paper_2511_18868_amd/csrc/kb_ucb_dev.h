@@ -79,22 +79,27 @@ __device__ __forceinline__ void ucb_add_candidate(const UcbArgs& a, size_t row, 
     ucb_count_candidate(p, j, bd, nalive, kmin);
 }
 
-// Mean reward `m` and UCB index (returned) of an arm with n visits and the reward sum R,
-// lnt = ln t of its search.
-__device__ __forceinline__ double ucb_score(const UcbArgs& a, unsigned n, unsigned long long R, bool valid,
-                                            double lnt, double& m) {
-    const double pn = (double)a.prior_n, pm = (double)a.prior_mu, cc = (double)a.c;
+// Mean reward of an arm with n visits and the reward sum R (NaN without visits and pseudo-visits),
+// and its UCB index, lnt = ln t of its search.
+__device__ __forceinline__ double ucb_mean(const UcbArgs& a, unsigned n, unsigned long long R) {
+    const double pn = (double)a.prior_n, pm = (double)a.prior_mu;
     const double nt = (double)n + pn;
     const double rt = (double)(long long)R * kRewardInv + pn * pm;
-    m = nt > 0.0 ? rt / nt : NAN;
+    return nt > 0.0 ? rt / nt : NAN;
+}
+__device__ __forceinline__ double ucb_index(const UcbArgs& a, unsigned n, bool valid, double lnt, double m) {
+    const double nt = (double)n + (double)a.prior_n;
     if (!valid) return -INFINITY;
-    return nt > 0.0 ? m + cc * sqrt(lnt / nt) : INFINITY;
+    return nt > 0.0 ? fma((double)a.c, sqrt(lnt / nt), m) : INFINITY;
 }
 
-// The best arm of a wave: the largest score, lowest flat index on ties; arm < 0: none in this
-// lane.  Cross-lane moves inside the vector registers (a chain of shuffles through LDS takes
-// four times as long).  Scores that are not numbers (c = +inf at t = 1) have no order: with one
-// of them in the wave the result is that of the pairwise exchange, in lane 0.
+// The best arm of a wave whose lanes hold an arm each: the largest score, lowest flat index on ties;
+// arm < 0: none in this lane.  Cross-lane moves inside the vector registers (a chain of shuffles
+// through LDS takes four times as long).  Scores that are not numbers (c = +inf at t = 1) have no order:
+// with one of them in the wave the result is that of the pairwise exchange, in lane 0.
+// ROWS: a lane's arms are lane, lane + 64, ..., the best of which `arm` is; ties between lanes are then
+// not in the order of the lanes.
+template <bool ROWS>
 __device__ __forceinline__ void wave_best_arm(double& u, int& arm) {
     if (__any(arm >= 0 && !(u == u))) {
 #pragma unroll
@@ -105,10 +110,12 @@ __device__ __forceinline__ void wave_best_arm(double& u, int& arm) {
         }
         return;
     }
-    const double best = wave_max_d(arm >= 0 ? u : -INFINITY);
-    const int low = wave_min_i(arm >= 0 && u == best ? arm : 0x7fffffff);
+    const int top = wave_top_lane(u, arm >= 0);
+    if (top < 0) { arm = -1; return; }
+    const double best = lane_d(u, top);
+    if constexpr (ROWS) arm = wave_min_i(arm >= 0 && u == best ? arm : 0x7fffffff);
+    else arm = __builtin_amdgcn_readlane(arm, top);
     u = best;
-    arm = low == 0x7fffffff ? -1 : low;
 }
 
 // Scores, outputs and selection of one search from its accumulated tables
@@ -131,8 +138,8 @@ __device__ __forceinline__ void ucb_finish(const UcbArgs& a, int g, int n0, int 
         const int cl = i / S;
         const unsigned n = Ncnt[i];
         const bool valid = nalive[cl] > 0u && (!a.M || a.M[(size_t)k0 * S + i] != 0);
-        double m;
-        const double u = ucb_score(a, n, R[i], valid, lnt, m);
+        const double m = ucb_mean(a, n, R[i]);
+        const double u = ucb_index(a, n, valid, lnt, m);
         const size_t o = (size_t)k0 * S + i;
         a.Ncs[o] = (int32_t)n;
         a.mu[o] = (float)m;
@@ -140,7 +147,7 @@ __device__ __forceinline__ void ucb_finish(const UcbArgs& a, int g, int n0, int 
         if (valid && (bf < 0 || u > bu)) { bu = u; bf = i; }
     }
     // argmax with the lowest flat index on ties: waves, then the block
-    wave_best_arm(bu, bf);
+    wave_best_arm<true>(bu, bf);
     if constexpr (NT > 64) {
         if ((tid & 63) == 0) { redv[tid >> 6] = bu; redi[tid >> 6] = bf; }
         __syncthreads();

@@ -66,6 +66,27 @@ __device__ __forceinline__ double wave_max_d(double v) {
     v = fmax(v, dpp_d<0x140>(v));
     return fmax(fmax(lane_d(v, 0), lane_d(v, 16)), fmax(lane_d(v, 32), lane_d(v, 48)));
 }
+// The lane that holds the largest value of the lanes with `has`, the lowest such lane on ties; -1:
+// none has.  The values are numbers.  Rounded to fp32 they keep their order, so a lane that alone
+// reaches the largest fp32 value is the one - a dozen instructions; only where several do (equal or
+// nearly equal values) the fp64 values are compared.
+__device__ __forceinline__ int wave_top_lane(double v, bool has) {
+    const unsigned long long any = __ballot(has);
+    if (!any) return -1;
+    const float f = has ? (float)v : -INFINITY;
+    float m = row_max_f(f);
+    // every row's maximum to the next row, then that of the lower half to the upper: lane 63 has it
+    m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(m), __float_as_int(m), 0x142, 0xa, 0xf, false)));
+    m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(m), __float_as_int(m), 0x143, 0xc, 0xf, false)));
+    m = lane_f(m, 63);
+    unsigned long long top = __ballot(has && f == m);
+    if (top & (top - 1)) {
+        const bool in = has && f == m;
+        const double best = wave_max_d(in ? v : -INFINITY);
+        top = __ballot(in && v == best);
+    }
+    return __ffsll((long long)top) - 1;
+}
 __device__ __forceinline__ int wave_min_i(int v) {
     auto step = [](int x, int y) { return x < y ? x : y; };
     v = step(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xf, 0xf, false));

@@ -44,3 +44,58 @@ def test_clustering_by_a_wave_equals_the_workgroup_kernel(kb, D, kcap, kdiv):
             np.testing.assert_array_equal(one[k].view(np.uint8), other[k].view(np.uint8), err_msg=k)
         assert_rel_close(one["objective"], other["objective"], what="objective")
     assert not np.array_equal(out[0]["cent"], out[2]["cent"]) or kcap == 1
+
+
+SHAPES = {
+    # G, nmin, nmax, D, S, kcap, kdiv, rounds: four waves a search, then one; one arm per lane, then four
+    "paper": (61, 12, 41, 5, 6, 3, 4, 70),
+    "many": (800, 1, 64, 5, 6, 3, 4, 19),
+    "edge": (37, 1, 64, 33, 16, 16, 1, 19),
+    "manyedge": (770, 1, 30, 13, 16, 16, 1, 9),
+    "onearm": (5, 1, 64, 64, 1, 1, 1, 19),
+    "morethanalaunch": (3, 20, 41, 8, 6, 4, 4, 1030),
+}
+
+
+@pytest.mark.parametrize("variant", ["cold", "warm", "masked", "notanumber"])
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_iterations_in_one_launch_equal_the_launches_one_by_one(kb, shape, variant):
+    """A signature of at most eight resources lets a batch run its iterations in one launch; with a
+    ninth, which no strategy works on, the same call goes through the launches of the stages.  Every
+    output byte for byte, searches too short to be clustered again (N_g < 2 K_g) among them."""
+    import torch
+    G, nmin, nmax, D, S, kcap, kdiv, T = SHAPES[shape]
+    b = synth.config5(G=G, nmin=nmin, nmax=nmax, D=D, S=S, kcap=kcap, kdiv=kdiv, iters=4, seed=600 + G)
+    R = 8 if shape == "edge" else 3
+    h, target, theta = synth.signatures(b, R)
+    fb = [synth.feedback(b, seed=r) for r in range(T)]
+    rw, ok = np.stack([f[0] for f in fb]), np.stack([f[1] for f in fb])
+    alive = (np.arange(b.N) % 3 != 1).astype(np.uint8) if variant == "masked" else None
+    if variant == "notanumber":       # inf * sqrt(ln 1 / n), beside untried arms
+        b.t[:] = 1
+        b.visits[:, ::2] = 0
+        b.rsum[:, ::2] = 0.0
+    got = []
+    for cols in (R, 9):
+        d = kb.DeviceBatch(b)
+        if variant == "notanumber":
+            d.params.c, d.params.prior_n = float("inf"), 0.0
+        up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(d.device)  # noqa: E731
+        hp = np.zeros((b.N, cols), np.float32)
+        hp[:, :R] = h
+        dh, dt = up(hp), up(target)
+        d.cluster()
+        d.cluster_geometry()
+        kb.kb_strategy_mask(d.batch, cols, dh, dt, d.rep, theta, d.M, d.nvalid)
+        sel_log = torch.full((T, b.G, 3), -7, dtype=torch.int32, device=d.device)
+        ksel_log = torch.full((T, b.G), -7, dtype=torch.int32, device=d.device)
+        ip = kb.kb_iterate_params(T, 5, 3, int(variant == "warm"), cols, theta, kb.kb_sample_params(9, 77, 0.8))
+        d.iterate(ip, dh, dt, up(rw), up(ok), sel_log, ksel_log, alive=None if alive is None else up(alive))
+        torch.cuda.synchronize()
+        out = {k: d.host(k).copy() for k in ("visits", "rsum", "t", "assign", "cent", "counts", "objective", "rep",
+                                             "radius", "M", "nvalid", "Ncs", "mu", "ucb")}
+        out["sel_log"], out["ksel_log"] = sel_log.cpu().numpy(), ksel_log.cpu().numpy()
+        got.append(out)
+    for k in got[0]:
+        np.testing.assert_array_equal(got[0][k].view(np.uint8), got[1][k].view(np.uint8), err_msg=k)
+    assert (got[0]["ksel_log"] >= 0).any()
