@@ -379,25 +379,33 @@ __device__ __forceinline__ void tile_scores(const bf16x8 (&Bh)[DS], const bf16x8
     // flight so that consecutive matrix instructions never depend on each
     // other: the two centroid tiles when there are two, otherwise the
     // hi*mid products are summed apart and added at the end.
-    constexpr int NA = 2;
-    f32x16 acc[NA];
-    const bool two = MT == 2 && mtiles == 2;
-#pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4) {
-        const float4 c4 = *reinterpret_cast<const float4*>(cn + 8 * g4 + 4 * h);
-        acc[0][4 * g4 + 0] = c4.x; acc[0][4 * g4 + 1] = c4.y;
-        acc[0][4 * g4 + 2] = c4.z; acc[0][4 * g4 + 3] = c4.w;
-    }
-    if (two) {
+    // Best and second best among this lane's rows with three vector instructions per
+    // score: the score's position replaces its 5 lowest mantissa bits (which moves
+    // it by less than 2^-18 of itself - part of the error bound), then a
+    // median-of-three and a minimum; the row of the best is read back from those
+    // bits.  Two independent chains; the lane-dependent part of the row number
+    // (4h) is added afterwards.
+    f32x16 acc[2];
+    float cb[2] = {kBig * 8.f, kBig * 8.f}, cs[2] = {kBig * 8.f, kBig * 8.f};
+    const auto norms = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
-            const float4 c4 = *reinterpret_cast<const float4*>(cn + 32 + 8 * g4 + 4 * h);
-            acc[1][4 * g4 + 0] = c4.x; acc[1][4 * g4 + 1] = c4.y;
-            acc[1][4 * g4 + 2] = c4.z; acc[1][4 * g4 + 3] = c4.w;
+            const float4 c4 = *reinterpret_cast<const float4*>(cn + 32 * t + 8 * g4 + 4 * h);
+            acc[t][4 * g4 + 0] = c4.x; acc[t][4 * g4 + 1] = c4.y;
+            acc[t][4 * g4 + 2] = c4.z; acc[t][4 * g4 + 3] = c4.w;
         }
-        // the first tile of centroids is finished before the second one is started, so
-        // that the vector unit can take its minimum while the matrix cores work on
-        // the second
+    };
+    const auto least = [&](int c, float score, unsigned position) __attribute__((always_inline)) {
+        const float v = __uint_as_float((__float_as_uint(score) & 0xffffffe0u) | position);
+        cs[c] = __builtin_amdgcn_fmed3f(cb[c], cs[c], v);
+        cb[c] = vmin(cb[c], v);
+    };
+    norms(0);
+    // (one block of code from the operands to the minimum in either case: the vector unit
+    // takes the minimum of the first tile of centroids while the matrix cores work on the
+    // second only if no branch lies between them)
+    if (MT == 2 && mtiles == 2) {
+        norms(1);
 #pragma unroll
         for (int s = 0; s < DS; ++s) {
             // centroid operands of this K-step, straight from LDS (operand order)
@@ -415,6 +423,17 @@ __device__ __forceinline__ void tile_scores(const bf16x8 (&Bh)[DS], const bf16x8
             acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1h, Bm[s], acc[1], 0, 0, 0);
             acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1m, Bh[s], acc[1], 0, 0, 0);
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) least(0, acc[0][r], (unsigned)r);
+        // one matrix instruction of the second tile to five vector instructions of
+        // the first tile's minimum
+#pragma unroll
+        for (int q = 0; q < 3 * DS; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) least(1, acc[1][r], 16u + (unsigned)r);
     } else {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[1][r] = 0.f;
@@ -427,42 +446,7 @@ __device__ __forceinline__ void tile_scores(const bf16x8 (&Bh)[DS], const bf16x8
             acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0m, Bh[s], acc[0], 0, 0, 0);
         }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[0][r] += acc[1][r];
-    }
-    // Best and second best among this lane's rows with three vector instructions per
-    // score: the score's position replaces its 5 lowest mantissa bits (which moves
-    // it by less than 2^-18 of itself - part of the error bound), then a
-    // median-of-three and a minimum; the row of the best is read back from those
-    // bits.  Two independent chains; the lane-dependent part of the row number
-    // (4h) is added afterwards.
-    float cb[2] = {kBig * 8.f, kBig * 8.f}, cs[2] = {kBig * 8.f, kBig * 8.f};
-    if (two) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float v = __uint_as_float((__float_as_uint(acc[t][r]) & 0xffffffe0u) | (unsigned)(16 * t + r));
-                cs[t] = __builtin_amdgcn_fmed3f(cb[t], cs[t], v);
-                cb[t] = vmin(cb[t], v);
-            }
-            if (t == 0) {
-                // one matrix instruction of the second tile to five vector instructions of
-                // the first tile's minimum
-#pragma unroll
-                for (int q = 0; q < 3 * DS; ++q) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
-                }
-            }
-        }
-    } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int c = r & 1;
-            const float v = __uint_as_float((__float_as_uint(acc[0][r]) & 0xffffffe0u) | (unsigned)r);
-            cs[c] = __builtin_amdgcn_fmed3f(cb[c], cs[c], v);
-            cb[c] = vmin(cb[c], v);
-        }
+        for (int r = 0; r < 16; ++r) least(r & 1, acc[0][r] + acc[1][r], (unsigned)r);
     }
     auto merge = [](float& b1, float& s1, int& i1, float b2, float s2, int i2) {
         const bool take = b2 < b1;
