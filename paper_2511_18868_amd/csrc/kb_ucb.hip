@@ -19,6 +19,8 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
+constexpr int kWideThreads = 1024;
+constexpr int kUcbHead = (8 + 4) * kWideThreads / kWave;      // reduction scratch ahead of the tables in LDS
 constexpr int kUcbLong = 16384;     // searches longer than this are cut into candidate ranges
 
 // Scatter the visits / reward sums of the alive candidates [q0, q1) of a search
@@ -115,8 +117,9 @@ __device__ __forceinline__ void ucb_accumulate_pieces(const UcbArgs& a, int n0, 
 // E, EXACT: how the rows are cut (ucb_accumulate_pieces); instantiations of their own,
 // so that each form has the registers it needs and no more (in one kernel the forms for
 // odd strategy counts raised the count from 64 to 99 and halved the resident waves of all)
-template <int E, bool EXACT>
-__global__ void __launch_bounds__(kThreads) ucb_kernel(UcbArgs a) {
+template <int E, bool EXACT, int NT>
+__global__ void __launch_bounds__(NT) ucb_kernel(UcbArgs a) {
+    constexpr int kThreads = NT;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
     const int S = a.S;
@@ -133,9 +136,9 @@ __global__ void __launch_bounds__(kThreads) ucb_kernel(UcbArgs a) {
     if (a.mixed && ng > kUcbLong) return;     // the range kernels take this search
     const int KS = K * S;
 
-    double* redv = reinterpret_cast<double*>(smem);                                      // [kWaves]
-    int* redi = reinterpret_cast<int*>(smem + 32);                                       // [kWaves]
-    unsigned long long* R = reinterpret_cast<unsigned long long*>(smem + 64);            // [Kmax*S]
+    double* redv = reinterpret_cast<double*>(smem);                                      // [waves]
+    int* redi = reinterpret_cast<int*>(smem + 8 * (kWideThreads / kWave));               // [waves]
+    unsigned long long* R = reinterpret_cast<unsigned long long*>(smem + kUcbHead);      // [Kmax*S]
     unsigned long long* kmin = R + (size_t)a.Kmax * S;                                   // [Kmax]
     unsigned* Ncnt = reinterpret_cast<unsigned*>(kmin + a.Kmax);                         // [Kmax*S]
     unsigned* nalive = Ncnt + (size_t)a.Kmax * S;                                        // [Kmax]
@@ -227,16 +230,18 @@ struct RoundsArgs {
     int32_t* sel_log;           // [rounds][G][3]
     int32_t* ksel_log;          // [rounds][G]
     int Nmax;
+    int means;                  // 1: the arms' mean rewards are kept in LDS beside the tables
 };
 
 struct RoundsLds {
-    size_t R, kmin, N, nalive, first, cursor, target, valid, member, total;
+    size_t R, mean, kmin, N, nalive, first, cursor, target, valid, member, total;
 };
-__host__ __device__ inline RoundsLds rounds_lds_layout(int Kmax, int S, int Nmax) {
+__host__ __device__ inline RoundsLds rounds_lds_layout(int Kmax, int S, int Nmax, bool means) {
     const size_t KS = (size_t)Kmax * S;
     RoundsLds l;
     size_t off = 0;
     l.R = off;      off += KS * 8;
+    l.mean = off;   off += means ? KS * 8 : 0;
     l.kmin = off;   off += (size_t)Kmax * 8;
     l.N = off;      off += KS * 4;
     l.nalive = off; off += (size_t)Kmax * 4;
@@ -276,7 +281,8 @@ __device__ __forceinline__ void rounds_search(const RoundsArgs& r, int g, unsign
         return;
     }
     const int KS = K * S;
-    const RoundsLds L = rounds_lds_layout(a.Kmax, S, r.Nmax);
+    const RoundsLds L = rounds_lds_layout(a.Kmax, S, r.Nmax, r.means != 0);
+    double* mean = r.means ? reinterpret_cast<double*>(smem + L.mean) : nullptr;
     unsigned long long* R = reinterpret_cast<unsigned long long*>(smem + L.R);
     unsigned long long* kmin = reinterpret_cast<unsigned long long*>(smem + L.kmin);
     unsigned* Ncnt = reinterpret_cast<unsigned*>(smem + L.N);
@@ -308,8 +314,10 @@ __device__ __forceinline__ void rounds_search(const RoundsArgs& r, int g, unsign
     }
     long long t = a.t[g];
     rounds_sync<NT>();
-    for (int i = tid; i < KS; i += NT)
+    for (int i = tid; i < KS; i += NT) {
         valid[i] = nalive[i / S] > 0u && (!a.M || a.M[(size_t)k0 * S + i] != 0);
+        if (mean) mean[i] = ucb_mean(a, Ncnt[i], R[i]);
+    }
     if (tid < kWave) {
         // exclusive prefix sums of the sizes (K <= 256: four clusters per lane)
         int c[4], sum = 0;
@@ -336,18 +344,22 @@ __device__ __forceinline__ void rounds_search(const RoundsArgs& r, int g, unsign
     }
     rounds_sync<NT>();
 
+    double lnl = 0.0;             // lane l: ln t of iteration 64 i + l
     for (int it = 0; it < r.rounds; ++it) {
         const bool last = it == r.rounds - 1;
         const size_t at = (size_t)it * a.G + g;
         const float reward = r.reward[at];           // (requested before they are needed)
         const bool ok = r.ok[at] != 0;
-        const long long tg = t + it < 1 ? 1 : t + it;
-        const double lnt = log((double)tg);
+        if ((it & 63) == 0) {
+            const long long tg = t + it + (tid & 63);
+            lnl = log((double)(tg < 1 ? 1 : tg));
+        }
+        const double lnt = lane_d(lnl, it & 63);
         double bu = -INFINITY;
         int bf = -1;
         for (int i = tid; i < KS; i += NT) {
             const unsigned n = Ncnt[i];
-            const double m = ucb_mean(a, n, R[i]);
+            const double m = mean ? mean[i] : ucb_mean(a, n, R[i]);
             const double u = ucb_index(a, n, valid[i] != 0, lnt, m);
             if (last) {
                 const size_t o = (size_t)k0 * S + i;
@@ -361,8 +373,7 @@ __device__ __forceinline__ void rounds_search(const RoundsArgs& r, int g, unsign
         auto merge_arm = [&](double ou, int of) {
             if (of >= 0 && (bf < 0 || ou > bu || (ou == bu && of < bf))) { bu = ou; bf = of; }
         };
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) merge_arm(__shfl_xor(bu, o), __shfl_xor(bf, o));
+        wave_best_arm<true>(bu, bf);
         if constexpr (NT > kWave) {
             if ((tid & 63) == 0) { redv[tid >> 6] = bu; redi[tid >> 6] = bf; }
             __syncthreads();
@@ -399,8 +410,15 @@ __device__ __forceinline__ void rounds_search(const RoundsArgs& r, int g, unsign
             auto merge_key = [&](double ok2, int oi) {
                 if (better(ok2, oi, bk, k)) { bk = ok2; k = oi; }
             };
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) merge_key(__shfl_xor(bk, o), __shfl_xor(k, o));
+            {
+                // (keys are numbers by now)
+                const int top = wave_top_lane(bk, k != kNoCandidate);
+                if (top >= 0) {
+                    const double best = lane_d(bk, top);
+                    k = wave_min_i(k != kNoCandidate && bk == best ? k : kNoCandidate);
+                    bk = best;
+                }
+            }
             if constexpr (NT > kWave) {
                 // (slots of their own: the first reduction's may still be read)
                 if ((tid & 63) == 0) { redv[NW + (tid >> 6)] = bk; redi[NW + (tid >> 6)] = k; }
@@ -428,6 +446,7 @@ __device__ __forceinline__ void rounds_search(const RoundsArgs& r, int g, unsign
             r.rsum[cell] = r_new;
             Ncnt[bf] += 1u;
             R[bf] += reward_fixed(r_new) - reward_fixed(r_old);
+            if (mean) mean[bf] = ucb_mean(a, Ncnt[bf], R[bf]);
         }
         rounds_sync<NT>();
     }
@@ -471,7 +490,7 @@ __global__ void __launch_bounds__(kThreads) ucb_partial(UcbArgs a) {
     const int64_t r0 = (int64_t)blockIdx.x * kUcbRange;
     if (r0 >= a.N) return;
     const int64_t r1 = r0 + kUcbRange < a.N ? r0 + kUcbRange : a.N;
-    unsigned long long* R = reinterpret_cast<unsigned long long*>(smem + 64);
+    unsigned long long* R = reinterpret_cast<unsigned long long*>(smem + kUcbHead);
     unsigned long long* kmin = R + (size_t)a.Kmax * S;
     unsigned* Ncnt = reinterpret_cast<unsigned*>(kmin + a.Kmax);
     unsigned* nalive = Ncnt + (size_t)a.Kmax * S;
@@ -542,16 +561,28 @@ bool ucb_wave_per_search(const kb_batch& b) {
     return b.G > 0 && b.Nmax <= kShortSearch && (size_t)wave_table_bytes(b) * kWaves <= 64 * 1024;
 }
 
+// Few searches get 1024 threads each, so that one with a compute unit to itself keeps more rows in
+// flight (256 / 1024 threads, us: one search of 4096 candidates, S = 16 36.9 / 16.6, of 16000 147 / 50, of
+// 300 5.2 / 4.8; 256 of 512, S = 32 15.0 / 10.2, 200 of 4096 90 / 36, 512 of 1000 32.6 / 30.4, 300 of 1900, S = 6
+// 25.9 / 21.0); beyond the compute units only for long ones (512 of 600, S = 3 11.2 / 12.4, of 512, S = 32
+// 18.0 / 18.5).
+constexpr int kUcbWideFewG = 256, kUcbWideMaxG = 512, kUcbWideMinN = 1000;
+
 namespace {
 
 // the aggregation kernels in the form that fits the strategy count (see ucb_accumulate_pieces)
-template <int E, bool EXACT>
-hipError_t launch_search_kernel(const UcbArgs& a, size_t lds, hipStream_t st) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ucb_kernel<E, EXACT>),
+template <int E, bool EXACT, int NT>
+hipError_t launch_search_kernel_nt(const UcbArgs& a, size_t lds, hipStream_t st) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ucb_kernel<E, EXACT, NT>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((ucb_kernel<E, EXACT>), dim3((unsigned)a.G), dim3(kThreads), lds, st, a);
+    hipLaunchKernelGGL((ucb_kernel<E, EXACT, NT>), dim3((unsigned)a.G), dim3(NT), lds, st, a);
     return hipGetLastError();
+}
+template <int E, bool EXACT>
+hipError_t launch_search_kernel(const UcbArgs& a, bool wide, size_t lds, hipStream_t st) {
+    return wide ? launch_search_kernel_nt<E, EXACT, kWideThreads>(a, lds, st)
+                : launch_search_kernel_nt<E, EXACT, kThreads>(a, lds, st);
 }
 template <int E, bool EXACT>
 hipError_t launch_range_kernel(const UcbArgs& a, unsigned ranges, size_t lds, hipStream_t st) {
@@ -569,12 +600,12 @@ int row_form(int S) {
     }
     return (S & 1) == 0 ? 2 : 3;
 }
-hipError_t launch_search_kernel(const UcbArgs& a, size_t lds, hipStream_t st) {
+hipError_t launch_search_kernel(const UcbArgs& a, bool wide, size_t lds, hipStream_t st) {
     switch (row_form(a.S)) {
-        case 0: return launch_search_kernel<4, true>(a, lds, st);
-        case 1: return launch_search_kernel<4, false>(a, lds, st);
-        case 2: return launch_search_kernel<2, false>(a, lds, st);
-        default: return launch_search_kernel<1, false>(a, lds, st);
+        case 0: return launch_search_kernel<4, true>(a, wide, lds, st);
+        case 1: return launch_search_kernel<4, false>(a, wide, lds, st);
+        case 2: return launch_search_kernel<2, false>(a, wide, lds, st);
+        default: return launch_search_kernel<1, false>(a, wide, lds, st);
     }
 }
 hipError_t launch_range_kernel(const UcbArgs& a, unsigned ranges, size_t lds, hipStream_t st) {
@@ -588,9 +619,13 @@ hipError_t launch_range_kernel(const UcbArgs& a, unsigned ranges, size_t lds, hi
 
 }  // namespace
 
+static bool ucb_wide(const kb_batch& b) {
+    return b.G <= kUcbWideFewG || (b.G <= kUcbWideMaxG && b.Nmax >= kUcbWideMinN);
+}
+
 hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
     UcbArgs a = make_ucb_args(b, c);
-    const size_t lds = 64 + (size_t)a.Kmax * b.S * 12 + (size_t)a.Kmax * 12;
+    const size_t lds = kUcbHead + (size_t)a.Kmax * b.S * 12 + (size_t)a.Kmax * 12;
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     if (c.from_tables) {
         if (!c.gN) return hipErrorInvalidValue;
@@ -610,7 +645,7 @@ hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
         hipLaunchKernelGGL(ucb_zero, dim3(zb), dim3(kThreads), 0, st, a);
         if (b.G > 1) {
             a.mixed = 1;
-            const hipError_t e = launch_search_kernel(a, lds, st);
+            const hipError_t e = launch_search_kernel(a, ucb_wide(b), lds, st);
             if (e != hipSuccess) return e;
         }
         const unsigned ranges = (unsigned)((b.N + kUcbRange - 1) / kUcbRange);
@@ -631,11 +666,11 @@ hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
                            (size_t)per * kWaves, st, a, per);
         return hipGetLastError();
     }
-    return launch_search_kernel(a, lds, st);
+    return launch_search_kernel(a, ucb_wide(b), lds, st);
 }
 
-static size_t rounds_lds(const kb_batch& b) {
-    return rounds_lds_layout(b.Kmax > 0 ? b.Kmax : 1, b.S, b.Nmax).total;
+static size_t rounds_lds(const kb_batch& b, bool means = false) {
+    return rounds_lds_layout(b.Kmax > 0 ? b.Kmax : 1, b.S, b.Nmax, means).total;
 }
 static bool rounds_wave_per_search(const kb_batch& b) {
     return b.Nmax <= kShortSearch && rounds_lds(b) * kWaves <= 64 * 1024;
@@ -682,7 +717,9 @@ hipError_t launch_rounds(const kb_batch& b, const UcbCall& c, const SampleCall& 
     r.rounds = rc.rounds; r.draw0 = sc.draw; r.reward = rc.reward; r.ok = rc.ok;
     r.visits = rc.visits; r.rsum = rc.rsum; r.t = rc.t; r.sel_log = rc.sel_log; r.ksel_log = rc.ksel_log;
     r.Nmax = b.Nmax;
-    const size_t lds = rounds_lds(b);
+    // (means beside the tables where two searches per compute unit still fit)
+    r.means = rounds_lds(b, true) <= (rounds_wave_per_search(b) ? 16 * 1024 : 78 * 1024);
+    const size_t lds = rounds_lds(b, r.means != 0);
     if (rounds_wave_per_search(b)) {
         hipLaunchKernelGGL(rounds_wave, dim3((unsigned)((b.G + kWaves - 1) / kWaves)), dim3(kThreads),
                            lds * kWaves, st, r, (int)lds);
