@@ -210,49 +210,61 @@ __device__ __forceinline__ void score_valu(const ClusterArgs& a, const float* __
 // cores read them - made a tile in which a few candidates are at risk pull in most of
 // its cache lines (9.2 GB of HBM traffic on the largest benchmark against 7.1 GB for a
 // candidate-major copy), and writing any copy costs more than converting again.
-// Everything that follows a change of a centroid, four lanes per row: the new centroid (fixed-point sum / 2^shift) / count in
+// Everything that follows a change of a centroid: the new centroid (fixed-point sum / 2^shift) / count in
 // fp64, rounded once to fp32; how far it moved (rounded up); |c_j|^2 in fp64; and
 // the matrix cores' operands -2 c_j split into bf16 (hi, mid), stored in LDS in
 // operand order [tile of 32 rows][16-feature step][hi|mid][lane] x 16 bytes so the
 // scorer reads them with conflict-free 16-byte loads.  Only rows whose membership
 // changed are touched (`init`: every row, nothing renewed; rows >= K get zero
 // operands).  Returns this thread's view of max_j |c_j|^2.
-// (Four lanes per row, lane q owning the 4-feature chunks q, q + 4, ...: all 64 rows of a
-// search are renewed in one pass, so a step pays this dependent chain - reciprocal,
-// means, fp64 sums across the four lanes, square root, operand conversion - once and
-// not once per group of sixteen rows.)
-__device__ __forceinline__ double quad_sum_d(double v) {
+// LPR lanes share a row, lane q owning the 4-feature chunks q, q + LPR, ...: a step pays this
+// dependent chain - reciprocal, means, fp64 sums across the lanes, square root, operand conversion -
+// for every chunk of a lane, so there are as many lanes as a row has chunks, up to sixteen, and as let
+// one pass renew all rows a kernel is compiled for.  (Four lanes per row / this, a round, 768
+// threads: 300 searches of 70-1900 rows of 50 features 342 / 309 us, one of 4096 rows of 32 228 / 221 us; with
+// sixteen lanes for the four chunks of 16 features one search of 256 rows 77.1 / 78.7 us.)
+constexpr int renew_lanes(int DS, int MT, int NT) {
+    const int rows = MT == 0 ? 4 : NT / (32 * MT), chunks = 4 * DS;
+    const int most = rows < chunks ? rows : chunks;
+    return most < 8 ? 4 : most < 12 ? 8 : 16;
+}
+template <int LPR>
+__device__ __forceinline__ double group_sum_d(double v) {
     v += dpp_d<0xB1>(v);
     v += dpp_d<0x4E>(v);
+    if constexpr (LPR >= 8) v += dpp_d<0x141>(v);
+    if constexpr (LPR >= 16) v += dpp_d<0x140>(v);
     return v;
 }
 
-template <int DS, bool OPERANDS, int NT>
+template <int DS, bool OPERANDS, int NT, int LPR>
 __device__ __forceinline__ float renew_rows(float* cent, float* cn, bf16x8* aop, const long long* sums,
                                             const int* cnt, unsigned char* dirty, float* delta, int K, int D,
                                             int SP, double inv, bool init, bool need_scores) {
     constexpr int DP = 16 * DS + 4;
-    const int tid = (int)threadIdx.x, q = tid & 3;
+    const int tid = (int)threadIdx.x, q = tid & (LPR - 1);
+    constexpr int NI = (4 * DS + LPR - 1) / LPR;         // chunks of a lane
     const int rows = init && OPERANDS ? ((K + 31) & ~31) : K;
     float cm = 0.f;
-    for (int j0 = 0; j0 < rows; j0 += NT / 4) {
-        const int j = j0 + (tid >> 2);
+    for (int j0 = 0; j0 < rows; j0 += NT / LPR) {
+        const int j = j0 + tid / LPR;
         const bool real = j < K;
         const int c = real ? cnt[j] : 0;
         const bool renew = !init && real && c > 0 && dirty[j] != 0;
         const bool fresh = renew || (init && j < rows);
-        float4 v[DS];
+        float4 v[NI];
 #pragma unroll
-        for (int i = 0; i < DS; ++i) {
+        for (int i = 0; i < NI; ++i) {
             v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (real) v[i] = *reinterpret_cast<const float4*>(cent + (size_t)j * DP + 4 * (q + 4 * i));
+            if (real && q + LPR * i < 4 * DS)
+                v[i] = *reinterpret_cast<const float4*>(cent + (size_t)j * DP + 4 * (q + LPR * i));
         }
         double mv = 0.0;
         if (renew) {
             const double cd = (double)c, rc = 1.0 / cd;
 #pragma unroll
-            for (int i = 0; i < DS; ++i) {
-                const int d0 = 4 * (q + 4 * i);
+            for (int i = 0; i < NI; ++i) {
+                const int d0 = 4 * (q + LPR * i);
                 float* vp = &v[i].x;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -263,12 +275,12 @@ __device__ __forceinline__ float renew_rows(float* cent, float* cn, bf16x8* aop,
                         vp[e] = cnew;
                     }
                 }
-                *reinterpret_cast<float4*>(cent + (size_t)j * DP + d0) = v[i];
+                if (d0 < 16 * DS) *reinterpret_cast<float4*>(cent + (size_t)j * DP + d0) = v[i];
             }
         }
-        // uniform over the four lanes of a row from here on
+        // uniform over the lanes of a row from here on
         if (!init) {
-            mv = quad_sum_d(mv);
+            mv = group_sum_d<LPR>(mv);
             if (real && q == 0) {
                 // rounded up: the fp32 square root is within 2^-23 of the true one
                 delta[j] = !renew ? 0.f
@@ -282,19 +294,20 @@ __device__ __forceinline__ float renew_rows(float* cent, float* cn, bf16x8* aop,
             if (fresh) {
                 double sq = 0.0;
 #pragma unroll
-                for (int i = 0; i < DS; ++i)
+                for (int i = 0; i < NI; ++i)
                     sq += (double)v[i].x * (double)v[i].x + (double)v[i].y * (double)v[i].y +
                           (double)v[i].z * (double)v[i].z + (double)v[i].w * (double)v[i].w;
-                sq = quad_sum_d(sq);
+                sq = group_sum_d<LPR>(sq);
                 f = (float)sq;
                 if (real && q == 0) cn[j] = f;
                 if constexpr (OPERANDS) {
                     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
                     const int mt = j >> 5;
 #pragma unroll
-                    for (int i = 0; i < DS; ++i) {
+                    for (int i = 0; i < NI; ++i) {
                         // chunk ch holds features 4 ch .. 4 ch + 3: half of the 8-feature piece ch / 2
-                        const int ch = q + 4 * i;
+                        const int ch = q + LPR * i;
+                        if (ch >= 4 * DS) continue;
                         const float w[4] = {-2.f * v[i].x, -2.f * v[i].y, -2.f * v[i].z, -2.f * v[i].w};
                         bf16x4 hi, mid;
 #pragma unroll
@@ -1267,7 +1280,7 @@ cluster_fused_kernel(ClusterArgs a) {
     double inv = ldexp(1.0, -sh);
 
     // |c_j|^2, their maximum and the matrix-core operands of the initial centroids
-    float cm = renew_rows<DS, (MT > 0), NT>(cent, cn, aop, sums, cnt, dirty, delta, K, D, SP, inv, true, true);
+    float cm = renew_rows<DS, (MT > 0), NT, renew_lanes(DS, MT, NT)>(cent, cn, aop, sums, cnt, dirty, delta, K, D, SP, inv, true, true);
     cm = block_max_f<kWaves>(cm, red, phase);
 
     bool first = true;
@@ -1432,7 +1445,7 @@ cluster_fused_kernel(ClusterArgs a) {
             }
         }
         // new centroids, and what the next step needs from them
-        cm = renew_rows<DS, (MT > 0), NT>(cent, cn, aop, sums, cnt, dirty, delta, K, D, SP, inv, false, !last);
+        cm = renew_rows<DS, (MT > 0), NT, renew_lanes(DS, MT, NT)>(cent, cn, aop, sums, cnt, dirty, delta, K, D, SP, inv, false, !last);
         cm = block_max_f<kWaves>(cm, red, phase);
         if (last) break;
     }
