@@ -1281,7 +1281,17 @@ cluster_fused_kernel(ClusterArgs a) {
 
     // |c_j|^2, their maximum and the matrix-core operands of the initial centroids
     float cm = renew_rows<DS, (MT > 0), NT, renew_lanes(DS, MT, NT)>(cent, cn, aop, sums, cnt, dirty, delta, K, D, SP, inv, true, true);
-    cm = block_max_f<kWaves>(cm, red, phase);
+    // largest |c_j|^2 of the search
+    auto largest_norm = [&](float seen) __attribute__((always_inline)) {
+        if constexpr (MT > 0) {
+            const int lane = tid & 63;                             // (K <= 64 on this path: every wave for itself)
+            __syncthreads();
+            return wave_max_f(lane < K ? cn[lane] : 0.f);
+        } else {
+            return block_max_f<kWaves>(seen, red, phase);
+        }
+    };
+    cm = largest_norm(cm);
 
     bool first = true;
     float drift = 0.f;          // cumulative (largest + second largest) centroid move, rounded up
@@ -1336,10 +1346,13 @@ cluster_fused_kernel(ClusterArgs a) {
             score_valu<4 * DS, NT>(a, Xg, n0, ng, K, D, DP, cent, cn, cm);
             st = 2;
         }
-        st = block_or_i<kWaves>(st, red, phase);
-        if (st & 2) {
+        // (whether anything moved matters only to a search that may stop there; what is listed for
+        // the exact pass says its counter)
+        if (MT == 0 || a.early_exit) st = block_or_i<kWaves>(st, red, phase);
+        else __syncthreads();
+        const int nf = MT > 0 ? *nflag : kFlagCap + 1;
+        if (nf > 0) {
             int moved;
-            const int nf = MT > 0 ? *nflag : kFlagCap + 1;
             if (nf <= kFlagCap) {
                 moved = refine_listed<DS, NT>(a, Xg, n0, nf, flist, K, D, DP, SP, cent, fsh, sums, cnt, dw,
                                       thr, lim, drift, Tc);
@@ -1362,7 +1375,8 @@ cluster_fused_kernel(ClusterArgs a) {
                         for (int t = tid; t < ((ng + 31) >> 5); t += kThreads) thr[t] = 0.f;
                 }
             }
-            st |= block_or_i<kWaves>(moved, red, phase);
+            if (a.early_exit) st |= block_or_i<kWaves>(moved, red, phase);
+            else __syncthreads();
             // every thread has read the counter before that barrier, and the barriers of
             // the renewal below separate this reset from the next step's additions
             if (tid == 0) *nflag = 0;
@@ -1446,7 +1460,7 @@ cluster_fused_kernel(ClusterArgs a) {
         }
         // new centroids, and what the next step needs from them
         cm = renew_rows<DS, (MT > 0), NT, renew_lanes(DS, MT, NT)>(cent, cn, aop, sums, cnt, dirty, delta, K, D, SP, inv, false, !last);
-        cm = block_max_f<kWaves>(cm, red, phase);
+        cm = largest_norm(cm);
         if (last) break;
     }
 

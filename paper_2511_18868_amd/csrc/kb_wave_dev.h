@@ -51,9 +51,13 @@ __device__ __forceinline__ double lane_d(double v, int l) {
     const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), l);
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
+// (rows are combined by handing lane 15's value to the next row, then lane 31's to the upper half: two
+// moves and one scalar read instead of four)
 __device__ __forceinline__ float wave_max_f(float v) {
     v = row_max_f(v);
-    return fmaxf(fmaxf(lane_f(v, 0), lane_f(v, 16)), fmaxf(lane_f(v, 32), lane_f(v, 48)));
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x142, 0xa, 0xf, false)));
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x143, 0xc, 0xf, false)));
+    return lane_f(v, 63);
 }
 __device__ __forceinline__ float wave_min_f(float v) {
     v = row_min_f(v);
@@ -74,11 +78,7 @@ __device__ __forceinline__ int wave_top_lane(double v, bool has) {
     const unsigned long long any = __ballot(has);
     if (!any) return -1;
     const float f = has ? (float)v : -INFINITY;
-    float m = row_max_f(f);
-    // every row's maximum to the next row, then that of the lower half to the upper: lane 63 has it
-    m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(m), __float_as_int(m), 0x142, 0xa, 0xf, false)));
-    m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(m), __float_as_int(m), 0x143, 0xc, 0xf, false)));
-    m = lane_f(m, 63);
+    const float m = wave_max_f(f);
     unsigned long long top = __ballot(has && f == m);
     if (top & (top - 1)) {
         const bool in = has && f == m;
