@@ -1,0 +1,7 @@
+// The Lloyd kernel for rows of up to 32 features (one translation unit per row length: they compile side
+// by side).
+#include "kb_cluster_lloyd.h"
+
+namespace kb {
+template hipError_t launch_lloyd<2>(const ClusterArgs&, const LloydForm&, hipStream_t);
+}  // namespace kb
