@@ -87,6 +87,7 @@ hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t s
     const int ds = (b.D + 15) / 16;   // 1..4 K-steps of 16 features
     // a batch of very short searches, in the library's default mode: one wave per search
     if (!c.mixed && cluster_wave_per_search(b, c.scorer)) return launch_cluster_wave(b, c, st);
+    if (!c.mixed && cluster_resident(b, c.scorer, c.iters)) return launch_cluster_resident(a, b.Nmax, st);
     const auto lds = [&](bool wide, bool state) {
         return lds_layout(a.Kmax, b.D, 16 * ds + 4, a.Nmax, (wide ? kThreadsWide : kThreadsNarrow) / kWave, state).total;
     };

@@ -41,6 +41,7 @@
 #pragma once
 #include "kb_cluster_dev.h"
 #include "kb_wave_dev.h"
+#include <type_traits>
 
 namespace kb {
 
@@ -78,6 +79,12 @@ struct LloydForm {
 // DS: feature K-steps of 16
 template <int DS>
 hipError_t launch_lloyd(const ClusterArgs& a, const LloydForm& f, hipStream_t st);
+
+// Searches whose rows stay in registers (kb_cluster_resident.hip): whether a batch is one of such, and
+// its launch.
+constexpr int kResidentMaxG = 256;
+bool cluster_resident(const kb_batch& b, int scorer, int iters);
+hipError_t launch_cluster_resident(const ClusterArgs& a, int Nmax, hipStream_t st);
 
 // Threads per workgroup (a template parameter NT of the kernel and of the device
 // functions that stride by it): 256, three workgroups per compute unit, is the
@@ -289,7 +296,7 @@ __device__ __forceinline__ double group_sum_d(double v) {
     return v;
 }
 
-template <int DS, bool OPERANDS, int NT, int LPR>
+template <int DS, bool OPERANDS, int NT, int LPR, bool DELTA = true>
 __device__ __forceinline__ float renew_rows(float* cent, float* cn, bf16x8* aop, const long long* sums,
                                             const int* cnt, unsigned char* dirty, float* delta, int K, int D,
                                             int SP, double inv, bool init, bool need_scores) {
@@ -322,8 +329,10 @@ __device__ __forceinline__ float renew_rows(float* cent, float* cn, bf16x8* aop,
                 for (int e = 0; e < 4; ++e) {
                     if (d0 + e < D) {
                         const float cnew = mean_f32((double)sums[(size_t)j * SP + d0 + e] * inv, cd, rc);
-                        const double df = (double)cnew - (double)vp[e];
-                        mv += df * df;
+                        if constexpr (DELTA) {
+                            const double df = (double)cnew - (double)vp[e];
+                            mv += df * df;
+                        }
                         vp[e] = cnew;
                     }
                 }
@@ -332,10 +341,10 @@ __device__ __forceinline__ float renew_rows(float* cent, float* cn, bf16x8* aop,
         }
         // uniform over the lanes of a row from here on
         if (!init) {
-            mv = group_sum_d<LPR>(mv);
+            if constexpr (DELTA) mv = group_sum_d<LPR>(mv);
             if (real && q == 0) {
                 // rounded up: the fp32 square root is within 2^-23 of the true one
-                delta[j] = !renew ? 0.f
+                if constexpr (DELTA) delta[j] = !renew ? 0.f
                            : mv < 1.0e-30 ? (float)sqrt(mv) * 1.0000005f
                                           : sqrtf((float)mv) * 1.0000005f;
                 dirty[j] = 0;
@@ -977,15 +986,100 @@ __device__ __forceinline__ void refine(const ClusterArgs& a, const float* __rest
     }
 }
 
-// ---- phases R + B over the list of marked candidates ----------------------------
-// One wave per listed candidate, lanes over centroids; the next candidate's row
-// is requested before the current one is worked on.  First every squared
+// Nearest centroid of one candidate, lane d holding its feature d (zeros beyond D), by a whole wave
+// with lanes over centroids.  First every squared
 // distance in fp32, direct differences: a sum of non-negative terms, so its
 // relative error is at most (D + 2) 2^-24.  If the two smallest are further apart
 // than twice that bound allows, the smallest is the unique nearest centroid.
 // Otherwise the distances are formed exactly as the plain definition does - fp64,
 // summed over the features in index order with separate multiply and add - and the
-// lowest index attaining the minimum wins.  Then, if the nearest centroid differs
+// lowest index attaining the minimum wins.  ub: upper bound on the nearest distance, lbd: lower
+// bound on all others.
+template <int DS>
+__device__ __forceinline__ int exact_nearest(float xv, const float* cent, int K, int D, int DP, float& ub, float& lbd) {
+    const int lane = threadIdx.x & 63;
+    const float eps = 2.f * (float)(D + 2) * 5.9604644775390625e-08f;
+    // rows are zero-padded to a multiple of 4 features (and xv is 0 beyond D), so
+    // whole float4 chunks can be summed: the extra terms are +0.0
+    float lb = INFINITY, ls = INFINITY;       // this lane's smallest and second smallest
+    int lj = 0x7fffffff;
+    for (int j0 = 0; j0 < K; j0 += kWave) {
+        const int j = j0 + lane;
+        const float* cr = cent + (size_t)(j < K ? j : 0) * DP;
+        float acc0 = 0.f, acc1 = 0.f;
+        // (feature numbers known at compile time: the row's values are read out of
+        // their lanes into scalar registers, no cross-lane traffic through LDS)
+#pragma unroll
+        for (int d = 0; d < 16 * DS; d += 4) {
+            if (d < D) {
+                const float4 cv = *reinterpret_cast<const float4*>(cr + d);
+                const float e0 = lane_f(xv, d) - cv.x, e1 = lane_f(xv, d + 1) - cv.y;
+                const float e2 = lane_f(xv, d + 2) - cv.z, e3 = lane_f(xv, d + 3) - cv.w;
+                acc0 = fmaf(e0, e0, acc0);
+                acc1 = fmaf(e1, e1, acc1);
+                acc0 = fmaf(e2, e2, acc0);
+                acc1 = fmaf(e3, e3, acc1);
+            }
+        }
+        const float acc = acc0 + acc1;
+        if (j < K) {
+            if (acc < lb) { ls = lb; lb = acc; lj = j; }
+            else if (acc < ls) ls = acc;
+        }
+    }
+    const float b32 = wave_min_f(lb);
+    const int fl = __ffsll((long long)__ballot(lb == b32)) - 1;
+    const float s32 = wave_min_f(lane == fl ? ls : lb);
+    int bj = __shfl(lj, fl);
+    if (s32 * (1.f - eps) > b32 * (1.f + eps) + 1.0e-35f) {     // uniform over the wave
+        ub = sqrtf(b32 * (1.f + eps)) * 1.0000005f;
+        lbd = sqrtf(s32 * (1.f - eps)) * 0.9999995f;
+    } else {
+        double bd = INFINITY, sd = INFINITY;
+        bj = 0x7fffffff;
+        for (int j0 = 0; j0 < K; j0 += kWave) {
+            const int j = j0 + lane;
+            const float* cr = cent + (size_t)(j < K ? j : 0) * DP;
+            double acc = 0.0;
+#pragma unroll
+            for (int d = 0; d < 16 * DS; d += 4) {
+                if (d < D) {
+                    const float4 cv = *reinterpret_cast<const float4*>(cr + d);
+                    double diff = __dsub_rn((double)lane_f(xv, d), (double)cv.x);
+                    acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+                    diff = __dsub_rn((double)lane_f(xv, d + 1), (double)cv.y);
+                    acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+                    diff = __dsub_rn((double)lane_f(xv, d + 2), (double)cv.z);
+                    acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+                    diff = __dsub_rn((double)lane_f(xv, d + 3), (double)cv.w);
+                    acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+                }
+            }
+            if (j < K) {
+                if (acc < bd) { sd = bd; bd = acc; bj = j; }
+                else if (acc < sd) sd = acc;
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const double od = __shfl_xor(bd, o);
+            const double os = __shfl_xor(sd, o);
+            const int oj = __shfl_xor(bj, o);
+            const bool take = od < bd || (od == bd && oj < bj);
+            const double hi2 = take ? bd : od;        // the larger of the two bests
+            const double sm = os < sd ? os : sd;
+            sd = sm < hi2 ? sm : hi2;
+            if (take) { bd = od; bj = oj; }
+        }
+        ub = (float)sqrt(bd) * 1.0000005f;
+        lbd = (float)sqrt(sd) * 0.9999995f;
+    }
+    return bj;
+}
+
+// ---- phases R + B over the list of marked candidates ----------------------------
+// One wave per listed candidate, lanes over centroids; the next candidate's row
+// is requested before the current one is worked on.  If the nearest centroid differs
 // from the recorded cluster, the row moves between the running sums.
 template <int DS, int NT>
 __device__ __forceinline__ int refine_listed(const ClusterArgs& a, const float* __restrict__ Xg,
@@ -995,7 +1089,6 @@ __device__ __forceinline__ int refine_listed(const ClusterArgs& a, const float* 
                                              float2* __restrict__ lim, float drift, float T) {
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform)
     const int lc = lane < D ? lane : 0;
-    const float eps = 2.f * (float)(D + 2) * 5.9604644775390625e-08f;
     int any = 0;
     if (wid >= n) return 0;
     constexpr int W = NT / kWave;
@@ -1020,82 +1113,8 @@ __device__ __forceinline__ int refine_listed(const ClusterArgs& a, const float* 
             xv_m = Xg[(size_t)p_m * D + lc];
             old_m = a.assign[(size_t)n0 + p_m];
         }
-        // rows are zero-padded to a multiple of 4 features (and xv is 0 beyond D), so
-        // whole float4 chunks can be summed: the extra terms are +0.0
-        float lb = INFINITY, ls = INFINITY;       // this lane's smallest and second smallest
-        int lj = 0x7fffffff;
-        for (int j0 = 0; j0 < K; j0 += kWave) {
-            const int j = j0 + lane;
-            const float* cr = cent + (size_t)(j < K ? j : 0) * DP;
-            float acc0 = 0.f, acc1 = 0.f;
-            // (feature numbers known at compile time: the row's values are read out of
-            // their lanes into scalar registers, no cross-lane traffic through LDS)
-#pragma unroll
-            for (int d = 0; d < 16 * DS; d += 4) {
-                if (d < D) {
-                    const float4 cv = *reinterpret_cast<const float4*>(cr + d);
-                    const float e0 = lane_f(xv, d) - cv.x, e1 = lane_f(xv, d + 1) - cv.y;
-                    const float e2 = lane_f(xv, d + 2) - cv.z, e3 = lane_f(xv, d + 3) - cv.w;
-                    acc0 = fmaf(e0, e0, acc0);
-                    acc1 = fmaf(e1, e1, acc1);
-                    acc0 = fmaf(e2, e2, acc0);
-                    acc1 = fmaf(e3, e3, acc1);
-                }
-            }
-            const float acc = acc0 + acc1;
-            if (j < K) {
-                if (acc < lb) { ls = lb; lb = acc; lj = j; }
-                else if (acc < ls) ls = acc;
-            }
-        }
-        const float b32 = wave_min_f(lb);
-        const int fl = __ffsll((long long)__ballot(lb == b32)) - 1;
-        const float s32 = wave_min_f(lane == fl ? ls : lb);
-        int bj = __shfl(lj, fl);
         float ub, lbd;      // upper bound on the nearest distance, lower bound on all others
-        if (s32 * (1.f - eps) > b32 * (1.f + eps) + 1.0e-35f) {     // uniform over the wave
-            ub = sqrtf(b32 * (1.f + eps)) * 1.0000005f;
-            lbd = sqrtf(s32 * (1.f - eps)) * 0.9999995f;
-        } else {
-            double bd = INFINITY, sd = INFINITY;
-            bj = 0x7fffffff;
-            for (int j0 = 0; j0 < K; j0 += kWave) {
-                const int j = j0 + lane;
-                const float* cr = cent + (size_t)(j < K ? j : 0) * DP;
-                double acc = 0.0;
-#pragma unroll
-                for (int d = 0; d < 16 * DS; d += 4) {
-                    if (d < D) {
-                        const float4 cv = *reinterpret_cast<const float4*>(cr + d);
-                        double diff = __dsub_rn((double)lane_f(xv, d), (double)cv.x);
-                        acc = __dadd_rn(acc, __dmul_rn(diff, diff));
-                        diff = __dsub_rn((double)lane_f(xv, d + 1), (double)cv.y);
-                        acc = __dadd_rn(acc, __dmul_rn(diff, diff));
-                        diff = __dsub_rn((double)lane_f(xv, d + 2), (double)cv.z);
-                        acc = __dadd_rn(acc, __dmul_rn(diff, diff));
-                        diff = __dsub_rn((double)lane_f(xv, d + 3), (double)cv.w);
-                        acc = __dadd_rn(acc, __dmul_rn(diff, diff));
-                    }
-                }
-                if (j < K) {
-                    if (acc < bd) { sd = bd; bd = acc; bj = j; }
-                    else if (acc < sd) sd = acc;
-                }
-            }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                const double od = __shfl_xor(bd, o);
-                const double os = __shfl_xor(sd, o);
-                const int oj = __shfl_xor(bj, o);
-                const bool take = od < bd || (od == bd && oj < bj);
-                const double hi2 = take ? bd : od;        // the larger of the two bests
-                const double sm = os < sd ? os : sd;
-                sd = sm < hi2 ? sm : hi2;
-                if (take) { bd = od; bj = oj; }
-            }
-            ub = (float)sqrt(bd) * 1.0000005f;
-            lbd = (float)sqrt(sd) * 0.9999995f;
-        }
+        int bj = exact_nearest<DS>(xv, cent, K, D, DP, ub, lbd);
         bj = bj < K ? bj : 0;
         const float Tb = __shfl(T, bj);
         if (lane == 0) {

@@ -1,0 +1,46 @@
+"""The Lloyd kernel that keeps a search's rows in registers (at most 256 searches, up to 512 candidates,
+256 with more than 32 clusters) against the kernel that fetches them, which scorer mode 2 takes: row
+lengths at the edges of K-steps and 16-byte pieces, tiles and pairs of tiles filled exactly and by one,
+equal distances, caller-supplied centroids, stopping early."""
+import numpy as np
+import pytest
+
+from paper_2511_18868_amd import synth
+from kbcheck import assert_rel_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def kb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2511_18868_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("D", [1, 2, 4, 7, 16, 17, 33, 48, 50, 64])
+@pytest.mark.parametrize("nmax,kcap,kdiv", [(256, 64, 2), (257, 32, 4), (512, 32, 8), (100, 3, 4)])
+@pytest.mark.parametrize("stop", [0, 1])
+def test_resident_rows_give_the_bytes_of_fetched_rows(kb, D, nmax, kcap, kdiv, stop):
+    import torch
+    b = synth.config5(G=24, nmin=1, nmax=nmax, D=D, S=3, iters=9, kcap=kcap, kdiv=kdiv, seed=900 + D)
+    longest = synth.config2(N=nmax, D=D, K=min(kcap, nmax // kdiv), S=3, iters=9, seed=3)
+    b = synth.concat(b, longest, "resident")
+    if D % 2:          # rows on a grid: equal distances
+        b.X[:] = np.rint(2.0 * b.X) / 2.0
+    rows = np.concatenate([np.arange(e - 1, e - 1 - k, -1) for e, k in
+                           zip(b.seg_off[1:], np.diff(b.koff))]).astype(np.int64)
+    for init in (False, True):
+        out = []
+        for mode in (0, 2):
+            d = kb.DeviceBatch(b, iters=9, scorer=mode, stop_early=stop)
+            start = torch.from_numpy(b.X[rows].copy()).to(d.device) if init else None
+            kb.kb_cluster(d.batch, d.params, d.X, start, d.assign, d.cent, d.counts, d.objective, d.ws, d.ws_bytes)
+            torch.cuda.synchronize()
+            out.append({k: d.host(k).copy() for k in ("assign", "cent", "counts", "objective")})
+        for k in ("assign", "cent", "counts"):
+            np.testing.assert_array_equal(out[0][k].view(np.uint8), out[1][k].view(np.uint8), err_msg=k)
+        assert_rel_close(out[0]["objective"], out[1]["objective"], what="objective")
