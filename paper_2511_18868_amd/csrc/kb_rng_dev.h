@@ -14,8 +14,9 @@ __device__ __forceinline__ void philox4x32_10(unsigned c0, unsigned c1, unsigned
                                               unsigned k0, unsigned k1, unsigned& o0, unsigned& o1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const unsigned h0 = __umulhi(0xD2511F53u, c0), l0 = 0xD2511F53u * c0;
-        const unsigned h1 = __umulhi(0xCD9E8D57u, c2), l1 = 0xCD9E8D57u * c2;
+        const unsigned long long p0 = (unsigned long long)0xD2511F53u * c0, p1 = (unsigned long long)0xCD9E8D57u * c2;
+        const unsigned h0 = (unsigned)(p0 >> 32), l0 = (unsigned)p0;
+        const unsigned h1 = (unsigned)(p1 >> 32), l1 = (unsigned)p1;
         c0 = h1 ^ c1 ^ k0;
         c1 = l1;
         c2 = h0 ^ c3 ^ k1;
