@@ -36,6 +36,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kNone = 0x7fffffff;
+constexpr int kGeoRangeMin = 512, kGeoFill = 300, kGeoFillRagged = 600;
 constexpr int kGeoMergeMax = 16384;    // longer searches: a wave of geo_merge would walk many slots
 
 struct GeoArgs {
@@ -52,6 +53,7 @@ struct GeoArgs {
     unsigned long long* gmin;      // [Ksum]
     unsigned long long* gmax;      // [Ksum]
     unsigned char* spare;          // [4 N] bytes: slots of searches that began before a range
+    int range;                     // candidates per workgroup
     int merged;                    // 1: geo_merge follows, gmin / gmax are not used
     int mixed;                     // 1: searches of at most kShortSearch candidates go to geo_wave, longer
                                    //    ones to the range kernels, in the same call
@@ -66,10 +68,10 @@ struct GeoSlot {
     unsigned long long* most;      // [Kmax] and of the largest
     int32_t* rep;                  // [Kmax] lowest candidate at the smallest, kNone
 };
-static_assert(20 * KB_MAX_K <= 4 * kGeoRange, "a slot fits the bytes of a range");
+static_assert(20 * KB_MAX_K <= 4 * kGeoRange, "a slot fits the bytes of a range");     // (range_of: of a shorter one)
 __device__ __forceinline__ GeoSlot geo_slot(const GeoArgs& a, int64_t range, bool began_before) {
-    unsigned char* base = began_before ? a.spare + (range - 1) * (4 * kGeoRange)
-                                       : reinterpret_cast<unsigned char*>(a.d2) + range * (8 * kGeoRange);
+    unsigned char* base = began_before ? a.spare + (range - 1) * (4 * (int64_t)a.range)
+                                       : reinterpret_cast<unsigned char*>(a.d2) + range * (8 * (int64_t)a.range);
     GeoSlot s;
     s.least = reinterpret_cast<unsigned long long*>(base);
     s.most = s.least + a.Kmax;
@@ -82,9 +84,11 @@ __global__ void __launch_bounds__(kThreads) geo_init(GeoArgs a) {
     if (i < a.Ksum) { a.gmin[i] = ~0ull; a.gmax[i] = 0ull; a.rep[i] = kNone; }
 }
 
-// VEC = 4: D is a multiple of 4, rows are moved as 16-byte pieces; VEC = 1: any D.
-template <int VEC>
-__global__ void __launch_bounds__(kThreads) geo_dist(GeoArgs a) {
+// VEC = 4: D is a multiple of 4 and pieces of 16 bytes stay inside a row; VEC = 1: any D, the tile is
+// one run of floats all the same, fetched in 16-byte pieces that may cross from row to row.
+// kPieces: pieces of a thread (4 times as many features at most).
+template <int VEC, int kPieces>
+__global__ void __launch_bounds__(kThreads, VEC == 1 ? 2 : 1) geo_dist(GeoArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
     // row stride of the transposed tile: D + 4 words keeps 16-byte pieces aligned and
@@ -96,18 +100,17 @@ __global__ void __launch_bounds__(kThreads) geo_dist(GeoArgs a) {
     float* lc = reinterpret_cast<float*>(lmax + a.Kmax);                              // [Kmax * D]
     float* lx = lc + (size_t)a.Kmax * D;                                              // [256 * DP]
 
-    const int64_t r0 = (int64_t)blockIdx.x * kGeoRange;
+    const int64_t r0 = (int64_t)blockIdx.x * a.range;
     if (r0 >= a.N) return;
-    const int64_t r1 = r0 + kGeoRange < a.N ? r0 + kGeoRange : a.N;
+    const int64_t r1 = r0 + a.range < a.N ? r0 + a.range : a.N;
 
-    // position of this thread's pieces inside a tile: piece i of the thread is
-    // element VEC * (tid + 256 i) of the tile = (row, col); advancing i adds
+    // position of this thread's pieces inside a tile: piece i of the thread begins at
+    // element 4 (tid + 256 i) of the tile = (row, col); advancing i adds
     // (qd, rd) with a carry
-    constexpr int kPieces = 64 / VEC;             // D <= 64: at most D / VEC pieces per thread
-    const int step = VEC * kThreads;
+    const int step = 4 * kThreads;
     const int qd = step / D, rd = step - qd * D;
-    const int row0 = (VEC * tid) / D, col0 = VEC * tid - row0 * D;
-    const int npieces = (D + VEC - 1) / VEC;      // pieces per thread of a full tile (D / VEC when VEC = 4)
+    const int row0 = (4 * tid) / D, col0 = 4 * tid - row0 * D;
+    const int npieces = (D + 3) / 4;              // pieces per thread of a full tile
 
     int lo = 0, hi = a.G;
     while (hi - lo > 1) {
@@ -141,63 +144,57 @@ __global__ void __launch_bounds__(kThreads) geo_dist(GeoArgs a) {
             for (int j = tid; j < K; j += kThreads) { lmin[j] = ~0ull; lmax[j] = 0ull; }
         }
 
-        float xr[kPieces][VEC];
+        float xr[kPieces][4];
         auto fetch = [&](int tb) {
             const int cnt = q1 - tb < kThreads ? q1 - tb : kThreads;
-            const int total = cnt * D / VEC;       // pieces in the tile (exact: VEC divides D or is 1)
+            const int total = cnt * D;
             const float* src = a.X + (size_t)tb * D;
 #pragma unroll
             for (int i = 0; i < kPieces; ++i) {
-                const int idx = tid + i * kThreads;
-                if (i < npieces && idx < total) {
+                const int at = 4 * (tid + i * kThreads);
+                if (i < npieces && at < total) {
+                    // (the last piece is moved back so that it ends with the tile, and shifted when it is stored)
+                    float4 v;
                     if constexpr (VEC == 4) {
-                        const float4 v = reinterpret_cast<const float4*>(src)[idx];
-                        xr[i][0] = v.x; xr[i][1] = v.y; xr[i][2] = v.z; xr[i][3] = v.w;
+                        v = *reinterpret_cast<const float4*>(src + at);
+                    } else if (total >= 4) {
+                        v = load4(src + (at + 4 <= total ? at : total - 4));
                     } else {
-                        xr[i][0] = src[idx];
+                        v = make_float4(0.f, total > 2 ? src[0] : 0.f, total > 1 ? src[total - 2] : 0.f, src[total - 1]);
                     }
+                    xr[i][0] = v.x; xr[i][1] = v.y; xr[i][2] = v.z; xr[i][3] = v.w;
                 }
             }
         };
-        if constexpr (VEC == 4) fetch(q0);
+        fetch(q0);
         for (int tb = q0; tb < q1; tb += kThreads) {
             const int cnt = q1 - tb < kThreads ? q1 - tb : kThreads;
-            const int total = cnt * D / VEC;
-            if constexpr (VEC == 1) {
-                // feature by feature: straight from memory into the transposed tile, eight
-                // values in flight per thread (holding a whole tile's 64 values per thread
-                // for the next round, as the 16-byte form does, leaves room for one
-                // workgroup per compute unit only)
-                const float* src = a.X + (size_t)tb * D;
-                int row = row0, col = col0;
-                for (int i0 = 0; i0 < npieces; i0 += 8) {
-                    float v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int idx = tid + (i0 + u) * kThreads;
-                        v[u] = (i0 + u < npieces && idx < total) ? src[idx] : 0.f;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int idx = tid + (i0 + u) * kThreads;
-                        if (i0 + u < npieces && idx < total) lx[row * DP + col] = v[u];
-                        row += qd; col += rd;
-                        if (col >= D) { col -= D; row += 1; }
-                    }
-                }
-            } else
+            const int total = cnt * D;
             // registers -> LDS, one row per candidate
             {
                 int row = row0, col = col0;
 #pragma unroll
                 for (int i = 0; i < kPieces; ++i) {
-                    const int idx = tid + i * kThreads;
-                    if (i < npieces && idx < total) {
+                    const int at = 4 * (tid + i * kThreads);
+                    if (i < npieces && at < total) {
                         float* dst = lx + row * DP + col;
                         if constexpr (VEC == 4) {
                             *reinterpret_cast<float4*>(dst) = make_float4(xr[i][0], xr[i][1], xr[i][2], xr[i][3]);
                         } else {
-                            dst[0] = xr[i][0];
+                            // (from the end of a row to the start of the next: DP - D words are skipped)
+                            float v[4] = {xr[i][0], xr[i][1], xr[i][2], xr[i][3]};
+                            const int over = at + 4 - total;          // values of the last piece that came before it
+                            if (over > 0) {
+                                if (over & 1) { v[0] = v[1]; v[1] = v[2]; v[2] = v[3]; }
+                                if (over & 2) { v[0] = v[2]; v[1] = v[3]; }
+                            }
+                            int c = col;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                if (e + over < 4) *dst = v[e];
+                                ++dst;
+                                if (++c == D) { c = 0; dst += DP - D; }
+                            }
                         }
                     }
                     row += qd; col += rd;
@@ -208,9 +205,7 @@ __global__ void __launch_bounds__(kThreads) geo_dist(GeoArgs a) {
             int j = p < q1 ? a.assign[p] : 0;
             j = (j >= 0 && j < K) ? j : 0;
             __syncthreads();
-            if constexpr (VEC == 4) {
-                if (tb + kThreads < q1) fetch(tb + kThreads);
-            }
+            if (tb + kThreads < q1) fetch(tb + kThreads);
             if (tid < cnt) {
                 const float* xrow = lx + tid * DP;
                 const float* crow = lc + (size_t)j * D;
@@ -295,9 +290,9 @@ __global__ void __launch_bounds__(kThreads) geo_dist(GeoArgs a) {
 
 __global__ void __launch_bounds__(kThreads) geo_rep(GeoArgs a) {
     const int tid = threadIdx.x;
-    const int64_t r0 = (int64_t)blockIdx.x * kGeoRange;
+    const int64_t r0 = (int64_t)blockIdx.x * a.range;
     if (r0 >= a.N) return;
-    const int64_t r1 = r0 + kGeoRange < a.N ? r0 + kGeoRange : a.N;
+    const int64_t r1 = r0 + a.range < a.N ? r0 + a.range : a.N;
     int lo = 0, hi = a.G;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -349,7 +344,7 @@ __global__ void __launch_bounds__(kThreads) geo_merge(GeoArgs a, int parts) {
     for (int j = Kc + kWave * part + lane; j < K; j += kWave * parts) { a.rep[k0 + j] = -1; a.radius[k0 + j] = 0.f; }
     const int j = kWave * part + lane;
     if (j >= Kc) return;
-    const int64_t ra = n0 / kGeoRange, rb = ((int64_t)n0 + ng - 1) / kGeoRange;
+    const int64_t ra = n0 / a.range, rb = ((int64_t)n0 + ng - 1) / a.range;
     if (ra == rb) return;                                // finished by its range
     unsigned long long least = ~0ull, most = 0ull;
     int rep = kNone;
@@ -448,12 +443,25 @@ size_t geometry_lds_bytes(int Kmax, int D) {
     return (size_t)16 * Kmax + (size_t)4 * Kmax * D + (size_t)4 * kThreads * (D + 4);
 }
 
+// Candidates per workgroup: as many as leave every compute unit two workgroups (what its LDS holds; more
+// where a piece crosses rows and takes longer), if the slots of the shorter ranges hold a
+// search's clusters.  geo_dist, 2048 / this (us): 512 searches of 64-4096 rows of 48 features 44 / 35 (in ranges
+// of 512 42), 200 of them 44 / 23, one of 10000 rows of 32 18 / 7.5; 1000 of 70-1900 rows of 50 97 / 64 with
+// pieces that cross rows (value by value 120), 300 of them 111 / 31.
+static int range_of(const kb_batch& b) {
+    const int fill = (b.D & 3) == 0 ? kGeoFill : kGeoFillRagged;
+    int range = kGeoRange;
+    while (range > kGeoRangeMin && b.N < (int64_t)fill * range && 5 * (int64_t)b.Kmax <= range / 2) range /= 2;
+    return range;
+}
+
 hipError_t launch_geometry(const kb_batch& b, const GeoCall& c, hipStream_t st) {
     GeoArgs a;
     a.G = b.G; a.D = b.D; a.Ksum = b.Ksum; a.Kmax = b.Kmax > 0 ? b.Kmax : 1; a.N = b.N;
     a.seg_off = b.seg_off; a.koff = b.koff; a.X = c.X; a.cent = c.cent; a.assign = c.assign;
     a.rep = c.rep; a.radius = c.radius; a.d2 = c.d2; a.gmin = c.gmin; a.gmax = c.gmax;
     a.spare = reinterpret_cast<unsigned char*>(c.spare); a.merged = 0;
+    a.range = range_of(b);
     if (b.Ksum <= 0) return hipSuccess;
     // a batch of short searches only: a wave per search, one launch; a batch of mostly
     // short searches (256 candidates or fewer on average) with longer ones among them: the
@@ -476,21 +484,19 @@ hipError_t launch_geometry(const kb_batch& b, const GeoCall& c, hipStream_t st) 
         if ((b.D & 3) == 0) hipLaunchKernelGGL(geo_wave<4>, wgrid, dim3(kThreads), wlds, st, a);
         else hipLaunchKernelGGL(geo_wave<1>, wgrid, dim3(kThreads), wlds, st, a);
     }
-    const unsigned ranges = (unsigned)((b.N + kGeoRange - 1) / kGeoRange);
+    const unsigned ranges = (unsigned)((b.N + a.range - 1) / a.range);
     if (ranges) {
         const size_t lds = geometry_lds_bytes(a.Kmax, b.D);
         if (lds > 160 * 1024) return hipErrorInvalidValue;
-        if ((b.D & 3) == 0) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(geo_dist<4>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const auto go = [&](auto kern) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(geo_dist<4>, dim3(ranges), dim3(kThreads), lds, st, a);
-        } else {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(geo_dist<1>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(geo_dist<1>, dim3(ranges), dim3(kThreads), lds, st, a);
-        }
+            hipLaunchKernelGGL(kern, dim3(ranges), dim3(kThreads), lds, st, a);
+            return hipSuccess;
+        };
+        const hipError_t e = (b.D & 3) == 0 ? go(geo_dist<4, 16>) : b.D <= 16 ? go(geo_dist<1, 4>) : go(geo_dist<1, 16>);
+        if (e != hipSuccess) return e;
         if (!a.merged) hipLaunchKernelGGL(geo_rep, dim3(ranges), dim3(kThreads), 0, st, a);
     }
     if (a.merged) {
