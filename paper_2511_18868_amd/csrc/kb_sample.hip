@@ -24,14 +24,18 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-// Searches of at most short_n candidates are drawn by one wave each (sample_wave).  In a
-// batch of many searches (1024 candidates or fewer on average, so that a range of the
-// range kernels holds several) that is 4096: a lane then walks up to 64 candidates,
-// reading 4 bytes of each and a little more of the chosen cluster's members.  Measured:
-// 1024 searches of 512 candidates 36 -> 12 us, the largest benchmark (64-4096) 41 -> 23
-// us against the range kernels; at 16384 a batch of 64 searches of that length went 27 ->
-// 198 us.  In a batch of few long searches a wave per search is the slower way (8
-// searches of 4000: 27 -> 44 us) and the limit stays at kShortSearch.
+// Which threads draw for a search (sample_search where nothing else is said; range kernels or a wave
+// each / 256 threads / 1024, us):
+//   up to 256 candidates: a wave.
+//   up to 4096: 256 threads.  1024 searches of 512 11.8 / 7.5 / 14.6, 300 of 70-1900 23.2 / 9.2 / 9.7, 512 of
+//     64-4096 32.7 / 10.1 / 11.8, 4096 of them 34.1 / 18.5 / 58.3, 2000 of 1500 43.9 / 19.5 / 40.9.
+//   few that may be longer than 2048, or up to 16384: 1024 threads.  One of 4096 10.8 / 5.8 / 4.9, 8 of 4000
+//     29.5 / 16.2 / 8.9, one of 16000 16.1 / 16.7 / 10.2, 64 of 16384 24.0 / 32.2 / 20.2.
+//   very many with few candidates on average: a wave (4000 of 300 15.8 / 16.1 / 54.3).
+//   otherwise the range kernels, and in a batch of several searches a wave for those of up to
+//     short_n (4096 where searches have 1024 candidates or fewer on average, else 256) in the same call.
+constexpr int kGroupN = 4096, kGroupMaxG = 4096, kGroupMeanN = 512;
+constexpr int kWideFewG = 256, kWideFewN = 2048, kWideMaxG = 512, kWideN = 16384;
 constexpr int kSampleShortMany = 4096;
 static int sample_short(const kb_batch& b) {
     return b.N <= (int64_t)1024 * b.G ? kSampleShortMany : kShortSearch;
@@ -62,7 +66,7 @@ __global__ void __launch_bounds__(kThreads) sample_range(SampleArgs a) {
         search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
         if (n0 >= r1) break;
         if (ng <= 0) continue;
-        if (a.mixed && ng <= a.short_n) continue;      // (uniform) a wave of sample_wave takes this search
+        if (a.mixed && ng <= a.short_n) continue;      // (uniform) a wave of sample_search takes this search
         const int n1 = n0 + ng;
         const int q0 = r0 > n0 ? (int)r0 : n0;
         const int q1 = r1 < n1 ? (int)r1 : n1;
@@ -143,25 +147,29 @@ __global__ void __launch_bounds__(kThreads) sample_final(SampleArgs a) {
     a.ksel[g] = bi == kNoCandidate ? -1 : bi;
 }
 
-// Batches of short searches: one wave per search, four searches per workgroup, one
-// launch.  (A workgroup of sample_range walks the searches of its range one after
+// A search to NT threads: a wave (four searches per workgroup) or a workgroup of its own, one launch.
+// (A workgroup of sample_range walks the searches of its range one after
 // the other, a barrier per search; with a few dozen candidates per search that is
 // hundreds of searches in a row.)  Same keys, same exact comparison, so the same draw.
-__global__ void __launch_bounds__(kThreads) sample_wave(SampleArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int g = (int)blockIdx.x * kWaves + (int)(threadIdx.x >> 6);
-    if (g >= a.G) return;
+template <int NT>
+__global__ void __launch_bounds__(NT < kThreads ? kThreads : NT) sample_search(SampleArgs a) {
+    constexpr int W = NT / kWave;
+    __shared__ double redk[W];
+    __shared__ int redi[W];
+    const int tid = NT == kWave ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
+    const int g = NT == kWave ? (int)blockIdx.x * kWaves + (int)(threadIdx.x >> 6) : (int)blockIdx.x;
+    if (g >= a.G) return;                  // (whole waves)
     int n0, ng, k0, K;
     search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
     if (ng <= 0) {
-        if (lane == 0) a.ksel[g] = -1;
+        if (tid == 0) a.ksel[g] = -1;
         return;
     }
     if (a.mixed && ng > a.short_n) return;         // the range kernels take this search
     const int I = a.sel[(size_t)g * 3];
     double bk = 0.0;
     int bi = kNoCandidate;
-    if (I >= 0) {
+    if (I >= 0) {                                  // (uniform over the search's threads)
         double pot_scale = 1.0;
         int tcol = 0;
         if (a.mode == 0) {
@@ -170,20 +178,40 @@ __global__ void __launch_bounds__(kThreads) sample_wave(SampleArgs a) {
             const int s = clampi(a.sel[(size_t)g * 3 + 1], 0, a.S - 1);
             tcol = clampi(a.target[s], 0, a.R - 1);
         }
-        for (int p = n0 + lane; p < n0 + ng; p += kWave) {
-            if (a.assign[p] != I) continue;
-            if (a.alive && !a.alive[p]) continue;
-            const double key = sample_key(a, p, pot_scale, tcol);
-            if (better(key, p, bk, bi)) { bk = key; bi = p; }
-        }
+        constexpr int U = NT == kWave ? 1 : 4;     // clusters of a thread's candidates requested together
+        const int n1 = n0 + ng;
+        for (int pb = n0 + tid; pb < n1; pb += NT * U) {
+            int jj[U];
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const double ok = __shfl_xor(bk, o);
-            const int oi = __shfl_xor(bi, o);
+            for (int u = 0; u < U; ++u) {
+                const int p = pb + u * NT;
+                jj[u] = p < n1 ? a.assign[p] : -1;
+            }
+#pragma unroll 1
+            for (int u = 0; u < U; ++u) {
+                const int p = pb + u * NT;
+                int j = jj[0];
+#pragma unroll
+                for (int v = 1; v < U; ++v) j = u == v ? jj[v] : j;
+                if (j != I) continue;
+                if (a.alive && !a.alive[p]) continue;
+                const double key = sample_key(a, p, pot_scale, tcol);
+                if (better(key, p, bk, bi)) { bk = key; bi = p; }
+            }
+        }
+        auto merge = [&](double ok, int oi) {
             if (better(ok, oi, bk, bi)) { bk = ok; bi = oi; }
+        };
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) merge(__shfl_xor(bk, o), __shfl_xor(bi, o));
+        if constexpr (NT > kWave) {
+            if ((tid & 63) == 0) { redk[tid >> 6] = bk; redi[tid >> 6] = bi; }
+            __syncthreads();
+            if (tid == 0)
+                for (int w = 1; w < W; ++w) merge(redk[w], redi[w]);
         }
     }
-    if (lane == 0) a.ksel[g] = bi == kNoCandidate ? -1 : bi;
+    if (tid == 0) a.ksel[g] = bi == kNoCandidate ? -1 : bi;
 }
 
 }  // namespace
@@ -193,10 +221,20 @@ hipError_t launch_sample(const kb_batch& b, const SampleCall& c, hipStream_t st)
     // a batch of short searches only: a wave per search, one launch; a batch of several
     // searches with longer ones among them: both kernels, each skipping the other's searches
     // (an empty launch of the other kernel costs a few microseconds)
+    const auto workgroup = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)b.G), dim3((unsigned)threads), 0, st, a);
+        return hipGetLastError();
+    };
+    a.mixed = 0;
+    if (b.Nmax > kShortSearch && b.Nmax <= kWideN) {
+        if (b.Nmax > (b.G <= kWideFewG ? kWideFewN : kGroupN) && b.G <= kWideMaxG) return workgroup(sample_search<1024>, 1024);
+        if (b.Nmax <= kGroupN && (b.G <= kGroupMaxG || b.N >= (int64_t)kGroupMeanN * b.G))
+            return workgroup(sample_search<kThreads>, kThreads);
+    }
     a.short_n = sample_short(b);
     a.mixed = b.Nmax > a.short_n && b.G > 1;
     if ((b.Nmax <= a.short_n || a.mixed) && b.G > 0) {
-        hipLaunchKernelGGL(sample_wave, dim3((unsigned)((b.G + kWaves - 1) / kWaves)), dim3(kThreads), 0, st, a);
+        hipLaunchKernelGGL(sample_search<kWave>, dim3((unsigned)((b.G + kWaves - 1) / kWaves)), dim3(kThreads), 0, st, a);
         if (!a.mixed) return hipGetLastError();
     }
     const unsigned ranges = (unsigned)((b.N + kSampleRange - 1) / kSampleRange);

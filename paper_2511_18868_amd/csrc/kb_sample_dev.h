@@ -29,7 +29,7 @@ struct SampleArgs {
     double* slot_key;          // [2 * ranges]  left slot of range r at 2r, right slot at 2r+1
     int32_t* slot_idx;         // [2 * ranges]
     int short_n;               // sample_short() of the batch
-    int mixed;                 // 1: searches of at most short_n candidates go to sample_wave, longer
+    int mixed;                 // 1: searches of at most short_n candidates go to the wave form of sample_search, longer
                                //    ones to the range kernels, in the same call
 };
 
