@@ -129,6 +129,8 @@ static kb_status do_cluster(const kb_batch* b, const float* X, const float* cent
                             int32_t iters, int scorer, int stop_early, int32_t* assign, float* cent,
                             int32_t* counts, float* objective, void* ws, hipStream_t st,
                             bool reclustering = false, bool* ordered = nullptr) {
+    // ordered: in, the order (and the offsets beside it) is in ws from an earlier clustering of this call;
+    // out, it is there now
     if (scorer < KB_SCORER_DEFAULT || scorer > KB_SCORER_MATRIX_EVERY) return KB_EINVAL;
     if (stop_early != 0 && stop_early != 1) return KB_EINVAL;
     // (a re-clustering may continue from the centroids it overwrites: every kernel
@@ -139,11 +141,12 @@ static kb_status do_cluster(const kb_batch* b, const float* X, const float* cent
     WsLayout w = ws_layout(*b);
     char* base = (char*)ws;
     int32_t* order = (int32_t*)(base + w.order);
-    // (a lone search on the one-workgroup path needs neither a scheduling order nor
+    // (few searches on the one-workgroup path need neither a scheduling order nor
     // tile offsets, and neither does a batch that runs one wave per search: one launch less)
-    const bool need_order = (b->G > 1 && !cluster_wave_per_search(*b, scorer)) || w.use_big;
-    if (ordered) *ordered = need_order;
-    if (need_order) {
+    const bool need_order = (order_matters(*b) && !cluster_wave_per_search(*b, scorer)) || w.use_big;
+    const bool have = ordered && *ordered;
+    if (ordered) *ordered = have || need_order;
+    if (need_order && !have) {
         hipError_t e = launch_order(*b, order, (int32_t*)(base + w.tile_off),
                                     w.use_big ? (int32_t*)(base + w.big.chunk_off) : nullptr, st);
         if (e != hipSuccess) return KB_EDEVICE;
@@ -151,7 +154,7 @@ static kb_status do_cluster(const kb_batch* b, const float* X, const float* cent
     ClusterCall c;
     c.X = X; c.cent_init = cent_init; c.iters = iters; c.assign = assign;
     c.cent_out = cent; c.counts = counts; c.objective = objective;
-    c.a_new = (int32_t*)(base + w.a_new); c.order = order;
+    c.a_new = (int32_t*)(base + w.a_new); c.order = order_matters(*b) ? order : nullptr;
     c.tile_off = (const int32_t*)(base + w.tile_off); c.xn = (float*)(base + w.xn);
     c.lim = (float*)(base + w.geo_d2);      // (the representative pass uses this array at other times)
     c.split = (void*)(base + w.split); c.max_tiles = (int64_t)w.max_tiles;
@@ -220,14 +223,15 @@ static kb_status do_ucb(const kb_batch* b, const kb_params* p, const int32_t* as
     kb_status s = check_ucb(b, p, assign, alive, bound, visits, rsum, t, Ncs, mu, ucb, sel,
                             optional_mask_inputs);
     if (s != KB_OK) return s;
-    if (!have_order && b->G > 1 && !ucb_wave_per_search(*b)) {
+    if (!have_order && order_matters(*b) && !ucb_wave_per_search(*b)) {
         hipError_t e = launch_order(*b, u.order, u.tile_off, nullptr, st);
         if (e != hipSuccess) return KB_EDEVICE;
     }
     UcbCall c;
     c.assign = assign; c.alive = alive; c.bound = bound; c.M = M; c.visits = visits; c.rsum = rsum;
     c.t = t; c.c = p->c; c.prior_n = p->prior_n; c.prior_mu = p->prior_mu;
-    c.Ncs = Ncs; c.mu = mu; c.ucb = ucb; c.sel = sel; c.order = u.order;
+    c.Ncs = Ncs; c.mu = mu; c.ucb = ucb; c.sel = sel;
+    c.order = order_matters(*b) ? u.order : nullptr;
     c.gN = u.gN; c.gR = u.gR; c.gnalive = u.gnalive; c.gkmin = u.gkmin;
     c.chunked = u.chunked ? 1 : 0;
     c.keep_tables = tables == 1; c.from_tables = tables == 2;
@@ -439,8 +443,8 @@ static kb_status do_seed(const kb_batch* batch, const float* X, float* cent, int
     char* base = (char*)ws;
     int32_t* order = (int32_t*)(base + w.order);
     hipStream_t st = (hipStream_t)stream;
-    hipError_t e = launch_order(*batch, order, (int32_t*)(base + w.tile_off), nullptr, st);
-    if (e != hipSuccess) return KB_EDEVICE;
+    if (!order_matters(*batch)) order = nullptr;
+    else if (launch_order(*batch, order, (int32_t*)(base + w.tile_off), nullptr, st) != hipSuccess) return KB_EDEVICE;
     return dev(launch_seed(*batch, X, cent, pick, (double*)(base + w.geo_d2), (double*)(base + w.seed_key),
                            (int32_t*)(base + w.seed_idx), order, dsquared, seed, draw0, st));
 }
@@ -554,11 +558,12 @@ kb_status kb_round(const kb_batch* batch, const kb_params* params, const kb_roun
     }
     s = do_prune(batch, params, io->flops, io->bytes, io->incumbent, io->bound, io->alive, st);
     if (s != KB_OK) return s;
+    bool ordered = false;
     s = do_cluster(batch, io->X, nullptr, params->iters, params->scorer, params->stop_early, io->assign, io->cent,
-                   io->counts, io->objective, ws, st);
+                   io->counts, io->objective, ws, st, false, &ordered);
     if (s != KB_OK) return s;
     return do_ucb(batch, params, io->assign, io->alive, io->bound, io->visits, io->rsum, io->t,
-                  io->Ncs, io->mu, io->ucb, io->sel, ucb_scratch_in_ws(batch, ws), true, st);
+                  io->Ncs, io->mu, io->ucb, io->sel, ucb_scratch_in_ws(batch, ws), ordered, st);
 }
 
 kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_iterate_params* ip,
@@ -597,7 +602,7 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
     char* base = (char*)ws;
     const size_t G = (size_t)batch->G;
     bool have_order = false;        // the scheduling order in ws, computed by the first stage that needs it
-    bool ordered = false;
+    bool ordered = false;           // ... by a clustering, with its offsets
     // The cluster-arm tables (visit counts and fixed-point reward sums of the alive
     // members of every cluster) are aggregated from the per-candidate history in the
     // first round and after every re-clustering and advanced by the updates in between:
@@ -655,7 +660,7 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
             uc.assign = io->assign; uc.alive = io->alive; uc.M = io->M; uc.visits = io->visits;
             uc.rsum = io->rsum; uc.t = io->t; uc.c = params->c; uc.prior_n = params->prior_n;
             uc.prior_mu = params->prior_mu; uc.Ncs = io->Ncs; uc.mu = io->mu; uc.ucb = io->ucb;
-            uc.order = us.order;
+            uc.order = rounds_need_order(*batch) ? us.order : nullptr;
             RoundsCall rc;
             rc.rounds = n; rc.reward = io->reward + (size_t)r * G; rc.ok = io->ok + (size_t)r * G;
             rc.visits = io->visits; rc.rsum = io->rsum; rc.t = io->t; rc.sel_log = sel; rc.ksel_log = ksel;

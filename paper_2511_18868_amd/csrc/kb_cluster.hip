@@ -27,7 +27,7 @@ static ClusterArgs cluster_args(const kb_batch& b, const ClusterCall& c) {
     a.seg_off = b.seg_off; a.koff = b.koff; a.X = c.X; a.cent_init = c.cent_init;
     a.iters = c.iters; a.early_exit = c.stop_early ? 1 : 0; a.assign = c.assign; a.cent_out = c.cent_out;
     a.counts = c.counts; a.objective = c.objective; a.a_new = c.a_new;
-    a.order = b.G > 1 ? c.order : nullptr;       // (one search: the order is the identity and was not computed)
+    a.order = c.order;
     a.use_bounds = c.scorer != 2;
     a.guard = c.guard;
     a.mixed = c.mixed;

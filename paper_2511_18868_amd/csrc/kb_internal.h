@@ -48,6 +48,11 @@ inline bool cluster_uses_big(const kb_batch& b) { return b.Kmax > kOneWgMaxK || 
 // (limit_n: one_wg_limit_n of the batch)
 __host__ __device__ inline bool search_is_big(int ng, int K, int limit_n) { return K > kOneWgMaxK || ng > limit_n; }
 
+// Up to one search per compute unit all searches of a batch run at once: no scheduling order
+// (longest first) is computed or read then, one launch less.
+constexpr int kResidentSearches = 256;
+inline bool order_matters(const kb_batch& b) { return b.G > kResidentSearches; }
+
 struct WsLayout {
     size_t a_new;   // int32 [N]     proposed assignment of the current step (bit 31: needs exact re-evaluation)
     size_t order;   // int32 [G]     searches sorted by decreasing work, for longest-first scheduling

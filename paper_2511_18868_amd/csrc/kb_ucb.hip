@@ -686,7 +686,7 @@ bool rounds_in_one_launch(const kb_batch& b) {
     return b.G > 0 && b.Nmax <= kUcbLong && b.Nmax <= members * (b.Kmax > 0 ? b.Kmax : 1) &&
            rounds_lds(b) + 1024 <= 160 * 1024;
 }
-bool rounds_need_order(const kb_batch& b) { return b.G > 1 && !rounds_wave_per_search(b); }
+bool rounds_need_order(const kb_batch& b) { return order_matters(b) && !rounds_wave_per_search(b); }
 
 // Batches of up to two searches per compute unit give every search 1024 threads, larger ones 256.
 constexpr int kRoundsWideMaxG = 512;

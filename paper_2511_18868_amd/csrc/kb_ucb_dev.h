@@ -178,7 +178,7 @@ inline UcbArgs make_ucb_args(const kb_batch& b, const UcbCall& c) {
     a.bound = c.bound; a.M = c.M; a.visits = c.visits; a.rsum = c.rsum; a.t = c.t; a.c = c.c;
     a.prior_n = c.prior_n; a.prior_mu = c.prior_mu; a.Ncs = c.Ncs; a.mu = c.mu; a.ucb = c.ucb;
     a.sel = c.sel;
-    a.order = b.G > 1 ? c.order : nullptr;       // (one search: the order is the identity and was not computed)
+    a.order = c.order;
     a.gN = c.gN; a.gR = c.gR; a.gnalive = c.gnalive; a.gkmin = c.gkmin; a.Nll = b.N;
     a.mixed = 0;
     a.keep = 0;

@@ -99,3 +99,21 @@ def test_iterations_in_one_launch_equal_the_launches_one_by_one(kb, shape, varia
     for k in got[0]:
         np.testing.assert_array_equal(got[0][k].view(np.uint8), got[1][k].view(np.uint8), err_msg=k)
     assert (got[0]["ksel_log"] >= 0).any()
+
+
+@pytest.mark.parametrize("G", [100, 300])
+def test_round_of_short_searches_with_many_strategies(kb, G):
+    """Strategy counts whose tables leave no room for four searches in a workgroup: clustering by a wave
+    per search, selection by a workgroup each, with a workspace that holds anything."""
+    import torch
+    b = synth.config5(G=G, nmin=1, nmax=60, D=6, S=110, iters=5, kcap=16, kdiv=2, seed=31)
+    outs = ("bound", "alive", "assign", "cent", "counts", "Ncs", "mu", "ucb", "sel")
+    one, three = kb.DeviceBatch(b), kb.DeviceBatch(b)
+    one.ws.fill_(0x5a)
+    one.round()
+    three.prune()
+    three.cluster()
+    three.ucb_select()
+    torch.cuda.synchronize()
+    for k in outs:
+        np.testing.assert_array_equal(one.host(k).view(np.uint8), three.host(k).view(np.uint8), err_msg=k)
