@@ -133,7 +133,7 @@ __global__ void __launch_bounds__(NT) ucb_kernel(UcbArgs a) {
         if (tid < 3) a.sel[(size_t)g * 3 + tid] = -1;
         return;
     }
-    if (a.mixed && ng > kUcbLong) return;     // the range kernels take this search
+    if (a.mixed && ng > a.longer) return;     // the range kernels take this search
     const int KS = K * S;
 
     double* redv = reinterpret_cast<double*>(smem);                                      // [waves]
@@ -473,7 +473,6 @@ __global__ void __launch_bounds__(kThreads) rounds_wave(RoundsArgs r, int per) {
 
 // ---- searches too long for one workgroup: partial tables per candidate range,
 // ---- merged in global memory with integer atomics (still order-independent)
-constexpr int kUcbRange = 8192;
 
 __global__ void __launch_bounds__(kThreads) ucb_zero(UcbArgs a) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -487,9 +486,9 @@ __global__ void __launch_bounds__(kThreads) ucb_partial(UcbArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
     const int S = a.S;
-    const int64_t r0 = (int64_t)blockIdx.x * kUcbRange;
+    const int64_t r0 = (int64_t)blockIdx.x * a.range;
     if (r0 >= a.N) return;
-    const int64_t r1 = r0 + kUcbRange < a.N ? r0 + kUcbRange : a.N;
+    const int64_t r1 = r0 + a.range < a.N ? r0 + a.range : a.N;
     unsigned long long* R = reinterpret_cast<unsigned long long*>(smem + kUcbHead);
     unsigned long long* kmin = R + (size_t)a.Kmax * S;
     unsigned* Ncnt = reinterpret_cast<unsigned*>(kmin + a.Kmax);
@@ -501,7 +500,7 @@ __global__ void __launch_bounds__(kThreads) ucb_partial(UcbArgs a) {
         if ((int64_t)a.seg_off[mid] <= r0) lo = mid; else hi = mid;
     }
     const auto mine = [&](int n0, int ng, int k0, int K) {
-        return n0 >= r1 || (ng > 0 && K > 0 && !(a.mixed && ng <= kUcbLong));
+        return n0 >= r1 || (ng > 0 && K > 0 && !(a.mixed && ng <= a.longer));
     };
     for (int g = lo; (g = next_search(a.seg_off, a.koff, g, a.G, a.N, a.Ksum, mine)) < a.G; ++g) {
         int n0, ng, k0, K;
@@ -509,7 +508,7 @@ __global__ void __launch_bounds__(kThreads) ucb_partial(UcbArgs a) {
         if (K > a.Kmax) K = a.Kmax;
         if (n0 >= r1) break;
         if (ng <= 0 || K <= 0) continue;
-        if (a.mixed && ng <= kUcbLong) continue;     // one workgroup takes this search whole
+        if (a.mixed && ng <= a.longer) continue;     // one workgroup takes this search whole
         const int64_t q0 = r0 > n0 ? r0 : n0;
         const int64_t q1 = r1 < (int64_t)n0 + ng ? r1 : (int64_t)n0 + ng;
         if (q0 >= q1) continue;
@@ -540,7 +539,7 @@ __global__ void __launch_bounds__(kThreads) ucb_final(UcbArgs a) {
     int n0, ng, k0, K;
     search_bounds(a.seg_off, a.koff, g, a.N, a.Ksum, n0, ng, k0, K);
     if (K > a.Kmax) K = a.Kmax;
-    if (a.mixed && ng <= kUcbLong) return;       // (uniform) done by ucb_kernel, empty searches included
+    if (a.mixed && ng <= a.longer) return;       // (uniform) done by ucb_kernel, empty searches included
     if (ng <= 0 || K <= 0) {
         if (threadIdx.x < 3) a.sel[(size_t)g * 3 + threadIdx.x] = -1;
         return;
@@ -623,6 +622,14 @@ static bool ucb_wide(const kb_batch& b) {
     return b.G <= kUcbWideFewG || (b.G <= kUcbWideMaxG && b.Nmax >= kUcbWideMinN);
 }
 
+// Long searches: ranges that give every compute unit a workgroup, of 512 candidates at least and not
+// below a quarter of a search's cluster arms, whose tables every range adds to the global ones.  (Ranges
+// of 8192 / these, the kernels of a call, us: one search of 20000, S = 32, K = 64 164 / 28, S = 3, K = 4 74 / 16,
+// of 200000, S = 8, K = 100 57 / 22, three of 60000, S = 32, K = 64 174 / 45, one of 2^20, S = 4, K = 256 37 / 30.)
+// In a batch of a few searches the ranges pay from 6000 candidates on (one workgroup of 1024 threads /
+// ranges: one of 16000 50 / 17.6, of 8000 18.0 / 15.4, of 4096 16.0 / 18.0).
+constexpr int kUcbFewG = 8, kUcbFewN = 6000, kUcbRanges = 256, kUcbRangeMin = 512, kUcbRangeMax = 8192;
+
 hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
     UcbArgs a = make_ucb_args(b, c);
     const size_t lds = kUcbHead + (size_t)a.Kmax * b.S * 12 + (size_t)a.Kmax * 12;
@@ -634,8 +641,15 @@ hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
     }
     if (c.keep_tables && !c.gN) return hipErrorInvalidValue;
     a.keep = c.keep_tables ? 1 : 0;
-    if (c.chunked) {
+    // (the tables in global memory are there unless the caller has none to give)
+    const bool few = c.gN && b.G <= kUcbFewG && b.Nmax > kUcbFewN;
+    if (c.chunked || few) {
         if (!c.gN) return hipErrorInvalidValue;
+        a.longer = few ? kUcbFewN : kUcbLong;
+        a.range = kUcbRangeMin;
+        while (a.range < kUcbRangeMax &&
+               (b.N > (int64_t)kUcbRanges * a.range || (int64_t)a.Kmax * b.S > 4 * a.range))
+            a.range *= 2;
         // long searches: candidate ranges -> partial tables -> global tables -> scores;
         // in a batch of several searches the short ones get a workgroup each as usual
         const size_t items = (size_t)b.Ksum * b.S;
@@ -648,7 +662,7 @@ hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
             const hipError_t e = launch_search_kernel(a, ucb_wide(b), lds, st);
             if (e != hipSuccess) return e;
         }
-        const unsigned ranges = (unsigned)((b.N + kUcbRange - 1) / kUcbRange);
+        const unsigned ranges = (unsigned)((b.N + a.range - 1) / a.range);
         if (ranges) {
             const hipError_t e = launch_range_kernel(a, ranges, lds, st);
             if (e != hipSuccess) return e;

@@ -29,7 +29,9 @@ struct UcbArgs {
     unsigned* gnalive;          // [Ksum]
     unsigned long long* gkmin;  // [Ksum]
     int64_t Nll;
-    int mixed;                  // 1: searches of up to kUcbLong candidates go to ucb_kernel, longer ones to the
+    int longer;                 // searches of more candidates than this are cut into ranges,
+    int range;                  // so many candidates each
+    int mixed;                  // 1: searches of up to `longer` candidates go to ucb_kernel, the others to the
                                 //    range kernels, in the same call
     int keep;                   // 1: ucb_kernel leaves a copy of its LDS tables in the global ones
 };
@@ -180,7 +182,7 @@ inline UcbArgs make_ucb_args(const kb_batch& b, const UcbCall& c) {
     a.sel = c.sel;
     a.order = c.order;
     a.gN = c.gN; a.gR = c.gR; a.gnalive = c.gnalive; a.gkmin = c.gkmin; a.Nll = b.N;
-    a.mixed = 0;
+    a.mixed = 0; a.longer = 0; a.range = 0;
     a.keep = 0;
     return a;
 }
