@@ -57,16 +57,18 @@ static ClusterArgs cluster_args(const kb_batch& b, const ClusterCall& c) {
 //   one of 2000 and G of 100, D = 32:   800: 279 / 229 (183 / 183)   1000: 235 / 244 (168 / 215)
 //   one of 600 and G of 100, D = 48:    300: 133 / 135   600: 113 / 190   1000: 143 / 262
 // Short searches gain less from more threads (a step is barriers and reductions), hence
-// the lower line for them, and so does a single step (64-4096, N/Nmax 242: 123 / 119, 358:
-// 154 / 179).  Rows of no whole 16-byte pieces cost the narrow shape more, hence their
-// higher line in G.  Batches of long searches only (2048 rows or more on average) are 13-20 %
-// faster in the wide shape however many they are.
+// the lower line for them, and so does a single step, whose narrow form holds more searches per
+// unit (64-4096, N/Nmax 148: 112 / 79, 182: 114 / 93, 227: 117 / 110, 340: 142 / 179).  Rows of no
+// whole 16-byte pieces cost the narrow shape more, hence their higher line in G.  Batches of long searches
+// only (2048 rows or more on average) are 13-20 % faster in the wide shape however many they are -
+// but for a single step, where they have the line of the long ones only (3000-8000, N/Nmax 368: 289 /
+// 258; 2048-2500, 543: 122 / 138, 2700: 434 / 547).
 // In a batch that holds searches of the multi-workgroup path as well, the longest is one of
 // those and the others' longest is not known: four times their average is taken, the ratio
 // of lengths that are spread evenly over their logarithm (4000 searches of 64-4096 rows
 // beside one of 100000, by the longest of all: 3666 / 3776).
 constexpr int kWideLoad = 400, kWideLoadStep = 250, kWideLoadShort = 200, kWideShortN = 1024;
-static bool wide_shape(const kb_batch& b, int iters, bool mixed) {
+static bool wide_shape(const kb_batch& b, bool one, bool mixed) {
     if (b.G <= kWideMaxG) return true;
     int64_t N = b.N, longest = b.Nmax;
     if (mixed) {
@@ -74,9 +76,10 @@ static bool wide_shape(const kb_batch& b, int iters, bool mixed) {
         longest = 4 * N / b.G;
         if (longest > one_wg_limit_n(b)) longest = one_wg_limit_n(b);
     }
-    const int load = longest < kWideShortN ? kWideLoadShort : (iters == 1 ? kWideLoadStep : kWideLoad);
+    const bool all_long = N >= (int64_t)2048 * b.G;
+    const int load = longest < kWideShortN ? kWideLoadShort : (one && !all_long ? kWideLoadStep : kWideLoad);
     const int many = (b.D & 3) == 0 ? 9 : 11;
-    return (N <= load * longest && 20 * (int64_t)b.G <= many * longest) || N >= (int64_t)2048 * b.G;
+    return (N <= load * longest && 20 * (int64_t)b.G <= many * longest) || (all_long && !one);
 }
 
 // Workgroups of a kernel that a compute unit holds by their LDS, which is handed out in pieces of 1280 bytes.
@@ -95,14 +98,17 @@ hipError_t launch_cluster(const kb_batch& b, const ClusterCall& c, hipStream_t s
     f.mt = a.Kmax <= 32 ? 1 : (a.Kmax <= 64 ? 2 : 0);
     if (c.scorer == 1) f.mt = 0;
     f.rows = (b.D & 3) == 0 ? kRowsWhole : b.D >= 4 ? kRowsRagged : kRowsTiny;
-    f.wide = wide_shape(b, c.iters, c.mixed != 0) && lds(true, false) <= kMaxLds;
+    const bool one = f.mt > 0 && c.iters == 1;
+    f.wide = wide_shape(b, one, c.mixed != 0) && lds(true, false) <= kMaxLds;
     // The candidates' states stay in LDS where that costs no resident workgroup: a step of a short
     // search then has a trip to L2 less (a round of one search of 4096 rows 243 -> 235 us, of 1024 of 512
     // 171 -> 170, ten iterations of 512 searches of 64-4096 1283 -> 1270).
     const int most = f.wide ? 1 : narrow_workgroups_per_cu(ds, f.mt);
     const auto fits = [&](bool state) { const int n = resident(lds(f.wide, state)); return n < most ? n : most; };
     f.state = f.mt > 0 && c.iters > 1 && lds(f.wide, true) <= kMaxLds && fits(true) >= fits(false);
-    f.lds = lds(f.wide, f.state);
+    f.one = one && !f.wide;
+    f.lds = f.one ? lds_layout(a.Kmax, b.D, 16 * ds + 4, a.Nmax, kThreadsNarrow / kWave, false, true).total
+                  : lds(f.wide, f.state);
     if (f.lds > kMaxLds) return hipErrorInvalidValue;
     switch (ds) {
         case 1: return launch_lloyd<1>(a, f, st);

@@ -74,6 +74,7 @@ struct LloydForm {
     bool wide;         // 768 threads per search instead of 256
     int rows;          // kRowsWhole, kRowsRagged, kRowsTiny
     bool state;        // the candidates' states in LDS
+    bool one;          // the form for a single step
     size_t lds;
 };
 // DS: feature K-steps of 16
@@ -102,15 +103,19 @@ constexpr int kQueue = 128;        // per wave: candidates waiting to be scored 
 struct Lds {
     size_t sums, cent, cn, cnt, dirty, delta, flist, aop, thr, queue, lim, total;
 };
-// (state: the candidates' states are kept here as well)
-__host__ __device__ inline Lds lds_layout(int Kmax, int D, int DP, int Nmax, int waves, bool state) {
+// (state: the candidates' states are kept here as well; one: the form for a single step, Kmax <= 64, in
+// which the centroids take the operands' place once the rows are scored - before that they pass through
+// the sums' - and which needs neither drift limits nor queues)
+__host__ __device__ inline Lds lds_layout(int Kmax, int D, int DP, int Nmax, int waves, bool state,
+                                          bool one = false) {
     const int SP = D | 1;   // odd row stride: clusters spread over the LDS banks
     Lds l;
     // reduction scratch: two slots of one double per wave, then the count of listed candidates
     size_t off = (size_t)waves * 16 + 64;
-    l.sums = off; off += (size_t)Kmax * SP * 8;
+    const size_t rows = (size_t)Kmax * DP * 4, ops = (size_t)((Kmax + 31) / 32) * ((DP - 4) / 16) * 2 * 64 * 16;
+    l.sums = off; off += one && rows > (size_t)Kmax * SP * 8 ? rows : (size_t)Kmax * SP * 8;
     off = (off + 15) & ~(size_t)15;
-    l.cent = off; off += (size_t)Kmax * DP * 4;
+    l.cent = off; off += one ? (rows > ops ? rows : ops) : rows;
     l.cn = off;   off += (size_t)((Kmax + 31) & ~31) * 4;   // padded to whole centroid tiles
     l.cnt = off;  off += (size_t)Kmax * 4;
     l.dirty = off; off += ((size_t)Kmax + 15) & ~(size_t)15;   // "membership changed" flags, one byte each
@@ -118,11 +123,12 @@ __host__ __device__ inline Lds lds_layout(int Kmax, int D, int DP, int Nmax, int
     l.flist = off; off += (size_t)kFlagCap * 2;          // 16-bit candidate numbers
     off = (off + 15) & ~(size_t)15;
     // centroid operands of the matrix-core scorer (only when Kmax <= 64)
-    l.aop = off;  if (Kmax <= 64) off += (size_t)((Kmax + 31) / 32) * ((DP - 4) / 16) * 2 * 64 * 16;
+    l.aop = one ? l.cent : off;
+    if (Kmax <= 64 && !one) off += ops;
     // one drift limit per tile of 32 candidates
-    l.thr = off; if (Kmax <= 64) off += ((((size_t)Nmax + 31) / 32) * 4 + 15) & ~(size_t)15;
+    l.thr = off; if (Kmax <= 64 && !one) off += ((((size_t)Nmax + 31) / 32) * 4 + 15) & ~(size_t)15;
     // per wave: the candidates waiting to be scored
-    l.queue = off; if (Kmax <= 64) off += (size_t)waves * kQueue * 2;
+    l.queue = off; if (Kmax <= 64 && !one) off += (size_t)waves * kQueue * 2;
     off = (off + 7) & ~(size_t)7;
     l.lim = off; if (state) off += (size_t)Nmax * 8;
     l.total = off;
@@ -135,6 +141,12 @@ __host__ __device__ inline Lds lds_layout(int Kmax, int D, int DP, int Nmax, int
 // (measured; five cost more in spills than they gain, and with two centroid tiles in
 // registers four were 4 % slower).
 constexpr int narrow_workgroups_per_cu(int DS, int MT) { return (MT == 1 && DS <= 3) ? 4 : 3; }
+// A call of a single step has no packed scorer and no states and so needs fewer registers, and less LDS
+// (lds_layout): one workgroup more per unit in the 256-thread shape, which covers more of the latency and
+// lets vector, LDS and memory work of different searches overlap (3917962 rows in 4096 searches of 64-4096,
+// K <= 64, D = 48: 291 -> 252 us = 3.3 TB/s, D = 64 476 -> 389; K <= 32: 287 -> 250, with four 261; 8000
+// searches of 64-300: 225 -> 180, K <= 32 218 -> 159).
+constexpr int step_workgroups_per_cu(int DS, int MT) { return MT == 1 ? (DS <= 3 ? 5 : 4) : DS <= 3 ? 4 : 3; }
 
 namespace {
 
@@ -784,7 +796,7 @@ __device__ __forceinline__ int score_packed(const ClusterArgs& a, const float* _
 // the fixed-point sums from the same registers; |x|^2 and the drift limit of every
 // candidate go to the workspace for the steps that follow.  Returns max |x| over the rows this thread saw in
 // `am_out`, which the caller checks against the estimate the scale was taken from.
-template <int DS, int MT, int NT, int ROWS>
+template <int DS, int MT, int NT, int ROWS, bool ONE>
 __device__ __forceinline__ int score_first(const ClusterArgs& a, const float* __restrict__ Xg,
                                            int n0, int ng, int K, int D,
                                            int SP, const float* cn, float cnmax, int fsh,
@@ -799,7 +811,7 @@ __device__ __forceinline__ int score_first(const ClusterArgs& a, const float* __
     const int ntiles = (ng + 31) >> 5;
     // |x|^2 and the limits serve the steps that follow: a call of one step
     // (kb_cluster_step) stores none of them
-    const bool later = a.iters > 1;
+    const bool later = !ONE && a.iters > 1;
 
     // this lane's 8 features of every 16-feature step of row `tile * 32 + m`
     auto load_rows = [&](int tile, float4 (&r)[DS][2]) {
@@ -1081,7 +1093,7 @@ __device__ __forceinline__ int exact_nearest(float xv, const float* cent, int K,
 // One wave per listed candidate, lanes over centroids; the next candidate's row
 // is requested before the current one is worked on.  If the nearest centroid differs
 // from the recorded cluster, the row moves between the running sums.
-template <int DS, int NT>
+template <int DS, int NT, bool ONE>
 __device__ __forceinline__ int refine_listed(const ClusterArgs& a, const float* __restrict__ Xg,
                                              int n0, int n, const unsigned short* flist, int K, int D, int DP,
                                              int SP, const float* cent, int fsh,
@@ -1121,8 +1133,8 @@ __device__ __forceinline__ int refine_listed(const ClusterArgs& a, const float* 
             // the slack is the difference of the bounds, rounded down; limits are
             // non-negative floats, which order like their bit patterns
             const float sl = fmaxf((lbd - ub) * 0.9999995f, 0.f);
-            lim[p].x = pack_limit(a.use_bounds ? tile_limit(Tb, sl) : 0.f, bj);
-            if (a.use_bounds)
+            if constexpr (!ONE) lim[p].x = pack_limit(a.use_bounds ? tile_limit(Tb, sl) : 0.f, bj);
+            if (!ONE && a.use_bounds)
                 atomicMin(reinterpret_cast<unsigned*>(&thr[p >> 5]), __float_as_uint(tile_limit(drift, sl)));
             a.a_new[(size_t)n0 + p] = bj;          // no longer waiting for the exact pass
         }
@@ -1202,8 +1214,9 @@ __device__ __forceinline__ int update(const ClusterArgs& a, const float* __restr
 // registers by the matrix-core scorer, MT = 0 selects the vector-ALU scorer.
 // ROWS: how the matrix-core scorers fetch rows (a compile-time choice, so the loops hold
 // one form only).
-template <int DS, int MT, int NT, int ROWS = kRowsWhole, bool STATE = false>
-__global__ void __launch_bounds__(NT, NT == kThreadsNarrow ? narrow_workgroups_per_cu(DS, MT) : 1)
+template <int DS, int MT, int NT, int ROWS = kRowsWhole, bool STATE = false, bool ONE = false>
+__global__ void __launch_bounds__(NT, ONE ? step_workgroups_per_cu(DS, MT)
+                                          : NT == kThreadsNarrow ? narrow_workgroups_per_cu(DS, MT) : 1)
 cluster_fused_kernel(ClusterArgs a) {
     constexpr int kThreads = NT, kWaves = NT / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1226,7 +1239,7 @@ cluster_fused_kernel(ClusterArgs a) {
     }
     if (a.guard && ng < 2 * K) return;      // too few candidates to re-cluster: nothing is touched
 
-    const Lds L = lds_layout(a.Kmax, D, DP, a.Nmax, kWaves, STATE);
+    const Lds L = lds_layout(a.Kmax, D, DP, a.Nmax, kWaves, STATE, ONE);
     double* red = reinterpret_cast<double*>(smem);
     long long* sums = reinterpret_cast<long long*>(smem + L.sums);   // [Kmax][SP]
     float* cent = reinterpret_cast<float*>(smem + L.cent);           // [Kmax][DP]
@@ -1261,15 +1274,23 @@ cluster_fused_kernel(ClusterArgs a) {
             for (int i = tid; i < srows * D; i += kThreads) am = fmaxf(am, fabsf(Xg[i]));
         }
     }
-    for (int idx = tid; idx < K * DP; idx += kThreads) {
-        const int j = idx / DP, d = idx - j * DP;
-        float v = 0.f;
-        if (d < D)
-            v = a.cent_init ? a.cent_init[(size_t)(k0 + j) * D + d]
-                            : Xg[(size_t)(j < ng ? j : ng - 1) * D + d];
-        cent[idx] = v;
-    }
-    for (int idx = tid; idx < K * SP; idx += kThreads) sums[idx] = 0;
+    auto initial_centroids = [&](float* to) __attribute__((always_inline)) {
+        for (int idx = tid; idx < K * DP; idx += kThreads) {
+            const int j = idx / DP, d = idx - j * DP;
+            float v = 0.f;
+            if (d < D)
+                v = a.cent_init ? a.cent_init[(size_t)(k0 + j) * D + d]
+                                : Xg[(size_t)(j < ng ? j : ng - 1) * D + d];
+            to[idx] = v;
+        }
+    };
+    auto clear_sums = [&]() __attribute__((always_inline)) {
+        for (int idx = tid; idx < K * SP; idx += kThreads) sums[idx] = 0;
+    };
+    // (single step: through the sums' place, see lds_layout)
+    float* cent0 = ONE ? reinterpret_cast<float*>(sums) : cent;
+    initial_centroids(cent0);
+    if constexpr (!ONE) clear_sums();
     for (int j = tid; j < K; j += kThreads) { cnt[j] = 0; dirty[j] = 0; delta[j] = 0.f; }
     for (int j = K + tid; j < ((a.Kmax + 31) & ~31); j += kThreads) cn[j] = kBig;
     if (tid == 0) *nflag = 0;
@@ -1318,7 +1339,7 @@ cluster_fused_kernel(ClusterArgs a) {
     double inv = ldexp(1.0, -sh);
 
     // |c_j|^2, their maximum and the matrix-core operands of the initial centroids
-    float cm = renew_rows<DS, (MT > 0), NT, renew_lanes(DS, MT, NT)>(cent, cn, aop, sums, cnt, dirty, delta, K, D, SP, inv, true, true);
+    float cm = renew_rows<DS, (MT > 0), NT, renew_lanes(DS, MT, NT)>(cent0, cn, aop, sums, cnt, dirty, delta, K, D, SP, inv, true, true);
     // largest |c_j|^2 of the search
     auto largest_norm = [&](float seen) __attribute__((always_inline)) {
         if constexpr (MT > 0) {
@@ -1330,6 +1351,10 @@ cluster_fused_kernel(ClusterArgs a) {
         }
     };
     cm = largest_norm(cm);
+    if constexpr (ONE) {
+        clear_sums();
+        __syncthreads();
+    }
 
     bool first = true;
     float drift = 0.f;          // cumulative (largest + second largest) centroid move, rounded up
@@ -1350,9 +1375,9 @@ cluster_fused_kernel(ClusterArgs a) {
 
         int st;
         if constexpr (MT > 0) {
-            if (first) {
+            if (ONE || first) {
                 float am_seen;
-                st = score_first<DS, MT, NT, ROWS>(a, Xg, n0, ng, K, D, SP, cn, cm, fsh, sums, cnt, nflag,
+                st = score_first<DS, MT, NT, ROWS, ONE>(a, Xg, n0, ng, K, D, SP, cn, cm, fsh, sums, cnt, nflag,
                                          flist, aop, dw, thr, lim, am_seen, tsq);
                 am_seen = block_max_f<kWaves>(am_seen, red, phase);
                 tsq = block_sum_d<kWaves>(tsq, red, phase);
@@ -1377,7 +1402,7 @@ cluster_fused_kernel(ClusterArgs a) {
                     }
                     __syncthreads();
                 }
-            } else
+            } else if constexpr (!ONE)
             st = score_packed<DS, MT, NT, ROWS>(a, Xg, n0, ng, K, D, DP, SP, cent, cn, cm, fsh, sums, cnt,
                                       nflag, flist, aop, dw, thr, lim, queue, drift, Tc);
         } else {
@@ -1388,11 +1413,15 @@ cluster_fused_kernel(ClusterArgs a) {
         // the exact pass says its counter)
         if (MT == 0 || a.early_exit) st = block_or_i<kWaves>(st, red, phase);
         else __syncthreads();
+        if constexpr (ONE) {
+            initial_centroids(cent);           // the operands have been read
+            __syncthreads();
+        }
         const int nf = MT > 0 ? *nflag : kFlagCap + 1;
         if (nf > 0) {
             int moved;
             if (nf <= kFlagCap) {
-                moved = refine_listed<DS, NT>(a, Xg, n0, nf, flist, K, D, DP, SP, cent, fsh, sums, cnt, dw,
+                moved = refine_listed<DS, NT, ONE>(a, Xg, n0, nf, flist, K, D, DP, SP, cent, fsh, sums, cnt, dw,
                                       thr, lim, drift, Tc);
             } else {
                 // the list overflowed (or the vector-ALU scorer ran): scan every candidate;
@@ -1499,7 +1528,7 @@ cluster_fused_kernel(ClusterArgs a) {
         // new centroids, and what the next step needs from them
         cm = renew_rows<DS, (MT > 0), NT, renew_lanes(DS, MT, NT)>(cent, cn, aop, sums, cnt, dirty, delta, K, D, SP, inv, false, !last);
         cm = largest_norm(cm);
-        if (last) break;
+        if (ONE || last) break;
     }
 
     for (int idx = tid; idx < K * D; idx += kThreads) {
@@ -1518,12 +1547,12 @@ hipError_t launch_one(Kernel kern, int threads, const ClusterArgs& a, size_t lds
     return hipGetLastError();
 }
 
-template <int DS, int MT, int NT, bool STATE>
+template <int DS, int MT, int NT, bool STATE, bool ONE = false>
 hipError_t launch_rows(const ClusterArgs& a, const LloydForm& f, hipStream_t st) {
-    if (f.rows == kRowsWhole) return launch_one(cluster_fused_kernel<DS, MT, NT, kRowsWhole, STATE>, NT, a, f.lds, st);
-    if (f.rows == kRowsRagged) return launch_one(cluster_fused_kernel<DS, MT, NT, kRowsRagged, STATE>, NT, a, f.lds, st);
+    if (f.rows == kRowsWhole) return launch_one(cluster_fused_kernel<DS, MT, NT, kRowsWhole, STATE, ONE>, NT, a, f.lds, st);
+    if (f.rows == kRowsRagged) return launch_one(cluster_fused_kernel<DS, MT, NT, kRowsRagged, STATE, ONE>, NT, a, f.lds, st);
     // (1 to 3 features: one K-step)
-    if constexpr (DS == 1) return launch_one(cluster_fused_kernel<1, MT, NT, kRowsTiny, STATE>, NT, a, f.lds, st);
+    if constexpr (DS == 1) return launch_one(cluster_fused_kernel<1, MT, NT, kRowsTiny, STATE, ONE>, NT, a, f.lds, st);
     else return hipErrorInvalidValue;
 }
 
@@ -1531,6 +1560,9 @@ template <int DS, int MT>
 hipError_t launch_matrix(const ClusterArgs& a, const LloydForm& f, hipStream_t st) {
     if (f.wide) return f.state ? launch_rows<DS, MT, kThreadsWide, true>(a, f, st)
                                : launch_rows<DS, MT, kThreadsWide, false>(a, f, st);
+    if constexpr (MT > 0) {
+        if (f.one) return launch_rows<DS, MT, kThreadsNarrow, false, true>(a, f, st);
+    }
     return f.state ? launch_rows<DS, MT, kThreadsNarrow, true>(a, f, st)
                    : launch_rows<DS, MT, kThreadsNarrow, false>(a, f, st);
 }
