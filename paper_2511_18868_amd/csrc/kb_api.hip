@@ -26,8 +26,8 @@ WsLayout ws_layout(const kb_batch& b) {
         w.big = big_ws_layout(b, off);
         off = w.big.end;
     }
-    // cluster-arm tables of the selection step in global memory: searches of more than
-    // 16384 candidates are aggregated there, and kb_iterate carries them from round to
+    // cluster-arm tables of the selection step in global memory: long searches are
+    // aggregated there, and kb_iterate carries them from round to
     // round
     w.ucb_chunked = b.Nmax > 16384;
     {

@@ -8,8 +8,8 @@
 namespace kb {
 
 constexpr int kWave = 64;
-constexpr int kGeoRange = 2048;      // candidates per workgroup of the representative / radius pass
-constexpr int kSampleRange = 4096;   // candidates per workgroup of the in-cluster draw
+constexpr int kGeoRange = 2048;      // most candidates per workgroup of the representative / radius pass
+constexpr int kSampleRange = 4096;   // candidates per workgroup of the in-cluster draw of long searches
 constexpr int kShortSearch = 256;    // a batch whose longest search has at most this many candidates runs
                                      // the selection and the representative pass one wave per search
 constexpr int kTilesPerChunk = 64;   // tiles of 32 candidates per workgroup of the multi-workgroup clustering path
@@ -60,9 +60,8 @@ struct WsLayout {
     size_t tile_off;// int32 [G+1]   prefix sum of ceil(N_g / 32): first 32-candidate tile of each search
     size_t xn;      // float [N]     |x_k|^2 of every candidate (multi-workgroup path)
     size_t split;   // bf16          feature rows split into bf16 (hi, mid) pieces, 4 * Dpad bytes per
-                    //               candidate: [candidate][16-feature step][half][hi|mid][8] on the
-                    //               one-workgroup path, [tile][16-feature step][hi|mid][lane][8] (the
-                    //               matrix cores' operand order) on the multi-workgroup path
+                    //               candidate: [tile][16-feature step][hi|mid][lane][8], the matrix
+                    //               cores' operand order (multi-workgroup path)
     size_t max_tiles;   // capacity of `split` in tiles (not an offset)
     bool use_big;
     BigWs big;
@@ -136,8 +135,9 @@ struct UcbCall {
     // cluster-arm tables in global memory: visit counts, reward sums in 2^-30 fixed
     // point, alive members and best member per cluster.  Searches of more than 16384
     // candidates are aggregated there (chunked != 0 says the batch has such a
-    // search; the tables must then be given); the others only when keep_tables asks
-    // for a copy of their LDS tables.  from_tables: no aggregation at all, scores
+    // search; the tables must then be given), and so are shorter ones in batches of a
+    // few where the tables are given; the others only when keep_tables asks for a copy
+    // of their LDS tables.  from_tables: no aggregation at all, scores
     // and selection come from the tables as they stand.
     unsigned* gN;
     unsigned long long* gR;
