@@ -14,6 +14,13 @@
 // 58 / 36 and 95 / 53; 256 of 64, K = 4 63 / 47 and 125 / 91; 512 of 32, K = 16 67 / 55 and 98 / 76; 512 of 64,
 // K = 32 79 / 71 and 114 / 109.  Two tiles of rows against two of centroids are slower than the bounds (500 of
 // 50, K = 40 92 / 95 and 122 / 131), hence 256 rows where a search may have more than 32 clusters.
+//
+// Up to two searches per compute unit, of at most 256 candidates, in 128 registers.  512 / 270 searches, 20
+// steps: 256 rows of 16, K = 16 92 / 68 and 90 / 58; of 32, K = 32 103 / 84 and 108 / 77; of 48, K = 16 100 / 94 and 85 /
+// 75; 40-256 rows of 30, K <= 64 96 / 89 and 89 / 76.  Not with 64 features (K = 16 100 / 112) nor with 48 and more
+// than 32 clusters (118 / 134), and not with 512 rows: where the bounds leave most rows unread, fetched
+// ones are faster (well-separated rows of 32, K = 16 129 / 141).  With more searches than are resident at
+// once the ratio falls below one (4096 of 100-256 301 / 314).
 #include "kb_cluster_lloyd.h"
 
 namespace kb {
@@ -39,9 +46,10 @@ __host__ __device__ inline ResidentLds resident_lds_layout(int Kmax, int D, int 
     return l;
 }
 
-// Two waves per SIMD: 256 registers a lane, of which the rows take 16 * DS * T.
-template <int DS, int MT, int T>
-__global__ void __launch_bounds__(kThreads, 2) cluster_resident_kernel(ClusterArgs a) {
+// Two waves per SIMD: 256 registers a lane, of which the rows take 16 * DS * T.  PAIR: two searches per
+// compute unit, 128 registers.
+template <int DS, int MT, int T, bool PAIR>
+__global__ void __launch_bounds__(kThreads, PAIR ? 4 : 2) cluster_resident_kernel(ClusterArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int DP = 16 * DS + 4;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -282,23 +290,33 @@ __global__ void __launch_bounds__(kThreads, 2) cluster_resident_kernel(ClusterAr
     for (int j = tid; j < K; j += kThreads) a.counts[k0 + j] = cnt[j];
 }
 
-template <int DS, int MT, int T>
+template <int DS, int MT, int T, bool PAIR = false>
 hipError_t launch(const ClusterArgs& a, hipStream_t st) {
     const size_t lds = resident_lds_layout(a.Kmax, a.D, 16 * DS + 4).total;
-    return launch_one(cluster_resident_kernel<DS, MT, T>, kThreads, a, lds, st);
+    return launch_one(cluster_resident_kernel<DS, MT, T, PAIR>, kThreads, a, lds, st);
 }
 
 }  // namespace
 
 bool cluster_resident(const kb_batch& b, int scorer, int iters) {
-    return scorer == KB_SCORER_DEFAULT && iters > 1 && b.G <= kResidentMaxG && b.Kmax >= 1 && b.Kmax <= 64 &&
-           b.Nmax <= (b.Kmax <= 32 ? 2 : 1) * 32 * kWaves;
+    if (scorer != KB_SCORER_DEFAULT || iters <= 1 || b.Kmax < 1 || b.Kmax > 64) return false;
+    if (b.G > kResidentMaxG) return b.G <= kResidentPairG && b.Nmax <= 32 * kWaves && b.D <= (b.Kmax <= 32 ? 48 : 32);
+    return b.Nmax <= (b.Kmax <= 32 ? 2 : 1) * 32 * kWaves;
 }
 
 hipError_t launch_cluster_resident(const ClusterArgs& a, int Nmax, hipStream_t st) {
     const int ds = (a.D + 15) / 16, mt = a.Kmax <= 32 ? 1 : 2, t = Nmax <= 32 * kWaves ? 1 : 2;
     const auto go = [&](auto d) {
         constexpr int DS = decltype(d)::value;
+        if (a.G > kResidentMaxG) {
+            if constexpr (DS <= 3) {
+                if (t == 1 && mt == 1) return launch<DS, 1, 1, true>(a, st);
+            }
+            if constexpr (DS <= 2) {
+                if (t == 1) return launch<DS, 2, 1, true>(a, st);
+            }
+            return hipErrorInvalidValue;
+        }
         if (mt == 2) return t == 1 ? launch<DS, 2, 1>(a, st) : hipErrorInvalidValue;
         return t == 1 ? launch<DS, 1, 1>(a, st) : launch<DS, 1, 2>(a, st);
     };

@@ -1,5 +1,5 @@
 """The Lloyd kernel that keeps a search's rows in registers (at most 256 searches, up to 512 candidates,
-256 with more than 32 clusters) against the kernel that fetches them, which scorer mode 2 takes: row
+256 with more than 32 clusters; at most 512 searches of up to 256) against the kernel that fetches them, which scorer mode 2 takes: row
 lengths at the edges of K-steps and 16-byte pieces, tiles and pairs of tiles filled exactly and by one,
 equal distances, caller-supplied centroids, stopping early."""
 import numpy as np
@@ -44,3 +44,23 @@ def test_resident_rows_give_the_bytes_of_fetched_rows(kb, D, nmax, kcap, kdiv, s
         for k in ("assign", "cent", "counts"):
             np.testing.assert_array_equal(out[0][k].view(np.uint8), out[1][k].view(np.uint8), err_msg=k)
         assert_rel_close(out[0]["objective"], out[1]["objective"], what="objective")
+
+
+@pytest.mark.parametrize("G", [256, 511])        # (and one of the longest)
+@pytest.mark.parametrize("D,kcap", [(1, 32), (6, 64), (16, 33), (17, 32), (32, 64), (33, 5), (48, 32)])
+def test_two_searches_per_compute_unit(kb, G, D, kcap):
+    import torch
+    b = synth.config5(G=G, nmin=1, nmax=256, D=D, S=3, iters=6, kcap=kcap, kdiv=2, seed=30 + D)
+    b = synth.concat(b, synth.config2(N=256, D=D, K=kcap, S=3, iters=6, seed=4), "pair")
+    if D % 2:          # rows on a grid: equal distances
+        b.X[:] = np.rint(2.0 * b.X) / 2.0
+    out = []
+    for mode in (0, 2):
+        d = kb.DeviceBatch(b, iters=6, scorer=mode)
+        d.ws.fill_(0x37)
+        kb.kb_cluster(d.batch, d.params, d.X, None, d.assign, d.cent, d.counts, d.objective, d.ws, d.ws_bytes)
+        torch.cuda.synchronize()
+        out.append({k: d.host(k).copy() for k in ("assign", "cent", "counts", "objective")})
+    for k in ("assign", "cent", "counts"):
+        np.testing.assert_array_equal(out[0][k].view(np.uint8), out[1][k].view(np.uint8), err_msg=k)
+    assert_rel_close(out[0]["objective"], out[1]["objective"], what="objective")
