@@ -10,17 +10,24 @@
 // between the fixed-point sums straight from the registers, a barrier, the renewal of the centroids, a
 // barrier.  Same scores, same exact pass, same fixed-point grid and renewal, so the same bytes.
 //
+// A step after one in which no candidate moved scores nothing: no centroid has moved, so nobody's
+// nearest has changed (what the drift bounds say there, too).  A doubtful candidate's row goes through LDS
+// to lanes over features: read again, it cost a trip to L2 each.  Together (a round, 20 steps unless said, us):
+// one search of 274 rows of 53, K = 3, 30 steps 126 -> 68, of 178 of 50, K = 2 63 -> 38, of 382 of 16, K = 15 64 ->
+// 45.
+//
 // A round of one search / of 200, 20 steps, rows fetched again / resident (us): 256 rows of 16 features, K = 8
-// 58 / 36 and 95 / 53; 256 of 64, K = 4 63 / 47 and 125 / 91; 512 of 32, K = 16 67 / 55 and 98 / 76; 512 of 64,
-// K = 32 79 / 71 and 114 / 109.  Two tiles of rows against two of centroids are slower than the bounds (500 of
-// 50, K = 40 92 / 95 and 122 / 131), hence 256 rows where a search may have more than 32 clusters.
+// 62 / 33 and 103 / 56; 256 of 64, K = 4 86 / 56 and 189 / 111; 512 of 32, K = 16 88 / 53 and 157 / 99; 512 of 64,
+// K = 32 85 / 54 and 188 / 87.  Two tiles of rows against two of centroids are slower than the bounds (500 of
+// 50, K = 40 92 / 95 and 122 / 131, without the two points above), hence 256 rows where a search may have more
+// than 32 clusters.
 //
 // Up to two searches per compute unit, of at most 256 candidates, in 128 registers.  512 / 270 searches, 20
-// steps: 256 rows of 16, K = 16 92 / 68 and 90 / 58; of 32, K = 32 103 / 84 and 108 / 77; of 48, K = 16 100 / 94 and 85 /
-// 75; 40-256 rows of 30, K <= 64 96 / 89 and 89 / 76.  Not with 64 features (K = 16 100 / 112) nor with 48 and more
-// than 32 clusters (118 / 134), and not with 512 rows: where the bounds leave most rows unread, fetched
-// ones are faster (well-separated rows of 32, K = 16 129 / 141).  With more searches than are resident at
-// once the ratio falls below one (4096 of 100-256 301 / 314).
+// steps: 256 rows of 16, K = 16 97 / 58 and 93 / 55; of 32, K = 32 117 / 69 and 117 / 68; of 48, K = 16 108 / 67
+// and 94 / 59.  Lines drawn without the two points above: not with 64 features (K = 16 100 / 112) nor with 48
+// and more than 32 clusters (118 / 134), and not with 512 rows, where fetched ones are faster if the bounds
+// leave most unread (well-separated rows of 32, K = 16 129 / 141).  With more searches than are
+// resident at once the ratio falls below one (4096 of 100-256 301 / 314).
 #include "kb_cluster_lloyd.h"
 
 namespace kb {
@@ -30,11 +37,13 @@ namespace {
 constexpr int kThreads = 512, kWaves = kThreads / kWave;
 
 struct ResidentLds {
-    size_t sums, cent, cn, cnt, dirty, aop, total;
+    size_t flags, row, sums, cent, cn, cnt, dirty, aop, total;
 };
 __host__ __device__ inline ResidentLds resident_lds_layout(int Kmax, int D, int DP) {
     ResidentLds l;
     size_t off = (size_t)kWaves * 16;                       // reduction scratch: two slots of one double per wave
+    l.flags = off; off += 16;                               // whether any candidate moved in an even / odd step
+    l.row = off; off += (size_t)kWaves * 16 * ((DP - 4) / 16) * 4;      // a wave's row for the exact pass
     l.sums = off; off += (size_t)Kmax * (D | 1) * 8;        // odd row stride: clusters spread over the LDS banks
     off = (off + 15) & ~(size_t)15;
     l.cent = off; off += (size_t)Kmax * DP * 4;
@@ -75,6 +84,8 @@ __global__ void __launch_bounds__(kThreads, PAIR ? 4 : 2) cluster_resident_kerne
     float* cn = reinterpret_cast<float*>(smem + L.cn);                  // [Kmax]
     int* cnt = reinterpret_cast<int*>(smem + L.cnt);                    // [Kmax]
     unsigned char* dirty = smem + L.dirty;                              // [Kmax]
+    int* flags = reinterpret_cast<int*>(smem + L.flags);
+    float* row = reinterpret_cast<float*>(smem + L.row) + 16 * DS * wid;
     bf16x8* aop = reinterpret_cast<bf16x8*>(smem + L.aop);
     const float* Xg = a.X + (size_t)n0 * D;
     const int mtiles = (K + 31) >> 5;
@@ -126,6 +137,7 @@ __global__ void __launch_bounds__(kThreads, PAIR ? 4 : 2) cluster_resident_kerne
     for (int idx = tid; idx < K * SP; idx += kThreads) sums[idx] = 0;
     for (int j = tid; j < K; j += kThreads) { cnt[j] = 0; dirty[j] = 0; }
     for (int j = K + tid; j < ((a.Kmax + 31) & ~31); j += kThreads) cn[j] = kBig;
+    if (tid < 2) flags[tid] = 0;
 
     bf16x8 Bh[T][DS], Bm[T][DS];
     float xn[T];
@@ -161,8 +173,10 @@ __global__ void __launch_bounds__(kThreads, PAIR ? 4 : 2) cluster_resident_kerne
     int mine[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) mine[t] = -1;
+    bool still = false;       // no candidate moved in the last step: no centroid did, so nobody's nearest has changed
     for (int it = 0; it < a.iters; ++it) {
         int moved = 0;
+        if (!still) {
 #pragma unroll
         for (int t = 0; t < T; ++t) {
             const int base = (wid + kWaves * t) * 32;
@@ -180,8 +194,18 @@ __global__ void __launch_bounds__(kThreads, PAIR ? 4 : 2) cluster_resident_kerne
                 while (doubt) {
                     const int b = __ffs((int)doubt) - 1;
                     doubt &= doubt - 1;
-                    // (rare: the row is read again, lanes over features)
-                    const float xv = lane < D ? Xg[(size_t)(base + b) * D + lane] : 0.f;
+                    // (its row to lanes over features, zeros beyond D)
+                    if (m == b) {
+#pragma unroll
+                        for (int s = 0; s < DS; ++s) {
+                            float4* to = reinterpret_cast<float4*>(row + 16 * s + 8 * h);
+                            to[0] = make_float4(x[t][s][0], x[t][s][1], x[t][s][2], x[t][s][3]);
+                            to[1] = make_float4(x[t][s][4], x[t][s][5], x[t][s][6], x[t][s][7]);
+                        }
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    const float xv = lane < 16 * DS ? row[lane] : 0.f;
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                     float ub, lbd;
                     int bj = exact_nearest<DS>(xv, cent, K, D, DP, ub, lbd);
                     bj = bj < K ? bj : 0;
@@ -227,9 +251,16 @@ __global__ void __launch_bounds__(kThreads, PAIR ? 4 : 2) cluster_resident_kerne
                 }
             }
         }
-        int changed = 1;
+        }
+        int changed;
         if (a.early_exit) changed = block_or_i<kWaves>(moved, red, phase) & 1;
-        else __syncthreads();
+        else {
+            if (moved && lane == 0) flags[it & 1] = 1;
+            __syncthreads();
+            changed = __builtin_amdgcn_readfirstlane(flags[it & 1]);
+            if (tid == 0) flags[(it + 1) & 1] = 0;      // (read before the last barrier, set after the next)
+        }
+        still = !changed;
 
         const bool last = (it == a.iters - 1) || (a.early_exit && !changed);
         if (last) {
