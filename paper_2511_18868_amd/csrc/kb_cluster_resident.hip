@@ -22,12 +22,13 @@
 // 50, K = 40 92 / 95 and 122 / 131, without the two points above), hence 256 rows where a search may have more
 // than 32 clusters.
 //
-// Up to two searches per compute unit, of at most 256 candidates, in 128 registers.  512 / 270 searches, 20
-// steps: 256 rows of 16, K = 16 97 / 58 and 93 / 55; of 32, K = 32 117 / 69 and 117 / 68; of 48, K = 16 108 / 67
-// and 94 / 59.  Lines drawn without the two points above: not with 64 features (K = 16 100 / 112) nor with 48
-// and more than 32 clusters (118 / 134), and not with 512 rows, where fetched ones are faster if the bounds
-// leave most unread (well-separated rows of 32, K = 16 129 / 141).  With more searches than are
-// resident at once the ratio falls below one (4096 of 100-256 301 / 314).
+// Two searches per compute unit, in 128 registers.  512 / 300 searches, 20 steps: 256 rows of 16, K = 16
+// 97 / 58 and 93 / 55; of 32, K = 32 117 / 69 and 117 / 68; of 48, K = 16 108 / 67 and 94 / 59; 512 rows of 16
+// 163 / 103 and 155 / 92 (around well-separated centres 115 / 75 and 111 / 67), of 32 199 / 140 and 188 / 123
+// (121 / 97 and 104 / 81).  Not with 64 features, nor with 48 and more than 32 clusters or 512 rows, whose
+// registers spill (100 / 112, 118 / 134, 241 / 251, before the first point above).
+// Up to 1024 searches, in turns, where a step is shortest: 256 rows of 16 103 / 87, of 32, K = 32 109 / 90, K <= 64 147 /
+// 112; 512 rows of 16 193 / 160 (145 / 122), but of 32 142 / 152, hence 16 features there.
 #include "kb_cluster_lloyd.h"
 
 namespace kb {
@@ -35,6 +36,7 @@ namespace kb {
 namespace {
 
 constexpr int kThreads = 512, kWaves = kThreads / kWave;
+constexpr int kResidentTurnsG = 1024;     // searches that take turns on the compute units, two at a time
 
 struct ResidentLds {
     size_t flags, row, sums, cent, cn, cnt, dirty, aop, total;
@@ -331,8 +333,11 @@ hipError_t launch(const ClusterArgs& a, hipStream_t st) {
 
 bool cluster_resident(const kb_batch& b, int scorer, int iters) {
     if (scorer != KB_SCORER_DEFAULT || iters <= 1 || b.Kmax < 1 || b.Kmax > 64) return false;
-    if (b.G > kResidentMaxG) return b.G <= kResidentPairG && b.Nmax <= 32 * kWaves && b.D <= (b.Kmax <= 32 ? 48 : 32);
-    return b.Nmax <= (b.Kmax <= 32 ? 2 : 1) * 32 * kWaves;
+    const bool two = b.Nmax > 32 * kWaves;                  // tiles of a wave
+    if (b.Nmax > 64 * kWaves || (two && b.Kmax > 32)) return false;
+    if (b.G <= kResidentMaxG) return true;
+    if (b.G <= kResidentPairG) return b.D <= (!two && b.Kmax <= 32 ? 48 : 32);
+    return b.G <= kResidentTurnsG && b.D <= (two ? 16 : 32);
 }
 
 hipError_t launch_cluster_resident(const ClusterArgs& a, int Nmax, hipStream_t st) {
@@ -343,8 +348,8 @@ hipError_t launch_cluster_resident(const ClusterArgs& a, int Nmax, hipStream_t s
             if constexpr (DS <= 3) {
                 if (t == 1 && mt == 1) return launch<DS, 1, 1, true>(a, st);
             }
-            if constexpr (DS <= 2) {
-                if (t == 1) return launch<DS, 2, 1, true>(a, st);
+            if constexpr (DS <= 2) {        // (two tiles of rows: one of centroids, cluster_resident)
+                return t == 1 ? launch<DS, 2, 1, true>(a, st) : launch<DS, 1, 2, true>(a, st);
             }
             return hipErrorInvalidValue;
         }

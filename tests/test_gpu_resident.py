@@ -1,5 +1,6 @@
 """The Lloyd kernel that keeps a search's rows in registers (at most 256 searches, up to 512 candidates,
-256 with more than 32 clusters; at most 512 searches of up to 256) against the kernel that fetches them, which scorer mode 2 takes: row
+256 with more than 32 clusters; two searches per compute unit, up to 1024
+searches of few features) against the kernel that fetches them, which scorer mode 2 takes: row
 lengths at the edges of K-steps and 16-byte pieces, tiles and pairs of tiles filled exactly and by one,
 equal distances, caller-supplied centroids, stopping early."""
 import numpy as np
@@ -46,12 +47,12 @@ def test_resident_rows_give_the_bytes_of_fetched_rows(kb, D, nmax, kcap, kdiv, s
         assert_rel_close(out[0]["objective"], out[1]["objective"], what="objective")
 
 
-@pytest.mark.parametrize("G", [256, 511])        # (and one of the longest)
-@pytest.mark.parametrize("D,kcap", [(1, 32), (6, 64), (16, 33), (17, 32), (32, 64), (33, 5), (48, 32)])
-def test_two_searches_per_compute_unit(kb, G, D, kcap):
+@pytest.mark.parametrize("G,nmax", [(256, 256), (511, 256), (256, 512), (512, 257), (1023, 256), (700, 512)])  # (and one)
+@pytest.mark.parametrize("D,kcap", [(1, 32), (6, 64), (16, 32), (17, 32), (32, 33), (33, 5), (48, 32)])
+def test_two_searches_per_compute_unit(kb, G, nmax, D, kcap):
     import torch
-    b = synth.config5(G=G, nmin=1, nmax=256, D=D, S=3, iters=6, kcap=kcap, kdiv=2, seed=30 + D)
-    b = synth.concat(b, synth.config2(N=256, D=D, K=kcap, S=3, iters=6, seed=4), "pair")
+    b = synth.config5(G=G, nmin=1, nmax=nmax, D=D, S=3, iters=6, kcap=kcap, kdiv=2, seed=30 + D)
+    b = synth.concat(b, synth.config2(N=nmax, D=D, K=kcap, S=3, iters=6, seed=4), "pair")
     if D % 2:          # rows on a grid: equal distances
         b.X[:] = np.rint(2.0 * b.X) / 2.0
     out = []
