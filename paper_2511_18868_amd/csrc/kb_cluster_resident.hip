@@ -41,8 +41,8 @@ constexpr int kResidentTurnsG = 1024;     // searches that take turns on the com
 struct ResidentLds {
     size_t flags, row, sums, cent, cn, cnt, dirty, aop, total;
 };
-__host__ __device__ inline ResidentLds resident_lds_layout(int Kmax, int D, int DP) {
-    ResidentLds l;
+__host__ __device__ constexpr ResidentLds resident_lds_layout(int Kmax, int D, int DP) {
+    ResidentLds l{};
     size_t off = (size_t)kWaves * 16;                       // reduction scratch: two slots of one double per wave
     l.flags = off; off += 16;                               // whether any candidate moved in an even / odd step
     l.row = off; off += (size_t)kWaves * 16 * ((DP - 4) / 16) * 4;      // a wave's row for the exact pass
@@ -51,11 +51,22 @@ __host__ __device__ inline ResidentLds resident_lds_layout(int Kmax, int D, int 
     l.cent = off; off += (size_t)Kmax * DP * 4;
     l.cn = off;   off += (size_t)((Kmax + 31) & ~31) * 4;
     l.cnt = off;  off += (size_t)Kmax * 4;
-    l.dirty = off; off += ((size_t)Kmax + 15) & ~(size_t)15;
+    l.dirty = off; off += (size_t)Kmax;
+    off = (off + 15) & ~(size_t)15;
     l.aop = off;  off += (size_t)((Kmax + 31) / 32) * ((DP - 4) / 16) * 2 * 64 * 16;
     l.total = off;
     return l;
 }
+// Everything that is moved in pieces of 16 bytes begins on such a piece, whatever the number of clusters.
+constexpr bool resident_lds_aligned() {
+    for (int Kmax = 1; Kmax <= 64; ++Kmax)
+        for (int D = 1; D <= KB_MAX_D; ++D) {
+            const ResidentLds l = resident_lds_layout(Kmax, D, 16 * ((D + 15) / 16) + 4);
+            if ((l.row | l.cent | l.cn | l.aop) & 15 || (l.sums & 7)) return false;
+        }
+    return true;
+}
+static_assert(resident_lds_aligned(), "16-byte pieces of the LDS layout");
 
 // Two waves per SIMD: 256 registers a lane, of which the rows take 16 * DS * T.  PAIR: two searches per
 // compute unit, 128 registers.
