@@ -278,7 +278,8 @@ __global__ void __launch_bounds__(kThreads, PAIR ? 4 : 2) cluster_resident_kerne
         const bool last = (it == a.iters - 1) || (a.early_exit && !changed);
         if (last) {
             // Objective relative to the centroids c_j that entered this step, as in the kernel for longer
-            // searches: from the exact sums, member by member where the subtraction cancels.
+            // searches: from the exact sums, member by member (four squares in fp32, their sums in fp64) where
+            // the subtraction cancels.
             double part = 0.0;
             for (int j0 = 0; j0 < K; j0 += kThreads / 16) {
                 const int j = j0 + (tid >> 4);
@@ -301,13 +302,12 @@ __global__ void __launch_bounds__(kThreads, PAIR ? 4 : 2) cluster_resident_kerne
                         const float* cr = cent + (size_t)mine[t] * DP + 8 * h;
 #pragma unroll
                         for (int s = 0; s < DS; ++s) {
-                            float e2 = 0.f;
 #pragma unroll
-                            for (int i = 0; i < 8; ++i) {
-                                const float e = x[t][s][i] - cr[16 * s + i];
-                                e2 = fmaf(e, e, e2);
+                            for (int i = 0; i < 8; i += 4) {
+                                const float e0 = x[t][s][i] - cr[16 * s + i], e1 = x[t][s][i + 1] - cr[16 * s + i + 1];
+                                const float e2 = x[t][s][i + 2] - cr[16 * s + i + 2], e3 = x[t][s][i + 3] - cr[16 * s + i + 3];
+                                acc += (double)fmaf(e0, e0, fmaf(e1, e1, fmaf(e2, e2, e3 * e3)));
                             }
-                            acc += (double)e2;
                         }
                     }
                 }

@@ -65,3 +65,20 @@ def test_two_searches_per_compute_unit(kb, G, nmax, D, kcap):
     for k in ("assign", "cent", "counts"):
         np.testing.assert_array_equal(out[0][k].view(np.uint8), out[1][k].view(np.uint8), err_msg=k)
     assert_rel_close(out[0]["objective"], out[1]["objective"], what="objective")
+
+
+@pytest.mark.parametrize("G,n", [(3, 128), (3, 512), (300, 128), (300, 512)])   # tiles of a wave; searches per unit
+def test_objective_member_by_member_sums_in_fp64(kb, G, n):
+    """Rows at c + d and c - d, c so far from the origin that sum |x|^2 leaves nothing to subtract from:
+    the squares are added member by member.  d^2 = 2^24 in the first four features together and 4 in the
+    next four - every group of four is exact in fp32, all eight together are not: fp64 takes them from there."""
+    import torch
+    b = synth.config5(G=G, nmin=n, nmax=n, D=8, S=3, iters=3, kcap=1, kdiv=1, seed=8)
+    sign = np.where(np.arange(b.N) % 2 == 0, 1.0, -1.0)[:, None]
+    b.X[:] = 2.0 ** 23 + sign * np.array([4096, 0, 0, 0, 1, 1, 1, 1])
+    for mode in (0, 2):
+        d = kb.DeviceBatch(b, iters=3, scorer=mode)
+        kb.kb_cluster(d.batch, d.params, d.X, None, d.assign, d.cent, d.counts, d.objective, d.ws, d.ws_bytes)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(d.host("cent"), np.float32(2.0 ** 23))
+        np.testing.assert_array_equal(d.host("objective"), np.float32(n * (2.0 ** 24 + 4)), err_msg=str(mode))
