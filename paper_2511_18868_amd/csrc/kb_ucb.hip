@@ -12,6 +12,7 @@
 #include "kb_internal.h"
 #include "kb_ucb_dev.h"
 #include "kb_sample_dev.h"
+#include <cmath>
 
 namespace kb {
 
@@ -618,7 +619,11 @@ hipError_t launch_range_kernel(const UcbArgs& a, unsigned ranges, size_t lds, hi
 
 }  // namespace
 
-static bool ucb_wide(const kb_batch& b) {
+// (Scores that are not numbers - possible only with an infinite parameter - have no order, and the arm chosen
+// among them follows from how the arms are dealt to the threads: always 256 then, so that a search's choice
+// does not depend on how many others the batch holds.)
+static bool ucb_wide(const kb_batch& b, const UcbArgs& a) {
+    if (!std::isfinite(a.c) || !std::isfinite(a.prior_n) || !std::isfinite(a.prior_mu)) return false;
     return b.G <= kUcbWideFewG || (b.G <= kUcbWideMaxG && b.Nmax >= kUcbWideMinN);
 }
 
@@ -659,7 +664,7 @@ hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
         hipLaunchKernelGGL(ucb_zero, dim3(zb), dim3(kThreads), 0, st, a);
         if (b.G > 1) {
             a.mixed = 1;
-            const hipError_t e = launch_search_kernel(a, ucb_wide(b), lds, st);
+            const hipError_t e = launch_search_kernel(a, ucb_wide(b, a), lds, st);
             if (e != hipSuccess) return e;
         }
         const unsigned ranges = (unsigned)((b.N + a.range - 1) / a.range);
@@ -680,7 +685,7 @@ hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
                            (size_t)per * kWaves, st, a, per);
         return hipGetLastError();
     }
-    return launch_search_kernel(a, ucb_wide(b), lds, st);
+    return launch_search_kernel(a, ucb_wide(b, a), lds, st);
 }
 
 static size_t rounds_lds(const kb_batch& b, bool means = false) {
