@@ -142,8 +142,10 @@ static kb_status do_cluster(const kb_batch* b, const float* X, const float* cent
     char* base = (char*)ws;
     int32_t* order = (int32_t*)(base + w.order);
     // (few searches on the one-workgroup path need neither a scheduling order nor
-    // tile offsets, and neither does a batch that runs one wave per search: one launch less)
-    const bool need_order = (order_matters(*b) && !cluster_wave_per_search(*b, scorer)) || w.use_big;
+    // tile offsets, and neither does a batch that runs one wave per search or keeps its rows in
+    // registers: one launch less)
+    const bool need_order = (order_matters(*b) && !cluster_wave_per_search(*b, scorer) &&
+                             !cluster_resident(*b, scorer, iters)) || w.use_big;
     const bool have = ordered && *ordered;
     if (ordered) *ordered = have || need_order;
     if (need_order && !have) {

@@ -81,10 +81,8 @@ struct LloydForm {
 template <int DS>
 hipError_t launch_lloyd(const ClusterArgs& a, const LloydForm& f, hipStream_t st);
 
-// Searches whose rows stay in registers (kb_cluster_resident.hip): whether a batch is one of such, and
-// its launch.
+// Searches whose rows stay in registers (kb_cluster_resident.hip).
 constexpr int kResidentMaxG = 256, kResidentPairG = 512;
-bool cluster_resident(const kb_batch& b, int scorer, int iters);
 hipError_t launch_cluster_resident(const ClusterArgs& a, int Nmax, hipStream_t st);
 
 // Threads per workgroup (a template parameter NT of the kernel and of the device

@@ -117,6 +117,7 @@ hipError_t launch_cluster_big(const kb_batch& b, const ClusterCall& c, const Big
 hipError_t launch_cluster_wave(const kb_batch& b, const ClusterCall& c, hipStream_t st);   // one wave per search
 bool cluster_supported(const kb_batch& b);   // shape fits the compiled clustering kernels
 bool cluster_wave_per_search(const kb_batch& b, int scorer);   // the batch runs one wave per search (no scheduling order needed)
+bool cluster_resident(const kb_batch& b, int scorer, int iters);   // the batch keeps its rows in registers (no order either)
 
 struct UcbCall {
     const int32_t* assign;
