@@ -9,7 +9,7 @@
 // What bounds it is one wave's chain of dependent instructions, so a Lloyd step is kept to the
 // pieces that it cannot do without:
 //   score    every lane forms the fp32 direct-difference distances of its candidate to all
-//            centroids, four centroids at a time (independent chains); no distance bounds, since
+//            centroids, two or four centroids at a time (independent chains); no distance bounds, since
 //            a step without a move ends the search anyway (below) and in every other step some
 //            lane has to score, which costs the wave the same as all lanes.
 //   decide   relative error <= (D + 2) 2^-24, sums of non-negative terms: if the two smallest are
@@ -154,15 +154,21 @@ __device__ __forceinline__ float short_cluster(int iters, int D, int ng, int K, 
     const int lg = D > 1 ? 32 - __clz(D - 1) : 0;
     const int E = K << lg, dmask = (1 << lg) - 1;
 
+    // Centroids scored side by side.  A step runs through its code once, so of rows of 17 to 48 features
+    // only two: their chains keep the unit busy, and four rows' worth of unrolled code took longer to fetch
+    // than it saved (four / two, 20 steps: 183 searches of 64 rows of 40, K = 16 82 / 75 us, 1500 of 17-64 rows of
+    // 24, K = 6 33 / 28, 20000 of 12-64 rows of 32 123 / 109).  Of longer rows four: a round of 500 searches of 64
+    // rows of 64, K = 16, ten steps 94 / 101.
+    constexpr int U = NC == 8 || NC == 12 ? 2 : 4;
     mine = -1;
     double J = 0.0;
     for (int it = 0;; ++it) {
         float b32 = INFINITY, s32 = INFINITY;
         int bj = 0;
-        for (int j0 = 0; j0 < K; j0 += 4) {
-            float acc[4];
+        for (int j0 = 0; j0 < K; j0 += U) {
+            float acc[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 // (one address for all lanes; rows and centroids are zero-padded: the extra terms are +0.0)
                 const float4* cr = reinterpret_cast<const float4*>(cent + (size_t)(j0 + u) * DP);
                 float a0 = 0.f, a1 = 0.f;
@@ -179,7 +185,7 @@ __device__ __forceinline__ float short_cluster(int iters, int D, int ng, int K, 
                 acc[u] = a0 + a1;
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const float v = j0 + u < K ? acc[u] : INFINITY;
                 const bool lt = v < b32;
                 s32 = lt ? b32 : (v < s32 ? v : s32);
