@@ -614,7 +614,12 @@ kb_status kb_iterate(const kb_batch* batch, const kb_params* params, const kb_it
     // (rounds_in_one_launch), in the workspace where every round is launches of its own.
     const UcbScratch us = ucb_scratch_in_ws(batch, ws);
     bool tables_valid = false;
-    const bool one_launch = iterate_in_one_launch(*batch, params->scorer, ip->R);
+    int64_t reclusterings = 0;
+    if (recluster) {
+        const int64_t first = (ip->tau_recluster - ip->t0 % ip->tau_recluster) % ip->tau_recluster;
+        if (first < ip->rounds) reclusterings = 1 + (ip->rounds - 1 - first) / ip->tau_recluster;
+    }
+    const bool one_launch = iterate_in_one_launch(*batch, params->scorer, ip->R, ip->rounds, reclusterings);
     for (int32_t r = 0; r < ip->rounds; ++r) {
         const bool now = !one_launch && recluster && (((int64_t)ip->t0 + r) % ip->tau_recluster) == 0;
         if (now) {

@@ -207,7 +207,7 @@ struct IterateCall {
     int32_t* rep;
     float* radius;
 };
-bool iterate_in_one_launch(const kb_batch& b, int scorer, int R);
+bool iterate_in_one_launch(const kb_batch& b, int scorer, int R, int64_t rounds, int64_t reclusterings);
 hipError_t launch_iterate(const kb_batch& b, const ClusterCall& c, const UcbCall& uc, const SampleCall& sc,
                           const RoundsCall& rc, const IterateCall& ic, hipStream_t st);
 

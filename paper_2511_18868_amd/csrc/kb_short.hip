@@ -472,11 +472,12 @@ __global__ void __launch_bounds__(kThreads) round_wave_kernel(ShortArgs a, Short
 // NW = 1: one wave does both, the variates of the next kAhead iterations after every kAhead.  A search
 // takes a fifth longer, but no wave waits for another: beyond the searches that fit the chip with
 // four waves each (three workgroups per compute unit with rows of at most 16 features and an arm per
-// lane, one otherwise) the batch is done sooner.  The searches above, launches / four waves / one
-// (us): 768 139 / 56 / 68, 4000 303 / 400 / 222 (D = 12, K = 6, S = 10), 20000 752 / 1178 / 372; 768 of
-// 40-64 candidates, D = 40, K = S = 16 342 / 560 / 366 (300: 327 / 373 / 304).
+// lane, one otherwise) the batch is done sooner (four waves / one, us: 768 searches above 56 / 68, 4000, D = 12,
+// K = 6, S = 10 400 / 222; 300 of 40-64 candidates, D = 40, K = S = 16 373 / 304).
 constexpr int kAhead = 8;
 constexpr int kIterateMaxR = 8, kIterateMaxArms = 256;
+constexpr size_t kIterateMaxLds = 40 * 1024, kLdsPerUnit = 160 * 1024;
+constexpr int kComputeUnits = 256;
 
 struct IterateArgs {
     ShortArgs c;
@@ -920,18 +921,48 @@ hipError_t launch_round_wave(const kb_batch& b, const ClusterCall& c, const UcbC
     });
 }
 
-// `kb_iterate` on a batch of such searches is one launch per 1024 iterations, provided that the
+// `kb_iterate` on a batch of such searches can be one launch per 1024 iterations, provided that the
 // resources and strategies are few enough for the tables of a search (a lane holds one or four
 // cluster arms; at least four workgroups' tables fit a compute unit).
-bool iterate_in_one_launch(const kb_batch& b, int scorer, int R) {
+static size_t iterate_lds(const kb_batch& b, int R) {
+    return iterate_lds_layout(kmax_of(b), b.D, row_pieces(b.D), b.S, R, b.Nmax).total;
+}
+static bool iterate_fits(const kb_batch& b, int scorer, int R) {
     return cluster_wave_per_search(b, scorer) && b.G > 0 && R <= kIterateMaxR &&
-           (int64_t)kmax_of(b) * b.S <= kIterateMaxArms && b.Nmax > 0 &&
-           iterate_lds_layout(kmax_of(b), b.D, row_pieces(b.D), b.S, R, b.Nmax).total <= 40 * 1024;
+           (int64_t)kmax_of(b) * b.S <= kIterateMaxArms && b.Nmax > 0 && iterate_lds(b, R) <= kIterateMaxLds;
+}
+
+// Whether that is faster than the launches one by one (their time / one launch's, us).  What it saves grows with
+// the iterations; a re-clustering, three launches more, counts as four of them: w in all.
+//   Up to one search per compute unit: always (1.1 to 2.5 times over 1500 random shapes).
+//   As long as the chip holds all searches at once - by LDS, and by registers 16 waves per unit with rows
+//     of up to 16 features, else 8 -: always (1.0 to 2.0 times), except that the four arms per lane spill beside
+//     short rows: beyond five searches per unit from w = 15 on (1500 searches of 12-41, K = 6, S = 16: one iteration
+//     37 / 40, four 47.5 / 47.7, twenty 136 / 113; 768 of 40-64, D = 40, K = S = 16, twenty 308 / 302).
+//   Beyond, the launches keep more waves in flight than the tables leave room for, and with an arm per lane the
+//     line falls with the waves that a unit holds: at 16 always (20000 of 12-41, K = 3, S = 6, one iteration
+//     113 / 108), at 8 from w = 20 on (4000 of 40-64, D = 3, S = 16, ten iterations 99 / 113, twenty 198 / 200; of 64
+//     rows of 64, S = 2, ten iterations with four re-clusterings 715 / 541).  With four arms the launches win (12000
+//     of 40-64, D = 16, K = 16, S = 10, ten iterations 307 / 542) but for rows of 17 to 32 features, which
+//     neither spill nor fill the registers, from w = 15 on if LDS holds as many (4000 of 40-64, D = 32, K = 10, S = 8,
+//     ten iterations with four re-clusterings 372 / 264).
+constexpr int kIterateWaves = 16, kIterateWavesLong = 8, kIterateShortRows = 16, kIterateMiddleRows = 32;
+bool iterate_in_one_launch(const kb_batch& b, int scorer, int R, int64_t rounds, int64_t reclusterings) {
+    if (!iterate_fits(b, scorer, R)) return false;
+    if (b.G <= kComputeUnits) return true;
+    const bool short_rows = b.D <= kIterateShortRows, one_arm = kmax_of(b) * b.S <= kWave;
+    const int by_lds = (int)(kLdsPerUnit / ((iterate_lds(b, R) + 1279) / 1280 * 1280));
+    const int by_registers = short_rows ? kIterateWaves : kIterateWavesLong;
+    const int waves = by_lds < by_registers ? by_lds : by_registers;
+    const int64_t w = rounds + 4 * reclusterings;
+    if (b.G <= kComputeUnits * waves) return one_arm || !short_rows || b.G <= 5 * kComputeUnits || w >= 15;
+    if (one_arm) return 2 * w >= 5 * (kIterateWaves - waves);
+    return !short_rows && b.D <= kIterateMiddleRows && waves == by_registers && w >= 15;
 }
 
 hipError_t launch_iterate(const kb_batch& b, const ClusterCall& c, const UcbCall& uc, const SampleCall& sc,
                           const RoundsCall& rc, const IterateCall& ic, hipStream_t st) {
-    if (!iterate_in_one_launch(b, c.scorer, sc.R) || c.mixed || uc.bound || !sc.h || rc.rounds < 1)
+    if (!iterate_fits(b, c.scorer, sc.R) || c.mixed || uc.bound || !sc.h || rc.rounds < 1)
         return hipErrorInvalidValue;
     IterateArgs r;
     r.c = short_args(b, c);
@@ -944,10 +975,10 @@ hipError_t launch_iterate(const kb_batch& b, const ClusterCall& c, const UcbCall
     r.Nmax = b.Nmax;
     return with_pieces(b.D, [&](auto nc) {
         constexpr int NC = decltype(nc)::value;
-        const size_t lds = iterate_lds_layout(r.c.Kmax, b.D, NC, b.S, sc.R, b.Nmax).total;
+        const size_t lds = iterate_lds(b, sc.R);
         const auto go = [&](auto kern, int waves) { return launch(kern, (unsigned)b.G, waves * kWave, lds, st, r); };
         const bool one = r.c.Kmax * b.S <= kWave;
-        const bool few = b.G <= (one && NC <= 4 ? 768 : 256);      // (the line: see above)
+        const bool few = b.G <= (one && NC <= 4 ? 768 : kComputeUnits);      // (the line: see above)
         return few ? (one ? go(iterate_kernel<NC, 1, 4>, 4) : go(iterate_kernel<NC, 4, 4>, 4))
                    : (one ? go(iterate_kernel<NC, 1, 1>, 1) : go(iterate_kernel<NC, 4, 1>, 1));
     });
