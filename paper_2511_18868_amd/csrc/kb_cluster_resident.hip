@@ -14,13 +14,18 @@
 // nearest has changed (what the drift bounds say there, too).  A doubtful candidate's row goes through LDS
 // to lanes over features: read again, it cost a trip to L2 each.  Together (a round, 20 steps unless said, us):
 // one search of 274 rows of 53, K = 3, 30 steps 126 -> 68, of 178 of 50, K = 2 63 -> 38, of 382 of 16, K = 15 64 ->
-// 45.
+// 45; rows fetched again 94 / resident 56, 63 / 36 and 69 / 39 where the other outputs are in cache.
 //
 // A round of one search / of 200, 20 steps, rows fetched again / resident (us): 256 rows of 16 features, K = 8
 // 62 / 33 and 103 / 56; 256 of 64, K = 4 86 / 56 and 189 / 111; 512 of 32, K = 16 88 / 53 and 157 / 99; 512 of 64,
 // K = 32 85 / 54 and 188 / 87.  Two tiles of rows against two of centroids are slower than the bounds (500 of
 // 50, K = 40 92 / 95 and 122 / 131, without the two points above), hence 256 rows where a search may have more
 // than 32 clusters.
+//
+// What the first step costs more - all rows move, most of them into the same sums - only later steps
+// bring back: with two tiles of rows of more than 32 features and at most 4 clusters not fewer than ten do
+// (rows fetched again / resident: one search of 512 rows of 64, K = 2, two steps 39.6 / 43.1 us, twenty 73 / 54; 256
+// of 200-512 rows of 48, K = 3 44.5 / 51.0 and 180 / 125).
 //
 // Two searches per compute unit, in 128 registers.  512 / 300 searches, 20 steps: 256 rows of 16, K = 16
 // 97 / 58 and 93 / 55; of 32, K = 32 117 / 69 and 117 / 68; of 48, K = 16 108 / 67 and 94 / 59; 512 rows of 16
@@ -37,6 +42,7 @@ namespace {
 
 constexpr int kThreads = 512, kWaves = kThreads / kWave;
 constexpr int kResidentTurnsG = 1024;     // searches that take turns on the compute units, two at a time
+constexpr int kResidentFewK = 4, kResidentFewIters = 10;
 
 struct ResidentLds {
     size_t flags, row, sums, cent, cn, cnt, dirty, aop, total;
@@ -346,6 +352,7 @@ bool cluster_resident(const kb_batch& b, int scorer, int iters) {
     if (scorer != KB_SCORER_DEFAULT || iters <= 1 || b.Kmax < 1 || b.Kmax > 64) return false;
     const bool two = b.Nmax > 32 * kWaves;                  // tiles of a wave
     if (b.Nmax > 64 * kWaves || (two && b.Kmax > 32)) return false;
+    if (two && b.D > 32 && b.Kmax <= kResidentFewK && iters < kResidentFewIters) return false;
     if (b.G <= kResidentMaxG) return true;
     if (b.G <= kResidentPairG) return b.D <= (!two && b.Kmax <= 32 ? 48 : 32);
     return b.G <= kResidentTurnsG && b.D <= (two ? 16 : 32);
