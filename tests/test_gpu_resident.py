@@ -49,17 +49,21 @@ def test_resident_rows_give_the_bytes_of_fetched_rows(kb, D, nmax, kcap, kdiv, s
 
 @pytest.mark.parametrize("G,nmax", [(256, 256), (511, 256), (256, 512), (512, 257), (1023, 256), (700, 512)])  # (and one)
 @pytest.mark.parametrize("D,kcap", [(1, 32), (6, 64), (16, 32), (17, 32), (32, 33), (33, 5), (48, 32)])
-def test_two_searches_per_compute_unit(kb, G, nmax, D, kcap):
+@pytest.mark.parametrize("stop,init", [(0, False), (1, True)])
+def test_two_searches_per_compute_unit(kb, G, nmax, D, kcap, stop, init):
     import torch
     b = synth.config5(G=G, nmin=1, nmax=nmax, D=D, S=3, iters=6, kcap=kcap, kdiv=2, seed=30 + D)
     b = synth.concat(b, synth.config2(N=nmax, D=D, K=kcap, S=3, iters=6, seed=4), "pair")
     if D % 2:          # rows on a grid: equal distances
         b.X[:] = np.rint(2.0 * b.X) / 2.0
+    rows = np.concatenate([np.arange(e - 1, e - 1 - k, -1) for e, k in
+                           zip(b.seg_off[1:], np.diff(b.koff))]).astype(np.int64)
     out = []
     for mode in (0, 2):
-        d = kb.DeviceBatch(b, iters=6, scorer=mode)
+        d = kb.DeviceBatch(b, iters=6, scorer=mode, stop_early=stop)
         d.ws.fill_(0x37)
-        kb.kb_cluster(d.batch, d.params, d.X, None, d.assign, d.cent, d.counts, d.objective, d.ws, d.ws_bytes)
+        start = torch.from_numpy(b.X[rows].copy()).to(d.device) if init else None
+        kb.kb_cluster(d.batch, d.params, d.X, start, d.assign, d.cent, d.counts, d.objective, d.ws, d.ws_bytes)
         torch.cuda.synchronize()
         out.append({k: d.host(k).copy() for k in ("assign", "cent", "counts", "objective")})
     for k in ("assign", "cent", "counts"):
