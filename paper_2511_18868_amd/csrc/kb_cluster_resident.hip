@@ -1,5 +1,7 @@
-// K-Means (Lloyd) clustering of searches whose rows fit the registers of one workgroup: batches of at
-// most one search per compute unit and at most 512 candidates per search (256 with more than 32 clusters).
+// K-Means (Lloyd) clustering of searches whose rows fit the registers of one workgroup: searches of at most 512
+// candidates (256 with more than 32 clusters) in batches of up to 256, one per compute unit; with fewer
+// features two per unit, in batches of up to 512, and with fewer still in turns, in batches of up to 1024
+// (cluster_resident says which).
 //
 // What a step of such a search costs in the kernel of kb_cluster_lloyd.h is not its scoring but
 // what decides which candidates have to be scored and fetches them: the clocks of the drift
@@ -8,32 +10,37 @@
 // registers from the first step to the last, as fp32 (for the sums) and as the matrix cores' bf16
 // operands, and scores them in every step: matrix instructions, exact pass for the doubtful, moves
 // between the fixed-point sums straight from the registers, a barrier, the renewal of the centroids, a
-// barrier.  Same scores, same exact pass, same fixed-point grid and renewal, so the same bytes.
+// barrier.  Same scores, same exact pass, same fixed-point grid and renewal, so the same bytes of
+// assignments, sizes and centroids (the objective, a sum in fp64, takes another order).
 //
 // A step after one in which no candidate moved scores nothing: no centroid has moved, so nobody's
 // nearest has changed (what the drift bounds say there, too).  A doubtful candidate's row goes through LDS
-// to lanes over features: read again, it cost a trip to L2 each.  Together (a round, 20 steps unless said, us):
-// one search of 274 rows of 53, K = 3, 30 steps 126 -> 68, of 178 of 50, K = 2 63 -> 38, of 382 of 16, K = 15 64 ->
-// 45; rows fetched again 94 / resident 56, 63 / 36 and 69 / 39 where the other outputs are in cache.
+// to lanes over features: read again, it cost a trip to L2 each.
 //
 // A round of one search / of 200, 20 steps, rows fetched again / resident (us): 256 rows of 16 features, K = 8
 // 62 / 33 and 103 / 56; 256 of 64, K = 4 86 / 56 and 189 / 111; 512 of 32, K = 16 88 / 53 and 157 / 99; 512 of 64,
-// K = 32 85 / 54 and 188 / 87.  Two tiles of rows against two of centroids are slower than the bounds (500 of
+// K = 32 85 / 54 and 188 / 87; one search of 274 rows of 53, K = 3, 30 steps 94 / 56, of 178 of 50, K = 2 63 / 36,
+// of 382 of 16, K = 15 69 / 39.  Two tiles of rows against two of centroids are slower than the bounds (500 of
 // 50, K = 40 92 / 95 and 122 / 131, without the two points above), hence 256 rows where a search may have more
 // than 32 clusters.
 //
 // What the first step costs more - all rows move, most of them into the same sums - only later steps
 // bring back: with two tiles of rows of more than 32 features and at most 4 clusters not fewer than ten do
-// (rows fetched again / resident: one search of 512 rows of 64, K = 2, two steps 39.6 / 43.1 us, twenty 73 / 54; 256
-// of 200-512 rows of 48, K = 3 44.5 / 51.0 and 180 / 125).
+// (one search of 512 rows of 64, K = 2, two steps 39.6 / 43.1 us, twenty 73 / 54; 256 of 200-512 rows of 48,
+// K = 3 44.5 / 51.0 and 180 / 125).
 //
-// Two searches per compute unit, in 128 registers.  512 / 300 searches, 20 steps: 256 rows of 16, K = 16
+// Two searches per compute unit, in 128 registers (which rows of up to 16 features, and one tile of up to 32
+// against one of centroids, never exceed).  512 / 300 searches, 20 steps: 256 rows of 16, K = 16
 // 97 / 58 and 93 / 55; of 32, K = 32 117 / 69 and 117 / 68; of 48, K = 16 108 / 67 and 94 / 59; 512 rows of 16
 // 163 / 103 and 155 / 92 (around well-separated centres 115 / 75 and 111 / 67), of 32 199 / 140 and 188 / 123
-// (121 / 97 and 104 / 81).  Not with 64 features, nor with 48 and more than 32 clusters or 512 rows, whose
-// registers spill (100 / 112, 118 / 134, 241 / 251, before the first point above).
+// (121 / 97 and 104 / 81) although 27 registers spill there.  Not with 64 features, nor with 48 and more than 32
+// clusters or 512 rows, whose registers spill and which lose (100 / 112, 118 / 134, 241 / 251, before the first
+// point above).
 // Up to 1024 searches, in turns, where a step is shortest: 256 rows of 16 103 / 87, of 32, K = 32 109 / 90, K <= 64 147 /
-// 112; 512 rows of 16 193 / 160 (145 / 122), but of 32 142 / 152, hence 16 features there.
+// 112; 512 rows of 16 193 / 160 (145 / 122), but of 32 142 / 152, hence 16 features there.  Beyond, batches of even
+// lengths gain as much (2000 of 512 rows 1.15 to 1.4 times, 3000 of 256 1.2 to 1.4), but those in which most
+// searches are far shorter than the longest lose: 1500 of 8-512 rows down to 0.88, 3000 of 4-256 to 0.86.
+// 1024 and 1200 searches lost in none of 170 random shapes.
 #include "kb_cluster_lloyd.h"
 
 namespace kb {
@@ -340,10 +347,12 @@ __global__ void __launch_bounds__(kThreads, PAIR ? 4 : 2) cluster_resident_kerne
     for (int j = tid; j < K; j += kThreads) a.counts[k0 + j] = cnt[j];
 }
 
+// (PAIR where the rows leave 128 registers unfilled anyway: one kernel for both kinds of batches)
 template <int DS, int MT, int T, bool PAIR = false>
 hipError_t launch(const ClusterArgs& a, hipStream_t st) {
+    constexpr bool kPair = PAIR || DS == 1 || (DS == 2 && MT == 1 && T == 1);
     const size_t lds = resident_lds_layout(a.Kmax, a.D, 16 * DS + 4).total;
-    return launch_one(cluster_resident_kernel<DS, MT, T, PAIR>, kThreads, a, lds, st);
+    return launch_one(cluster_resident_kernel<DS, MT, T, kPair>, kThreads, a, lds, st);
 }
 
 }  // namespace
