@@ -25,11 +25,11 @@
 // after the full count of steps.
 //
 // Measured against the form with distance bounds, four lanes per centroid and a centroid at a time
-// in the score: ten steps of 183 searches of 12-41 candidates (D = 5, K = 3) 22.4 -> 12.0 us, the
-// whole round 27.2 -> 15.5 us; rounds of 20000 searches of 1-40 111 -> 58 us, of 4000 searches of 64
-// candidates, K = 16, D = 64 (20 steps) 362 -> 242 us, of 20000 with D = 32 526 -> 353 us.  What a lane
+// in the score: ten steps of 183 searches of 12-41 candidates (D = 5, K = 3) 22.8 -> 12.1 us, the
+// whole round 26.9 -> 14.3 us; rounds of 20000 searches of 1-40 112 -> 55 us, of 4000 searches of 64
+// candidates, K = 16, D = 64 (20 steps) 334 -> 205 us, of 20000 with D = 32 474 -> 280 us.  What a lane
 // could keep over the steps beside its row - its fixed-point image, its fp64 form - is formed
-// again in each: kept, the registers leave one wave per SIMD (D = 32: 1022 us).
+// again in each: kept, the registers leave one wave per SIMD (D = 32: three times as long).
 #include "kb_cluster_dev.h"
 #include "kb_ucb_dev.h"
 #include "kb_wave_dev.h"
