@@ -565,8 +565,13 @@ bool ucb_wave_per_search(const kb_batch& b) {
 // flight (256 / 1024 threads, us: one search of 4096 candidates, S = 16 36.9 / 16.6, of 16000 147 / 50, of
 // 300 5.2 / 4.8; 256 of 512, S = 32 15.0 / 10.2, 200 of 4096 90 / 36, 512 of 1000 32.6 / 30.4, 300 of 1900, S = 6
 // 25.9 / 21.0); beyond the compute units only for long ones (512 of 600, S = 3 11.2 / 12.4, of 512, S = 32
-// 18.0 / 18.5).
-constexpr int kUcbWideFewG = 256, kUcbWideMaxG = 512, kUcbWideMinN = 1000;
+// 18.0 / 18.5), and where there is little to a row - its pieces (ucb_accumulate_pieces) a power of two, a thread
+// each - only from 6000 pieces on (512 of 201-1118, S = 1 11.4 / 13.9, 512 of 1227-2752, S = 8 29 / 34) or beside
+// much shorter ones, when the longest decide (300 of 22-2853, S = 8 21.9 / 15.7, 512 of 134-5551, S = 1 21.3 / 17.5).
+constexpr int kUcbWideFewG = 256, kUcbWideMaxG = 512, kUcbWideMinN = 1000, kUcbWidePieces = 6000;
+
+// pieces of a candidate's row, see ucb_accumulate_pieces
+static int ucb_pieces(int S) { return (S & 3) == 0 ? S / 4 : (S & 1) == 0 ? S / 2 : S; }
 
 namespace {
 
@@ -624,7 +629,11 @@ hipError_t launch_range_kernel(const UcbArgs& a, unsigned ranges, size_t lds, hi
 // does not depend on how many others the batch holds.)
 static bool ucb_wide(const kb_batch& b, const UcbArgs& a) {
     if (!std::isfinite(a.c) || !std::isfinite(a.prior_n) || !std::isfinite(a.prior_mu)) return false;
-    return b.G <= kUcbWideFewG || (b.G <= kUcbWideMaxG && b.Nmax >= kUcbWideMinN);
+    if (b.G <= kUcbWideFewG) return true;
+    const int pieces = ucb_pieces(b.S);
+    return b.G <= kUcbWideMaxG && b.Nmax >= kUcbWideMinN &&
+           ((pieces & (pieces - 1)) != 0 || (int64_t)b.Nmax * pieces >= kUcbWidePieces ||
+            3 * (int64_t)b.Nmax * b.G >= 8 * b.N);
 }
 
 // Long searches: ranges that give every compute unit a workgroup, of 512 candidates at least and not
@@ -632,8 +641,14 @@ static bool ucb_wide(const kb_batch& b, const UcbArgs& a) {
 // of 8192 / these, the kernels of a call, us: one search of 20000, S = 32, K = 64 164 / 28, S = 3, K = 4 74 / 16,
 // of 200000, S = 8, K = 100 57 / 22, three of 60000, S = 32, K = 64 174 / 45, one of 2^20, S = 4, K = 256 37 / 30.)
 // In a batch of a few searches the ranges pay from 6000 candidates on (one workgroup of 1024 threads /
-// ranges: one of 16000 50 / 17.6, of 8000 18.0 / 15.4, of 4096 16.0 / 18.0).
+// ranges: one of 16000 50 / 17.6, of 8000 18.0 / 15.4, of 4096 16.0 / 18.0), where a row is one piece later (S = 1: one of
+// 6277 12.8 / 14.1, of 8201 15.9 / 14.8, two of up to 9307 16.6 / 17.4, of up to 10834 19.5 / 17.0; S = 4: eight of up to
+// 9616 31 / 36, of up to 14890 51 / 27).
 constexpr int kUcbFewG = 8, kUcbFewN = 6000, kUcbRanges = 256, kUcbRangeMin = 512, kUcbRangeMax = 8192;
+constexpr int kUcbFewOneN = 8000, kUcbFewOnesN = 12000;
+static int ucb_few_n(const kb_batch& b) {
+    return ucb_pieces(b.S) > 1 ? kUcbFewN : b.G == 1 ? kUcbFewOneN : kUcbFewOnesN;
+}
 
 hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
     UcbArgs a = make_ucb_args(b, c);
@@ -647,10 +662,10 @@ hipError_t launch_ucb(const kb_batch& b, const UcbCall& c, hipStream_t st) {
     if (c.keep_tables && !c.gN) return hipErrorInvalidValue;
     a.keep = c.keep_tables ? 1 : 0;
     // (the tables in global memory are there unless the caller has none to give)
-    const bool few = c.gN && b.G <= kUcbFewG && b.Nmax > kUcbFewN;
+    const bool can = c.gN && b.G <= kUcbFewG, few = can && b.Nmax > ucb_few_n(b);
     if (c.chunked || few) {
         if (!c.gN) return hipErrorInvalidValue;
-        a.longer = few ? kUcbFewN : kUcbLong;
+        a.longer = can ? kUcbFewN : kUcbLong;        // (with the launches of the ranges paid for)
         a.range = kUcbRangeMin;
         while (a.range < kUcbRangeMax &&
                (b.N > (int64_t)kUcbRanges * a.range || (int64_t)a.Kmax * b.S > 4 * a.range))

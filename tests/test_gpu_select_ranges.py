@@ -21,7 +21,8 @@ def kb():
 
 
 @pytest.mark.parametrize("sizes,K,S", [((6000,), 4, 3), ((6001,), 4, 6), ((6001, 40, 9000), 64, 32),
-                                       ((16385, 3), 8, 5), ((7000,) * 9, 4, 4), ((20000,), 256, 32), ((70000,), 3, 12)])
+                                       ((16385, 3), 8, 5), ((7000,) * 9, 4, 4), ((8000,), 4, 4), ((8001,), 4, 1),
+                                       ((12000, 50), 8, 2), ((12001, 7000, 12000), 8, 4), ((20000,), 256, 32), ((70000,), 3, 12)])
 def test_selection_in_ranges(kb, sizes, K, S):
     import torch
     parts = [synth.config2(N=n, D=4, K=min(K, n), S=S, iters=1, seed=40 + i) for i, n in enumerate(sizes)]
