@@ -29,13 +29,17 @@ constexpr int kWaves = kThreads / kWave;
 //   up to 256 candidates: a wave.
 //   up to 4096: 256 threads.  1024 searches of 512 11.8 / 7.5 / 14.6, 300 of 70-1900 23.2 / 9.2 / 9.7, 512 of
 //     64-4096 32.7 / 10.1 / 11.8, 4096 of them 34.1 / 18.5 / 58.3, 2000 of 1500 43.9 / 19.5 / 40.9.
-//   few that may be longer than 2048, or up to 16384: 1024 threads.  One of 4096 10.8 / 5.8 / 4.9, 8 of 4000
-//     29.5 / 16.2 / 8.9, one of 16000 16.1 / 16.7 / 10.2, 64 of 16384 24.0 / 32.2 / 20.2.
+//   few that may be longer than 2048, up to 11000, or to 16384 where a cluster has few members: 1024 threads.
+//     One of 4096 10.8 / 5.8 / 4.9, 8 of 4000 29.5 / 16.2 / 8.9.  Every member of the chosen cluster is two
+//     logarithms, which the ranges spread over the chip: the longest searches take the ranges from 1200 members on
+//     (range kernels / 1024: 30 of up to 15132, K = 2 26.6 / 60.8, K = 4 34.5 / 62.7, 8 of up to 13880, K = 1
+//     25.7 / 32.7; 100 of 35-12445, K = 16 34 / 13.6, of 256-9689, K = 1 36 / 25; over random searches with more
+//     members, of 8192-11000 rows 1.18, of 12300-16384 0.83 times as fast in 1024 threads).
 //   very many with few candidates on average: a wave (4000 of 300 15.8 / 16.1 / 54.3).
 //   otherwise the range kernels, and in a batch of several searches a wave for those of up to
 //     short_n (4096 where searches have 1024 candidates or fewer on average, else 256) in the same call.
 constexpr int kGroupN = 4096, kGroupMaxG = 4096, kGroupMeanN = 512;
-constexpr int kWideFewG = 256, kWideFewN = 2048, kWideMaxG = 512, kWideN = 16384;
+constexpr int kWideFewG = 256, kWideFewN = 2048, kWideMaxG = 512, kWideN = 11000, kWideMembersN = 16384, kWideMembers = 1200;
 constexpr int kSampleShortMany = 4096;
 static int sample_short(const kb_batch& b) {
     return b.N <= (int64_t)1024 * b.G ? kSampleShortMany : kShortSearch;
@@ -226,7 +230,8 @@ hipError_t launch_sample(const kb_batch& b, const SampleCall& c, hipStream_t st)
         return hipGetLastError();
     };
     a.mixed = 0;
-    if (b.Nmax > kShortSearch && b.Nmax <= kWideN) {
+    if (b.Nmax > kShortSearch &&
+        (b.Nmax <= kWideN || (b.Nmax <= kWideMembersN && b.Nmax <= (int64_t)kWideMembers * b.Kmax))) {
         if (b.Nmax > (b.G <= kWideFewG ? kWideFewN : kGroupN) && b.G <= kWideMaxG) return workgroup(sample_search<1024>, 1024);
         if (b.Nmax <= kGroupN && (b.G <= kGroupMaxG || b.N >= (int64_t)kGroupMeanN * b.G))
             return workgroup(sample_search<kThreads>, kThreads);

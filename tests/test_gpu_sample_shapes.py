@@ -38,7 +38,7 @@ def _draw(kb, b, signature):
 
 
 @pytest.mark.parametrize("signature", [False, True])
-@pytest.mark.parametrize("longest", [257, 2048, 2049, 4096])
+@pytest.mark.parametrize("longest", [257, 2048, 2049, 4096, 11001])
 def test_every_form_of_the_draw_chooses_alike(kb, longest, signature):
     first = synth.config5(G=9, nmin=1, nmax=longest, D=4, S=4, iters=1, kcap=8, kdiv=8, seed=60)
     first = synth.concat(first, synth.config2(N=longest, D=4, K=2, S=4, iters=1, seed=61), "draw")
@@ -46,6 +46,7 @@ def test_every_form_of_the_draw_chooses_alike(kb, longest, signature):
     assert (want >= 0).any()
     fillers = (synth.config2(N=17000, D=4, K=2, S=4, iters=1, seed=62),                         # ranges
                synth.config2(N=5000, D=4, K=2, S=4, iters=1, seed=63),                          # 1024 threads
+               synth.config2(N=5000, D=4, K=32, S=4, iters=1, seed=66),                         # beyond 11000, too
                synth.config5(G=300, nmin=1, nmax=200, D=4, S=4, iters=1, kcap=4, kdiv=8, seed=64),      # 256
                synth.config5(G=5000, nmin=1, nmax=30, D=4, S=4, iters=1, kcap=2, kdiv=8, seed=65))      # a wave
     for f in fillers:
