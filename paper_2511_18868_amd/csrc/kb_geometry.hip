@@ -86,9 +86,11 @@ __global__ void __launch_bounds__(kThreads) geo_init(GeoArgs a) {
 
 // VEC = 4: D is a multiple of 4 and pieces of 16 bytes stay inside a row; VEC = 1: any D, the tile is
 // one run of floats all the same, fetched in 16-byte pieces that may cross from row to row.
-// kPieces: pieces of a thread (4 times as many features at most).
+// kPieces: pieces of a thread (4 times as many features at most).  They are its registers, and with them
+// the workgroups of a unit: as many forms as make a difference (one for all rows of 17 features and more / these:
+// 300 searches of 4489-9820 rows of 17 82 / 50 us, 256 of 4395-7118 of 33 103 / 62).
 template <int VEC, int kPieces>
-__global__ void __launch_bounds__(kThreads, VEC == 1 ? 2 : 1) geo_dist(GeoArgs a) {
+__global__ void __launch_bounds__(kThreads, VEC == 4 ? 1 : kPieces <= 8 ? 4 : kPieces <= 12 ? 3 : 2) geo_dist(GeoArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
     // row stride of the transposed tile: D + 4 words keeps 16-byte pieces aligned and
@@ -443,13 +445,15 @@ size_t geometry_lds_bytes(int Kmax, int D) {
     return (size_t)16 * Kmax + (size_t)4 * Kmax * D + (size_t)4 * kThreads * (D + 4);
 }
 
-// Candidates per workgroup: as many as leave every compute unit two workgroups (what its LDS holds; more
-// where a piece crosses rows and takes longer), if the slots of the shorter ranges hold a
-// search's clusters.  geo_dist, 2048 / this (us): 512 searches of 64-4096 rows of 48 features 44 / 35 (in ranges
-// of 512 42), 200 of them 44 / 23, one of 10000 rows of 32 18 / 7.5; 1000 of 70-1900 rows of 50 97 / 64 with
-// pieces that cross rows (value by value 120), 300 of them 111 / 31.
+// Candidates per workgroup: as many as leave every compute unit the workgroups that its LDS holds, two, or
+// one where centroids and rows of whole pieces take half of it (more where a piece crosses rows and takes longer), if the slots
+// of the shorter ranges hold a search's clusters.  geo_dist, 2048 / this (us): 512 searches of 64-4096 rows of 48
+// features 44 / 35 (in ranges of 512 42), 200 of them 44 / 23, one of 10000 rows of 32 18 / 7.5; 1000 of 70-1900
+// rows of 50 97 / 64 with pieces that cross rows (value by value 120), 300 of them 111 / 31; 1000 of 284-839
+// rows of 64, K = 52, whose workgroups have a unit to themselves, 64 as if two fitted and 59.
 static int range_of(const kb_batch& b) {
-    const int fill = (b.D & 3) == 0 ? kGeoFill : kGeoFillRagged;
+    const bool two = geometry_lds_bytes(b.Kmax, b.D) <= 80 * 1024;
+    const int fill = (b.D & 3) != 0 ? kGeoFillRagged : two ? kGeoFill : kGeoFill / 2;
     int range = kGeoRange;
     while (range > kGeoRangeMin && b.N < (int64_t)fill * range && 5 * (int64_t)b.Kmax <= range / 2) range /= 2;
     return range;
@@ -495,7 +499,8 @@ hipError_t launch_geometry(const kb_batch& b, const GeoCall& c, hipStream_t st) 
             hipLaunchKernelGGL(kern, dim3(ranges), dim3(kThreads), lds, st, a);
             return hipSuccess;
         };
-        const hipError_t e = (b.D & 3) == 0 ? go(geo_dist<4, 16>) : b.D <= 16 ? go(geo_dist<1, 4>) : go(geo_dist<1, 16>);
+        const hipError_t e = (b.D & 3) == 0 ? go(geo_dist<4, 16>) : b.D <= 16 ? go(geo_dist<1, 4>)
+                             : b.D <= 32 ? go(geo_dist<1, 8>) : b.D <= 48 ? go(geo_dist<1, 12>) : go(geo_dist<1, 16>);
         if (e != hipSuccess) return e;
         if (!a.merged) hipLaunchKernelGGL(geo_rep, dim3(ranges), dim3(kThreads), 0, st, a);
     }

@@ -33,7 +33,7 @@ def _run(kb, b):
     np.testing.assert_array_equal(d.host("radius"), geo.radius.astype(np.float32))
 
 
-@pytest.mark.parametrize("D", [1, 2, 3, 5, 6, 15, 16, 17, 31, 50, 63])
+@pytest.mark.parametrize("D", [1, 2, 3, 5, 6, 15, 16, 17, 31, 33, 47, 50, 63])
 @pytest.mark.parametrize("kcap", [4, 64, 200])
 def test_geometry_over_ranges_and_row_lengths(kb, D, kcap):
     # one row alone, then rows enough for several ranges of 512 (kcap 64), 1024 (200) and for whole ones
