@@ -1,12 +1,12 @@
-"""The form of the Lloyd kernel for a single step (more than 256 searches) against the vector-ALU scorer,
-which takes the general form: one and two centroid tiles, row lengths at the edges of K-steps and of
-16-byte pieces, searches of fewer rows than centroids, equal distances, more doubtful candidates than
-the list holds, rows larger than the first ones."""
+"""The form of the Lloyd kernel for a single step (256 threads per search: many searches beside the
+longest) against the vector-ALU scorer, which takes the general form: one and two centroid tiles, row
+lengths at the edges of K-steps and of 16-byte pieces, searches of fewer rows than centroids, equal
+distances, more doubtful candidates than the list holds, rows larger than the first ones."""
 import numpy as np
 import pytest
 
 from paper_2511_18868_amd import synth
-from kbcheck import assert_rel_close
+from kbcheck import assert_rel_close, takes_256_threads
 
 pytestmark = pytest.mark.gpu
 
@@ -26,9 +26,10 @@ def kb():
 @pytest.mark.parametrize("rows", ["plain", "grid", "late"])
 def test_single_step(kb, D, kcap, rows):
     import torch
-    b = synth.config5(G=300, nmin=1, nmax=200, D=D, S=3, iters=1, kcap=kcap, kdiv=2, seed=70 + D)
+    b = synth.config5(G=900, nmin=1, nmax=100, D=D, S=3, iters=1, kcap=kcap, kdiv=2, seed=70 + D)
     long = synth.config2(N=1500, D=D, K=kcap, S=3, iters=1, seed=5)
     b = synth.concat(b, long, "step")
+    assert takes_256_threads(b)
     if rows == "grid":          # equal distances
         b.X[:] = np.rint(b.X)
     if rows == "late":          # beyond the rows from which the scale is estimated
