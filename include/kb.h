@@ -125,8 +125,9 @@ typedef struct {
     int32_t scorer;   /* how kb_cluster / kb_round form the fast distance scores of a Lloyd
                        * step: one of KB_SCORER_*; 0 is the default.  Every mode gives
                        * identical results (doubtful candidates are re-evaluated exactly in
-                       * every mode); only speed differs.  kb_cluster_step always runs the
-                       * default. */
+                       * every mode) but for the last bit of the objective, an fp64 sum whose
+                       * order follows the kernel; only speed differs.  kb_cluster_step always
+                       * runs the default. */
     int32_t stop_early; /* 0: every search runs all `iters` Lloyd steps.  1: a search stops at
                        * its first step in which no candidate changes cluster - such a step
                        * leaves sums, sizes and centroids as they were, so every later step

@@ -197,7 +197,8 @@ hipError_t launch_rounds(const kb_batch& b, const UcbCall& c, const SampleCall& 
                          hipStream_t st);
 
 // Whole iterations - re-clusterings, representatives and masks included - of a batch of very short
-// searches in one launch: `first_due` is the first iteration of the launch that re-clusters (every
+// searches in one launch (iterate_in_one_launch: the batch can and, for a call of so many iterations and
+// re-clusterings, that is faster): `first_due` is the first iteration of the launch that re-clusters (every
 // tau-th one then does; tau <= 0: none).  The ClusterCall carries the clustering's arrays and steps
 // (cent_init unused: `warm` says where its centroids start from).
 struct IterateCall {
